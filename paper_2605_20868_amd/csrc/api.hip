@@ -784,8 +784,8 @@ int32_t cqa_dense_fallback(cqa_cache* h, int32_t layer, const void* q_fp16_dev,
     CQA_HIP(hipEventRecord(c->ev_ready[buf], c->side));
     CQA_HIP(hipStreamWaitEvent(st, c->ev_ready[buf], 0));
     const int64_t row = (int64_t)b * hq + kh * g;
-    const int32_t rc = launch_dense_group(
-        q + row * D, c->stage[buf][0], c->stage[buf][1], g, len, O_dev + row * D,
+    const int32_t rc = launch_dense(
+        q + row * D, c->stage[buf][0], c->stage[buf][1], g, 1, (int64_t)bt * hkv, len, O_dev + row * D,
         all_heads ? nullptr : c->select_dev + row, cert_dev ? cert_dev + row : nullptr,
         flags_dev ? flags_dev + row : nullptr, rung, c->dense_ws + buf * ws_floats, st);
     if (rc != CQA_OK) return rc;
@@ -1099,19 +1099,9 @@ int32_t cqa_dense_attention(const void* q_fp16_dev, const void* k_fp16_dev,
     return CQA_ERR_INVALID_ARG;
   const int g = n_q_heads / n_kv_heads;
   if (g != 1 && g != 2 && g != 4) return CQA_ERR_UNSUPPORTED;
-  const __half* q = (const __half*)q_fp16_dev;
-  const __half* k = (const __half*)k_fp16_dev;
-  const __half* v = (const __half*)v_fp16_dev;
-  for (int b = 0; b < batch; ++b)
-    for (int kh = 0; kh < n_kv_heads; ++kh) {
-      const int64_t row = (int64_t)b * n_q_heads + kh * g;
-      const int64_t kv = ((int64_t)b * n_kv_heads + kh) * n_tokens * D;
-      const int32_t rc =
-          launch_dense_group(q + row * D, k + kv, v + kv, g, n_tokens, O_dev + row * D, nullptr,
-                             nullptr, nullptr, 0, (float*)workspace_dev, (hipStream_t)stream);
-      if (rc != CQA_OK) return rc;
-    }
-  return CQA_OK;
+  const int64_t groups = (int64_t)batch * n_kv_heads;
+  return launch_dense((const __half*)q_fp16_dev, (const __half*)k_fp16_dev, (const __half*)v_fp16_dev, g, groups,
+                      groups, n_tokens, O_dev, nullptr, nullptr, nullptr, 0, (float*)workspace_dev, (hipStream_t)stream);
 }
 
 }  // extern "C"

@@ -268,14 +268,14 @@ int32_t launch_split_mfma(const DecodeArgs& a, int group, dim3 grid, hipEvent_t 
 int32_t launch_stream_read(const uint8_t* t1, int64_t nq_cap, int nb, dim3 grid, bool nt, int wpb,
                            uint32_t* sink, hipStream_t st);
 
-int dense_splits(int64_t n_tokens);
-// Dense FP16 attention for the G query heads of ONE kv group: k, v point at [n_tokens][128];
-// q_group at the group's first query head.  O rows are written only where select (device,
-// indexed from the group's first head; NULL = all) is nonzero.
-int32_t launch_dense_group(const __half* q_group, const __half* k, const __half* v, int group,
-                           int64_t n_tokens, float* O_group, const uint32_t* select_group,
-                           cqa_head_cert* cert_group, uint32_t* flags_group, int rung,
-                           float* ws, hipStream_t st);
+// Dense FP16 attention of `groups` consecutive KV groups: q [groups][group][128], k, v
+// [groups][n_tokens][128] (device or mapped host memory).  O rows are written only where select
+// (device, [groups][group]; null = all) is nonzero; cert / flags rows (null = none) are marked with
+// `rung`.  layer_groups: KV groups the sequence split is chosen for (>= groups).  ws: at least
+// dense_ws_floats(4, n_tokens) floats, or dense_ws_floats(group, n) for groups = 1, n >= n_tokens.
+int32_t launch_dense(const __half* q, const __half* k, const __half* v, int group, int64_t groups,
+                     int64_t layer_groups, int64_t n_tokens, float* O, const uint32_t* select, cqa_head_cert* cert,
+                     uint32_t* flags, int rung, float* ws, hipStream_t st);
 int64_t dense_ws_floats(int group, int64_t n_tokens);
 
 // Device-resolved fallback ladder (dense_ladder_kernel).

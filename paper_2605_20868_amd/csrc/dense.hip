@@ -1,176 +1,318 @@
 // Dense FP16 decode attention, softmax(q K^T / sqrt d) V with FP32 accumulation:
 // the O_dense the paper's Rung 3 / Rung 4 return (its "Fallback Ladder" section).
-// One launch serves the G query heads of one KV group over device-resident
-// FP16 K, V of [n_tokens][128]; split over the sequence, merged by a second
-// kernel that also rewrites the served heads' certificates.
+// One launch serves every KV group of a call (or the one group of a fallback) over FP16 K, V of
+// [n_tokens][128], split over the sequence; a second kernel merges the splits and also rewrites
+// the served heads' certificates.  With one split per group the first kernel finishes the rows
+// itself and there is no second one.
+#include <algorithm>
+
 #include "cqa_internal.h"
 #include "reduce_inl.h"
 
 namespace cqa {
 
-constexpr int DP_FLOATS = 4 + D;  // m, l, pad, pad, o[128]
-constexpr int DENSE_TILES_PER_SPLIT = 8;
-constexpr int DENSE_MAX_SPLITS = 1024;
+constexpr int DP_FLOATS = 4 + D;  // m (base 2), l, pad, pad, o[128]
+constexpr int DENSE_WAVES = 8;    // waves per workgroup of the dense pass
+constexpr int DENSE_WG_TARGET = 256;  // one workgroup of eight waves on each of the compute units
+constexpr int DENSE_TILE = 32;    // tokens a wave takes per iteration
+// ... when the ladder reads the pinned originals, where the host link is the bound and more requests in
+// flight only make the workgroups' shares of it uneven.  One group of 131072 tokens: 8 tokens 1213 us,
+// 32 tokens 1221, no prefetch 1270; two of 20000: 401, 447, 452; four or five of 32768: 1240 / 1565,
+// 1249 / 1575, 1249 / 1548.
+constexpr int LADDER_TILE = 8;
+constexpr float M_EMPTY = -1.0e30f;   // running maximum of a state that has seen no token: finite, below every score
 
-int dense_splits(int64_t n_tokens) {
+// Splits per KV group that the caller's workspace holds for a sequence of this length when one
+// group of four heads is served at a time: what cqa_dense_workspace_bytes is sized by.
+static int64_t dense_ws_units(int64_t n_tokens) {
   const int64_t tiles = (n_tokens + BLK - 1) / BLK;
-  int64_t s = (tiles + DENSE_TILES_PER_SPLIT - 1) / DENSE_TILES_PER_SPLIT;
-  if (s > DENSE_MAX_SPLITS) s = DENSE_MAX_SPLITS;
+  int64_t s = std::min<int64_t>((tiles + 7) / 8, 1024);
+  const int64_t tps = (tiles + s - 1) / s;
+  return (tiles + tps - 1) / tps;
+}
+
+int64_t dense_ws_floats(int group, int64_t n_tokens) {
+  return (int64_t)group * dense_ws_units(n_tokens) * DP_FLOATS;
+}
+
+// Splits per KV group of a call that serves `groups` KV groups (a fallback, which may serve fewer
+// of them, uses the geometry of its whole layer, so that its rows are bit-equal to the dense
+// call's): one workgroup per compute unit over all groups, but at least a tile per wave, and no
+// more than the workspace (sized for the groups one after the other) holds for all groups at
+// once.  At most 256, which is what a cache's own workspace holds for one group at any length
+// that allows so many.
+static int dense_splits(int group, int64_t groups, int64_t n_tokens) {
+  const int64_t tiles = (n_tokens + DENSE_TILE - 1) / DENSE_TILE;
+  int64_t s = std::min<int64_t>(DENSE_WG_TARGET / std::min<int64_t>(groups, DENSE_WG_TARGET),
+                                (tiles + DENSE_WAVES - 1) / DENSE_WAVES);
+  s = std::min<int64_t>(s, 4 * dense_ws_units(n_tokens) / ((int64_t)group * groups));
   if (s < 1) s = 1;
   const int64_t tps = (tiles + s - 1) / s;
   return (int)((tiles + tps - 1) / tps);
 }
 
-int64_t dense_ws_floats(int group, int64_t n_tokens) {
-  return (int64_t)group * dense_splits(n_tokens) * DP_FLOATS;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <bool NT>
+__device__ __forceinline__ uint4 ld_dense(const char* p) {
+  const u32x4* x = reinterpret_cast<const u32x4*>(p);
+  const u32x4 v = NT ? __builtin_nontemporal_load(x) : *x;
+  return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// One split of the dense pass for the G heads of one KV group: tiles [split * tiles_per_split, ...)
-// of k, v ([n_tokens][128], device or mapped host memory); writes (m, l, o) per head to
-// ws[h][split].  Called by all 256 threads of a workgroup.
-template <int G>
-__device__ __forceinline__ void dense_split_work(const __half* __restrict__ q,
-                                                 const __half* __restrict__ k,
-                                                 const __half* __restrict__ v, int64_t n_tokens,
-                                                 int tiles_per_split, int nsplit, int split,
-                                                 float* __restrict__ ws) {
+template <int G, int W>
+struct DenseSmem {
+  float mo[W][G][D];
+  float ms[W][G][2];
+};
+
+// The W waves of a workgroup attend tiles [t0, t1) of 32 tokens of k, v ([n_tokens][128], device or
+// mapped host memory) for the G heads of one KV group, dealt round-robin; on return (after a
+// workgroup barrier) each wave's state is in LDS.
+// Bound by the memory stream.  Every load covers 1 KB of consecutive memory: a row of 16 lanes
+// holds one token, a lane 8 channels of it, so a wave's four rows take tokens r, 4 + r, 8 + r, ...
+// of a tile.  A score is 8 products per head and a row sum on DPP; after it every lane of the row
+// holds the score, so the softmax state is kept per row and nothing goes through LDS before the
+// end.  Registers are re-requested for the wave's next tile right after their last use: with tiles
+// of 32 tokens 16 KB in flight per wave, 128 KB per compute unit.  Measured on 16 groups of 32775
+// tokens, 268 MB, four heads per group: 46.4 us = 5.8 TB/s (plain loads, tiles of 32: 85 us with the
+// reduction; the non-temporal hint: 49; one launch pair per group before: 2074).
+template <int G, int W, int TILE, bool NT>
+__device__ __forceinline__ void dense_split_work(const __half* __restrict__ q, const __half* __restrict__ k,
+                                                 const __half* __restrict__ v, int64_t n_tokens, int64_t t0,
+                                                 int64_t t1, DenseSmem<G, W>& sm) {
+  constexpr int T = TILE / 4;   // tokens per row and tile
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int tok = l & 15, kg = l >> 4;   // score phase: token of the tile, 32-channel slice
-  const int vc = l & 15, vt = l >> 4;    // value phase: 8-channel slice, 4-token slice
-  const int64_t tiles = (n_tokens + BLK - 1) / BLK;
-  const int64_t t0 = (int64_t)split * tiles_per_split;
-  const int64_t t1 = min(t0 + (int64_t)tiles_per_split, tiles);
-  const float inv_sqrt_d = 0.08838834764831845f;
+  const int c8 = l & 15, row = l >> 4;
+  const float scale = 0.08838834764831845f * 1.4426950408889634f;   // 1 / sqrt(128), in base-2 units
 
-  __shared__ __align__(16) float qf[G][D];
-  __shared__ __align__(16) float ps[4][BLK][G];
-  __shared__ __align__(16) float mo[4][G][D];
-  __shared__ float ms[4][G][2];
-
-  for (int i = threadIdx.x; i < G * D; i += 256) qf[i / D][i % D] = __half2float(q[i]);
-  __syncthreads();
+  uint4 qr[G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) qr[h] = *reinterpret_cast<const uint4*>(q + h * D + c8 * 8);
 
   float m_run[G], l_run[G], acc[8][G];
 #pragma unroll
   for (int h = 0; h < G; ++h) {
-    m_run[h] = -INFINITY;
+    m_run[h] = M_EMPTY;
     l_run[h] = 0.0f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j][h] = 0.0f;
   }
 
-  for (int64_t tile = t0 + w; tile < t1; tile += 4) {
-    const int64_t t = tile * BLK + tok;
-    const bool valid = t < n_tokens;
-    const int64_t tc = valid ? t : n_tokens - 1;
-    const uint4* kp = reinterpret_cast<const uint4*>(k + tc * D + kg * 32);
-    float dot[G];
+  uint4 kr[T], vr[T];
+  // address = the tile's wave-uniform base + a 32-bit lane offset; tokens past the end read the last
+  // token's row, their scores are masked.  The request of a wave's last iteration is not used:
+  // it is aimed at the first query row, in cache, and costs no memory traffic.
+#define CQA_DENSE_LOAD(DST, SRC, TI, ON)                                                        \
+  {                                                                                             \
+    const char* base__ = reinterpret_cast<const char*>((ON) ? (SRC) + (TI) * (TILE * D) : q); \
+    const int last__ = (ON) ? (int)min((int64_t)(TILE - 1), n_tokens - 1 - (TI) * TILE) : 0; \
+    _Pragma("unroll") for (int i = 0; i < T; ++i)                                               \
+      DST[i] = ld_dense<NT>(base__ + (uint32_t)(min(i * 4 + row, last__) * (D * 2) + c8 * 16)); \
+  }
+  int64_t tile = t0 + __builtin_amdgcn_readfirstlane(w);
+  if (tile < t1) {
+    CQA_DENSE_LOAD(kr, k, tile, true)
+    CQA_DENSE_LOAD(vr, v, tile, true)
+  }
+  for (; tile < t1; tile += W) {
+    const int64_t nxt = tile + W;
+    const int live = (int)min((int64_t)TILE, n_tokens - tile * TILE);
+    float s[T][G];
 #pragma unroll
-    for (int h = 0; h < G; ++h) dot[h] = 0.0f;
+    for (int i = 0; i < T; ++i) {
+      const __half2* kh = reinterpret_cast<const __half2*>(&kr[i]);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint4 x = kp[u];
-      const __half2* hh = reinterpret_cast<const __half2*>(&x);
+      for (int h = 0; h < G; ++h) {
+        const __half2* qh = reinterpret_cast<const __half2*>(&qr[h]);
+        float d = 0.0f;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float k0 = __low2float(hh[j]), k1 = __high2float(hh[j]);
-        const int c = kg * 32 + u * 8 + j * 2;
-#pragma unroll
-        for (int h = 0; h < G; ++h) dot[h] = fmaf(qf[h][c + 1], k1, fmaf(qf[h][c], k0, dot[h]));
+        for (int j = 0; j < 4; ++j) {
+          d = fmaf(__low2float(qh[j]), __low2float(kh[j]), d);
+          d = fmaf(__high2float(qh[j]), __high2float(kh[j]), d);
+        }
+        s[i][h] = d;
       }
     }
-    float alpha[G];
+    CQA_DENSE_LOAD(kr, k, nxt, nxt < t1)
 #pragma unroll
     for (int h = 0; h < G; ++h) {
-      dot[h] += __shfl_xor(dot[h], 16);
-      dot[h] += __shfl_xor(dot[h], 32);
-      const float s = valid ? dot[h] * inv_sqrt_d : -INFINITY;
-      float mb = s;
+      float m_new = m_run[h];
 #pragma unroll
-      for (int m = 1; m < 16; m <<= 1) mb = fmaxf(mb, __shfl_xor(mb, m));
-      const float m_new = fmaxf(m_run[h], mb);
-      alpha[h] = __expf(m_run[h] - m_new);
-      const float p = __expf(s - m_new);
-      float sb = p;
+      for (int i = 0; i < T; ++i) {
+        const float sum16 = row_sum(s[i][h]);
+        s[i][h] = i * 4 + row < live ? sum16 * scale : -INFINITY;
+        m_new = fmaxf(m_new, s[i][h]);
+      }
+      const float alpha = __builtin_amdgcn_exp2f(m_run[h] - m_new);
+      float sum = 0.0f;
 #pragma unroll
-      for (int m = 1; m < 16; m <<= 1) sb += __shfl_xor(sb, m);
-      l_run[h] = l_run[h] * alpha[h] + sb;
+      for (int i = 0; i < T; ++i) {
+        s[i][h] = __builtin_amdgcn_exp2f(s[i][h] - m_new);
+        sum += s[i][h];
+      }
+      l_run[h] = fmaf(l_run[h], alpha, sum);
       m_run[h] = m_new;
-      if (kg == 0) ps[w][tok][h] = p;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[j][h] *= alpha;
     }
-    wave_sync();
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-      for (int h = 0; h < G; ++h) acc[j][h] *= alpha[h];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int tt = vt * 4 + i;
-      int64_t tv = tile * BLK + tt;
-      if (tv >= n_tokens) tv = n_tokens - 1;  // its probability is exactly 0
-      const uint4 x = *reinterpret_cast<const uint4*>(v + tv * D + vc * 8);
-      const __half2* hh = reinterpret_cast<const __half2*>(&x);
-      float pr[G];
-#pragma unroll
-      for (int h = 0; h < G; ++h) pr[h] = ps[w][tt][h];
+    for (int i = 0; i < T; ++i) {
+      const __half2* vh = reinterpret_cast<const __half2*>(&vr[i]);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float v0 = __low2float(hh[j]), v1 = __high2float(hh[j]);
+        const float v0 = __low2float(vh[j]), v1 = __high2float(vh[j]);
 #pragma unroll
         for (int h = 0; h < G; ++h) {
-          acc[2 * j][h] = fmaf(pr[h], v0, acc[2 * j][h]);
-          acc[2 * j + 1][h] = fmaf(pr[h], v1, acc[2 * j + 1][h]);
+          acc[2 * j][h] = fmaf(s[i][h], v0, acc[2 * j][h]);
+          acc[2 * j + 1][h] = fmaf(s[i][h], v1, acc[2 * j + 1][h]);
         }
       }
     }
-    wave_sync();
+    CQA_DENSE_LOAD(vr, v, nxt, nxt < t1)
   }
+#undef CQA_DENSE_LOAD
 
+  // merge the wave's four rows
 #pragma unroll
-  for (int j = 0; j < 8; ++j)
+  for (int h = 0; h < G; ++h) {
+    float M = fmaxf(m_run[h], __shfl_xor(m_run[h], 16));
+    M = fmaxf(M, __shfl_xor(M, 32));
+    const float f = __builtin_amdgcn_exp2f(m_run[h] - M);
+    float L = l_run[h] * f;
+    L += __shfl_xor(L, 16);
+    L += __shfl_xor(L, 32);
+    float x[8];
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      float x = acc[j][h];
-      x += __shfl_xor(x, 16);
-      x += __shfl_xor(x, 32);
-      if (vt == 0) mo[w][h][vc * 8 + j] = x;
+    for (int j = 0; j < 8; ++j) {
+      x[j] = acc[j][h] * f;
+      x[j] += __shfl_xor(x[j], 16);
+      x[j] += __shfl_xor(x[j], 32);
     }
-  if (l == 0) {
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      ms[w][h][0] = m_run[h];
-      ms[w][h][1] = l_run[h];
+    if (row == 0) {
+      *reinterpret_cast<float4*>(&sm.mo[w][h][c8 * 8]) = make_float4(x[0], x[1], x[2], x[3]);
+      *reinterpret_cast<float4*>(&sm.mo[w][h][c8 * 8 + 4]) = make_float4(x[4], x[5], x[6], x[7]);
+      sm.ms[w][h][0] = M;
+      sm.ms[w][h][1] = L;
     }
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < G * D; idx += 256) {
-    const int h = idx / D, c = idx % D;
-    float M = -INFINITY;
+}
+
+// (m, l, o[c]) of head h over the workgroup's waves, from LDS
+template <int G, int W>
+__device__ __forceinline__ void dense_wg_merge(const DenseSmem<G, W>& sm, int h, int c, float& M, float& L, float& o) {
+  M = sm.ms[0][h][0];
 #pragma unroll
-    for (int ww = 0; ww < 4; ++ww) M = fmaxf(M, ms[ww][h][0]);
-    float o = 0.0f;
+  for (int w = 1; w < W; ++w) M = fmaxf(M, sm.ms[w][h][0]);
+  L = 0.0f;
+  o = 0.0f;
 #pragma unroll
-    for (int ww = 0; ww < 4; ++ww) o += __expf(ms[ww][h][0] - M) * mo[ww][h][c];
-    ws[((int64_t)h * nsplit + split) * DP_FLOATS + 4 + c] = o;
-  }
-  if (threadIdx.x < G) {
-    const int h = threadIdx.x;
-    float M = -INFINITY;
-    for (int ww = 0; ww < 4; ++ww) M = fmaxf(M, ms[ww][h][0]);
-    float L = 0.0f;
-    for (int ww = 0; ww < 4; ++ww) L += __expf(ms[ww][h][0] - M) * ms[ww][h][1];
-    ws[((int64_t)h * nsplit + split) * DP_FLOATS + 0] = M;
-    ws[((int64_t)h * nsplit + split) * DP_FLOATS + 1] = L;
+  for (int w = 0; w < W; ++w) {
+    const float f = __builtin_amdgcn_exp2f(sm.ms[w][h][0] - M);
+    L = fmaf(f, sm.ms[w][h][1], L);
+    o = fmaf(f, sm.mo[w][h][c], o);
   }
 }
 
+// this workgroup's partial sets: ws[h][split]
+template <int G, int W>
+__device__ __forceinline__ void dense_store_partials(const DenseSmem<G, W>& sm, float* ws, int nsplit, int split) {
+  for (int idx = threadIdx.x; idx < G * D; idx += 64 * W) {
+    const int h = idx / D, c = idx % D;
+    float M, L, o;
+    dense_wg_merge<G, W>(sm, h, c, M, L, o);
+    float* p = ws + ((int64_t)h * nsplit + split) * DP_FLOATS;
+    p[4 + c] = o;
+    if (c == 0) {
+      p[0] = M;
+      p[1] = L;
+    }
+  }
+}
+
+// Output channel c of one row over its `nsplit` partial sets.  All threads of a wave work on the
+// same row; the loads of eight sets are in flight at a time.
+__device__ __forceinline__ float dense_merge_row(const float* part, int nsplit, int c) {
+  float M = M_EMPTY;
+  for (int s = 0; s < nsplit; s += 64) M = fmaxf(M, part[(int64_t)min(s + (int)(threadIdx.x & 63), nsplit - 1) * DP_FLOATS]);
+  M = wave_max(M);
+  float L = 0.0f, o = 0.0f;
+  for (int s0 = 0; s0 < nsplit; s0 += 8) {
+    float m[8], l[8], x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float* p = part + (int64_t)min(s0 + i, nsplit - 1) * DP_FLOATS;
+      m[i] = p[0];
+      l[i] = p[1];
+      x[i] = p[4 + c];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float f = s0 + i < nsplit ? __builtin_amdgcn_exp2f(m[i] - M) : 0.0f;
+      L = fmaf(f, l[i], L);
+      o = fmaf(f, x[i], o);
+    }
+  }
+  return o / L;
+}
+
+__device__ __forceinline__ void dense_mark_served(cqa_head_cert* cert, uint32_t* flags, int64_t row, int rung) {
+  if (cert != nullptr) {
+    cert[row].E_key = 0.0f;
+    cert[row].E_val = 0.0f;
+    cert[row].served_rung = rung;
+  }
+  if (flags != nullptr) flags[row] = (flags[row] & ~(7u << CQA_RUNG_SHIFT)) | ((uint32_t)rung << CQA_RUNG_SHIFT);
+}
+
+struct DenseArgs {
+  const __half* q;          // [groups][G][128]
+  const __half* k;          // [groups][n_tokens][128]
+  const __half* v;
+  int64_t n_tokens;
+  int nsplit, tiles_per_split;
+  float* ws;                // [groups][G][nsplit][DP_FLOATS], unused with one split
+  float* O;                 // [groups][G][128]
+  const uint32_t* select;   // [groups][G] or null = all: rows that are written
+  cqa_head_cert* cert;      // or null
+  uint32_t* flags;          // or null
+  int rung;
+};
+
 template <int G>
-__global__ __launch_bounds__(256) void dense_split_kernel(const __half* __restrict__ q,
-                                                          const __half* __restrict__ k,
-                                                          const __half* __restrict__ v,
-                                                          int64_t n_tokens, int tiles_per_split,
-                                                          int nsplit, float* __restrict__ ws) {
-  dense_split_work<G>(q, k, v, n_tokens, tiles_per_split, nsplit, (int)blockIdx.x, ws);
+__global__ __launch_bounds__(64 * DENSE_WAVES, 2) void dense_split_kernel(DenseArgs a) {
+  __shared__ __align__(16) DenseSmem<G, DENSE_WAVES> sm;
+  const int64_t grp = blockIdx.x / a.nsplit;
+  const int split = (int)(blockIdx.x - grp * a.nsplit);
+  const int64_t tiles = (a.n_tokens + DENSE_TILE - 1) / DENSE_TILE;
+  const int64_t t0 = (int64_t)split * a.tiles_per_split;
+  const int64_t t1 = min(t0 + (int64_t)a.tiles_per_split, tiles);
+  dense_split_work<G, DENSE_WAVES, DENSE_TILE, true>(a.q + grp * G * D, a.k + grp * a.n_tokens * D, a.v + grp * a.n_tokens * D,
+                                   a.n_tokens, t0, t1, sm);
+  if (a.nsplit > 1) {
+    dense_store_partials<G, DENSE_WAVES>(sm, a.ws + grp * G * a.nsplit * DP_FLOATS, a.nsplit, split);
+    return;
+  }
+  for (int idx = threadIdx.x; idx < G * D; idx += 64 * DENSE_WAVES) {
+    const int h = idx / D, c = idx % D;
+    const int64_t row = grp * G + h;
+    if (a.select != nullptr && a.select[row] == 0) continue;
+    float M, L, o;
+    dense_wg_merge<G, DENSE_WAVES>(sm, h, c, M, L, o);
+    a.O[row * D + c] = o / L;
+    if (c == 0) dense_mark_served(a.cert, a.flags, row, a.rung);
+  }
+}
+
+// One workgroup of 128 threads per row.  (Before: one thread per channel walked all splits twice,
+// one load in flight: 112 us for 256 splits of one group, which made it 16 times 125 us for the
+// 268 MB call.)
+__global__ __launch_bounds__(128) void dense_reduce_kernel(DenseArgs a) {
+  const int64_t row = blockIdx.x;
+  if (a.select != nullptr && a.select[row] == 0) return;
+  const int c = threadIdx.x;
+  a.O[row * D + c] = dense_merge_row(a.ws + row * a.nsplit * DP_FLOATS, a.nsplit, c);
+  if (c == 0) dense_mark_served(a.cert, a.flags, row, a.rung);
 }
 
 // The fallback ladder resolved on the device (the paper's "Fallback Ladder": Rung 3 returns the
@@ -238,9 +380,12 @@ __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
 
   const int64_t row0 = (int64_t)grp * G;
   float* ws = a.ws + row0 * a.nsplit * DP_FLOATS;
-  dense_split_work<G>(a.q + row0 * D, a.t2_k + (int64_t)grp * a.max_tokens * D,
-                      a.t2_v + (int64_t)grp * a.max_tokens * D, a.n_tokens, a.tiles_per_split,
-                      a.nsplit, split, ws);
+  __shared__ __align__(16) DenseSmem<G, 4> sm;
+  const int64_t t0 = (int64_t)split * a.tiles_per_split;
+  const int64_t t1 = min(t0 + (int64_t)a.tiles_per_split, (a.n_tokens + LADDER_TILE - 1) / LADDER_TILE);
+  dense_split_work<G, 4, LADDER_TILE, false>(a.q + row0 * D, a.t2_k + (int64_t)grp * a.max_tokens * D,
+                         a.t2_v + (int64_t)grp * a.max_tokens * D, a.n_tokens, t0, t1, sm);
+  dense_store_partials<G, 4>(sm, ws, a.nsplit, split);
   // every thread publishes its partial stores device-wide before the workgroup draws its ticket
   __threadfence();
   __syncthreads();
@@ -258,22 +403,9 @@ __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
     const int h = idx / D, c = idx % D;
     const int64_t row = row0 + h;
     if (rung != 4 && (a.flags[row] & CQA_FLAG_ANY) == 0u) continue;   // Rung 3 serves flagged heads only
-    const float* part = ws + (int64_t)h * a.nsplit * DP_FLOATS;
-    float M = -INFINITY;
-    for (int sidx = 0; sidx < a.nsplit; ++sidx) M = fmaxf(M, part[sidx * DP_FLOATS]);
-    float L = 0.0f, o = 0.0f;
-    for (int sidx = 0; sidx < a.nsplit; ++sidx) {
-      const float f = __expf(part[sidx * DP_FLOATS] - M);
-      L += f * part[sidx * DP_FLOATS + 1];
-      o += f * part[sidx * DP_FLOATS + 4 + c];
-    }
-    a.O[row * D + c] = o / L;
-    if (c == 0) {
-      a.cert[row].E_key = 0.0f;
-      a.cert[row].E_val = 0.0f;
-      a.cert[row].served_rung = rung;
-      a.flags[row] = (a.flags[row] & ~(7u << CQA_RUNG_SHIFT)) | ((uint32_t)rung << CQA_RUNG_SHIFT);
-    }
+    // (a wave's 64 channels belong to one row, so the branch above is uniform in the wave)
+    a.O[row * D + c] = dense_merge_row(ws + (int64_t)h * a.nsplit * DP_FLOATS, a.nsplit, c);
+    if (c == 0) dense_mark_served(a.cert, a.flags, row, rung);
   }
 }
 
@@ -282,7 +414,7 @@ int ladder_splits(const Cache* c, int64_t n_tokens) {
   int64_t want = (2 * (int64_t)c->n_cu) / groups;   // the launch's cost does not depend on it
   if (want < 4) want = 4;
   if (want > LADDER_MAX_SPLITS) want = LADDER_MAX_SPLITS;
-  const int64_t tiles = (n_tokens + BLK - 1) / BLK;
+  const int64_t tiles = (n_tokens + LADDER_TILE - 1) / LADDER_TILE;
   if (want > tiles) want = tiles;
   const int64_t tps = (tiles + want - 1) / want;
   return (int)((tiles + tps - 1) / tps);
@@ -307,7 +439,7 @@ int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_
   a.n_tokens = len;
   a.n_rows = bt * hq;
   a.nsplit = ladder_splits(c, len);
-  const int64_t tiles = (len + BLK - 1) / BLK;
+  const int64_t tiles = (len + LADDER_TILE - 1) / LADDER_TILE;
   a.tiles_per_split = (int)((tiles + a.nsplit - 1) / a.nsplit);
   a.rung4_min_groups = rung4_min_groups;
   a.ws = c->ladder_ws;
@@ -327,62 +459,37 @@ int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_
   return CQA_OK;
 }
 
-__global__ __launch_bounds__(128) void dense_reduce_kernel(const float* __restrict__ ws, int nsplit,
-                                                           float* __restrict__ O,
-                                                           const uint32_t* __restrict__ select,
-                                                           cqa_head_cert* cert, uint32_t* flags,
-                                                           int rung) {
-  const int h = blockIdx.x, c = threadIdx.x;
-  if (select != nullptr && select[h] == 0) return;
-  const float* part = ws + (int64_t)h * nsplit * DP_FLOATS;
-  float M = -INFINITY;
-  for (int s = 0; s < nsplit; ++s) M = fmaxf(M, part[s * DP_FLOATS]);
-  float L = 0.0f, o = 0.0f;
-  for (int s = 0; s < nsplit; ++s) {
-    const float f = __expf(part[s * DP_FLOATS] - M);
-    L += f * part[s * DP_FLOATS + 1];
-    o += f * part[s * DP_FLOATS + 4 + c];
-  }
-  O[(int64_t)h * D + c] = o / L;
-  if (c == 0) {
-    if (cert != nullptr) {
-      cert[h].E_key = 0.0f;
-      cert[h].E_val = 0.0f;
-      cert[h].served_rung = rung;
-    }
-    if (flags != nullptr)
-      flags[h] = (flags[h] & ~(7u << CQA_RUNG_SHIFT)) | ((uint32_t)rung << CQA_RUNG_SHIFT);
-  }
-}
-
-int32_t launch_dense_group(const __half* q_group, const __half* k, const __half* v, int group,
-                           int64_t n_tokens, float* O_group, const uint32_t* select_group,
-                           cqa_head_cert* cert_group, uint32_t* flags_group, int rung,
-                           float* ws, hipStream_t st) {
-  if (n_tokens <= 0) return CQA_ERR_INVALID_ARG;
-  const int nsplit = dense_splits(n_tokens);
-  const int64_t tiles = (n_tokens + BLK - 1) / BLK;
-  const int tps = (int)((tiles + nsplit - 1) / nsplit);
+int32_t launch_dense(const __half* q, const __half* k, const __half* v, int group, int64_t groups,
+                     int64_t layer_groups, int64_t n_tokens, float* O, const uint32_t* select, cqa_head_cert* cert,
+                     uint32_t* flags, int rung, float* ws, hipStream_t st) {
+  if (n_tokens <= 0 || groups <= 0) return CQA_ERR_INVALID_ARG;
+  const int64_t tiles = (n_tokens + DENSE_TILE - 1) / DENSE_TILE;
+  DenseArgs a{};
+  a.q = q;
+  a.k = k;
+  a.v = v;
+  a.n_tokens = n_tokens;
+  a.nsplit = dense_splits(group, layer_groups, n_tokens);
+  a.tiles_per_split = (int)((tiles + a.nsplit - 1) / a.nsplit);
+  a.ws = ws;
+  a.O = O;
+  a.select = select;
+  a.cert = cert;
+  a.flags = flags;
+  a.rung = rung;
+  if (groups * std::max(a.nsplit, group) > 0x7FFFFFFF) return CQA_ERR_UNSUPPORTED;   // one grid dimension
+  const dim3 grid((unsigned)(groups * a.nsplit));
   switch (group) {
-    case 1:
-      hipLaunchKernelGGL(dense_split_kernel<1>, dim3(nsplit), dim3(256), 0, st, q_group, k, v,
-                         n_tokens, tps, nsplit, ws);
-      break;
-    case 2:
-      hipLaunchKernelGGL(dense_split_kernel<2>, dim3(nsplit), dim3(256), 0, st, q_group, k, v,
-                         n_tokens, tps, nsplit, ws);
-      break;
-    case 4:
-      hipLaunchKernelGGL(dense_split_kernel<4>, dim3(nsplit), dim3(256), 0, st, q_group, k, v,
-                         n_tokens, tps, nsplit, ws);
-      break;
-    default:
-      return CQA_ERR_UNSUPPORTED;
+    case 1: hipLaunchKernelGGL(dense_split_kernel<1>, grid, dim3(64 * DENSE_WAVES), 0, st, a); break;
+    case 2: hipLaunchKernelGGL(dense_split_kernel<2>, grid, dim3(64 * DENSE_WAVES), 0, st, a); break;
+    case 4: hipLaunchKernelGGL(dense_split_kernel<4>, grid, dim3(64 * DENSE_WAVES), 0, st, a); break;
+    default: return CQA_ERR_UNSUPPORTED;
   }
   CQA_HIP(hipGetLastError());
-  hipLaunchKernelGGL(dense_reduce_kernel, dim3(group), dim3(128), 0, st, ws, nsplit, O_group,
-                     select_group, cert_group, flags_group, rung);
-  CQA_HIP(hipGetLastError());
+  if (a.nsplit > 1) {
+    hipLaunchKernelGGL(dense_reduce_kernel, dim3((unsigned)(groups * group)), dim3(128), 0, st, a);
+    CQA_HIP(hipGetLastError());
+  }
   return CQA_OK;
 }
 
