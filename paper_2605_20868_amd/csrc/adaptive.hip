@@ -907,8 +907,8 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   //         log-masses, eta_b and the partial sets the promoted-block pass will correct.  Every
   //         threshold is off: its certificate only feeds the selector (lse, Delta_h, V_max) and
   //         is overwritten below.
-  int nsplit = 0, bps = 0;
-  split_geometry(c, nb, &nsplit, &bps);
+  int nsplit = 0, wpb = 0;
+  split_geometry(c, nb, &nsplit, &wpb);
   const int total = nsplit + 2 * PROM_SPLITS;
   cqa_tolerances loose = tol;
   loose.eps_total = loose.eps_key = loose.eps_val = loose.v_tol = INFINITY;
@@ -1026,7 +1026,6 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   a.nb = (int)nb;
   a.nsplit = nsplit;
   a.pstride = total;
-  a.bps = bps;
   a.n_q = hq;
   a.n_kv = hkv;
   a.slot = w.slot;

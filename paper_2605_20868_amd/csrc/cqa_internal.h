@@ -198,11 +198,10 @@ struct DecodeArgs {
   int64_t nq_cap;      // quad records per head
   int nb;              // sealed blocks
   int nsplit;
-  int bps;             // blocks per split
   int n_q, n_kv;
   int pstride;         // partial sets per (batch, q-head) row of `partials` (>= nsplit)
   int int8_query;      // matrix-core pass: 1 = INT8 x INT8 scoring of the quantised scaled query
-  int wpb;             // matrix-core pass: waves per workgroup, 8 or 4 (waves_per_workgroup)
+  int wpb;             // matrix-core pass: waves per workgroup, 8 or 4 (split_geometry)
   // promoted-block pass of the adaptive decode (null slot = not that pass)
   const int32_t* slot;      // [Bt][Hkv][4 nq_cap]: bit 0 = FP16 keys, bit 1 = FP16 values, 0 = neither
   __half* sc_k;             // layer base of the FP16 scratch's key halves [Bt * Hkv][sc_cap][16][128], or null
@@ -257,8 +256,7 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
 int32_t static_scratch(int device, void** out);
 int pick_splits(const Cache* c, int64_t n_blocks);
 int stream_nt(const Cache* c, int64_t n_blocks);
-void split_geometry(const Cache* c, int64_t n_blocks, int* nsplit, int* bps);
-int waves_per_workgroup(const Cache* c);
+void split_geometry(const Cache* c, int64_t n_blocks, int* nsplit, int* wpb);
 int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_tolerances& tol,
                         const cqa_selector& sel, float* O, cqa_head_cert* cert, uint32_t* flags,
                         uint32_t* flags_mirror, uint32_t mirror_tag, hipStream_t st);

@@ -12,6 +12,7 @@
 //   the reduction merges the splits, attends the trailing FP16 tokens exactly and
 //   evaluates  E_key = 2 V_max min(tanh Delta_h, min{1, e^{c Delta_h} alpha_hat}(e^{2 Delta_h} - 1)),
 //   E_val = sum_b rho_b eta_b  and the flag word.
+#include <algorithm>
 #include <mutex>
 
 #include "cqa_internal.h"
@@ -438,55 +439,68 @@ __global__ __launch_bounds__(256) void certified_reduce_kernel(ReduceArgs a) {
   if (hq < a.n_q) reduce_head_wave(a, b, hq, wsm[w]);
 }
 
-// Waves per workgroup of the matrix-core split pass.  Eight -- one workgroup per compute unit, two
-// waves per SIMD -- as long as there are no more (batch, kv-head) sequences than compute units: all
-// of a launch's waves are then dispatched in one sweep (with two workgroups of four waves per
-// compute unit the second one started ~2 us after the first and finished as much later), and a head
-// has half as many partial sets to merge.  With more sequences than compute units every sequence is
-// one workgroup anyway, and workgroups of four waves, two per compute unit, keep the launch at one
-// resident generation for up to twice as many of them.
-int waves_per_workgroup(const Cache* c) {
-  return (int64_t)c->desc.batch * c->desc.n_kv_heads > c->n_cu ? 4 : 8;
-}
-
-// Workgroups ("splits") per (batch, kv-head) and, for the vector-ALU kernel, blocks per split.
-// The launch is sized to ONE resident generation (the matrix-core kernel runs at two waves per
-// SIMD), so no workgroup waits for a slot and the per-wave start-up latency is paid once.  The
-// matrix-core kernel deals the head's quads of blocks evenly over all wpb * nsplit waves; short
-// sequences get fewer workgroups so that every workgroup still has a quad.
-void split_geometry(const Cache* c, int64_t n_blocks, int* nsplit, int* bps) {
-  *nsplit = 0;
-  *bps = 0;
-  if (n_blocks <= 0) return;
+// Workgroups ("splits") per (batch, kv-head) and waves per workgroup of the matrix-core split pass.
+// A compute unit holds eight of its waves: one workgroup of eight, or two of four.  The quads of a
+// head are dealt evenly over its waves, so a workgroup takes ceil(quads / (waves * splits)) rounds of
+// one quad per wave, and the launch costs about  generations * (rounds + 1):  every generation of
+// resident workgroups walks its rounds and pays about one more for start-up and merge.
+//   Up to one sequence per compute unit: as many splits as fit ONE generation (rounding up instead
+//     left a second, nearly empty one: 48 sequences of 20011 tokens, 6 splits 82.5 us, 5 splits
+//     63.2 us for pass and reduction; 72 of 14000: 86.6 -> 64.9; 25 x 4 of 10000: 83.3 -> 64.9).
+//     Eight-wave workgroups when both forms take the same rounds (half as many partial sets,
+//     all waves dispatched in one sweep: 200 of 5000: 66.9 against 72.1 us), four-wave ones where they
+//     divide better (130 of 8000: 74.3 against 81.3 us; 152 of 7000: 73.3 against 75.8 us).
+//   More sequences than compute units: four-wave workgroups, up to four splits where a last
+//     generation would be nearly empty (288 of 3600: 1 split 91.2, 2 90.9, 3 78.8 us; 384 of 2700: 1
+//     78.5, 2 82.5; 560 of 1900: 1 93.4, 2 84.5, 3 85.1; 704 of 1500: 1 90.3, 2 84.4; 1104 of 950: 1 92.7, 2 95.1).
+//     Several splits only within three generations: that bounds the partial sets (no-allocation scratch).
+// Short sequences get no more workgroups than have a quad for every wave but the last workgroup's.
+void split_geometry(const Cache* c, int64_t n_blocks, int* nsplit, int* wpb) {
   const int64_t heads = (int64_t)c->desc.batch * c->desc.n_kv_heads;
-  const int wpb = waves_per_workgroup(c);
-  int64_t want = c->forced_splits > 0 ? c->forced_splits
-                                      : ((8 / wpb) * (int64_t)c->n_cu + heads - 1) / heads;
-  if (want < 1) want = 1;
-  if (want > c->max_splits) want = c->max_splits;
-  if (want > MAX_SPLITS) want = MAX_SPLITS;
+  const int64_t limit = std::min<int64_t>(c->max_splits, MAX_SPLITS);
   const int64_t quads = (n_blocks + 3) / 4;
-  const int64_t cap = (quads + wpb - 1) / wpb;   // at least one quad per workgroup's wave
-  if (want > cap) want = cap;
-  *nsplit = (int)want;
-  *bps = (int)((n_blocks + want - 1) / want);
+  *nsplit = 0;
+  *wpb = heads > c->n_cu ? 4 : 8;
+  if (n_blocks <= 0) return;
+  int64_t best_cost = -1;
+  const auto consider = [&](int64_t w, int64_t s) {
+    s = std::max<int64_t>(std::min(std::min(s, limit), (quads + w - 1) / w), 1);
+    const int64_t slots = (8 / w) * (int64_t)c->n_cu;
+    const int64_t cost = ((heads * s + slots - 1) / slots) * ((quads + w * s - 1) / (w * s) + 1);
+    if (best_cost < 0 || cost < best_cost) {
+      best_cost = cost;
+      *nsplit = (int)s;
+      *wpb = (int)w;
+    }
+  };
+  if (c->forced_splits > 0) {
+    consider(*wpb, c->forced_splits);
+  } else if (heads <= c->n_cu) {
+    consider(8, c->n_cu / heads);
+    consider(4, 2 * c->n_cu / heads);
+  } else {
+    for (int64_t s = 1; s <= 4; ++s)
+      if (s == 1 || heads * s <= 6 * (int64_t)c->n_cu) consider(4, s);
+  }
 }
 
 // Whether the matrix-core pass reads Tier-1 with the non-temporal hint.  One decode step of a
 // model walks every layer, so the bytes read between two visits of the same record are one
-// pass's bytes times the layer count.  Up to about the size of the memory-side cache (256 MB)
-// plain loads gain from what is left there from the previous step (measured: 51.8 against
-// 52.5 us at 303 MB); beyond it the hinted loads stream faster (98 against 109 us at 606 MB).
+// pass's bytes times the layer count.  Up to the size of the memory-side cache (256 MB) plain
+// loads gain from what is left there from the previous step (four layers of 8229 tokens, 76 MB:
+// 70 us a pass against 75); beyond it the hinted loads stream faster: 278 MB 81 -> 76 us, 303 MB
+// 65 -> 60 us a step when three caches take turns and the same (59.4) when one is read over and
+// over, 606 MB 109 -> 98 us.
 int stream_nt(const Cache* c, int64_t n_blocks) {
   if (c->stream_hint == 1) return 0;
   if (c->stream_hint == 2) return 1;
   const int64_t pass = (int64_t)c->desc.batch * c->desc.n_kv_heads * ((n_blocks + 3) / 4) * QUAD_BYTES;
-  return pass * c->desc.n_layers > ((int64_t)384 << 20) ? 1 : 0;
+  return pass * c->desc.n_layers > ((int64_t)256 << 20) ? 1 : 0;
 }
 
 int pick_splits(const Cache* c, int64_t n_blocks) {
-  int nsplit = 0, bps = 0;
-  split_geometry(c, n_blocks, &nsplit, &bps);
+  int nsplit = 0, wpb = 0;
+  split_geometry(c, n_blocks, &nsplit, &wpb);
   return nsplit;
 }
 
@@ -543,8 +557,8 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
   const int64_t len = c->length[layer];
   const int64_t nb = len / BLK;
   const int r = (int)(len % BLK);
-  int nsplit = 0, bps = 0;
-  split_geometry(c, nb, &nsplit, &bps);
+  int nsplit = 0, wpb = 0;
+  split_geometry(c, nb, &nsplit, &wpb);
   const int64_t layer_head0 = head_index(c, layer, 0, 0);
   ReduceArgs ra{};
   ra.partials = partials;
@@ -598,12 +612,11 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
       a.ap_pos = len - 1;
       a.ap_max_tokens = c->desc.max_tokens;
     }
-    a.bps = bps;
     a.n_q = hq;
     a.n_kv = hkv;
     a.stream_nt = stream_nt(c, nb);
     a.int8_query = tol.int8_query;
-    a.wpb = waves_per_workgroup(c);
+    a.wpb = wpb;
     // the quantised-query scoring exists in the matrix-core pass (and in the promoted-block pass of
     // the adaptive calls), not in the vector-ALU cross-check kernel
     if (tol.int8_query != 0 && c->variant != 0) return CQA_ERR_UNSUPPORTED;

@@ -1,0 +1,45 @@
+"""The split pass's launch geometry where its rule changes: one generation of eight-wave workgroups, four-wave
+workgroups that divide better, and several splits with more sequences than compute units."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import GpuLayerCache, assert_head_matches
+
+pytestmark = pytest.mark.gpu
+
+
+# (batch, kv heads, group, tokens, splits the rule gives on 256 compute units)
+@pytest.mark.parametrize("bt,hkv,g,n,splits", [
+    (3, 16, 2, 16 * 160 + 3, 5),      # 48 sequences: floor(256 / 48), not 6
+    (13, 10, 1, 16 * 40 + 1, 3),      # 130: three four-wave workgroups each instead of one of eight waves
+    (25, 8, 1, 16 * 30, 1),           # 200: both forms take as many rounds
+    (36, 8, 1, 16 * 96 + 5, 3),       # 288: one split would leave the second half of the chip idle
+    (32, 16, 1, 16 * 9, 1),           # 512: exactly one generation
+    (70, 8, 2, 16 * 64 + 2, 2),       # 560: two generations, the second of 48 workgroups, cost more than three of half the rounds
+])
+def test_results_do_not_depend_on_the_launch_geometry(bt, hkv, g, n, splits):
+    import torch
+    print("geometry", bt, hkv, g, n, flush=True)
+    rng = np.random.default_rng(n + bt)
+    k = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    v = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    q = rng.standard_normal((bt, hkv * g, 128)).astype(np.float16)
+    rows = [0, bt // 2, bt - 1]
+    oc = oracle.OracleLayerCache(len(rows), hkv)
+    oc.append(k[rows], v[rows])
+    ref = oc.certified_decode(q[rows], oracle.Tolerances())
+    with GpuLayerCache(bt, hkv * g, hkv, n + 16, tier2=False) as gc:
+        gc.append(k, v)
+        if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+            assert gc.cqa.cqa_decode_splits(gc.h, 0) == splits
+        O, cert, flags, lm = gc.certified_decode(q, want_logmass=True)
+        for (i, h), r in zip([(i, h) for i in range(len(rows)) for h in range(hkv * g)], ref):
+            assert_head_matches(r, O[rows[i], h], cert[rows[i], h], flags[rows[i], h], (bt, hkv, g, rows[i], h))
+            assert np.abs(lm[rows[i], h] - r["blk_logmass"]).max() <= 1e-4
+        # the other sequences against one more geometry: a different split moves O only by the rounding of its
+        # weights against another running maximum (2^-17 per weight, the bound of the split-invariance test)
+        gc.cqa.cqa_set_splits(gc.h, splits + 1)
+        O2, cert2, _ = gc.certified_decode(q)
+        assert np.abs(O2 - O).max() <= 1e-4 * np.abs(O).max()
+        assert np.allclose(cert2["lse"], cert["lse"], rtol=5e-6, atol=0)
