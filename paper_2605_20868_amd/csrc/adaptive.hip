@@ -123,16 +123,32 @@ __device__ __forceinline__ void hist_add(uint32_t* hist, uint32_t bin, bool pred
   if (pred) atomicAdd(&hist[bin], 1u);
 }
 
-// Inclusive scan over the threads of a workgroup with two barriers: shuffles inside each wave,
-// then the preceding waves' totals.  `tot` = one word of LDS scratch per wave.
+// v plus the lane that DPP control CTRL points at (0 where there is none, or where ROWS masks the row out)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, true);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t scan_step(uint32_t v) { return v + dpp_or_zero<CTRL, ROWS>(v); }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int scan_step(int v) { return v + (int)dpp_or_zero<CTRL, ROWS>((uint32_t)v); }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double scan_step(double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  return v + pack_d(dpp_or_zero<CTRL, ROWS>((uint32_t)u), dpp_or_zero<CTRL, ROWS>((uint32_t)(u >> 32)));
+}
+// Inclusive scan over the threads of a workgroup with two barriers: DPP shifts inside each row of
+// 16 lanes, the totals of the preceding rows by DPP broadcasts, then the preceding waves' totals.
+// `tot` = one word of LDS scratch per wave.
 template <typename T>
 __device__ __forceinline__ T block_scan_incl(T v, T* tot, int tid) {
   const int l = tid & 63, w = tid >> 6;
-#pragma unroll
-  for (int s = 1; s < 64; s <<= 1) {
-    const T u = __shfl_up(v, s);
-    if (l >= s) v += u;
-  }
+  v = scan_step<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8
+  v = scan_step<0x112, 0xf>(v);
+  v = scan_step<0x114, 0xf>(v);
+  v = scan_step<0x118, 0xf>(v);
+  v = scan_step<0x142, 0xa>(v);   // row_bcast 15 into rows 1 and 3
+  v = scan_step<0x143, 0xc>(v);   // row_bcast 31 into rows 2 and 3
   __syncthreads();            // protects `tot` against the previous use
   if (l == 63) tot[w] = v;
   __syncthreads();
@@ -717,27 +733,13 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
   __shared__ double s_sum[3];
   __shared__ float wsm[64];
   __shared__ AdaptiveIn s_ad;
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {
-    // larger value wins; equal values: the lower block index (-1 = nothing seen loses)
-    const float ox = __shfl_xor(best_x, m);
-    const int oix = __shfl_xor(ix, m);
-    if (oix >= 0 && (ix < 0 || ox > best_x || (ox == best_x && oix < ix))) {
-      best_x = ox;
-      ix = oix;
-    }
-    const float o8 = __shfl_xor(best_8, m);
-    const int oi8 = __shfl_xor(i8, m);
-    if (oi8 >= 0 && (i8 < 0 || o8 > best_8 || (o8 == best_8 && oi8 < i8))) {
-      best_8 = o8;
-      i8 = oi8;
-    }
-    tail_max = fmaxf(tail_max, __shfl_xor(tail_max, m));
-    maxc8 = fmaxf(maxc8, __shfl_xor(maxc8, m));
-    tail_mass += __shfl_xor(tail_mass, m);
-    l8u += __shfl_xor(l8u, m);
-    ev8u += __shfl_xor(ev8u, m);
-  }
+  wave_best(best_x, ix);
+  wave_best(best_8, i8);
+  tail_max = wave_max(tail_max);
+  maxc8 = wave_max(maxc8);
+  tail_mass = wave_sum_d(tail_mass);
+  l8u = wave_sum_d(l8u);
+  ev8u = wave_sum_d(ev8u);
   if ((tid & 63) == 0) {
     const int w = tid >> 6;
     w_bx[w] = best_x;
@@ -756,14 +758,8 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
     int jx = w_ix[0], j8 = w_i8[0];
     double ms = w_mass[0], lu = w_l8u[0], eu = w_ev8u[0];
     for (int w = 1; w < NW; ++w) {
-      if (w_ix[w] >= 0 && (jx < 0 || w_bx[w] > bx || (w_bx[w] == bx && w_ix[w] < jx))) {
-        bx = w_bx[w];
-        jx = w_ix[w];
-      }
-      if (w_i8[w] >= 0 && (j8 < 0 || w_b8[w] > b8 || (w_b8[w] == b8 && w_i8[w] < j8))) {
-        b8 = w_b8[w];
-        j8 = w_i8[w];
-      }
+      best_merge(bx, jx, w_bx[w], w_ix[w]);
+      best_merge(b8, j8, w_b8[w], w_i8[w]);
       tm = fmaxf(tm, w_tm[w]);
       mc = fmaxf(mc, w_mc[w]);
       ms += w_mass[w];

@@ -202,8 +202,7 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a) {
       }
 #pragma unroll
       for (int h = 0; h < G; ++h) {
-        dot[h] += __shfl_xor(dot[h], 16);
-        dot[h] += __shfl_xor(dot[h], 32);
+        dot[h] = sum_x32(sum_x16(dot[h]));
         s16[h] = dot[h] * inv_sqrt_d;
       }
       wave_sync();   // the LDS buffer is rewritten below
@@ -223,9 +222,7 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a) {
         rsum[h] = 0.0f;
         sqv[h] = 1.0f;
         if (a.int8_query) {
-          float amax = fmaxf(fabsf(q0), fabsf(q1));
-#pragma unroll
-          for (int m = 1; m < 64; m <<= 1) amax = fmaxf(amax, __shfl_xor(amax, m));
+          const float amax = wave_max(fmaxf(fabsf(q0), fabsf(q1)));
           const float inv = amax > 0.0f ? 127.0f / amax : 0.0f;
           const float sq = amax / 127.0f;
           const float MAGIC = 12582912.0f;   // 1.5 * 2^23: fl(x + MAGIC) - MAGIC = round-half-even(x)
@@ -243,15 +240,12 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a) {
         reinterpret_cast<float2*>(&qs[w][h][0])[l] = make_float2(q0, q1);
       }
 #pragma unroll
-      for (int m = 1; m < 64; m <<= 1) {
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-          csum[h] += __shfl_xor(csum[h], m);
-          dsum[h] += __shfl_xor(dsum[h], m);
-          if (a.int8_query) {
-            tsum[h] += __shfl_xor(tsum[h], m);
-            rsum[h] += __shfl_xor(rsum[h], m);
-          }
+      for (int h = 0; h < G; ++h) {
+        csum[h] = wave_sum(csum[h]);
+        dsum[h] = wave_sum(dsum[h]);
+        if (a.int8_query) {
+          tsum[h] = wave_sum(tsum[h]);
+          rsum[h] = wave_sum(rsum[h]);
         }
       }
       if (a.int8_query) {
@@ -275,8 +269,7 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a) {
       }
 #pragma unroll
       for (int h = 0; h < G; ++h) {
-        dot[h] += __shfl_xor(dot[h], 16);
-        dot[h] += __shfl_xor(dot[h], 32);
+        dot[h] = sum_x32(sum_x16(dot[h]));
         // quantised query: s_q * (sum T byte - 128 sum T) + q.z, the bracket in exact integers
         s8[h] = fmaf(sqv[h], dot[h] - 128.0f * tsum[h], csum[h]) * inv_sqrt_d;
       }
@@ -293,13 +286,9 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a) {
     for (int h = 0; h < G; ++h) {
       const bool use16 = ((hkb >> h) & 1) != 0;
       const float s = use16 ? s16[h] : s8[h];
-      float mb = s;
-#pragma unroll
-      for (int m = 1; m < 16; m <<= 1) mb = fmaxf(mb, __shfl_xor(mb, m));
+      const float mb = row_max(s);
       const float pt = __expf(s - mb);
-      float sb = pt;
-#pragma unroll
-      for (int m = 1; m < 16; m <<= 1) sb += __shfl_xor(sb, m);
+      const float sb = row_sum(pt);
       const float lb = mb + __logf(sb);
       const float m_new = fmaxf(m_run[h], mb);
       alpha[h] = __expf(m_run[h] - m_new);
@@ -357,9 +346,7 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a) {
     // deviations are non-negative floats: their bit patterns order like integers
 #pragma unroll
     for (int h = 0; h < G; ++h) {
-      float d = dev[h];
-#pragma unroll
-      for (int m = 1; m < 64; m <<= 1) d = fmaxf(d, __shfl_xor(d, m));
+      const float d = wave_max(dev[h]);
       if (l == 0 && d > 0.0f)
         atomicMax(reinterpret_cast<int*>(a.score_dev + (int64_t)b * a.n_q + kvh * G + h), __float_as_int(d));
     }
@@ -371,7 +358,7 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a) {
   for (int gq = 0; gq < 4; ++gq)
 #pragma unroll
     for (int h = 0; h < G; ++h) {
-      const float v = acc[gq][h] + __shfl_xor(acc[gq][h], 32);
+      const float v = sum_x32(acc[gq][h]);
       if (vo == 0) mo[(w * G + h) * D + (vgh * 4 + gq) * 16 + vn] = v;
     }
   if (l == 0) {

@@ -265,9 +265,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   // Lane (h, kg) reads channels (u>>1)*64 + kg*16 + (u&1)*8 + e of head h when it forms slice u.
   if (w < 4) {   // qbuf has four rows; the other waves of the workgroup have none to prepare
     float2 qq = __half22float2(q_in);
-    float qmax = fmaxf(fabsf(qq.x), fabsf(qq.y));
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) qmax = fmaxf(qmax, __shfl_xor(qmax, m));
+    const float qmax = wave_max(fmaxf(fabsf(qq.x), fabsf(qq.y)));
     const float bound = qmax * sigmax_head;
     int e = 0;
     (void)frexpf(bound, &e);                       // bound < 2^e
@@ -417,8 +415,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
           amax = fmaxf(amax, fabsf(t));
         }
       }
-      amax = fmaxf(amax, __shfl_xor(amax, 16));
-      amax = fmaxf(amax, __shfl_xor(amax, 32));
+      amax = max_x32(max_x16(amax));
       // binary32, correctly rounded quotients (the power-of-two pre-scale of q commutes with both)
       const float inv = amax > 0.0f ? 127.0f / amax : 0.0f;
       sq = amax / 127.0f;
@@ -465,14 +462,10 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
     }
     // per-block constant c_b = q.z and Delta_b (both still times S_h): summed over the four
     // channel slices, then handed to the rows that own head kg
-    float cb = csum;
-    cb += __shfl_xor(cb, 16);
-    cb += __shfl_xor(cb, 32);
-    dsum += __shfl_xor(dsum, 16);
-    dsum += __shfl_xor(dsum, 32);
+    const float cb = sum_x32(sum_x16(csum));
+    dsum = sum_x32(sum_x16(dsum));
     if constexpr (Q8) {
-      qres += __shfl_xor(qres, 16);
-      qres += __shfl_xor(qres, 32);
+      qres = sum_x32(sum_x16(qres));
       dsum = fmaf(256.0f, qres, dsum);   // Delta_b + Delta^q_b = (sum |q| sigma + 256 sum |q~ - s_q T|) / (2 sqrt d)
       cbuf[w][2][h][j] = sq;
     }
@@ -635,8 +628,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   //      complete in every lane of row kg
 #pragma unroll
   for (int gs = 0; gs < 2; ++gs) {
-    offacc[gs] += __shfl_xor(offacc[gs], 16);
-    offacc[gs] += __shfl_xor(offacc[gs], 32);
+    offacc[gs] = sum_x32(sum_x16(offacc[gs]));
   }
 #pragma unroll
   for (int g = 0; g < 8; ++g) {

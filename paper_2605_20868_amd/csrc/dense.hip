@@ -175,19 +175,12 @@ __device__ __forceinline__ void dense_split_work(const __half* __restrict__ q, c
   // merge the wave's four rows
 #pragma unroll
   for (int h = 0; h < G; ++h) {
-    float M = fmaxf(m_run[h], __shfl_xor(m_run[h], 16));
-    M = fmaxf(M, __shfl_xor(M, 32));
+    const float M = max_x32(max_x16(m_run[h]));
     const float f = __builtin_amdgcn_exp2f(m_run[h] - M);
-    float L = l_run[h] * f;
-    L += __shfl_xor(L, 16);
-    L += __shfl_xor(L, 32);
+    const float L = sum_x32(sum_x16(l_run[h] * f));
     float x[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      x[j] = acc[j][h] * f;
-      x[j] += __shfl_xor(x[j], 16);
-      x[j] += __shfl_xor(x[j], 32);
-    }
+    for (int j = 0; j < 8; ++j) x[j] = sum_x32(sum_x16(acc[j][h] * f));
     if (row == 0) {
       *reinterpret_cast<float4*>(&sm.mo[w][h][c8 * 8]) = make_float4(x[0], x[1], x[2], x[3]);
       *reinterpret_cast<float4*>(&sm.mo[w][h][c8 * 8 + 4]) = make_float4(x[4], x[5], x[6], x[7]);
