@@ -731,7 +731,6 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
   __shared__ float s_top[4];
   __shared__ int s_topi[2];
   __shared__ double s_sum[3];
-  __shared__ float wsm[64];
   __shared__ AdaptiveIn s_ad;
   wave_best(best_x, ix);
   wave_best(best_8, i8);
@@ -881,14 +880,15 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
     a.alpha_out[row] = ad.alpha;
   }
   __syncthreads();
-  if (tid < 64) reduce_head_wave(ra, b, hq, wsm, &s_ad);
+  if (tid < 64) reduce_head_wave<64>(ra, b, hq, &s_ad);
 }
 
 }  // namespace
 
 int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_tolerances& tol,
                         const cqa_selector& sel, float* O, cqa_head_cert* cert, uint32_t* flags,
-                        uint32_t* flags_mirror, uint32_t mirror_tag, hipStream_t st) {
+                        uint32_t* flags_mirror, uint32_t mirror_tag, hipStream_t st, uint32_t* raised,
+                        uint32_t raised_tag) {
   // quantised-query scoring: the pass over all blocks scores on the INT8 matrix cores, the
   // promoted-block pass reproduces those scores for the blocks (and heads) that stay in INT8
   if (tol.int8_query != 0 && c->variant != 0) return CQA_ERR_UNSUPPORTED;
@@ -912,7 +912,8 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   loose.force_flags = 0;
   if (nb == 0) {
     // nothing sealed: the exact trailing tokens are the answer, with the caller's thresholds
-    return launch_certified(c, layer, q, tol, O, cert, flags, flags_mirror, mirror_tag, nullptr, st);
+    return launch_certified(c, layer, q, tol, O, cert, flags, flags_mirror, mirror_tag, nullptr, st, nullptr, nullptr, 0,
+                            nullptr, nullptr, raised, raised_tag);
   }
   int32_t rc = launch_certified(c, layer, q, loose, O, cert, flags, nullptr, 0u, w.lm8, st, nullptr, nullptr,
                                 total, w.eta_blk);
@@ -1006,6 +1007,8 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   ra.flags = flags;
   ra.flags_mirror = flags_mirror;
   ra.mirror_tag = mirror_tag;
+  ra.raised = raised;
+  ra.raised_tag = raised_tag;
   ra.tol = tol;
   ra.nsplit = total;
   ra.nb = (int)nb;

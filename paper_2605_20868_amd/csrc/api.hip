@@ -215,7 +215,7 @@ int32_t cqa_workspace_bytes(const cqa_cache_desc* desc, int64_t* device_bytes,
     if (t2) {
       n += 3 * s.ad_lm + 2 * s.ad_sel + 4 * s.ad_head + 2 * s.ad_mask + s.ad_slot + s.ad_group + s.ad_ulist +
            s.ad_eta + 8;
-      n += 4 * s.stage + s.ladder_ws + groups * 4 + 8;
+      n += 4 * s.stage + s.ladder_ws + groups * 4 + 12;
       // ... and what the first cqa_set_scratch_slots(n > 0) adds: key and value halves, map, three words per slot
       n += 2 * s.sc_k + s.sc_map + 3 * s.sc_tag;
     }
@@ -319,8 +319,8 @@ static int32_t create_cache(const cqa_cache_desc* desc, __half* caller_k, __half
     CQA_ALLOC_DEV(c->ladder_ws, s.ladder_ws);
     CQA_ALLOC_DEV(c->ladder_tickets, (int64_t)desc->batch * desc->n_kv_heads * 4);
     CQA_TRY(hipMemset(c->ladder_tickets, 0, (size_t)desc->batch * desc->n_kv_heads * 4));
-    CQA_ALLOC_DEV(c->ladder_counts, 8);
-    CQA_TRY(hipMemset(c->ladder_counts, 0, 8));
+    CQA_ALLOC_DEV(c->ladder_counts, 12);
+    CQA_TRY(hipMemset(c->ladder_counts, 0, 12));
     if (c->t2_borrowed) {
       c->t2_k = caller_k;
       c->t2_v = caller_v;
@@ -964,14 +964,16 @@ int32_t cqa_decode_step_enqueue(cqa_cache* h, int32_t layer, const void* k_fp16_
     if (rc != CQA_OK) return rc;
   }
   if (c->length[layer] <= 0) return CQA_ERR_INVALID_ARG;
+  const uint32_t tag = next_ladder_tag(c);
   int32_t rc = launch_certified(c, layer, (const __half*)q_fp16_dev, *tol, O_dev, cert_dev, flags_dev,
-                                nullptr, 0u, nullptr, (hipStream_t)stream, rk, rv);
+                                nullptr, 0u, nullptr, (hipStream_t)stream, rk, rv, 0, nullptr, nullptr,
+                                ladder_raised(c), tag);
   if (rc != CQA_OK) {
     if (rk != nullptr) c->length[layer] -= 1;   // the launch that was to store the token did not happen
     return rc;
   }
   return launch_dense_ladder(c, layer, (const __half*)q_fp16_dev, tol->rung4_min_groups, O_dev,
-                             cert_dev, flags_dev, (hipStream_t)stream);
+                             cert_dev, flags_dev, tag, (hipStream_t)stream);
 }
 
 int32_t cqa_ladder_counts(cqa_cache* h, int64_t* rung3_steps, int64_t* rung4_steps) {
@@ -1016,11 +1018,12 @@ int32_t cqa_adaptive_step_enqueue(cqa_cache* h, int32_t layer, const void* q_fp1
   if (rc != CQA_OK) return rc;
   rc = check_selector(h, sel);
   if (rc != CQA_OK) return rc;
+  const uint32_t tag = next_ladder_tag(&h->impl);
   rc = launch_adaptive(&h->impl, layer, (const __half*)q_fp16_dev, *tol, *sel, O_dev, cert_dev,
-                       flags_dev, nullptr, 0u, (hipStream_t)stream);
+                       flags_dev, nullptr, 0u, (hipStream_t)stream, ladder_raised(&h->impl), tag);
   if (rc != CQA_OK) return rc;
   return launch_dense_ladder(&h->impl, layer, (const __half*)q_fp16_dev, tol->rung4_min_groups,
-                             O_dev, cert_dev, flags_dev, (hipStream_t)stream);
+                             O_dev, cert_dev, flags_dev, tag, (hipStream_t)stream);
 }
 
 int32_t cqa_adaptive_state(cqa_cache* h, int32_t layer, int32_t* k_star_host,

@@ -155,7 +155,8 @@ struct Cache {
   int64_t nq_cap;            // quad records of capacity per head
   float* ladder_ws;          // device-resolved ladder: split partials, arrival counters, rung counters
   uint32_t* ladder_tickets;
-  uint32_t* ladder_counts;
+  uint32_t* ladder_counts;   // [2] steps served by Rung 3 / 4, [1] word of the last step that raised a flag
+  uint32_t ladder_seq;       // host: number of the last enqueue-only step, never 0
   float* sigmax;             // [heads_total] running max of sigma (non-negative: ordered as ints)
   // trailing FP16 partial blocks [heads_total][16][128]
   __half* trail_k;
@@ -201,6 +202,7 @@ struct DecodeArgs {
   int n_q, n_kv;
   int pstride;         // partial sets per (batch, q-head) row of `partials` (>= nsplit)
   int int8_query;      // matrix-core pass: 1 = INT8 x INT8 scoring of the quantised scaled query
+  int keep_sets;       // matrix-core pass: 1 = the partial sets are read by a later launch too
   int wpb;             // matrix-core pass: waves per workgroup, 8 or 4 (split_geometry)
   // promoted-block pass of the adaptive decode (null slot = not that pass)
   const int32_t* slot;      // [Bt][Hkv][4 nq_cap]: bit 0 = FP16 keys, bit 1 = FP16 values, 0 = neither
@@ -252,16 +254,19 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
                          uint32_t mirror_tag, float* blk_logmass, hipStream_t st,
                          const __half* k_new = nullptr,
                          const __half* v_new = nullptr, int pstride = 0, float* eta_out = nullptr,
-                         float* partials = nullptr);   // null = the cache's own split workspace
+                         float* partials = nullptr,   // null = the cache's own split workspace
+                         uint32_t* raised = nullptr, uint32_t raised_tag = 0u);
 int32_t static_scratch(int device, void** out);
 int pick_splits(const Cache* c, int64_t n_blocks);
 int stream_nt(const Cache* c, int64_t n_blocks);
 void split_geometry(const Cache* c, int64_t n_blocks, int* nsplit, int* wpb);
 int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_tolerances& tol,
                         const cqa_selector& sel, float* O, cqa_head_cert* cert, uint32_t* flags,
-                        uint32_t* flags_mirror, uint32_t mirror_tag, hipStream_t st);
-int32_t launch_split_mfma(const DecodeArgs& a, int group, dim3 grid, hipEvent_t ev0, hipEvent_t ev1,
-                          hipStream_t st);
+                        uint32_t* flags_mirror, uint32_t mirror_tag, hipStream_t st,
+                        uint32_t* raised = nullptr, uint32_t raised_tag = 0u);
+struct ReduceArgs;
+int32_t launch_split_mfma(const DecodeArgs& a, const ReduceArgs& ra, int group, dim3 grid, hipEvent_t ev0,
+                          hipEvent_t ev1, hipStream_t st);
 
 int32_t launch_stream_read(const uint8_t* t1, int64_t nq_cap, int nb, dim3 grid, bool nt, int wpb,
                            uint32_t* sink, hipStream_t st);
@@ -289,6 +294,9 @@ struct LadderArgs {
   float* ws;                // [Bt * Hq][nsplit][4 + 128]
   uint32_t* tickets;        // [Bt * Hkv], zero between launches
   uint32_t* counts;         // [2]: steps served by Rung 3, by Rung 4
+  const uint32_t* raised;   // equals raised_tag when some head of this step requests a fallback (it may
+  uint32_t raised_tag;      // do so without one: a recorded step that is replayed keeps its number)
+  int groups;               // Bt * Hkv
   float* O;
   cqa_head_cert* cert;
   uint32_t* flags;
@@ -296,6 +304,11 @@ struct LadderArgs {
 int ladder_splits(const Cache* c, int64_t n_tokens);
 int64_t ladder_ws_floats(int64_t rows);
 int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_groups, float* O,
-                            cqa_head_cert* cert, uint32_t* flags, hipStream_t st);
+                            cqa_head_cert* cert, uint32_t* flags, uint32_t raised_tag, hipStream_t st);
+inline uint32_t* ladder_raised(Cache* c) { return c->ladder_counts + 2; }
+inline uint32_t next_ladder_tag(Cache* c) {
+  c->ladder_seq = c->ladder_seq == 0xFFFFFFFFu ? 1u : c->ladder_seq + 1u;
+  return c->ladder_seq;
+}
 
 }  // namespace cqa

@@ -121,7 +121,7 @@ constexpr int P_HEAD = 4 * BLK + 16;    // floats per head in the probability bu
 //     grows by the explicit term (128 / sqrt d) sum_c |q~_c - s_q T_c|.
 // W: waves per workgroup, 8 (one workgroup per compute unit) or 4 (two); either way a SIMD holds two waves.
 template <int G, bool LM, bool NT, bool Q8, int W>
-__global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(DecodeArgs a, ReduceArgs ra) {
   const int l = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = l & 15, kg = l >> 4;
@@ -641,55 +641,70 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   }
   if (n == 0 && kg < G) {
     float* m = ms[w][kg < G ? kg : 0];
-    m[0] = m_run * LN2;   // the running maximum was kept in base 2
-    m[1] = l_run;
-    m[2] = ev;
-    m[3] = evmax;
-    m[4] = dmax;
-    m[5] = vmax;
-    m[6] = t1;
-    m[7] = t2;
-    m[8] = __int_as_float(i1);
+    m[P_M] = m_run * LN2;   // the running maximum was kept in base 2
+    m[P_L] = l_run;
+    m[P_EV] = ev;
+    m[P_EVMAX] = evmax;
+    m[P_DMAX] = dmax;
+    m[P_VMAX] = vmax;
+    m[P_T1] = t1;
+    m[P_T2] = t2;
+    m[P_I1] = __int_as_float(i1);
+  }
+  // ---- the rows themselves: a sequence served by one workgroup is finished here, from the waves'
+  //      states, and needs no launch for the reduction (64 sequences x 8 KV heads of 4107 tokens:
+  //      115 -> 106 us a step, with the ladder's early exit).  With several workgroups the reduction is a launch of its own: the last one
+  //      to arrive finishing the rows (agent-scope stores, a ticket, agent-scope loads) measured
+  //      8.9 -> 15.8 us for this launch at 1K and 11.7 -> 18.2 us at 8K, against a reduction of 4.7 us.
+  const int hq0 = kvh * G;
+  const bool finish = a.nsplit == 1;
+  TrailRegs tr;
+  if (finish && w < G) {
+    __builtin_amdgcn_s_setprio(2);
+    load_trail(ra, b, hq0 + w, a.ap_k_new, a.ap_v_new, tr);
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < G * D; idx += 64 * W) {
-    const int hh = idx / D, c = idx % D;
-    float M = -INFINITY;
+  if (!finish || a.keep_sets) {
+    for (int idx = threadIdx.x; idx < G * D; idx += 64 * W) {
+      const int hh = idx / D, c = idx % D;
+      float M = -INFINITY;
 #pragma unroll
-    for (int ww = 0; ww < W; ++ww) M = fmaxf(M, ms[ww][hh][0]);
-    const float Mr = (M == -INFINITY) ? 0.0f : M;   // a workgroup that drew no quad writes zeros
-    float o = 0.0f;
+      for (int ww = 0; ww < W; ++ww) M = fmaxf(M, ms[ww][hh][P_M]);
+      const float Mr = (M == -INFINITY) ? 0.0f : M;   // a workgroup that drew no quad writes zeros
+      float o = 0.0f;
 #pragma unroll
-    for (int ww = 0; ww < W; ++ww) o += __expf(ms[ww][hh][0] - Mr) * mo[ww][hh][c];
-    a.partials[(((int64_t)b * a.n_q + kvh * G + hh) * a.pstride + split) * PART_FLOATS + P_O + c] = o;
-  }
-  if (threadIdx.x < G) {
-    const int hh = threadIdx.x;
-    float M = -INFINITY;
-    for (int ww = 0; ww < W; ++ww) M = fmaxf(M, ms[ww][hh][0]);
-    const float Mr = (M == -INFINITY) ? 0.0f : M;
-    float L = 0.0f, EV = 0.0f, EVM = 0.0f, DM = 0.0f, VM = 0.0f, T1 = -INFINITY, T2 = -INFINITY;
-    int I1 = -1;
-    for (int ww = 0; ww < W; ++ww) {
-      const float fw = __expf(ms[ww][hh][0] - Mr);
-      L += fw * ms[ww][hh][1];
-      EV += fw * ms[ww][hh][2];
-      EVM = fmaxf(EVM, fw * ms[ww][hh][3]);
-      DM = fmaxf(DM, ms[ww][hh][4]);
-      VM = fmaxf(VM, ms[ww][hh][5]);
-      top2_merge(T1, I1, T2, ms[ww][hh][6], __float_as_int(ms[ww][hh][8]), ms[ww][hh][7]);
+      for (int ww = 0; ww < W; ++ww) o += __expf(ms[ww][hh][P_M] - Mr) * mo[ww][hh][c];
+      a.partials[(((int64_t)b * a.n_q + hq0 + hh) * a.pstride + split) * PART_FLOATS + P_O + c] = o;
     }
-    float* pp = a.partials + (((int64_t)b * a.n_q + kvh * G + hh) * a.pstride + split) * PART_FLOATS;
-    pp[P_M] = M;
-    pp[P_L] = L;
-    pp[P_EV] = EV;
-    pp[P_EVMAX] = EVM;
-    pp[P_DMAX] = DM;
-    pp[P_VMAX] = VM;
-    pp[P_T1] = T1;
-    pp[P_T2] = T2;
-    pp[P_I1] = __int_as_float(I1);
+    if (threadIdx.x < G) {
+      const int hh = threadIdx.x;
+      float M = -INFINITY;
+      for (int ww = 0; ww < W; ++ww) M = fmaxf(M, ms[ww][hh][P_M]);
+      const float Mr = (M == -INFINITY) ? 0.0f : M;
+      float L = 0.0f, EV = 0.0f, EVM = 0.0f, DM = 0.0f, VM = 0.0f, T1 = -INFINITY, T2 = -INFINITY;
+      int I1 = -1;
+      for (int ww = 0; ww < W; ++ww) {
+        const float fw = __expf(ms[ww][hh][P_M] - Mr);
+        L += fw * ms[ww][hh][P_L];
+        EV += fw * ms[ww][hh][P_EV];
+        EVM = fmaxf(EVM, fw * ms[ww][hh][P_EVMAX]);
+        DM = fmaxf(DM, ms[ww][hh][P_DMAX]);
+        VM = fmaxf(VM, ms[ww][hh][P_VMAX]);
+        top2_merge(T1, I1, T2, ms[ww][hh][P_T1], __float_as_int(ms[ww][hh][P_I1]), ms[ww][hh][P_T2]);
+      }
+      float* pp = a.partials + (((int64_t)b * a.n_q + hq0 + hh) * a.pstride + split) * PART_FLOATS;
+      pp[P_M] = M;
+      pp[P_L] = L;
+      pp[P_EV] = EV;
+      pp[P_EVMAX] = EVM;
+      pp[P_DMAX] = DM;
+      pp[P_VMAX] = VM;
+      pp[P_T1] = T1;
+      pp[P_T2] = T2;
+      pp[P_I1] = __int_as_float(I1);
+    }
   }
+  if (finish && w < G) finish_head(ra, b, hq0 + w, reduce_lds(ms[0][w], G * 12, mo[0][w], G * D, W), tr, nullptr);
 }
 
 #undef CQA_REC
@@ -745,17 +760,17 @@ int32_t launch_stream_read(const uint8_t* t1, int64_t nq_cap, int nb, dim3 grid,
 
 // ev0 / ev1 (both or neither): HIP events attached to the dispatch itself, so their elapsed time
 // is the kernel's own execution time (what a kernel trace reports), not launch overhead.
-int32_t launch_split_mfma(const DecodeArgs& a, int group, dim3 grid, hipEvent_t ev0, hipEvent_t ev1,
-                          hipStream_t st) {
+int32_t launch_split_mfma(const DecodeArgs& a, const ReduceArgs& ra, int group, dim3 grid, hipEvent_t ev0,
+                          hipEvent_t ev1, hipStream_t st) {
   const bool lm = a.blk_logmass != nullptr;
   if (a.wpb != 4 && a.wpb != 8) return CQA_ERR_INVALID_ARG;
 #define CQA_LAUNCH_W(GG, NTV, Q8V, WV)                                                             \
   if (lm)                                                                                          \
     hipExtLaunchKernelGGL((certified_split_mfma_kernel<GG, true, NTV, Q8V, WV>), grid, dim3(64 * WV), 0, st, \
-                          ev0, ev1, 0, a);                                                         \
+                          ev0, ev1, 0, a, ra);                                                     \
   else                                                                                             \
     hipExtLaunchKernelGGL((certified_split_mfma_kernel<GG, false, NTV, Q8V, WV>), grid, dim3(64 * WV), 0,   \
-                          st, ev0, ev1, 0, a);
+                          st, ev0, ev1, 0, a, ra);
 #define CQA_LAUNCH_Q(GG, NTV, Q8V)                                                                 \
   if (a.wpb == 8) { CQA_LAUNCH_W(GG, NTV, Q8V, 8) } else { CQA_LAUNCH_W(GG, NTV, Q8V, 4) }
 #define CQA_LAUNCH_NT(GG, NTV)                                                                     \

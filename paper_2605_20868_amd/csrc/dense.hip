@@ -310,25 +310,26 @@ __global__ __launch_bounds__(128) void dense_reduce_kernel(DenseArgs a) {
 
 // The fallback ladder resolved on the device (the paper's "Fallback Ladder": Rung 3 returns the
 // dense FP16 result for the flagged heads, Rung 4 for every head of the layer-step).  Launched
-// behind the reduction on every step, grid (splits, batch * kv heads).  Every workgroup reads
-// the step's flag words and takes the ladder decision itself -- no head flagged: nothing to do;
+// behind the reduction on every step.  The reduction leaves the step's number in `raised` when it
+// flags a head; without it every workgroup leaves at once (one word instead of all flag words:
+// 2.5 -> 1.6 us at 8K, 7.3 -> 5.7 us with 64 x 8 KV groups).  Otherwise every workgroup reads the step's flag words and takes the ladder decision itself -- no head flagged: nothing to do;
 // a PRECOND flag anywhere, or at least rung4_min_groups (> 0) flagged KV groups: all groups
-// are served (Rung 4); else the flagged groups (Rung 3) -- and leaves at once unless its KV
-// group is served.  The workgroups of a served group attend the group's FP16 originals
+// are served (Rung 4); else the flagged groups (Rung 3) -- and walks the (KV group, split) items of the
+// served groups.  An item attends a run of the group's FP16 originals
 // straight from the pinned host arrays (the device reads host memory over the link: no copy
-// call, no staging buffer, no host decision), and the last of them to arrive merges the
+// call, no staging buffer, no host decision), and the last of a group's items to arrive merges the
 // splits and rewrites O, the certificate and the rung bits of the heads that are served.
 template <int G>
 __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
-  const int split = blockIdx.x, grp = blockIdx.y;
-  __shared__ int s_rung, s_mine, s_last;
-  __shared__ int s_cnt[4], s_pre[4], s_my[4];
+  if (*a.raised != a.raised_tag) return;
+  __shared__ int s_rung, s_last;
+  __shared__ int s_cnt[4], s_pre[4];
   {
     // each wave takes every fourth chunk of 64 flag words (a group's heads never straddle a
     // chunk: G divides 64), four chunks per trip with all loads issued first
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     int flagged_groups = 0;
-    bool precond = false, mine = false;
+    bool precond = false;
     for (int base = 0; base < a.n_rows; base += 1024) {
       uint32_t f[4];
 #pragma unroll
@@ -338,7 +339,6 @@ __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int i0 = base + (j * 4 + w) * 64;
         const uint64_t m = __ballot((f[j] & CQA_FLAG_ANY) != 0u);
         precond = precond || __ballot((f[j] & CQA_FLAG_PRECOND) != 0u) != 0ull;
         uint64_t gm = m;
@@ -346,59 +346,64 @@ __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
         for (int jj = 1; jj < G; ++jj) gm |= m >> jj;
         gm &= G == 1 ? ~0ull : (G == 2 ? 0x5555555555555555ull : 0x1111111111111111ull);
         flagged_groups += __popcll(gm);
-        const int r0 = grp * G - i0;
-        if (r0 >= 0 && r0 < 64) mine = mine || ((m >> r0) & ((1ull << G) - 1ull)) != 0ull;
       }
     }
     if (l == 0) {
       s_cnt[w] = flagged_groups;
       s_pre[w] = precond ? 1 : 0;
-      s_my[w] = mine ? 1 : 0;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
       const int cnt = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
       const bool pre = (s_pre[0] | s_pre[1] | s_pre[2] | s_pre[3]) != 0;
-      const bool my = (s_my[0] | s_my[1] | s_my[2] | s_my[3]) != 0;
       int rung = cnt > 0 ? 3 : 0;
       if (rung != 0 && (pre || (a.rung4_min_groups > 0 && cnt >= a.rung4_min_groups))) rung = 4;
       s_rung = rung;
-      s_mine = (rung == 4 || my) ? 1 : 0;
-      if (rung != 0 && split == 0 && grp == 0) atomicAdd(a.counts + (rung - 3), 1u);
+      if (rung != 0 && blockIdx.x == 0) atomicAdd(a.counts + (rung - 3), 1u);
     }
   }
   __syncthreads();
   const int rung = s_rung;
-  if (rung == 0 || s_mine == 0) return;
+  if (rung == 0) return;
 
-  const int64_t row0 = (int64_t)grp * G;
-  float* ws = a.ws + row0 * a.nsplit * DP_FLOATS;
   __shared__ __align__(16) DenseSmem<G, 4> sm;
-  const int64_t t0 = (int64_t)split * a.tiles_per_split;
-  const int64_t t1 = min(t0 + (int64_t)a.tiles_per_split, (a.n_tokens + LADDER_TILE - 1) / LADDER_TILE);
-  dense_split_work<G, 4, LADDER_TILE, false>(a.q + row0 * D, a.t2_k + (int64_t)grp * a.max_tokens * D,
-                         a.t2_v + (int64_t)grp * a.max_tokens * D, a.n_tokens, t0, t1, sm);
-  dense_store_partials<G, 4>(sm, ws, a.nsplit, split);
-  // every thread publishes its partial stores device-wide before the workgroup draws its ticket
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t* tk = a.tickets + grp;
-    const uint32_t t = __hip_atomic_fetch_add(tk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const bool last = t == (uint32_t)a.nsplit - 1u;
-    if (last) __hip_atomic_store(tk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
-    s_last = last ? 1 : 0;
-  }
-  __syncthreads();
-  if (s_last == 0) return;
-  __threadfence();
-  for (int idx = threadIdx.x; idx < G * D; idx += 256) {
-    const int h = idx / D, c = idx % D;
-    const int64_t row = row0 + h;
-    if (rung != 4 && (a.flags[row] & CQA_FLAG_ANY) == 0u) continue;   // Rung 3 serves flagged heads only
-    // (a wave's 64 channels belong to one row, so the branch above is uniform in the wave)
-    a.O[row * D + c] = dense_merge_row(ws + (int64_t)h * a.nsplit * DP_FLOATS, a.nsplit, c);
-    if (c == 0) dense_mark_served(a.cert, a.flags, row, rung);
+  const int64_t items = (int64_t)a.groups * a.nsplit;
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+    const int64_t grp = item / a.nsplit;
+    const int split = (int)(item - grp * a.nsplit);
+    const int64_t row0 = grp * G;
+    // (the rung bits that a finished group's rows get do not touch the bits looked at here)
+    bool mine = rung == 4;
+    for (int h = 0; h < G && !mine; ++h) mine = (a.flags[row0 + h] & CQA_FLAG_ANY) != 0u;
+    if (!mine) continue;   // uniform over the workgroup
+    float* ws = a.ws + row0 * a.nsplit * DP_FLOATS;
+    const int64_t t0 = (int64_t)split * a.tiles_per_split;
+    const int64_t t1 = min(t0 + (int64_t)a.tiles_per_split, (a.n_tokens + LADDER_TILE - 1) / LADDER_TILE);
+    __syncthreads();       // the previous item's LDS has been read
+    dense_split_work<G, 4, LADDER_TILE, false>(a.q + row0 * D, a.t2_k + grp * a.max_tokens * D,
+                                               a.t2_v + grp * a.max_tokens * D, a.n_tokens, t0, t1, sm);
+    dense_store_partials<G, 4>(sm, ws, a.nsplit, split);
+    // every thread publishes its partial stores device-wide before the workgroup draws its ticket
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t* tk = a.tickets + grp;
+      const uint32_t t = __hip_atomic_fetch_add(tk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const bool last = t == (uint32_t)a.nsplit - 1u;
+      if (last) __hip_atomic_store(tk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
+      s_last = last ? 1 : 0;
+    }
+    __syncthreads();
+    if (s_last == 0) continue;
+    __threadfence();
+    for (int idx = threadIdx.x; idx < G * D; idx += 256) {
+      const int h = idx / D, c = idx % D;
+      const int64_t row = row0 + h;
+      if (rung != 4 && (a.flags[row] & CQA_FLAG_ANY) == 0u) continue;   // Rung 3 serves flagged heads only
+      // (a wave's 64 channels belong to one row, so the branch above is uniform in the wave)
+      a.O[row * D + c] = dense_merge_row(ws + (int64_t)h * a.nsplit * DP_FLOATS, a.nsplit, c);
+      if (c == 0) dense_mark_served(a.cert, a.flags, row, rung);
+    }
   }
 }
 
@@ -416,7 +421,7 @@ int ladder_splits(const Cache* c, int64_t n_tokens) {
 int64_t ladder_ws_floats(int64_t rows) { return rows * LADDER_MAX_SPLITS * DP_FLOATS; }
 
 int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_groups, float* O,
-                            cqa_head_cert* cert, uint32_t* flags, hipStream_t st) {
+                            cqa_head_cert* cert, uint32_t* flags, uint32_t raised_tag, hipStream_t st) {
   if (c->desc.tier2_mode != CQA_TIER2_PINNED) return CQA_ERR_NO_TIER2;
   const int64_t len = c->length[layer];
   if (len <= 0 || q == nullptr || O == nullptr || cert == nullptr || flags == nullptr)
@@ -438,10 +443,13 @@ int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_
   a.ws = c->ladder_ws;
   a.tickets = c->ladder_tickets;
   a.counts = c->ladder_counts;
+  a.raised = ladder_raised(c);
+  a.raised_tag = raised_tag;
+  a.groups = bt * hkv;
   a.O = O;
   a.cert = cert;
   a.flags = flags;
-  const dim3 grid(a.nsplit, bt * hkv);
+  const dim3 grid((unsigned)std::min<int64_t>((int64_t)a.nsplit * a.groups, 2 * (int64_t)c->n_cu));
   switch (g) {
     case 1: hipLaunchKernelGGL(dense_ladder_kernel<1>, grid, dim3(256), 0, st, a); break;
     case 2: hipLaunchKernelGGL(dense_ladder_kernel<2>, grid, dim3(256), 0, st, a); break;

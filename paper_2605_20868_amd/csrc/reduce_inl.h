@@ -24,6 +24,8 @@ struct ReduceArgs {
   uint32_t* flags;
   uint32_t* flags_mirror;  // optional second copy of the flag words (mapped pinned host memory)
   uint32_t mirror_tag;     // OR-ed into each mirrored word (bits 16-31): the host polls for it
+  uint32_t* raised;        // optional: set to raised_tag when a head requests a fallback (the ladder kernel
+  uint32_t raised_tag;     // looks at the flag words only then)
   cqa_tolerances tol;
   int nsplit, nb, r, n_q, n_kv;
   int pstride;           // partial sets per (batch, q-head) row of `partials`; 0 = nsplit
@@ -213,80 +215,143 @@ struct AdaptiveIn {
   float L8u, EV8u, maxc8, lse8;
 };
 
-// wsm: wave-private LDS scratch of at least 64 floats.  All 64 lanes of the wave must call.
-// This code runs on the critical tail of the launch: it is written for few dependent memory
-// round trips (all loads of a chunk of 64 splits are issued before anything is consumed) and
-// short cross-lane chains, not for few instructions.
-__device__ __forceinline__ void reduce_head_wave(const ReduceArgs& a, int b, int hq, float* wsm,
-                                                 const AdaptiveIn* ad = nullptr) {
-  const int l = threadIdx.x & 63;
-  const int kvh = hq / (a.n_q / a.n_kv);
-  const float inv_sqrt_d = 0.08838834764831845f;
-  const float* part = a.partials + ((int64_t)b * a.n_q + hq) * (a.pstride > 0 ? a.pstride : a.nsplit) * PART_FLOATS;
+// Merged softmax state of one (batch, query head): scalars in every lane, o2 = channels 2l, 2l + 1 of lane l.
+struct HeadState {
+  float M, L, EV, EVM, DM, VM, T1, T2;
+  int I1;
+  float2 o2;
+};
 
-  // trailing FP16 tokens (at most 15): request them first, they are used last.
-  //   scores / norms: lane (t = l >> 2, cpart = l & 3) covers channels 32 cpart .. 32 cpart + 31 of
-  //   token t; values for the output: lane l covers channels 2l, 2l+1 of every token.
-  const __half* tk = a.trail_k + ((int64_t)b * a.n_kv + kvh) * BLK * D;
-  const __half* tv = a.trail_v + ((int64_t)b * a.n_kv + kvh) * BLK * D;
-  const int tt = min(l >> 2, max(a.r - 1, 0)), cpart = l & 3;
+__device__ __forceinline__ float lane_of(float x, int lane) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), lane));
+}
+
+// Merges the n_sets partial sets of one head (set s at part + s * PART_FLOATS), CH per trip.
+// All 64 lanes of the wave must call.  This code runs on the critical tail of a launch: it is
+// written for few dependent memory round trips (all loads of a trip are issued before anything is
+// consumed) and short cross-lane chains, not for few instructions.
+template <int CH>
+__device__ __forceinline__ HeadState reduce_sets(const float* part, int n_sets, const AdaptiveIn* ad) {
+  const int l = threadIdx.x & 63;
+  HeadState r;
+  r.M = -INFINITY;
+  r.L = r.EV = r.EVM = r.DM = r.VM = 0.0f;
+  r.T1 = r.T2 = -INFINITY;
+  r.I1 = -1;
+  r.o2 = make_float2(0.0f, 0.0f);
+  for (int s0 = 0; s0 < n_sets; s0 += CH) {
+    // scalars of set s0 + l (one set per lane) and, for my two channels, the outputs of all sets
+    const int s = s0 + l;
+    const bool on = l < CH && s < n_sets;
+    const float* ps = part + (int64_t)(on ? s : n_sets - 1) * PART_FLOATS;
+    float2 sc[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) sc[i] = *reinterpret_cast<const float2*>(ps + 2 * i);   // (P_M P_L) (P_EV P_EVMAX) (P_DMAX P_VMAX) (P_T1 P_T2) (P_I1 -)
+    float2 x[CH];
+#pragma unroll
+    for (int i = 0; i < CH; ++i)
+      x[i] = *reinterpret_cast<const float2*>(part + (int64_t)min(s0 + i, n_sets - 1) * PART_FLOATS + P_O + 2 * l);
+
+    const float m = on ? sc[0].x : -INFINITY;
+    const float Mn = fmaxf(r.M, wave_max(m));
+    const float fo = __expf(r.M - Mn);        // rescales what earlier trips accumulated
+    const float f = on ? __expf(m - Mn) : 0.0f;
+    const float fc = (ad == nullptr || (s >= ad->pos_set0 && s < ad->pos_set1)) ? f : 0.0f;
+    r.L = r.L * fo + wave_sum(fc * sc[0].y);
+    r.EV = r.EV * fo + wave_sum(fc * sc[1].x);
+    r.EVM = fmaxf(r.EVM * fo, wave_max(fc * sc[1].y));
+    r.DM = fmaxf(r.DM, wave_max(on ? sc[2].x : 0.0f));
+    r.VM = fmaxf(r.VM, wave_max(on ? sc[2].y : 0.0f));
+    float u1 = on ? sc[3].x : -INFINITY, u2 = on ? sc[3].y : -INFINITY;
+    int j1 = on ? __float_as_int(sc[4].x) : -1;
+    wave_top2(u1, j1, u2);
+    top2_merge(r.T1, r.I1, r.T2, u1, j1, u2);
+    r.M = Mn;
+    r.o2.x *= fo;
+    r.o2.y *= fo;
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      const float fi = lane_of(f, i);            // zero for sets past the end
+      r.o2.x = fmaf(fi, x[i].x, r.o2.x);
+      r.o2.y = fmaf(fi, x[i].y, r.o2.y);
+    }
+  }
+  return r;
+}
+
+// Merges the states of n waves kept in LDS: scalars (in the order of the partial set's) at
+// ms + i * ms_stride, channels at mo + i * mo_stride.
+__device__ __forceinline__ HeadState reduce_lds(const float* ms, int ms_stride, const float* mo, int mo_stride, int n) {
+  const int l = threadIdx.x & 63;
+  const bool on = l < n;
+  const float* m = ms + (on ? l : 0) * ms_stride;
+  HeadState r;
+  const float mx = on ? m[P_M] : -INFINITY;
+  r.M = wave_max(mx);
+  const float f = on ? __expf(mx - r.M) : 0.0f;
+  r.L = wave_sum(f * m[P_L]);
+  r.EV = wave_sum(f * m[P_EV]);
+  r.EVM = wave_max(f * m[P_EVMAX]);
+  r.DM = wave_max(on ? m[P_DMAX] : 0.0f);
+  r.VM = wave_max(on ? m[P_VMAX] : 0.0f);
+  r.T1 = on ? m[P_T1] : -INFINITY;
+  r.T2 = on ? m[P_T2] : -INFINITY;
+  r.I1 = on ? __float_as_int(m[P_I1]) : -1;
+  wave_top2(r.T1, r.I1, r.T2);
+  r.o2 = make_float2(0.0f, 0.0f);
+  for (int i = 0; i < n; ++i) {
+    const float fi = lane_of(f, i);
+    const float2 x = *reinterpret_cast<const float2*>(mo + i * mo_stride + 2 * l);
+    r.o2.x = fmaf(fi, x.x, r.o2.x);
+    r.o2.y = fmaf(fi, x.y, r.o2.y);
+  }
+  return r;
+}
+
+// Trailing FP16 tokens of one head (at most 15), requested before the partial sets and used after them.
+//   scores / norms: lane (t = l >> 2, cpart = l & 3) covers channels 32 cpart .. 32 cpart + 31 of
+//   token t; values for the output: lane l covers channels 2l, 2l + 1 of every token.
+struct TrailRegs {
   uint4 kq[4], vq[4], qq[4];
+  __half2 vt[BLK - 1];
+};
+
+// new_k, new_v (null = none): the last trailing token, when the launch that calls this also appends it
+__device__ __forceinline__ void load_trail(const ReduceArgs& a, int b, int hq, const __half* new_k,
+                                           const __half* new_v, TrailRegs& t) {
+  const int l = threadIdx.x & 63;
+  const int64_t grp = (int64_t)b * a.n_kv + hq / (a.n_q / a.n_kv);
+  const __half* tk = a.trail_k + grp * BLK * D;
+  const __half* tv = a.trail_v + grp * BLK * D;
+  const int last = max(a.r - 1, 0);
+  const int tt = min(l >> 2, last), cpart = l & 3;
+  const bool fresh = new_k != nullptr && tt == last;
+  const __half* kp = (fresh ? new_k + grp * D : tk + tt * D) + cpart * 32;
+  const __half* vp = (fresh ? new_v + grp * D : tv + tt * D) + cpart * 32;
+  const __half* qp = a.q + ((int64_t)b * a.n_q + hq) * D + cpart * 32;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    kq[i] = reinterpret_cast<const uint4*>(tk + tt * D + cpart * 32)[i];
-    vq[i] = reinterpret_cast<const uint4*>(tv + tt * D + cpart * 32)[i];
-    qq[i] = reinterpret_cast<const uint4*>(a.q + ((int64_t)b * a.n_q + hq) * D + cpart * 32)[i];
+    t.kq[i] = reinterpret_cast<const uint4*>(kp)[i];
+    t.vq[i] = reinterpret_cast<const uint4*>(vp)[i];
+    t.qq[i] = reinterpret_cast<const uint4*>(qp)[i];
   }
-  __half2 vt[BLK - 1];
 #pragma unroll
-  for (int t = 0; t < BLK - 1; ++t)
-    vt[t] = reinterpret_cast<const __half2*>(tv + min(t, max(a.r - 1, 0)) * D)[l];
-
-  float M = -INFINITY, L = 0.0f, EV = 0.0f, EVM = 0.0f, DM = 0.0f, VM = 0.0f;
-  float T1 = -INFINITY, T2 = -INFINITY;
-  int I1 = -1;
-  float2 o2 = make_float2(0.0f, 0.0f);
-  for (int s0 = 0; s0 < a.nsplit; s0 += 64) {
-    // scalars of split s0 + l (one split per lane) and, for my two channels, the partial
-    // outputs of all 64 splits of the chunk
-    const int s = s0 + l;
-    const bool on = s < a.nsplit;
-    const float* ps = part + (int64_t)(on ? s : a.nsplit - 1) * PART_FLOATS;
-    float sc[9];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) sc[i] = ps[i];
-    float2 x[64];
-#pragma unroll
-    for (int i = 0; i < 64; ++i)
-      x[i] = *reinterpret_cast<const float2*>(part + (int64_t)min(s0 + i, a.nsplit - 1) * PART_FLOATS + P_O + 2 * l);
-
-    const float m = on ? sc[P_M] : -INFINITY;
-    const float Mn = fmaxf(M, wave_max(m));
-    const float fo = __expf(M - Mn);        // rescales what earlier chunks accumulated
-    const float f = on ? __expf(m - Mn) : 0.0f;
-    wsm[l] = f;
-    const float fc = (ad == nullptr || (s >= ad->pos_set0 && s < ad->pos_set1)) ? f : 0.0f;
-    L = L * fo + wave_sum(fc * sc[P_L]);
-    EV = EV * fo + wave_sum(fc * sc[P_EV]);
-    EVM = fmaxf(EVM * fo, wave_max(fc * sc[P_EVMAX]));
-    DM = fmaxf(DM, wave_max(on ? sc[P_DMAX] : 0.0f));
-    VM = fmaxf(VM, wave_max(on ? sc[P_VMAX] : 0.0f));
-    float u1 = on ? sc[P_T1] : -INFINITY, u2 = on ? sc[P_T2] : -INFINITY;
-    int j1 = on ? __float_as_int(sc[P_I1]) : -1;
-    wave_top2(u1, j1, u2);
-    top2_merge(T1, I1, T2, u1, j1, u2);
-    M = Mn;
-    wave_sync();
-    o2.x *= fo;
-    o2.y *= fo;
-#pragma unroll
-    for (int i = 0; i < 64; ++i) {
-      const float fi = wsm[i];            // zero for splits past the end
-      o2.x = fmaf(fi, x[i].x, o2.x);
-      o2.y = fmaf(fi, x[i].y, o2.y);
-    }
-    wave_sync();
+  for (int i = 0; i < BLK - 1; ++i) {
+    const int j = min(i, last);
+    const __half* row = new_v != nullptr && j == last ? new_v + grp * D : tv + j * D;
+    t.vt[i] = reinterpret_cast<const __half2*>(row)[l];
   }
+}
+
+// Attends the trailing tokens, evaluates the certificate and writes the row.
+__device__ __forceinline__ void finish_head(const ReduceArgs& a, int b, int hq, const HeadState& hs, const TrailRegs& tr,
+                                            const AdaptiveIn* ad) {
+  const int l = threadIdx.x & 63;
+  const float inv_sqrt_d = 0.08838834764831845f;
+  float M = hs.M, L = hs.L, EV = hs.EV, EVM = hs.EVM, VM = hs.VM;
+  const float DM = hs.DM, T1 = hs.T1, T2 = hs.T2;
+  int I1 = hs.I1;
+  float2 o2 = hs.o2;
   if (ad != nullptr) {
     // the blocks no second pass touched: their mass and value term from the scan
     const float g8 = __expf(ad->lse8 - M);
@@ -301,9 +366,9 @@ __device__ __forceinline__ void reduce_head_wave(const ReduceArgs& a, int b, int
     float dot = 0.0f, n2 = 0.0f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const __half2* kh = reinterpret_cast<const __half2*>(&kq[i]);
-      const __half2* vh = reinterpret_cast<const __half2*>(&vq[i]);
-      const __half2* qh = reinterpret_cast<const __half2*>(&qq[i]);
+      const __half2* kh = reinterpret_cast<const __half2*>(&tr.kq[i]);
+      const __half2* vh = reinterpret_cast<const __half2*>(&tr.vq[i]);
+      const __half2* qh = reinterpret_cast<const __half2*>(&tr.qq[i]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         dot = fmaf(__low2float(qh[e]), __low2float(kh[e]), dot);
@@ -329,13 +394,11 @@ __device__ __forceinline__ void reduce_head_wave(const ReduceArgs& a, int b, int
     EVM *= fs;
     L_sealed = L;
     L += wave_sum(pt) * 0.25f;      // every token is held by four lanes
-    if (cpart == 0) wsm[l >> 2] = pt;
-    wave_sync();
 #pragma unroll
     for (int t = 0; t < BLK - 1; ++t) {
-      const float p = wsm[t];       // zero for t >= r
-      o2.x = fmaf(p, __low2float(vt[t]), o2.x);
-      o2.y = fmaf(p, __high2float(vt[t]), o2.y);
+      const float p = lane_of(pt, 4 * t);       // zero for t >= r
+      o2.x = fmaf(p, __low2float(tr.vt[t]), o2.x);
+      o2.y = fmaf(p, __high2float(tr.vt[t]), o2.y);
     }
     M = M2;
   }
@@ -401,6 +464,7 @@ __device__ __forceinline__ void reduce_head_wave(const ReduceArgs& a, int b, int
     ct.served_rung = 0;
     a.cert[(int64_t)b * a.n_q + hq] = ct;
     a.flags[(int64_t)b * a.n_q + hq] = fl;
+    if (a.raised != nullptr && (fl & CQA_FLAG_ANY) != 0u) *a.raised = a.raised_tag;
     // last store of this head: a host thread polling the mirror may take the tagged word as
     // "this head's row, certificate and flags have been issued" (device consumers rely on
     // stream order, not on this word)
@@ -408,6 +472,17 @@ __device__ __forceinline__ void reduce_head_wave(const ReduceArgs& a, int b, int
       __hip_atomic_store(a.flags_mirror + (int64_t)b * a.n_q + hq, fl | a.mirror_tag,
                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
+}
+
+// One head by one wave: all its partial sets (written by earlier launches), the trailing tokens, the row.
+// CH: sets per trip; a trip costs CH loads whether or not there are as many sets.
+template <int CH>
+__device__ __forceinline__ void reduce_head_wave(const ReduceArgs& a, int b, int hq, const AdaptiveIn* ad = nullptr) {
+  TrailRegs tr;
+  load_trail(a, b, hq, nullptr, nullptr, tr);
+  const float* part = a.partials + ((int64_t)b * a.n_q + hq) * (a.pstride > 0 ? a.pstride : a.nsplit) * PART_FLOATS;
+  const HeadState hs = reduce_sets<CH>(part, a.nsplit, ad);
+  finish_head(a, b, hq, hs, tr, ad);
 }
 
 }  // namespace cqa
