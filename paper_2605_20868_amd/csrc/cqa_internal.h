@@ -42,7 +42,9 @@ constexpr int AN_BYTES = 8;
 //   [K codes 4 x 2048][K meta 4 x 1024][V codes 4 x 1024][V meta 4 x 512][annotations 4 x 8]
 // so that a wave, which works on one quad at a time, streams a single 18464-byte run instead of
 // five separate arrays (measured: 7.1 TB/s against 6.5 TB/s for the same bytes in five arrays).
-// Blocks that are not sealed (yet) always read as zeros: the memory is cleared at creation and at reset.
+// The sigma, z, scale, offset, eta and nu of blocks that are not sealed (yet) read as zeros in every record
+// that holds a sealed block: the memory is cleared at creation, and the seal that ends inside a
+// record clears the rest of it.
 constexpr int Q_KC = 0;
 constexpr int Q_KM = Q_KC + 4 * KC_BYTES;   //  8192
 constexpr int Q_VC = Q_KM + 4 * KM_BYTES;   // 12288
@@ -157,7 +159,10 @@ struct Cache {
   uint32_t* ladder_tickets;
   uint32_t* ladder_counts;   // [2] steps served by Rung 3 / 4, [1] word of the last step that raised a flag
   uint32_t ladder_seq;       // host: number of the last enqueue-only step, never 0
-  float* sigmax;             // [heads_total] running max of sigma (non-negative: ordered as ints)
+  float* sigmax;             // [2][heads_total] running max of sigma (non-negative: ordered as ints); a layer uses
+                             // one of the two until it is reset, see layer_sigmax
+  uint8_t* sigmax_half;      // host, per layer: the half in use
+  bool* sealed;              // host, per layer: a block has been sealed since the last reset
   // trailing FP16 partial blocks [heads_total][16][128]
   __half* trail_k;
   __half* trail_v;
@@ -234,6 +239,12 @@ struct DecodeArgs {
 
 inline int64_t head_index(const Cache* c, int layer, int b, int kvh) {
   return ((int64_t)layer * c->desc.batch + b) * c->desc.n_kv_heads + kvh;
+}
+
+// The layer's running maxima of sigma, [batch][n_kv_heads]: the ones in use, or (next) the ones it uses
+// after its next reset.  The first seal after a reset clears the next ones, so a reset only switches.
+inline float* layer_sigmax(const Cache* c, int layer, bool next) {
+  return c->sigmax + (int64_t)(c->sigmax_half[layer] ^ (next ? 1 : 0)) * c->heads_total + head_index(c, layer, 0, 0);
 }
 
 extern thread_local int g_last_hip_error;

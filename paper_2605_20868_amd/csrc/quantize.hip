@@ -13,6 +13,8 @@
 // Inputs are assumed finite.
 #pragma clang fp contract(off)
 
+#include <algorithm>
+
 #include "cqa_internal.h"
 
 namespace cqa {
@@ -20,17 +22,20 @@ namespace cqa {
 struct SealArgs {
   const __half* k_in;   // [Bt][Hkv][n_new][128]
   const __half* v_in;
-  const __half* trail_k;  // [heads][16][128]
-  const __half* trail_v;
+  __half* trail_k;      // [heads][16][128]
+  __half* trail_v;
   uint8_t* t1;          // Tier-1 quad records
-  float* sigmax;        // [heads]: running max of sigma per (layer, batch, kv-head)
+  float* sigmax;        // [Bt][Hkv] running max of sigma of the layer's sequences
+  float* sigmax_next;   // [Bt][Hkv] the one the layer uses after its next reset: cleared by the first seal
   int64_t nq_cap;
   int64_t nb_old;       // sealed blocks before this append
   int64_t n_new;
   int r;                // tokens in the trailing block before this append
+  int r_new;            // ... and after it: the last r_new of the new tokens
   int layer, batch, n_kv;
-  // short appends that end on a block boundary: the kernel also stores the FP16 originals of the
-  // new tokens into the pinned Tier-2 arrays (null = Tier 2 is written elsewhere)
+  int n_seal, per;      // blocks to seal, consecutive ones per workgroup
+  // short appends: the kernel also stores the FP16 originals of the new tokens into the pinned
+  // Tier-2 arrays (null = Tier 2 is written elsewhere)
   __half* t2_k;         // [heads][t2_cap][128]
   __half* t2_v;
   int64_t t2_cap;
@@ -44,21 +49,35 @@ struct SealArgs {
 // last place, so after the step r is the rounded value of a number within 2^-44 of 1/d (relative
 // error <= 2^-24), x * r carries one more rounding (2^-24), and |x r - x/d| <= 2^8 * 2^-23 = 2^-15;
 // the exact quotient's own rounding moves it by at most 2^-17.  Unless the approximation lies
-// within 2^-13 of a half-integer, both therefore round to the same integer; the rare lanes that
-// are closer -- and anything not finite -- take the exact division.  Bit-identical to
-// rintf(x / d) by construction.
+// within 2^-14 of a half-integer, both therefore round to the same integer; elements that
+// are closer take the exact division.  Bit-identical to rintf(x / d) by construction.  (d = 0: r = 0,
+// every code is 0.  A quotient that is not a number rounds to one, and its code saturates as the
+// exact division's would.)
 __device__ __forceinline__ float refined_rcp(float d) {
   const float r0 = __builtin_amdgcn_rcpf(d);
-  return fmaf(fmaf(-d, r0, 1.0f), r0, r0);
+  return d != 0.0f ? fmaf(fmaf(-d, r0, 1.0f), r0, r0) : 0.0f;
 }
-__device__ __forceinline__ float rint_quotient(float x, float d, float r) {
-  const float qa = x * r;
-  float q = rintf(qa);
-  if (!(fabsf(qa - q) <= 0.5f - 0.0001220703125f)) q = rintf(x / d);
-  return q;
-}
+constexpr float HALF_SAFE = 0.5f - 0.00006103515625f;
 
-// DPP moves for the few cross-lane sums of FP64 annotations (lanes of one token are adjacent)
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+union H2 {
+  uint32_t u;
+  f16x2 h;
+};
+__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
+  H2 x{a}, y{b}, r;
+  r.h = __builtin_elementwise_min(x.h, y.h);
+  return r.u;
+}
+__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
+  H2 x{a}, y{b}, r;
+  r.h = __builtin_elementwise_max(x.h, y.h);
+  return r.u;
+}
+__device__ __forceinline__ float lo_f(uint32_t u) { return (float)H2{u}.h[0]; }
+__device__ __forceinline__ float hi_f(uint32_t u) { return (float)H2{u}.h[1]; }
+
+// FP64 lane exchanges for the block annotations
 template <int CTRL>
 __device__ __forceinline__ double dpp_d(double x) {
   const unsigned long long u = (unsigned long long)__double_as_longlong(x);
@@ -66,211 +85,313 @@ __device__ __forceinline__ double dpp_d(double x) {
   const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
-// sum over the 8 lanes of an aligned octet: quad xor 1, quad xor 2, half-row mirror
-__device__ __forceinline__ double octet_sum_d(double x) {
+// sum over the 4 lanes of an aligned quad, then the largest of the wave's 16 quads
+__device__ __forceinline__ double quad_sum_wave_max_d(double x) {
   x += dpp_d<0xB1>(x);
   x += dpp_d<0x4E>(x);
-  x += dpp_d<0x141>(x);
-  return x;
+  x = fmax(x, dpp_d<0x141>(x));
+  x = fmax(x, dpp_d<0x140>(x));
+  x = fmax(x, __shfl_xor(x, 16));
+  return fmax(x, __shfl_xor(x, 32));
+}
+__device__ __forceinline__ void lds_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One workgroup of 128 threads seals one block of 16 tokens.  Two thread roles, so that every
-// reduction the quantizers need runs inside one thread's registers:
-//   keys   : thread = channel c; its 16 values (one per token) give l_c, u_c, sigma_c, z_c and
-//            the 16 codes of the channel;
-//   values : thread = (token t, group g) = (tid >> 3, tid & 7); its 16 values (32 contiguous
-//            bytes) give lo, hi, the FP16 scale and offset, the 16 codes of the group and the
-//            group's share of the token's squared reconstruction error and squared norm (FP64).
-// Codes pass through LDS to reach the physical layout of the Tier-1 record.
-// (Measured and not adopted: fetching the keys as whole rows with 128-bit loads too and handing
-// the columns to the channel threads through LDS -- 0.28 ms against 0.25 ms for the 128K prefill.)
-__global__ __launch_bounds__(128) void seal_kernel(SealArgs a) {
-  const int tid = threadIdx.x;
-  const int j = blockIdx.x;             // new block index
+// One workgroup of two waves seals a run of up to eight consecutive blocks of 16 tokens, each wave requesting its
+// share of the next block while it works on one; the waves do not wait for each other.
+//   wave 0, keys   : lane = channels 2 l, 2 l + 1; its 2 x 16 values give l_c, u_c, sigma_c, z_c and the
+//                    32 codes;
+//   wave 1, values : lane = (token t, quarter p) = (l >> 2, l & 3), groups p and 4 + p; its 2 x 16 values
+//                    give lo, hi, the FP16 scales and offsets, the 32 codes and the groups' share of
+//                    the token's squared reconstruction error and squared norm (FP64).
+// Codes pass through LDS, inside a wave, to reach the physical layout of the Tier-1 record.
+// Bound by memory (8 KB in, 4.6 KB out per block) once the vector ALU keeps up: minima and maxima
+// are taken on packed FP16, a code is one subtraction, product, rounding and saturating byte
+// conversion, and elements near a half-integer are looked at again only in lanes that have one.
+// 65549 tokens x 8 heads (268 MB in, 151 MB out): 168 us with both roles in every wave, one after the
+// other; 105 us like this one block at a time, 95 us in runs of eight = 4.4 TB/s.  (Four waves per SIMD
+// instead of three spill: 112 us; runs of 2: 98 us, of 21: 108 us.  FP32 annotation sums: no faster.)
+// The first workgroup of a head also moves the tokens that stay unsealed into the trailing block
+// (it is the one that reads the old ones), the last clears the metadata of the blocks that
+// its quad record does not hold yet (the decode pass reads whole records).
+// (Measured and not adopted: fetching the keys as whole rows with 128-bit loads and handing the
+// columns to the channel lanes through LDS.)
+__global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int j = (int)blockIdx.x * a.per;      // new block index
+  const int j1 = min(j + a.per, a.n_seal);
   const int kvh = blockIdx.y, b = blockIdx.z;
-  const int64_t head = ((int64_t)a.layer * a.batch + b) * a.n_kv + kvh;
-  const int64_t blk = a.nb_old + j;
-  const int64_t in_head = ((int64_t)b * a.n_kv + kvh) * a.n_new;
+  const int64_t grp = (int64_t)b * a.n_kv + kvh;
+  const int64_t head = (int64_t)a.layer * a.batch * a.n_kv + grp;
+  const int64_t in_head = grp * a.n_new;
+  const int64_t rec = head * a.nq_cap;
 
   __shared__ __align__(16) uint8_t kbuf[KC_BYTES];
-  __shared__ __align__(16) uint8_t vnib[BLK][D];
+  constexpr int VROW = D + 16;          // bytes per token in vnib (+16: rows t and t + 8 in different banks)
+  __shared__ __align__(16) uint8_t vnib[BLK * VROW];
+  __shared__ __align__(16) uint32_t vout[VC_BYTES / 4];
   __shared__ __align__(16) __half vmeta[2 * BLK * NG];
-  __shared__ double red[BLK][2];        // [token][err^2 | norm^2]
 
-  // token i of this block: one of the r tokens waiting in the trailing block, or a new one
-  const int64_t i0 = (int64_t)j * BLK;
-  // ---- values first (their loads are the wide ones): thread (t, g)
-  {
-    const int t = tid >> 3, g = tid & 7;
-    const int64_t i = i0 + t;
-    const __half* src = i < a.r ? a.trail_v + (head * BLK + i) * D : a.v_in + (in_head + (i - a.r)) * D;
-    const uint4 x0 = *reinterpret_cast<const uint4*>(src + g * VG);
-    const uint4 x1 = *reinterpret_cast<const uint4*>(src + g * VG + 8);
-    if (a.t2_v != nullptr && i >= a.r) {
-      __half* dst = a.t2_v + (head * a.t2_cap + a.len_before + (i - a.r)) * D + g * VG;
-      *reinterpret_cast<uint4*>(dst) = x0;
-      *reinterpret_cast<uint4*>(dst + 8) = x1;
-    }
-    const __half2* h0 = reinterpret_cast<const __half2*>(&x0);
-    const __half2* h1 = reinterpret_cast<const __half2*>(&x1);
-    float vf[VG];
+  if (w == 0) {
+    // ---- keys
+    // channels (2 l, 2 l + 1) of each token of the block in work and of the next one.  Token i of this
+    // append is one of the r waiting ones, or new token i - r.
+    uint32_t kx[BLK], kn[BLK];
+    const uint32_t* const kin = reinterpret_cast<const uint32_t*>(a.k_in + (in_head - a.r) * D);
+    if (j == 0 && a.r > 0) {            // the first block of an append that finds tokens waiting
+      const uint32_t* ktr = reinterpret_cast<const uint32_t*>(a.trail_k + head * BLK * D);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      vf[2 * e] = __low2float(h0[e]);
-      vf[2 * e + 1] = __high2float(h0[e]);
-      vf[8 + 2 * e] = __low2float(h1[e]);
-      vf[8 + 2 * e + 1] = __high2float(h1[e]);
-    }
-    float vlo = vf[0], vhi = vf[0];
+      for (int t = 0; t < BLK; ++t) kn[t] = (t < a.r ? ktr : kin)[t * (D / 2) + l];
+    } else {
 #pragma unroll
-    for (int e = 1; e < VG; ++e) {
-      vlo = fminf(vlo, vf[e]);
-      vhi = fmaxf(vhi, vf[e]);
+      for (int t = 0; t < BLK; ++t) kn[t] = (kin + (int64_t)j * (BLK * D / 2))[t * (D / 2) + l];
     }
-    const __half sh = __float2half_rn((vhi - vlo) / 15.0f);
-    const float sc = __half2float(sh);
-    const float rs = refined_rcp(sc);
-    uint32_t packed[4] = {0u, 0u, 0u, 0u};   // the group's 16 codes, one per byte, channel order
-    double e2 = 0.0, n2 = 0.0;
-    const double dlo = (double)vlo;
+    float smax = 0.0f;
+    for (; j < j1; ++j) {
+      const int64_t blk = a.nb_old + j;
 #pragma unroll
-    for (int e = 0; e < VG; ++e) {
-      float q = 0.0f;
-      if (sc != 0.0f) {
-        q = rint_quotient(vf[e] - vlo, sc, rs);
-        q = fminf(fmaxf(q, 0.0f), 15.0f);
+      for (int t = 0; t < BLK; ++t) kx[t] = kn[t];
+      if (j + 1 < j1) {
+#pragma unroll
+        for (int t = 0; t < BLK; ++t) kn[t] = (kin + (int64_t)(j + 1) * (BLK * D / 2))[t * (D / 2) + l];
       }
-      packed[e >> 2] |= (uint32_t)(int)q << (8 * (e & 3));
-      // v_hat - v = code * scale + (lo - v): the product is exact in binary32 (4 x 11 bits), the
-      // difference and the sum are taken in double
-      const double dv = (double)vf[e];
-      const double err = (double)(q * sc) + (dlo - dv);
-      e2 += err * err;
-      n2 += dv * dv;
-    }
-    *reinterpret_cast<uint4*>(&vnib[t][g * VG]) = make_uint4(packed[0], packed[1], packed[2], packed[3]);
-    vmeta[vm_index(t, g)] = sh;
-    vmeta[BLK * NG + vm_index(t, g)] = __float2half_rn(vlo);  // exact: vlo is an FP16 input
-    e2 = octet_sum_d(e2);
-    n2 = octet_sum_d(n2);
-    if (g == 0) {
-      red[t][0] = e2;
-      red[t][1] = n2;
-    }
-  }
-
-  // ---- keys: thread = channel c, per-channel affine INT8 over the block's 16 tokens
-  {
-    const int c = tid;
-    float kf[BLK];
+      uint32_t mn = kx[0], mx = kx[0];
 #pragma unroll
-    for (int t = 0; t < BLK; ++t) {
-      const int64_t i = i0 + t;
-      const __half kh = i < a.r ? a.trail_k[(head * BLK + i) * D + c] : a.k_in[(in_head + (i - a.r)) * D + c];
-      kf[t] = __half2float(kh);
-      if (a.t2_k != nullptr && i >= a.r) a.t2_k[(head * a.t2_cap + a.len_before + (i - a.r)) * D + c] = kh;
-    }
-    float lo = kf[0], hi = kf[0];
-#pragma unroll
-    for (int t = 1; t < BLK; ++t) {
-      lo = fminf(lo, kf[t]);
-      hi = fmaxf(hi, kf[t]);
-    }
-    const float sigma = (hi - lo) / 255.0f;
-    const float z = lo + 128.0f * sigma;
-    const float rsig = refined_rcp(sigma);
-#pragma unroll
-    for (int t = 0; t < BLK; ++t) {
-      int code = 0;
-      if (sigma != 0.0f) {
-        float q = rint_quotient(kf[t] - z, sigma, rsig);
-        q = fminf(fmaxf(q, -128.0f), 127.0f);
-        code = (int)q;
+      for (int t = 1; t < BLK; ++t) {
+        mn = pk_min(mn, kx[t]);
+        mx = pk_max(mx, kx[t]);
       }
-      kbuf[kc_offset(t, c)] = (uint8_t)(code + 128);
+      const float lo[2] = {lo_f(mn), hi_f(mn)}, hi[2] = {lo_f(mx), hi_f(mx)};
+      float sg[2], z[2], r[2], near = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        sg[e] = (hi[e] - lo[e]) / 255.0f;
+        z[e] = lo[e] + 128.0f * sg[e];
+        r[e] = refined_rcp(sg[e]);
+      }
+      uint32_t code[BLK];                 // two biased codes per token
+#pragma unroll
+      for (int t = 0; t < BLK; ++t) {
+        code[t] = 0u;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const float x = fmaf(e == 0 ? lo_f(kx[t]) : hi_f(kx[t]), 1.0f, -z[e]);   // k - z, one rounding
+          const float qa = x * r[e];
+          const float q = rintf(qa);
+          near = fmaxf(near, fabsf(qa - q));
+          code[t] = __builtin_amdgcn_cvt_pk_u8_f32(q + 128.0f, e, code[t]);        // saturates at 0 and 255
+        }
+      }
+      if (near > HALF_SAFE) {
+        // (hides from the compiler that the quotients are the same: kept from above they cost 50 registers)
+        asm volatile("" : "+v"(r[0]), "+v"(r[1]));
+#pragma unroll
+        for (int t = 0; t < BLK; ++t)
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const float x = fmaf(e == 0 ? lo_f(kx[t]) : hi_f(kx[t]), 1.0f, -z[e]);
+            const float qa = x * r[e];
+            if (fabsf(qa - rintf(qa)) > HALF_SAFE)
+              code[t] = __builtin_amdgcn_cvt_pk_u8_f32(rintf(x / sg[e]) + 128.0f, e, code[t]);
+          }
+      }
+      const int koff = kc_offset(0, 2 * l);
+#pragma unroll
+      for (int t = 0; t < BLK; ++t) *reinterpret_cast<uint16_t*>(&kbuf[koff + t * 16]) = (uint16_t)code[t];
+      float* km = reinterpret_cast<float*>(a.t1 + t1_offset(rec, blk, Q_KM, KM_BYTES));
+      reinterpret_cast<float2*>(km)[l] = make_float2(sg[0], sg[1]);
+      reinterpret_cast<float2*>(km + D)[l] = make_float2(z[0], z[1]);
+      lds_wave_sync();
+      uint8_t* kc = a.t1 + t1_offset(rec, blk, Q_KC, KC_BYTES);
+      reinterpret_cast<uint4*>(kc)[l] = reinterpret_cast<const uint4*>(kbuf)[l];
+      reinterpret_cast<uint4*>(kc)[64 + l] = reinterpret_cast<const uint4*>(kbuf)[64 + l];
+      smax = fmaxf(smax, fmaxf(sg[0], sg[1]));
+      if (a.t2_k != nullptr) {
+#pragma unroll
+        for (int t = 0; t < BLK; ++t) {
+          const int64_t i = (int64_t)j * BLK + t;
+          if (i >= a.r) reinterpret_cast<uint32_t*>(a.t2_k + (head * a.t2_cap + a.len_before + (i - a.r)) * D)[l] = kx[t];
+        }
+      }
+      lds_wave_sync();
     }
-    float* km = reinterpret_cast<float*>(a.t1 + t1_offset(head * a.nq_cap, blk, Q_KM, KM_BYTES));
-    km[c] = sigma;
-    km[D + c] = z;
     // running maximum of sigma over the head's blocks (used by the decode pass to pick an
     // overflow-free power-of-two scaling); sigma >= 0, so its bit pattern orders like an int
-    float smax = sigma;
 #pragma unroll
     for (int m = 1; m < 64; m <<= 1) smax = fmaxf(smax, __shfl_xor(smax, m));
     // thousands of blocks of one head would queue up on the same word: the running maximum is
     // read first (it only grows, so a stale value merely costs a redundant atomic) and the atomic
-    // is issued only by a block that raises it
-    if ((c & 63) == 0 && __float_as_int(smax) > __hip_atomic_load(reinterpret_cast<int*>(a.sigmax + head),
-                                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(reinterpret_cast<int*>(a.sigmax + head), __float_as_int(smax));
-  }
-  __syncthreads();
-
-  // ---- write out, 16 bytes per thread where possible
-  const int c = tid;
-  uint8_t* kc = a.t1 + t1_offset(head * a.nq_cap, blk, Q_KC, KC_BYTES);
-  reinterpret_cast<uint4*>(kc)[c] = reinterpret_cast<const uint4*>(kbuf)[c];
-
-  uint32_t* vc = reinterpret_cast<uint32_t*>(a.t1 + t1_offset(head * a.nq_cap, blk, Q_VC, VC_BYTES));
-#pragma unroll
-  for (int rep = 0; rep < 2; ++rep) {
-    const int dw = c + rep * 128;
-    const int o = dw >> 7, gh = (dw >> 6) & 1, n = (dw >> 2) & 15, gq = dw & 3;
-    const int ch = (gh * 4 + gq) * 16 + n;
-    uint32_t x = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x |= (uint32_t)vnib[o * 8 + i][ch] << (4 * i);
-    vc[dw] = x;
-  }
-  __half* vm = reinterpret_cast<__half*>(a.t1 + t1_offset(head * a.nq_cap, blk, Q_VM, VM_BYTES));
-  reinterpret_cast<uint32_t*>(vm)[c] = reinterpret_cast<const uint32_t*>(vmeta)[c];
-
-  if (c == 0) {
-    double eta2 = 0.0, nu2 = 0.0;
-    for (int t = 0; t < BLK; ++t) {
-      eta2 = fmax(eta2, red[t][0]);
-      nu2 = fmax(nu2, red[t][1]);
+    // is issued only by a workgroup that raises it
+    if (l == 0) {
+      if (__float_as_int(smax) > __hip_atomic_load(reinterpret_cast<int*>(a.sigmax + grp), __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(reinterpret_cast<int*>(a.sigmax + grp), __float_as_int(smax));
+      if (blockIdx.x == 0 && a.nb_old == 0) a.sigmax_next[grp] = 0.0f;
     }
-    float* an = reinterpret_cast<float*>(a.t1 + t1_offset(head * a.nq_cap, blk, Q_AN, AN_BYTES));
-    an[0] = (float)sqrt(eta2);
-    an[1] = (float)sqrt(nu2);
+  } else {
+    // ---- values
+    const int t = l >> 2, p = l & 3;
+    uint4 raw[2][2], nxt[2][2];
+    const __half* const vin = a.v_in + (in_head - a.r + t) * D;
+    {
+      const __half* row = (int64_t)j * BLK + t < a.r ? a.trail_v + (head * BLK + t) * D : vin + (int64_t)j * (BLK * D);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) nxt[k >> 1][k & 1] = reinterpret_cast<const uint4*>(row)[8 * (k >> 1) + 2 * p + (k & 1)];
+    }
+    for (; j < j1; ++j) {
+      const int64_t blk = a.nb_old + j;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) raw[k >> 1][k & 1] = nxt[k >> 1][k & 1];
+      if (j + 1 < j1) {
+        const __half* row = vin + (int64_t)(j + 1) * (BLK * D);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) nxt[k >> 1][k & 1] = reinterpret_cast<const uint4*>(row)[8 * (k >> 1) + 2 * p + (k & 1)];
+      }
+      double e2 = 0.0, n2 = 0.0;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int g = 4 * k + p;
+        const uint32_t vx[8] = {raw[k][0].x, raw[k][0].y, raw[k][0].z, raw[k][0].w,
+                                raw[k][1].x, raw[k][1].y, raw[k][1].z, raw[k][1].w};
+        uint32_t mn = vx[0], mx = vx[0];
+#pragma unroll
+        for (int e = 1; e < 8; ++e) {
+          mn = pk_min(mn, vx[e]);
+          mx = pk_max(mx, vx[e]);
+        }
+        const float vlo = fminf(lo_f(mn), hi_f(mn)), vhi = fmaxf(lo_f(mx), hi_f(mx));
+        const __half sh = __float2half_rn((vhi - vlo) / 15.0f);
+        const float sc = __half2float(sh);
+        float rs = refined_rcp(sc);
+        float q[VG], near = 0.0f;
+#pragma unroll
+        for (int e = 0; e < VG; ++e) {
+          const float x = fmaf((e & 1) ? hi_f(vx[e >> 1]) : lo_f(vx[e >> 1]), 1.0f, -vlo);   // v - lo, one rounding
+          const float qa = x * rs;
+          const float qr = rintf(qa);
+          near = fmaxf(near, fabsf(qa - qr));
+          q[e] = fminf(fmaxf(qr, 0.0f), 15.0f);
+        }
+        if (near > HALF_SAFE) {
+          asm volatile("" : "+v"(rs));
+#pragma unroll
+          for (int e = 0; e < VG; ++e) {
+            const float x = fmaf((e & 1) ? hi_f(vx[e >> 1]) : lo_f(vx[e >> 1]), 1.0f, -vlo);
+            const float qa = x * rs;
+            if (fabsf(qa - rintf(qa)) > HALF_SAFE) q[e] = fminf(fmaxf(rintf(x / sc), 0.0f), 15.0f);
+          }
+        }
+        uint32_t packed[4] = {0u, 0u, 0u, 0u};   // the group's 16 codes, one per byte, channel order
+        const double dlo = (double)vlo, dsc = (double)sc;
+#pragma unroll
+        for (int e = 0; e < VG; ++e) {
+          packed[e >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(q[e], e & 3, packed[e >> 2]);
+          // v_hat - v = code * scale + (lo - v): the product is exact (4 x 11 bits), the difference and the
+          // sum are taken in double
+          const double dv = (double)((e & 1) ? hi_f(vx[e >> 1]) : lo_f(vx[e >> 1]));
+          const double err = fma((double)q[e], dsc, dlo - dv);
+          e2 = fma(err, err, e2);
+          n2 = fma(dv, dv, n2);
+        }
+        *reinterpret_cast<uint4*>(&vnib[t * VROW + g * VG]) = make_uint4(packed[0], packed[1], packed[2], packed[3]);
+        vmeta[vm_index(t, g)] = sh;
+        vmeta[BLK * NG + vm_index(t, g)] = __float2half_rn(vlo);  // exact: vlo is an FP16 input
+        __builtin_amdgcn_sched_barrier(0);   // the groups one after the other (registers)
+      }
+      lds_wave_sync();
+      // eight tokens (octet o) x four channels: token pairs share a byte, then a 4 x 4 byte transpose
+      {
+        const int o = l >> 5, cc = l & 31;
+        uint32_t wd[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) wd[k] = *reinterpret_cast<const uint32_t*>(&vnib[(o * 8 + k) * VROW + 4 * cc]);
+        uint32_t pr[4];                   // byte c = channel c of tokens 2 k (low nibble), 2 k + 1
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pr[k] = wd[2 * k] | (wd[2 * k + 1] << 4);
+        const uint32_t a01 = __builtin_amdgcn_perm(pr[1], pr[0], 0x05010400u), a23 = __builtin_amdgcn_perm(pr[3], pr[2], 0x05010400u);
+        const uint32_t b01 = __builtin_amdgcn_perm(pr[1], pr[0], 0x07030602u), b23 = __builtin_amdgcn_perm(pr[3], pr[2], 0x07030602u);
+        const uint32_t out[4] = {__builtin_amdgcn_perm(a23, a01, 0x05040100u), __builtin_amdgcn_perm(a23, a01, 0x07060302u),
+                                 __builtin_amdgcn_perm(b23, b01, 0x05040100u), __builtin_amdgcn_perm(b23, b01, 0x07060302u)};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) vout[vc_dword_offset(o, 4 * cc + k) / 4] = out[k];
+      }
+      lds_wave_sync();
+      reinterpret_cast<uint4*>(a.t1 + t1_offset(rec, blk, Q_VC, VC_BYTES))[l] = reinterpret_cast<const uint4*>(vout)[l];
+      reinterpret_cast<uint2*>(a.t1 + t1_offset(rec, blk, Q_VM, VM_BYTES))[l] = reinterpret_cast<const uint2*>(vmeta)[l];
+      e2 = quad_sum_wave_max_d(e2);
+      n2 = quad_sum_wave_max_d(n2);
+      if (l == 0)
+        *reinterpret_cast<float2*>(a.t1 + t1_offset(rec, blk, Q_AN, AN_BYTES)) = make_float2((float)sqrt(e2), (float)sqrt(n2));
+      const int64_t i = (int64_t)j * BLK + t;
+      if (a.t2_v != nullptr && i >= a.r) {
+        __half* dst = a.t2_v + (head * a.t2_cap + a.len_before + (i - a.r)) * D;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          reinterpret_cast<uint4*>(dst)[8 * k + 2 * p] = raw[k][0];
+          reinterpret_cast<uint4*>(dst)[8 * k + 2 * p + 1] = raw[k][1];
+        }
+      }
+      lds_wave_sync();
+    }
+  }
+
+  if (blockIdx.x == 0) {
+    // the last r_new new tokens: to the trailing block, whose old tokens this wave has consumed, and, for
+    // short appends, to Tier 2 (16 lanes per token row)
+    const __half* in = w == 0 ? a.k_in : a.v_in;
+    __half* tr = w == 0 ? a.trail_k : a.trail_v;
+    __half* t2 = w == 0 ? a.t2_k : a.t2_v;
+    for (int t = l >> 4; t < a.r_new; t += 4) {
+      const int64_t src = a.n_new - a.r_new + t;
+      const uint4 x = reinterpret_cast<const uint4*>(in + (in_head + src) * D)[l & 15];
+      reinterpret_cast<uint4*>(tr + (head * BLK + t) * D)[l & 15] = x;
+      if (t2 != nullptr) reinterpret_cast<uint4*>(t2 + (head * a.t2_cap + a.len_before + src) * D)[l & 15] = x;
+    }
+  }
+  if (j1 == a.n_seal) {
+    const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+    for (int64_t nb = a.nb_old + j1; (nb & 3) != 0; ++nb) {
+      if (w == 0) {
+        reinterpret_cast<uint4*>(a.t1 + t1_offset(rec, nb, Q_KM, KM_BYTES))[l] = zero;
+      } else {
+        reinterpret_cast<uint2*>(a.t1 + t1_offset(rec, nb, Q_VM, VM_BYTES))[l] = make_uint2(0u, 0u);
+        if (l == 0) *reinterpret_cast<float2*>(a.t1 + t1_offset(rec, nb, Q_AN, AN_BYTES)) = make_float2(0.0f, 0.0f);
+      }
+    }
   }
 }
 
-// Moves the tokens that stay unsealed into the trailing FP16 block and, for short appends,
-// stores the FP16 originals of ALL new tokens straight into the pinned Tier-2 arrays (device
-// stores to mapped host memory: a decode-time append of one token per head is then a single
-// small launch instead of two strided copies).
-// src_first: index (within this append's input) of the first token to keep in the trailing
-// block; dst_first: its slot there; count tokens.  t2_k / t2_v: null = Tier-2 handled elsewhere.
-__global__ __launch_bounds__(128) void trail_kernel(const __half* k_in, const __half* v_in,
-                                                    __half* trail_k, __half* trail_v,
-                                                    int64_t n_new, int64_t src_first,
-                                                    int dst_first, int count, int layer, int batch,
-                                                    int n_kv, __half* t2_k, __half* t2_v,
-                                                    int64_t t2_cap, int64_t len_before) {
-  const int c = threadIdx.x;
+// An append that completes no block: its tokens join the trailing block and, for short appends with
+// Tier 2, the FP16 originals go straight into the pinned arrays (device stores to mapped host
+// memory: a decode-time append of one token per head is one small launch).  16 lanes per token row.
+// dst_first: slot of the first new token; n_new < 16.  t2_k / t2_v: null = Tier-2 handled elsewhere.
+__global__ __launch_bounds__(256) void trail_kernel(const __half* k_in, const __half* v_in,
+                                                    __half* trail_k, __half* trail_v, int n_new,
+                                                    int dst_first, int layer, int batch, int n_kv,
+                                                    __half* t2_k, __half* t2_v, int64_t t2_cap,
+                                                    int64_t len_before) {
+  const int t = threadIdx.x >> 4, c = threadIdx.x & 15;
   const int kvh = blockIdx.x, b = blockIdx.y;
   const int64_t head = ((int64_t)layer * batch + b) * n_kv + kvh;
   const int64_t in_head = ((int64_t)b * n_kv + kvh) * n_new;
-  for (int t = 0; t < count; ++t) {
-    trail_k[(head * BLK + dst_first + t) * D + c] = k_in[(in_head + src_first + t) * D + c];
-    trail_v[(head * BLK + dst_first + t) * D + c] = v_in[(in_head + src_first + t) * D + c];
-  }
+  if (t >= n_new) return;
+  const uint4 k = reinterpret_cast<const uint4*>(k_in + (in_head + t) * D)[c];
+  const uint4 v = reinterpret_cast<const uint4*>(v_in + (in_head + t) * D)[c];
+  reinterpret_cast<uint4*>(trail_k + (head * BLK + dst_first + t) * D)[c] = k;
+  reinterpret_cast<uint4*>(trail_v + (head * BLK + dst_first + t) * D)[c] = v;
   if (t2_k != nullptr) {
-    for (int64_t t = 0; t < n_new; ++t) {
-      t2_k[(head * t2_cap + len_before + t) * D + c] = k_in[(in_head + t) * D + c];
-      t2_v[(head * t2_cap + len_before + t) * D + c] = v_in[(in_head + t) * D + c];
-    }
+    reinterpret_cast<uint4*>(t2_k + (head * t2_cap + len_before + t) * D)[c] = k;
+    reinterpret_cast<uint4*>(t2_v + (head * t2_cap + len_before + t) * D)[c] = v;
   }
 }
 
 int32_t launch_seal(Cache* c, int layer, const __half* k_in, const __half* v_in, int64_t n_new,
                     int64_t len_before, bool tier2_by_kernel, hipStream_t st) {
   const int r = (int)(len_before % BLK);
-  const int64_t nb_old = len_before / BLK;
   const int64_t n_seal = (r + n_new) / BLK;
-  const int r_new = (int)((r + n_new) % BLK);
   const int bt = c->desc.batch, hkv = c->desc.n_kv_heads;
   if (n_seal > 0) {
     SealArgs a;
@@ -279,43 +400,34 @@ int32_t launch_seal(Cache* c, int layer, const __half* k_in, const __half* v_in,
     a.trail_k = c->trail_k;
     a.trail_v = c->trail_v;
     a.t1 = c->t1;
-    a.sigmax = c->sigmax;
+    a.sigmax = layer_sigmax(c, layer, false);
+    a.sigmax_next = layer_sigmax(c, layer, true);
     a.nq_cap = c->nq_cap;
-    a.nb_old = nb_old;
+    a.nb_old = len_before / BLK;
     a.n_new = n_new;
     a.r = r;
+    a.r_new = (int)((r + n_new) % BLK);
     a.layer = layer;
     a.batch = bt;
     a.n_kv = hkv;
-    // an append that ends on a block boundary leaves nothing for the trailing block: its Tier-2
-    // stores ride on the seal launch and the second launch is saved
-    const bool t2_here = tier2_by_kernel && r_new == 0;
-    a.t2_k = t2_here ? c->t2_k : nullptr;
-    a.t2_v = t2_here ? c->t2_v : nullptr;
+    a.t2_k = tier2_by_kernel ? c->t2_k : nullptr;
+    a.t2_v = tier2_by_kernel ? c->t2_v : nullptr;
     a.t2_cap = c->desc.max_tokens;
     a.len_before = len_before;
+    // one block per workgroup until the launch has two thousand of them (about what is resident at a
+    // time), then runs of up to eight
+    a.n_seal = (int)n_seal;
+    a.per = (int)std::min<int64_t>(std::max<int64_t>(n_seal * hkv * bt / 2048, 1), 8);
     // grid.x is limited to 2^31-1 blocks; n_seal <= nb_cap is far below that
-    hipLaunchKernelGGL(seal_kernel, dim3((unsigned)n_seal, hkv, bt), dim3(128), 0, st, a);
+    hipLaunchKernelGGL(seal_kernel, dim3((unsigned)((n_seal + a.per - 1) / a.per), hkv, bt), dim3(128), 0, st, a);
     CQA_HIP(hipGetLastError());
+    c->sealed[layer] = true;
+    return CQA_OK;
   }
-  int64_t src_first;
-  int dst_first, count;
-  if (n_seal == 0) {
-    src_first = 0;
-    dst_first = r;
-    count = (int)n_new;
-  } else {
-    src_first = n_new - r_new;
-    dst_first = 0;
-    count = r_new;
-  }
-  if (count > 0 || (tier2_by_kernel && n_seal == 0)) {
-    hipLaunchKernelGGL(trail_kernel, dim3(hkv, bt), dim3(128), 0, st, k_in, v_in, c->trail_k,
-                       c->trail_v, n_new, src_first, dst_first, count, layer, bt, hkv,
-                       tier2_by_kernel ? c->t2_k : nullptr, tier2_by_kernel ? c->t2_v : nullptr,
-                       (int64_t)c->desc.max_tokens, len_before);
-    CQA_HIP(hipGetLastError());
-  }
+  hipLaunchKernelGGL(trail_kernel, dim3(hkv, bt), dim3(256), 0, st, k_in, v_in, c->trail_k, c->trail_v, (int)n_new, r,
+                     layer, bt, hkv, tier2_by_kernel ? c->t2_k : nullptr, tier2_by_kernel ? c->t2_v : nullptr,
+                     (int64_t)c->desc.max_tokens, len_before);
+  CQA_HIP(hipGetLastError());
   return CQA_OK;
 }
 
