@@ -35,27 +35,35 @@ __device__ __forceinline__ uint32_t ord32(float f) {
   const uint32_t u = __float_as_uint(f);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
+__device__ __forceinline__ float from_ord32(uint32_t k) {
+  return __uint_as_float((k & 0x80000000u) ? (k ^ 0x80000000u) : ~k);
+}
 
-struct SelectArgs {
-  const float* lm8;            // [Bt][Hq][nb]: the row that is ranked (log-masses, or contributions)
-  const cqa_head_cert* cert;   // first pass: lse, delta_h, v_max
+// What one ranking of a head's blocks reads and writes: by log-mass (keys) or by contribution (values).
+struct SelectSide {
   int32_t* sel;                // [Bt][Hq][MAX_K_LIMIT]
   int32_t* kstar;              // [Bt][Hq]
   uint32_t* umask;             // [Bt][Hq][mask_words]: the head's own selection
+  int k_min, k_max, k_limit;
+};
+struct SelectArgs {
+  SelectSide side[2];          // [0] keys, [1] values
+  const float* lm8;            // [Bt][Hq][nb]: log-masses of the pass over all blocks
+  const float* eta_blk;        // [Bt][Hkv][nb] (values)
+  float* contrib;              // [Bt][Hq][nb]: estimated contributions p_b eta_b, written here (values)
+  const cqa_head_cert* cert;   // first pass: lse, delta_h, v_max
   float v_tol, eps_val;        // value selection: local threshold and budget
   float* score_dev;            // [Bt][Hq] canary output, cleared here (null = no canary)
   int v_greedy;
   int64_t mask_words;
   int nb, n_q, n_kv;
   float tau_cov;
-  int k_min, k_max, k_limit;
   float eps_key;
   int mass_exp, key_bound_mode;
 };
 
 // Strided pass over a row in batches: all loads of a batch are issued before anything is consumed
 // (a plain strided loop has one load in flight per thread and is bound by its latency).
-constexpr int BATCH = 16;
 constexpr int ST = 1024;          // threads of the selector workgroup
 constexpr int SBATCH = 8;
 #define CQA_ROW_PASS(ROW, N, TID, BODY)                                           \
@@ -137,6 +145,19 @@ __device__ __forceinline__ double scan_step(double v) {
   const unsigned long long u = (unsigned long long)__double_as_longlong(v);
   return v + pack_d(dpp_or_zero<CTRL, ROWS>((uint32_t)u), dpp_or_zero<CTRL, ROWS>((uint32_t)(u >> 32)));
 }
+__device__ __forceinline__ uint32_t row_total(uint32_t v) {
+  v += (uint32_t)dpp_movi<0xB1>((int)v);
+  v += (uint32_t)dpp_movi<0x4E>((int)v);
+  v += (uint32_t)dpp_movi<0x141>((int)v);
+  return v + (uint32_t)dpp_movi<0x140>((int)v);
+}
+__device__ __forceinline__ int row_total(int v) { return (int)row_total((uint32_t)v); }
+__device__ __forceinline__ double row_total(double v) {
+  v += dpp_mov_d<0xB1>(v);
+  v += dpp_mov_d<0x4E>(v);
+  v += dpp_mov_d<0x141>(v);
+  return v + dpp_mov_d<0x140>(v);
+}
 // Inclusive scan over the threads of a workgroup with two barriers: DPP shifts inside each row of
 // 16 lanes, the totals of the preceding rows by DPP broadcasts, then the preceding waves' totals.
 // `tot` = one word of LDS scratch per wave.
@@ -152,151 +173,246 @@ __device__ __forceinline__ T block_scan_incl(T v, T* tot, int tid) {
   __syncthreads();            // protects `tot` against the previous use
   if (l == 63) tot[w] = v;
   __syncthreads();
-  T off = 0;
-  for (int j = 0; j < w; ++j) off += tot[j];
-  return v + off;
+  // at most 16 waves: every row of lanes adds up the totals of the waves before this one
+  return v + row_total((l & 15) < w ? tot[l & 15] : T(0));
 }
 
-// One workgroup per (batch, query head).  Finds the KL = min(k_limit, nb) best blocks under the
-// total order (larger value first, equal values: lower index first) by radix selection over the
-// row, ranks them, and takes a prefix.
+// Histogram bin of a value in the selector's first pass: not decreasing with the value (the order the
+// selection keeps), 1024 bins where the KL-th best can lie -- log-masses by their distance below the total
+// log-mass, 1/32 apart up to 16 (diffuse heads), 1/8 up to 64, 1 beyond (heads with a few dominant blocks);
+// contributions by octave eighths of the binary representation.
+template <bool VALUES>
+__device__ __forceinline__ int select_bin(float x, float lse) {
+  if (VALUES) {
+    const int i = (int)(__float_as_uint(x) >> 20) - 18;
+    return __float_as_uint(x) >> 31 ? 0 : min(max(i, 0), ST - 1);
+  }
+  const float d = lse - x;
+  const float t = d < 16.0f ? d * 32.0f : (d < 64.0f ? fmaf(d - 16.0f, 8.0f, 512.0f) : 832.0f + d);
+  return ST - 1 - (int)fminf(fmaxf(t, 0.0f), (float)(ST - 1));
+}
+
+// One workgroup per (batch, query head) and ranking (blockIdx.z: 0 keys, 1 values).  Finds the
+// KL = min(k_limit, nb) best blocks
+// under the total order (larger value first, equal values: lower index first), ranks them, and takes a prefix.
 //   VALUES = false: the row holds INT8 block log-masses; the prefix is the smallest one whose
 //                   estimated masses cover tau_cov, clamped, then grown by Rung 1.
-//   VALUES = true : the row holds estimated contributions c_b = p_b eta_b (second rung of the
-//                   ladder); the prefix is every block with c_b > v_tol and, in the hard-budget
+//   VALUES = true : the row holds estimated contributions c_b = p_b eta_b (the paper's rho_hat_b eta_b of its
+//                   value-promotion rule, formed here; second rung of the ladder); the prefix is every
+//                   block with c_b > v_tol and, in the hard-budget
 //                   variant, as many more as bring the estimate left under eps_val; cap k_limit.
+// Bound by its chain of barriers, scans and passes over the row, so there are few of them: one pass
+// over memory with a 1024-bin histogram; the blocks from the bin of the KL-th best up, usually a few dozen
+// more than KL, are rank-sorted as they are.  Only when that bin is crowded (equal
+// or nearly equal values) a radix selection narrows them down to KL.
+// 128K, 32 heads: 18.9 -> 14.6 us (four radix passes before).  4 x 32K, keys and values in one launch: 9.9 us
+// (16.1 + 15.1 in two launches and 4.8 for one that formed the contributions, before).
+constexpr int CAND_SLACK = 256;   // blocks beyond KL that the rank sort takes rather than another pass
+
+struct SelectSmem {
+  unsigned long long cand[MAX_K_LIMIT + CAND_SLACK + 32];   // candidates, unordered
+  unsigned long long sorted[MAX_K_LIMIT];   // the winners, best first: (key, ~index)
+  double pm[MAX_K_LIMIT];                   // prefix sums of their masses
+  uint32_t hist[ST];
+  uint32_t keys[LDS_KEYS];
+};
+
 template <bool VALUES>
-__global__ __launch_bounds__(ST) void select_kernel(SelectArgs a) {
+__device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm) {
   const int tid = threadIdx.x;
   const int hq = blockIdx.x, b = blockIdx.y;
   const int64_t row = (int64_t)b * a.n_q + hq;
-  const float* lm = a.lm8 + row * a.nb;
+  const SelectSide& side = a.side[VALUES ? 1 : 0];
   const int nb = a.nb;
-  const int KL = min(max(a.k_limit, a.k_max), min(nb, MAX_K_LIMIT));
+  float* contrib = VALUES ? a.contrib + row * nb : nullptr;
+  const float* lm = a.lm8 + row * nb;
+  const float* eta = VALUES ? a.eta_blk + ((int64_t)b * a.n_kv + hq / (a.n_q / a.n_kv)) * nb : nullptr;
+  const float* ranked = VALUES ? contrib : lm;         // the row as later passes re-read it
+  const int KL = min(max(side.k_limit, side.k_max), min(nb, MAX_K_LIMIT));
 
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t keys[LDS_KEYS];
+  uint32_t* const hist = sm.hist;
+  uint32_t* const keys = sm.keys;
+  unsigned long long* const cand = sm.cand;
+  unsigned long long* const sorted = sm.sorted;
+  double* const pm = sm.pm;
   const bool cached = nb <= LDS_KEYS;
-  __shared__ unsigned long long cand[MAX_K_LIMIT];     // winners, unordered
-  __shared__ int sorted_idx[MAX_K_LIMIT];              // their block indices, best first
-  __shared__ double pm[MAX_K_LIMIT];                   // prefix sums of their masses
-  __shared__ double dtot[ST / 64];
+  __shared__ double dtot[ST / 64], dsum[ST / 64];
   __shared__ uint32_t utot[ST / 64];
   __shared__ uint32_t s_prefix, s_want, s_cnt;
   __shared__ uint32_t s_idx_prefix, s_idx_want;
-  __shared__ int s_k, s_first;
+  __shared__ int s_k, s_first, s_bin, s_found, s_done;
 
+  const float lse_f = a.cert[row].lse;
+  const double lse = (double)lse_f;
+  if (!VALUES && tid == 0 && a.score_dev != nullptr) a.score_dev[row] = 0.0f;
   if (KL == 0) {
-    if (tid == 0) a.kstar[row] = 0;
+    if (tid == 0) side.kstar[row] = 0;
     return;
   }
-  const double lse = (double)a.cert[row].lse;
-  const float lse_f = a.cert[row].lse;
 
-  // ---- radix selection of the KL-th largest key, 8 bits at a time from the top.  The first pass
-  //      also keeps the keys in LDS and sums the estimated mass of the sealed blocks (single-
-  //      precision exponentials, accumulated in double; the rest of 1 is the exact trailing tokens).
-  double part = 0.0;
-  __shared__ int s_done;
+  // ---- the one pass over memory: keys to LDS, the estimated mass of the sealed blocks (single-
+  //      precision exponentials, accumulated in double; the rest of 1 is the exact trailing tokens), histogram
+  hist[tid] = 0u;
   if (tid == 0) {
-    s_prefix = 0u;
-    s_want = (uint32_t)KL;
-    s_done = 0;
-  }
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    const uint32_t himask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
-    if (tid < 256) hist[tid] = 0u;
-    __syncthreads();
-    const uint32_t prefix = s_prefix;
-    const uint32_t want = s_want;
-    if (pass == 0) {
-      CQA_ROW_PASS(lm, nb, tid, {
-        const uint32_t k = ord32(x);
-        if (in) {
-          part += VALUES ? (double)x : (double)__expf(x - lse_f);
-          if (cached) keys[i] = k;
-        }
-        hist_add(hist, k >> 24, in);
-      })
-    } else {
-      CQA_KEY_PASS(lm, nb, tid, cached, keys, {
-        hist_add(hist, (k >> shift) & 255u, in && (k & himask) == prefix);
-      })
-    }
-    __syncthreads();
-    // thread t looks at bin 255 - t, so an inclusive scan over threads counts from the top bin down;
-    // the bin to descend into is the one where that count first reaches `want`
-    const uint32_t mine = tid < 256 ? hist[255 - tid] : 0u;
-    const uint32_t upto = block_scan_incl<uint32_t>(mine, utot, tid);
-    if (upto >= want && upto - mine < want) {
-      s_want = want - (upto - mine);               // still to take inside the chosen bin
-      s_prefix = prefix | ((uint32_t)(255 - tid) << shift);
-      // every block of the chosen bin is taken: its lower edge already is the threshold (with
-      // distinct log-masses this happens once a bin holds a single block, usually a pass early)
-      if (want - (upto - mine) == mine) s_done = 1;
-    }
-    __syncthreads();
-    if (s_done != 0) break;
-  }
-  const double total_blocks = block_scan_incl<double>(part, dtot, tid);   // last thread: the total
-  __shared__ double s_total;
-  if (tid == ST - 1) s_total = total_blocks;
-  const uint32_t T = s_prefix;                   // key of the KL-th best block
-  // blocks with key == T: s_want of them are needed, the ones with the lowest indices.  The last
-  // histogram still holds how many there are: when all of them are wanted, which is the rule
-  // unless log-masses tie exactly, no index needs to be selected.
-  const bool all_ties = s_done != 0 || hist[T & 255u] == s_want;
-  __syncthreads();
-  if (tid == 0) {
-    s_idx_prefix = all_ties ? 0xFFFFFFFFu : 0u;
-    s_idx_want = s_want;
     s_cnt = 0u;
     s_first = MAX_K_LIMIT + 1;
+    s_bin = 0;
+    s_found = nb;
   }
-  for (int pass = 0; pass < (all_ties ? 0 : 4); ++pass) {
-    const int shift = 24 - 8 * pass;
-    const uint32_t himask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
-    if (tid < 256) hist[tid] = 0u;
-    __syncthreads();
-    const uint32_t prefix = s_idx_prefix;
-    const uint32_t want = s_idx_want;
-    CQA_KEY_PASS(lm, nb, tid, cached, keys, {
-      hist_add(hist, (((uint32_t)i) >> shift) & 255u, in && k == T && (((uint32_t)i) & himask) == prefix);
+  __syncthreads();
+  double part = 0.0;
+  if (VALUES) {
+    for (int base = 0; base < nb; base += ST * SBATCH) {
+      float v[SBATCH], e[SBATCH];
+#pragma unroll
+      for (int j = 0; j < SBATCH; ++j) {
+        const int i = base + j * ST + tid;
+        v[j] = i < nb ? lm[i] : 0.0f;
+        e[j] = i < nb ? eta[i] : 0.0f;
+      }
+#pragma unroll
+      for (int j = 0; j < SBATCH; ++j) {
+        const int i = base + j * ST + tid;
+        if (i < nb) {
+          const float x = __expf(v[j] - lse_f) * e[j];
+          contrib[i] = x;
+          part += (double)x;
+          if (cached) keys[i] = ord32(x);
+          atomicAdd(&hist[select_bin<true>(x, lse_f)], 1u);
+        }
+      }
+    }
+  } else {
+    CQA_ROW_PASS(lm, nb, tid, {
+      if (in) {
+        part += (double)__expf(x - lse_f);
+        if (cached) keys[i] = ord32(x);
+        atomicAdd(&hist[select_bin<false>(x, lse_f)], 1u);
+      }
     })
-    __syncthreads();
-    const uint32_t mine = tid < 256 ? hist[tid] : 0u;   // ascending: the lowest indices are taken first
+  }
+  part = wave_sum_d(part);
+  if ((tid & 63) == 0) dsum[tid >> 6] = part;
+  __syncthreads();
+  // thread t looks at bin ST - 1 - t, so an inclusive scan over threads counts from the top bin down;
+  // the bin to stop at is the one where that count first reaches KL
+  {
+    const uint32_t mine = hist[ST - 1 - tid];
     const uint32_t upto = block_scan_incl<uint32_t>(mine, utot, tid);
-    if (upto >= want && upto - mine < want) {
-      s_idx_want = want - (upto - mine);
-      s_idx_prefix = prefix | ((uint32_t)tid << shift);
+    if (upto >= (uint32_t)KL && upto - mine < (uint32_t)KL) {
+      s_bin = ST - 1 - tid;
+      s_found = (int)upto;
     }
-    __syncthreads();
   }
   __syncthreads();
-  const uint32_t Tidx = s_idx_prefix;            // largest index taken among the ties
-  const double total = s_total;
+  double total = 0.0;
+  for (int w = 0; w < ST / 64; ++w) total += dsum[w];
 
-  // ---- collect the KL winners as composite keys (log-mass order, then lower index first)
-  CQA_KEY_PASS(lm, nb, tid, cached, keys, {
-    if (in && (k > T || (k == T && (uint32_t)i <= Tidx))) {
-      const uint32_t pos = atomicAdd(&s_cnt, 1u);
-      if (pos < (uint32_t)MAX_K_LIMIT)
-        cand[pos] = ((unsigned long long)k << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)i);
+  if (s_found <= KL + CAND_SLACK) {
+    // ---- every block from that bin up is a candidate
+    const int bin = s_bin;
+    CQA_KEY_PASS(ranked, nb, tid, cached, keys, {
+      if (in && select_bin<VALUES>(from_ord32(k), lse_f) >= bin) {
+        const uint32_t pos = atomicAdd(&s_cnt, 1u);
+        if (pos < (uint32_t)(MAX_K_LIMIT + CAND_SLACK))
+          cand[pos] = ((unsigned long long)k << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)i);
+      }
+    })
+  } else {
+    // ---- radix selection of the KL-th largest key, 8 bits at a time from the top
+    if (tid == 0) {
+      s_prefix = 0u;
+      s_want = (uint32_t)KL;
+      s_done = 0;
     }
-  })
+    for (int pass = 0; pass < 4; ++pass) {
+      const int shift = 24 - 8 * pass;
+      const uint32_t himask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
+      if (tid < 256) hist[tid] = 0u;
+      __syncthreads();
+      const uint32_t prefix = s_prefix;
+      const uint32_t want = s_want;
+      CQA_KEY_PASS(ranked, nb, tid, cached, keys, {
+        hist_add(hist, (k >> shift) & 255u, in && (k & himask) == prefix);
+      })
+      __syncthreads();
+      const uint32_t mine = tid < 256 ? hist[255 - tid] : 0u;
+      const uint32_t upto = block_scan_incl<uint32_t>(mine, utot, tid);
+      if (upto >= want && upto - mine < want) {
+        s_want = want - (upto - mine);               // still to take inside the chosen bin
+        s_prefix = prefix | ((uint32_t)(255 - tid) << shift);
+        // every block of the chosen bin is taken: its lower edge already is the threshold (with
+        // distinct log-masses this happens once a bin holds a single block, usually a pass early)
+        if (want - (upto - mine) == mine) s_done = 1;
+      }
+      __syncthreads();
+      if (s_done != 0) break;
+    }
+    const uint32_t T = s_prefix;                   // key of the KL-th best block
+    // blocks with key == T: s_want of them are needed, the ones with the lowest indices.  The last
+    // histogram still holds how many there are: when all of them are wanted, which is the rule
+    // unless log-masses tie exactly, no index needs to be selected.
+    const bool all_ties = s_done != 0 || hist[T & 255u] == s_want;
+    __syncthreads();
+    if (tid == 0) {
+      s_idx_prefix = all_ties ? 0xFFFFFFFFu : 0u;
+      s_idx_want = s_want;
+    }
+    for (int pass = 0; pass < (all_ties ? 0 : 4); ++pass) {
+      const int shift = 24 - 8 * pass;
+      const uint32_t himask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
+      if (tid < 256) hist[tid] = 0u;
+      __syncthreads();
+      const uint32_t prefix = s_idx_prefix;
+      const uint32_t want = s_idx_want;
+      CQA_KEY_PASS(ranked, nb, tid, cached, keys, {
+        hist_add(hist, (((uint32_t)i) >> shift) & 255u, in && k == T && (((uint32_t)i) & himask) == prefix);
+      })
+      __syncthreads();
+      const uint32_t mine = tid < 256 ? hist[tid] : 0u;   // ascending: the lowest indices are taken first
+      const uint32_t upto = block_scan_incl<uint32_t>(mine, utot, tid);
+      if (upto >= want && upto - mine < want) {
+        s_idx_want = want - (upto - mine);
+        s_idx_prefix = prefix | ((uint32_t)tid << shift);
+      }
+      __syncthreads();
+    }
+    __syncthreads();
+    const uint32_t Tidx = s_idx_prefix;            // largest index taken among the ties
+    // ---- collect the KL winners as composite keys (log-mass order, then lower index first)
+    CQA_KEY_PASS(ranked, nb, tid, cached, keys, {
+      if (in && (k > T || (k == T && (uint32_t)i <= Tidx))) {
+        const uint32_t pos = atomicAdd(&s_cnt, 1u);
+        if (pos < (uint32_t)MAX_K_LIMIT)
+          cand[pos] = ((unsigned long long)k << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)i);
+      }
+    })
+  }
   __syncthreads();
-  const int n = (int)min(s_cnt, (uint32_t)KL);
-  // ---- rank sort: a winner's place is the number of winners that precede it (keys are distinct)
-  for (int i = tid; i < n; i += ST) {
+  const int nc = (int)min(s_cnt, (uint32_t)(MAX_K_LIMIT + CAND_SLACK));
+  const int n = min(nc, KL);
+  // ---- rank sort: a candidate's place is the number of candidates that precede it (keys are distinct)
+  //      Four threads share a candidate, each against a quarter of the others.
+  if (tid < 32) cand[nc + tid] = 0ull;             // precede nothing: 32 candidates per round of the four
+  __syncthreads();
+  for (int i = tid >> 2; i < nc; i += ST / 4) {
     const unsigned long long mine = cand[i];
     int rank = 0;
-    for (int j = 0; j < n; ++j) rank += cand[j] > mine ? 1 : 0;
-    sorted_idx[rank] = (int)(0xFFFFFFFFu - (uint32_t)(mine & 0xFFFFFFFFull));
+    for (int j = 0; j < nc; j += 32) {
+      ulonglong2 c[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) c[u] = reinterpret_cast<const ulonglong2*>(&cand[j + 8 * (tid & 3)])[u];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) rank += (c[u].x > mine ? 1 : 0) + (c[u].y > mine ? 1 : 0);
+    }
+    rank += dpp_movi<0xB1>(rank);
+    rank += dpp_movi<0x4E>(rank);
+    if ((tid & 3) == 0 && rank < n) sorted[rank] = mine;
   }
   __syncthreads();
   // ---- masses of the winners, best first, and their inclusive prefix sums: thread t owns place t
-  const double m0 = tid < n ? (VALUES ? (double)lm[sorted_idx[tid]] : exp((double)lm[sorted_idx[tid]] - lse)) : 0.0;
+  const float val0 = tid < n ? from_ord32((uint32_t)(sorted[tid] >> 32)) : 0.0f;
+  const double m0 = tid < n ? (VALUES ? (double)val0 : exp((double)val0 - lse)) : 0.0;
   const double upto1 = block_scan_incl<double>(m0, dtot, tid);
   if (tid < MAX_K_LIMIT) pm[tid] = upto1;
   __syncthreads();
@@ -304,7 +420,7 @@ __global__ __launch_bounds__(ST) void select_kernel(SelectArgs a) {
     // ---- covering prefix: C_k = rho_trail + (mass of the k best); K* never exceeds k_max, so
     //      the search stops there; then clamps and Rung-1 growth
     const double rho_trail = 1.0 - total;
-    const int look = min(n, a.k_max);
+    const int look = min(n, side.k_max);
     for (int kk = tid; kk <= look; kk += ST) {
       const double covered = rho_trail + (kk > 0 ? pm[kk - 1] : 0.0);
       if (covered >= (double)a.tau_cov) atomicMin(&s_first, kk);
@@ -312,20 +428,19 @@ __global__ __launch_bounds__(ST) void select_kernel(SelectArgs a) {
     __syncthreads();
     if (tid == 0) {
       int k = s_first <= look ? s_first : nb;             // no prefix up to k_max covers tau_cov
-      k = max(a.k_min, min(k, a.k_max));
+      k = max(side.k_min, min(k, side.k_max));
       k = min(k, nb);
       k = min(k, n);
-      // Rung 1
+      // Rung 1 (an infinite threshold is never exceeded: its test, a chain of double-precision functions, is skipped)
       const double delta = (double)a.cert[row].delta_h, vmax = (double)a.cert[row].v_max;
-      const int cap = min(max(a.k_limit, a.k_max), n);
+      const int cap = a.eps_key == INFINITY ? 0 : min(max(side.k_limit, side.k_max), n);
       while (k < cap) {
         const double tail = total - (k > 0 ? pm[k - 1] : 0.0);
         if (!(key_term_d(delta, tail, vmax, a.mass_exp, a.key_bound_mode) > (double)a.eps_key)) break;
         k = min(max(2 * k, 1), cap);
       }
       s_k = k;
-      a.kstar[row] = k;
-      if (a.score_dev != nullptr) a.score_dev[row] = 0.0f;
+      side.kstar[row] = k;
     }
   } else {
     // ---- value selection: the blocks over the local threshold form a prefix of the ranking
@@ -334,8 +449,7 @@ __global__ __launch_bounds__(ST) void select_kernel(SelectArgs a) {
     __shared__ int s_over;
     if (tid == 0) s_over = 0;
     __syncthreads();
-    for (int kk = tid; kk < n; kk += ST)
-      if (lm[sorted_idx[kk]] > a.v_tol) atomicAdd(&s_over, 1);
+    if (tid < n && val0 > a.v_tol) atomicAdd(&s_over, 1);
     if (a.v_greedy) {
       for (int kk = tid; kk <= n; kk += ST) {
         const double left = total - (kk > 0 ? pm[kk - 1] : 0.0);
@@ -348,30 +462,25 @@ __global__ __launch_bounds__(ST) void select_kernel(SelectArgs a) {
       if (a.v_greedy) k = max(k, s_first <= n ? s_first : nb);
       k = min(k, min(n, nb));
       s_k = k;
-      a.kstar[row] = k;
+      side.kstar[row] = k;
     }
   }
   __syncthreads();
   const int k = s_k;
-  uint32_t* um = a.umask + row * a.mask_words;
+  uint32_t* um = side.umask + row * a.mask_words;
   for (int i = tid; i < k; i += ST) {
-    const int idx = sorted_idx[i];
-    a.sel[row * MAX_K_LIMIT + i] = idx;
+    const int idx = (int)(0xFFFFFFFFu - (uint32_t)(sorted[i] & 0xFFFFFFFFull));
+    side.sel[row * MAX_K_LIMIT + i] = idx;
     if (idx >= 0 && idx < nb) atomicOr(&um[idx >> 5], 1u << (idx & 31));
   }
 }
 
-// Estimated contribution of every block to a head's value term: c_b = exp(l_b - lse) eta_b
-// (the paper's rho_hat_b eta_b of its value-promotion rule), one thread per (head, block).
-__global__ __launch_bounds__(256) void contrib_kernel(const float* lm8, const float* eta_blk,
-                                                      const cqa_head_cert* cert, float* contrib,
-                                                      int nb, int n_q, int n_kv) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  const int hq = blockIdx.y, b = blockIdx.z;
-  if (i >= nb) return;
-  const int64_t row = (int64_t)b * n_q + hq;
-  const int64_t grp = (int64_t)b * n_kv + hq / (n_q / n_kv);
-  contrib[row * nb + i] = __expf(lm8[row * nb + i] - cert[row].lse) * eta_blk[grp * nb + i];
+__global__ __launch_bounds__(ST) void select_kernel(SelectArgs a) {
+  __shared__ __align__(16) SelectSmem sm;
+  if (blockIdx.z == 0)
+    select_rows<false>(a, sm);
+  else
+    select_rows<true>(a, sm);
 }
 
 // The exploration draw: 32-bit multiply-xorshift mixer over (block, KV group, seed).
@@ -655,12 +764,15 @@ struct AdaptiveReduceArgs {
   const int32_t* ucount; // [Bt][Hkv]
 };
 
-// One workgroup per (batch, query head): all threads scan the block log-masses of both passes
-// (estimated mass left in INT8, best promoted block under either ranking, best unpromoted
-// block), then the first wave merges the partial sets of the pass over all blocks and of the
-// promoted-block pass and finalises the
-// certificate with these substituted.
-constexpr int ART = 512;   // threads of the adaptive reduction: 8192 blocks in one trip of 16 per thread
+// One workgroup per (batch, query head).  Its first wave merges the partial sets of the pass over all blocks
+// and of the promoted-block pass while the others scan the block log-masses (estimated mass left in INT8, best
+// unpromoted block) and the list of the promoted ones (best under either ranking); then the first wave
+// finalises the certificate with these substituted.
+// Bound by latency: 128K, 32 heads 13.6 -> 9.5 us (scan and merge one after the other, the FP16 log-mass of
+// every block requested, before).
+constexpr int ART = 1024;                // threads of the adaptive reduction
+constexpr int ASCAN = ART - 64;          // ... of which scan: 8192 blocks in one trip of nine
+constexpr int ABATCH = 9;
 __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs a) {
   const int tid = threadIdx.x;
   const int hq = blockIdx.x, b = blockIdx.y;
@@ -674,40 +786,47 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
   // the first wave overwrites it
   const float lse8 = ra.cert[row].lse;
   const float delta = ra.cert[row].delta_h;
-
-  const float* eta = a.eta + grp * ra.nb;
   const int kbit = 1 << (SLOT_HK_SHIFT + hq % (ra.n_q / ra.n_kv));   // this head scores the block with FP16 keys
-  float best_x = -INFINITY, best_8 = -INFINITY, tail_max = -INFINITY, maxc8 = 0.0f;
-  int ix = -1, i8 = -1;
-  double tail_mass = 0.0, l8u = 0.0, ev8u = 0.0;
-  for (int base = 0; base < ra.nb; base += ART * BATCH) {
-    float b8[BATCH], bx[BATCH], be[BATCH];
-    int bs[BATCH];
+
+  constexpr int NW = ART / 64;
+  __shared__ float s_bx[ART], s_b8[ART];     // (for the deeper places of the ranking below)
+  __shared__ int s_ix[ART], s_i8[ART];
+  __shared__ float w_bx[NW], w_b8[NW], w_tm[NW], w_mc[NW];
+  __shared__ int w_ix[NW], w_i8[NW];
+  __shared__ double w_mass[NW], w_l8u[NW], w_ev8u[NW];
+  __shared__ float s_top[4];
+  __shared__ int s_topi[2];
+  __shared__ double s_sum[3];
+  AdaptiveIn ad;
+  ad.pos_set0 = a.pos_set0;
+  ad.pos_set1 = a.pos_set1;
+  HeadState hs;
+  if (tid < 64) {
+    hs = reduce_sets<16>(ra.partials + row * ra.pstride * PART_FLOATS, ra.nsplit, &ad);
+  } else {
+    const int t = tid - 64;
+    const int n_list = min(a.ucount[grp], MAX_UNION);
+    const int32_t* ulist = a.ulist + grp * MAX_UNION;
+    int blk = ulist[t];                      // valid for t < n_list
+    const float* eta = a.eta + grp * ra.nb;
+    float best_x = -INFINITY, best_8 = -INFINITY, tail_max = -INFINITY, maxc8 = 0.0f;
+    int ix = -1, i8 = -1;
+    double tail_mass = 0.0, l8u = 0.0, ev8u = 0.0;
+    for (int base = 0; base < ra.nb; base += ASCAN * ABATCH) {
+      float b8[ABATCH], be[ABATCH];
+      int bs[ABATCH];
 #pragma unroll
-    for (int j = 0; j < BATCH; ++j) {       // all loads of the batch first
-      const int i = base + j * ART + tid;
-      const bool in = i < ra.nb;
-      b8[j] = in ? l8[i] : 0.0f;
-      bs[j] = in ? slot[i] : 0;
-      bx[j] = in ? lx[i] : 0.0f;            // written for listed blocks only; used for key-promoted ones
-      be[j] = in ? eta[i] : 0.0f;
-    }
+      for (int j = 0; j < ABATCH; ++j) {       // all loads of the batch first
+        const int i = base + j * ASCAN + t;
+        const bool in = i < ra.nb;
+        b8[j] = in ? l8[i] : 0.0f;
+        bs[j] = in ? slot[i] : kbit;
+        be[j] = in ? eta[i] : 0.0f;
+      }
 #pragma unroll
-    for (int j = 0; j < BATCH; ++j) {
-      const int i = base + j * ART + tid;
-      if (i >= ra.nb) continue;
-      const float v8 = b8[j];
-      if (bs[j] & kbit) {
-        const float vx = bx[j];
-        if (vx > best_x) {      // ascending scan per thread: strict > keeps the lowest index
-          best_x = vx;
-          ix = i;
-        }
-        if (v8 > best_8) {
-          best_8 = v8;
-          i8 = i;
-        }
-      } else {
+      for (int j = 0; j < ABATCH; ++j) {
+        if (bs[j] & kbit) continue;            // key-promoted for this head (or past the end)
+        const float v8 = b8[j];
         const float mass = expf(v8 - lse8);
         tail_max = fmaxf(tail_max, v8);
         tail_mass += (double)mass;
@@ -720,60 +839,56 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
         }
       }
     }
-  }
-  // reduce over the workgroup: shuffles inside each wave, then the waves' results through LDS
-  constexpr int NW = ART / 64;
-  __shared__ float s_bx[ART], s_b8[ART];     // (the full-size arrays serve the deeper places below)
-  __shared__ int s_ix[ART], s_i8[ART];
-  __shared__ float w_bx[NW], w_b8[NW], w_tm[NW], w_mc[NW];
-  __shared__ int w_ix[NW], w_i8[NW];
-  __shared__ double w_mass[NW], w_l8u[NW], w_ev8u[NW];
-  __shared__ float s_top[4];
-  __shared__ int s_topi[2];
-  __shared__ double s_sum[3];
-  __shared__ AdaptiveIn s_ad;
-  wave_best(best_x, ix);
-  wave_best(best_8, i8);
-  tail_max = wave_max(tail_max);
-  maxc8 = wave_max(maxc8);
-  tail_mass = wave_sum_d(tail_mass);
-  l8u = wave_sum_d(l8u);
-  ev8u = wave_sum_d(ev8u);
-  if ((tid & 63) == 0) {
-    const int w = tid >> 6;
-    w_bx[w] = best_x;
-    w_ix[w] = ix;
-    w_b8[w] = best_8;
-    w_i8[w] = i8;
-    w_tm[w] = tail_max;
-    w_mc[w] = maxc8;
-    w_mass[w] = tail_mass;
-    w_l8u[w] = l8u;
-    w_ev8u[w] = ev8u;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    float bx = w_bx[0], b8 = w_b8[0], tm = w_tm[0], mc = w_mc[0];
-    int jx = w_ix[0], j8 = w_i8[0];
-    double ms = w_mass[0], lu = w_l8u[0], eu = w_ev8u[0];
-    for (int w = 1; w < NW; ++w) {
-      best_merge(bx, jx, w_bx[w], w_ix[w]);
-      best_merge(b8, j8, w_b8[w], w_i8[w]);
-      tm = fmaxf(tm, w_tm[w]);
-      mc = fmaxf(mc, w_mc[w]);
-      ms += w_mass[w];
-      lu += w_l8u[w];
-      eu += w_ev8u[w];
+    for (int i = t; i < n_list; i += ASCAN) {
+      if (i != t) blk = ulist[i];
+      if (blk < 0 || blk >= ra.nb || !(slot[blk] & kbit)) continue;
+      best_merge(best_x, ix, lx[blk], blk);
+      best_merge(best_8, i8, l8[blk], blk);
     }
-    s_top[0] = bx;
-    s_top[1] = b8;
-    s_top[2] = tm;
-    s_top[3] = mc;
-    s_topi[0] = jx;
-    s_topi[1] = j8;
-    s_sum[0] = ms;
-    s_sum[1] = lu;
-    s_sum[2] = eu;
+    // reduce over each wave, then (below) over the waves' results
+    wave_best(best_x, ix);
+    wave_best(best_8, i8);
+    tail_max = wave_max(tail_max);
+    maxc8 = wave_max(maxc8);
+    tail_mass = wave_sum_d(tail_mass);
+    l8u = wave_sum_d(l8u);
+    ev8u = wave_sum_d(ev8u);
+    if ((tid & 63) == 0) {
+      const int w = tid >> 6;
+      w_bx[w] = best_x;
+      w_ix[w] = ix;
+      w_b8[w] = best_8;
+      w_i8[w] = i8;
+      w_tm[w] = tail_max;
+      w_mc[w] = maxc8;
+      w_mass[w] = tail_mass;
+      w_l8u[w] = l8u;
+      w_ev8u[w] = ev8u;
+    }
+  }
+  TrailRegs tr;
+  if (tid < 64) load_trail(ra, b, hq, nullptr, nullptr, tr);
+  __syncthreads();
+  if (tid < 64) {
+    const bool on = tid >= 1 && tid < NW;    // one scanning wave's results per lane
+    float bx = on ? w_bx[tid] : -INFINITY, b8 = on ? w_b8[tid] : -INFINITY;
+    int jx = on ? w_ix[tid] : -1, j8 = on ? w_i8[tid] : -1;
+    wave_best(bx, jx);
+    wave_best(b8, j8);
+    const float tm = wave_max(on ? w_tm[tid] : -INFINITY), mc = wave_max(on ? w_mc[tid] : 0.0f);
+    const double ms = wave_sum_d(on ? w_mass[tid] : 0.0), lu = wave_sum_d(on ? w_l8u[tid] : 0.0),
+                 eu = wave_sum_d(on ? w_ev8u[tid] : 0.0);
+    if (tid == 0) {
+      s_top[0] = bx;
+      s_top[1] = b8;
+      s_top[2] = tm;
+      s_top[3] = mc;
+      s_topi[0] = jx;
+      s_topi[1] = j8;
+      s_sum[0] = ms;
+      s_sum[1] = lu;
+      s_sum[2] = eu;
+    }
   }
   __syncthreads();
   // ---- ranking check (the paper's "Ranking-Consistency Check" with its boundary verification)
@@ -857,30 +972,24 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
       pi8 = ni8;
     }
   }
-  if (tid == 0) {
-    AdaptiveIn ad;
-    ad.alpha = (float)s_sum[0];
-    ad.delta = delta;
-    ad.top_block = top_ix;
-    ad.top_fp16 = top_ix >= 0 ? top_x : -INFINITY;
-    ad.kth_fp16 = top_ix >= 0 ? kth_x : -INFINITY;
-    const float tmax = s_top[2];
-    const bool has_tail = tmax > -INFINITY;
-    ad.tail_ub = has_tail ? tmax + delta : -INFINITY;
-    const bool boundary = top_ix >= 0 && has_tail && tmax + delta + ra.tol.eps_guard > kth_x;
-    ad.rank_fail = (disagree || boundary) ? 1 : 0;
-    ad.precond = (a.score_dev != nullptr && a.score_dev[row] > delta + ra.tol.eps_guard) ? 1 : 0;
-    ad.pos_set0 = a.pos_set0;
-    ad.pos_set1 = a.pos_set1;
-    ad.L8u = (float)s_sum[1];
-    ad.EV8u = (float)s_sum[2];
-    ad.maxc8 = s_top[3];
-    ad.lse8 = lse8;
-    s_ad = ad;
-    a.alpha_out[row] = ad.alpha;
-  }
-  __syncthreads();
-  if (tid < 64) reduce_head_wave<64>(ra, b, hq, &s_ad);
+  if (tid >= 64) return;
+  ad.alpha = (float)s_sum[0];
+  ad.delta = delta;
+  ad.top_block = top_ix;
+  ad.top_fp16 = top_ix >= 0 ? top_x : -INFINITY;
+  ad.kth_fp16 = top_ix >= 0 ? kth_x : -INFINITY;
+  const float tmax = s_top[2];
+  const bool has_tail = tmax > -INFINITY;
+  ad.tail_ub = has_tail ? tmax + delta : -INFINITY;
+  const bool boundary = top_ix >= 0 && has_tail && tmax + delta + ra.tol.eps_guard > kth_x;
+  ad.rank_fail = (disagree || boundary) ? 1 : 0;
+  ad.precond = (a.score_dev != nullptr && a.score_dev[row] > delta + ra.tol.eps_guard) ? 1 : 0;
+  ad.L8u = (float)s_sum[1];
+  ad.EV8u = (float)s_sum[2];
+  ad.maxc8 = s_top[3];
+  ad.lse8 = lse8;
+  if (tid == 0) a.alpha_out[row] = ad.alpha;
+  finish_head(ra, b, hq, hs, tr, &ad);
 }
 
 }  // namespace
@@ -920,20 +1029,19 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   if (rc != CQA_OK) return rc;
 
   // ---- 2. selection per head (+ Rung 1), union bit mask per group
+  const bool values = sel.v_limit > 0;   // value promotion ranks the estimated contributions p_b eta_b
   SelectArgs sa{};
+  sa.side[0] = {w.sel, w.kstar, w.umask, sel.k_min, sel.k_max, sel.k_limit};
+  sa.side[1] = {w.vsel, w.vcount, w.vmask, 0, sel.v_limit, sel.v_limit};
   sa.lm8 = w.lm8;
+  sa.eta_blk = w.eta_blk;
+  sa.contrib = w.contrib;
   sa.cert = cert;
-  sa.sel = w.sel;
-  sa.kstar = w.kstar;
-  sa.umask = w.umask;
   sa.mask_words = w.mask_words;
   sa.nb = (int)nb;
   sa.n_q = hq;
   sa.n_kv = hkv;
   sa.tau_cov = sel.tau_cov;
-  sa.k_min = sel.k_min;
-  sa.k_max = sel.k_max;
-  sa.k_limit = sel.k_limit;
   sa.eps_key = tol.eps_key;
   sa.mass_exp = tol.mass_exp;
   sa.key_bound_mode = tol.key_bound_mode;
@@ -941,26 +1049,8 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   sa.eps_val = tol.eps_val;
   sa.v_greedy = sel.v_greedy;
   sa.score_dev = sel.canary ? w.score_dev : nullptr;
-  hipLaunchKernelGGL(select_kernel<false>, dim3(hq, bt), dim3(ST), 0, st, sa);
+  hipLaunchKernelGGL(select_kernel, dim3(hq, bt, values ? 2 : 1), dim3(ST), 0, st, sa);
   CQA_HIP(hipGetLastError());
-  const bool values = sel.v_limit > 0;
-  if (values) {
-    // value promotion: rank the estimated contributions p_b eta_b
-    hipLaunchKernelGGL(contrib_kernel, dim3((unsigned)((nb + 255) / 256), hq, bt), dim3(256), 0, st,
-                       w.lm8, w.eta_blk, cert, w.contrib, (int)nb, hq, hkv);
-    CQA_HIP(hipGetLastError());
-    SelectArgs va = sa;
-    va.lm8 = w.contrib;
-    va.sel = w.vsel;
-    va.kstar = w.vcount;
-    va.umask = w.vmask;
-    va.k_min = 0;
-    va.k_max = sel.v_limit;
-    va.k_limit = sel.v_limit;
-    va.score_dev = nullptr;
-    hipLaunchKernelGGL(select_kernel<true>, dim3(hq, bt), dim3(ST), 0, st, va);
-    CQA_HIP(hipGetLastError());
-  }
 
   // ---- 3. slot map and ordered list per group
   CompactArgs ca{};
@@ -1011,6 +1101,7 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   ra.raised_tag = raised_tag;
   ra.tol = tol;
   ra.nsplit = total;
+  ra.pstride = total;
   ra.nb = (int)nb;
   ra.r = r;
   ra.n_q = hq;

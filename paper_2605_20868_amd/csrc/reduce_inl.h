@@ -477,12 +477,12 @@ __device__ __forceinline__ void finish_head(const ReduceArgs& a, int b, int hq, 
 // One head by one wave: all its partial sets (written by earlier launches), the trailing tokens, the row.
 // CH: sets per trip; a trip costs CH loads whether or not there are as many sets.
 template <int CH>
-__device__ __forceinline__ void reduce_head_wave(const ReduceArgs& a, int b, int hq, const AdaptiveIn* ad = nullptr) {
+__device__ __forceinline__ void reduce_head_wave(const ReduceArgs& a, int b, int hq) {
   TrailRegs tr;
   load_trail(a, b, hq, nullptr, nullptr, tr);
   const float* part = a.partials + ((int64_t)b * a.n_q + hq) * (a.pstride > 0 ? a.pstride : a.nsplit) * PART_FLOATS;
-  const HeadState hs = reduce_sets<CH>(part, a.nsplit, ad);
-  finish_head(a, b, hq, hs, tr, ad);
+  const HeadState hs = reduce_sets<CH>(part, a.nsplit, nullptr);
+  finish_head(a, b, hq, hs, tr, nullptr);
 }
 
 }  // namespace cqa

@@ -786,3 +786,46 @@ def test_per_head_promoted_sets_against_the_union_variant():
             say(f"  K_max {kmax}: (head, block) pairs with FP16 keys per-head "
                 f"{int(sum(bin(int(x)).count('1') for x in ph['head_keys'].ravel()))} / union "
                 f"{int(sum(bin(int(x)).count('1') for x in un['head_keys'].ravel()))}")
+
+
+@pytest.mark.parametrize("kmax,klimit,vlimit", [(128, 128, 64), (512, 512, 512), (1, 3, 1)])
+@pytest.mark.parametrize("nblocks", [900, 300, 11000])
+def test_selector_where_its_histogram_is_crowded_empty_or_tied(nblocks, kmax, klimit, vlimit):
+    """Decisions of both rankings on the GPU's own numbers: all log-masses equal, half of the blocks equal, one head
+    whose mass sits in a few blocks far above the rest, a diffuse one; rows that fit the selector's LDS and one that
+    does not (11000 blocks)."""
+    say(f"selector: {nblocks} blocks, K {kmax}/{klimit}, V {vlimit}")
+    rng = np.random.Generator(np.random.Philox(nblocks + kmax))
+    n = nblocks * 16 + 5
+    k = workloads.normal_f16(rng, (1, 1, n, 128))
+    v = workloads.normal_f16(rng, (1, 1, n, 128))
+    half = (nblocks // 2) * 16
+    for x in (k, v):                                    # the second half of the blocks repeats one block
+        x[0, 0, half:nblocks * 16] = np.tile(x[0, 0, :16], (nblocks - nblocks // 2, 1))
+    q = workloads.normal_f16(rng, (1, 4, 128))
+    q[0, 0] = 0
+    q[0, 2] = (k[0, 0, 40].astype(np.float32) * 6).astype(np.float16)
+    with GpuLayerCache(1, 4, 1, n + 16) as gc:
+        gc.append(k, v)
+        for greedy in (False, True):
+            tol = att.Tolerances(v_tol=1e-4, eps_val=0.02)
+            sel = ad.SelectorParams(0.9, 0, kmax, klimit, v_limit=vlimit, v_greedy=greedy)
+            out = gpu_adaptive(gc, q, tol, sel)
+            tol32 = att.Tolerances(v_tol=float(np.float32(tol.v_tol)), eps_val=float(np.float32(tol.eps_val)))
+            for h in range(4):
+                c0 = out["cert0"][0, h]
+                s = ad.select_blocks(out["l8"][0, h].astype(np.float64), float(c0["lse"]), sel)
+                kk = int(out["k_star"][0, h])
+                # single-precision exponentials in the total: a coverage within 1e-6 of tau_cov may fall on either side
+                near = [ad.select_blocks(out["l8"][0, h].astype(np.float64), float(c0["lse"]),
+                                         ad.SelectorParams(0.9 + d, 0, kmax, klimit))["k_star"] for d in (-1e-6, 1e-6)]
+                assert min(near) <= kk <= max(near), (h, kk, near)
+                assert out["selected"][0, h, :kk].tolist() == s["order"][:kk].tolist(), ("selection", h)
+                vs = ad.select_value_blocks_from(out["contrib"][0, h].astype(np.float64), tol32, sel)
+                got = out["v_selected"][0, h, :int(out["v_count"][0, h])].tolist()
+                m = min(len(vs), len(got))
+                assert got[:m] == vs[:m].tolist(), ("value selection", h)
+                if greedy:                              # the sum it stops on is rounded: one block of slack
+                    assert abs(len(vs) - len(got)) <= 1, (h, len(vs), len(got))
+                else:
+                    assert len(vs) == len(got)
