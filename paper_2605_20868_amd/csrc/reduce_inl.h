@@ -280,7 +280,8 @@ __device__ __forceinline__ HeadState reduce_sets(const float* part, int n_sets, 
 }
 
 // Merges the states of n waves kept in LDS: scalars (in the order of the partial set's) at
-// ms + i * ms_stride, channels at mo + i * mo_stride.
+// ms + i * ms_stride, channels at mo + i * mo_stride.  Waves that saw no block hold zeros and a maximum of
+// -infinity; the result of only such waves is one more of the kind.
 __device__ __forceinline__ HeadState reduce_lds(const float* ms, int ms_stride, const float* mo, int mo_stride, int n) {
   const int l = threadIdx.x & 63;
   const bool on = l < n;
@@ -288,7 +289,7 @@ __device__ __forceinline__ HeadState reduce_lds(const float* ms, int ms_stride, 
   HeadState r;
   const float mx = on ? m[P_M] : -INFINITY;
   r.M = wave_max(mx);
-  const float f = on ? __expf(mx - r.M) : 0.0f;
+  const float f = on ? __expf(mx - (r.M == -INFINITY ? 0.0f : r.M)) : 0.0f;
   r.L = wave_sum(f * m[P_L]);
   r.EV = wave_sum(f * m[P_EV]);
   r.EVM = wave_max(f * m[P_EVMAX]);

@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 # (batch, kv heads, group, tokens, splits the rule gives on 256 compute units)
 @pytest.mark.parametrize("bt,hkv,g,n,splits", [
     (3, 16, 2, 16 * 160 + 3, 5),      # 48 sequences: floor(256 / 48), not 6
+    (1, 2, 4, 16 * 60 + 4, 4),        # 2: a quad per four-wave workgroup's wave, each wave with a SIMD to itself
     (13, 10, 1, 16 * 40 + 1, 3),      # 130: three four-wave workgroups each instead of one of eight waves
     (25, 8, 1, 16 * 30, 1),           # 200: both forms take as many rounds
     (36, 8, 1, 16 * 96 + 5, 3),       # 288: one split would leave the second half of the chip idle
