@@ -439,7 +439,9 @@ __global__ __launch_bounds__(256) void certified_reduce_kernel(ReduceArgs a) {
 //     divide better (130 of 8000: 74.3 against 81.3 us; 152 of 7000: 73.3 against 75.8 us), and where a quad
 //     per wave needs no more of them than there are compute units: a wave that has its SIMD to itself is
 //     through its only quad 0.9 us earlier (1 sequence of 1029: 13.9 -> 13.3 us, 8 of 1000: 14.4 -> 13.8), as
-//     long as the reduction still takes its sets in one trip of 32.
+//     long as the reduction still takes its sets in one trip of 32.  Up to eight quads are one workgroup,
+//     which finishes the rows itself: 300 tokens 12.8 -> 11.6 us, 520 12.9 -> 12.1 (with 16 quads the second
+//     round costs more than the reduction's launch: 13.0 against 14.9).
 //   More sequences than compute units: four-wave workgroups, up to four splits where a last
 //     generation would be nearly empty (288 of 3600: 1 split 91.2, 2 90.9, 3 78.8 us; 384 of 2700: 1
 //     78.5, 2 82.5; 560 of 1900: 1 93.4, 2 84.5, 3 85.1; 704 of 1500: 1 90.3, 2 84.4; 1104 of 950: 1 92.7, 2 95.1).
@@ -466,6 +468,7 @@ void split_geometry(const Cache* c, int64_t n_blocks, int* nsplit, int* wpb) {
   if (c->forced_splits > 0) {
     consider(*wpb, c->forced_splits);
   } else if (heads <= c->n_cu) {
+    if (quads <= 8) consider(8, 1);
     if (heads * ((quads + 3) / 4) <= c->n_cu && quads <= 4 * 32) consider(4, (quads + 3) / 4);
     consider(8, c->n_cu / heads);
     consider(4, 2 * c->n_cu / heads);

@@ -34,8 +34,8 @@ struct SealArgs {
   int r_new;            // ... and after it: the last r_new of the new tokens
   int layer, batch, n_kv;
   int n_seal, per;      // blocks to seal, consecutive ones per workgroup
-  // short appends: the kernel also stores the FP16 originals of the new tokens into the pinned
-  // Tier-2 arrays (null = Tier 2 is written elsewhere)
+  // the kernel also stores the FP16 originals of the new tokens into the pinned Tier-2 arrays, unless they go
+  // through the copy engines (null)
   __half* t2_k;         // [heads][t2_cap][128]
   __half* t2_v;
   int64_t t2_cap;
@@ -98,6 +98,23 @@ __device__ __forceinline__ void lds_wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A wave stores the originals of 16 new tokens, first, first + 1, ... (those that are not negative), in runs of
+// 1 KB: the link takes whole lines.  (The rows are in cache: the wave has just read them.)
+__device__ __forceinline__ void store_originals(const __half* in, __half* t2, int64_t first) {
+  const int l = threadIdx.x & 63;
+  uint4 x[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int64_t i = first + r * 4 + (l >> 4);
+    if (i >= 0) x[r] = reinterpret_cast<const uint4*>(in + i * D)[l & 15];
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int64_t i = first + r * 4 + (l >> 4);
+    if (i >= 0) reinterpret_cast<uint4*>(t2 + i * D)[l & 15] = x[r];
+  }
 }
 
 // One workgroup of two waves seals a run of up to eight consecutive blocks of 16 tokens, each wave requesting its
@@ -209,13 +226,7 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
       reinterpret_cast<uint4*>(kc)[l] = reinterpret_cast<const uint4*>(kbuf)[l];
       reinterpret_cast<uint4*>(kc)[64 + l] = reinterpret_cast<const uint4*>(kbuf)[64 + l];
       smax = fmaxf(smax, fmaxf(sg[0], sg[1]));
-      if (a.t2_k != nullptr) {
-#pragma unroll
-        for (int t = 0; t < BLK; ++t) {
-          const int64_t i = (int64_t)j * BLK + t;
-          if (i >= a.r) reinterpret_cast<uint32_t*>(a.t2_k + (head * a.t2_cap + a.len_before + (i - a.r)) * D)[l] = kx[t];
-        }
-      }
+      if (a.t2_k != nullptr) store_originals(a.k_in + in_head * D, a.t2_k + (head * a.t2_cap + a.len_before) * D, (int64_t)j * BLK - a.r);
       lds_wave_sync();
     }
     // running maximum of sigma over the head's blocks (used by the decode pass to pick an
@@ -325,15 +336,7 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
       n2 = quad_sum_wave_max_d(n2);
       if (l == 0)
         *reinterpret_cast<float2*>(a.t1 + t1_offset(rec, blk, Q_AN, AN_BYTES)) = make_float2((float)sqrt(e2), (float)sqrt(n2));
-      const int64_t i = (int64_t)j * BLK + t;
-      if (a.t2_v != nullptr && i >= a.r) {
-        __half* dst = a.t2_v + (head * a.t2_cap + a.len_before + (i - a.r)) * D;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          reinterpret_cast<uint4*>(dst)[8 * k + 2 * p] = raw[k][0];
-          reinterpret_cast<uint4*>(dst)[8 * k + 2 * p + 1] = raw[k][1];
-        }
-      }
+      if (a.t2_v != nullptr) store_originals(a.v_in + in_head * D, a.t2_v + (head * a.t2_cap + a.len_before) * D, (int64_t)j * BLK - a.r);
       lds_wave_sync();
     }
   }
