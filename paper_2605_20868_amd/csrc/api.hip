@@ -982,16 +982,11 @@ int32_t cqa_decode_step_enqueue(cqa_cache* h, int32_t layer, const void* k_fp16_
     if (rc != CQA_OK) return rc;
   }
   if (c->length[layer] <= 0) return CQA_ERR_INVALID_ARG;
-  const uint32_t tag = next_ladder_tag(c);
-  int32_t rc = launch_certified(c, layer, (const __half*)q_fp16_dev, *tol, O_dev, cert_dev, flags_dev,
-                                nullptr, 0u, nullptr, (hipStream_t)stream, rk, rv, 0, nullptr, nullptr,
-                                ladder_raised(c), tag);
-  if (rc != CQA_OK) {
-    if (rk != nullptr) c->length[layer] -= 1;   // the launch that was to store the token did not happen
-    return rc;
-  }
-  return launch_dense_ladder(c, layer, (const __half*)q_fp16_dev, tol->rung4_min_groups, O_dev,
-                             cert_dev, flags_dev, tag, (hipStream_t)stream);
+  bool launched = false;
+  const int32_t rc = launch_step(c, layer, (const __half*)q_fp16_dev, *tol, O_dev, cert_dev, flags_dev, (hipStream_t)stream,
+                                 rk, rv, &launched);
+  if (!launched && rk != nullptr) c->length[layer] -= 1;   // the launch that was to store the token did not happen
+  return rc;
 }
 
 int32_t cqa_ladder_counts(cqa_cache* h, int64_t* rung3_steps, int64_t* rung4_steps) {

@@ -257,6 +257,7 @@ extern thread_local int g_last_hip_error;
     }                                                   \
   } while (0)
 
+struct ReduceArgs;
 // ---- launchers implemented in the kernel translation units ---------------------
 int32_t launch_seal(Cache* c, int layer, const __half* k_in, const __half* v_in, int64_t n_new,
                     int64_t len_before, bool tier2_by_kernel, hipStream_t st);
@@ -266,7 +267,8 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
                          const __half* k_new = nullptr,
                          const __half* v_new = nullptr, int pstride = 0, float* eta_out = nullptr,
                          float* partials = nullptr,   // null = the cache's own split workspace
-                         uint32_t* raised = nullptr, uint32_t raised_tag = 0u);
+                         uint32_t* raised = nullptr, uint32_t raised_tag = 0u,
+                         ReduceArgs* defer = nullptr);   // nsplit set > 0: the reduction is left to the caller
 int32_t static_scratch(int device, void** out);
 int pick_splits(const Cache* c, int64_t n_blocks);
 int stream_nt(const Cache* c, int64_t n_blocks);
@@ -275,7 +277,6 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
                         const cqa_selector& sel, float* O, cqa_head_cert* cert, uint32_t* flags,
                         uint32_t* flags_mirror, uint32_t mirror_tag, hipStream_t st,
                         uint32_t* raised = nullptr, uint32_t raised_tag = 0u);
-struct ReduceArgs;
 int32_t launch_split_mfma(const DecodeArgs& a, const ReduceArgs& ra, int group, dim3 grid, hipEvent_t ev0,
                           hipEvent_t ev1, hipStream_t st);
 
@@ -294,6 +295,8 @@ int64_t dense_ws_floats(int group, int64_t n_tokens);
 
 // Device-resolved fallback ladder (dense_ladder_kernel).
 constexpr int LADDER_MAX_SPLITS = 64;
+// Steps that finish_ladder_kernel reduces as well: up to this many (batch, q-head) rows and partial sets per row.
+constexpr int FINISH_ROWS = 8, FINISH_SETS = 8;
 struct LadderArgs {
   const __half* q;          // [Bt][Hq][128]
   const __half* t2_k;       // layer base of the pinned originals: [Bt * Hkv][max_tokens][128]
@@ -315,7 +318,12 @@ struct LadderArgs {
 int ladder_splits(const Cache* c, int64_t n_tokens);
 int64_t ladder_ws_floats(int64_t rows);
 int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_groups, float* O,
-                            cqa_head_cert* cert, uint32_t* flags, uint32_t raised_tag, hipStream_t st);
+                            cqa_head_cert* cert, uint32_t* flags, uint32_t raised_tag, hipStream_t st,
+                            const ReduceArgs* reduce = nullptr);   // set = the rows are still to be reduced, here
+// certified decode and ladder, enqueue-only (k_new, v_new: a token that rides on the split launch, or null);
+// *launched (may be null) tells whether the split launch, which stores that token, was reached
+int32_t launch_step(Cache* c, int layer, const __half* q, const cqa_tolerances& tol, float* O, cqa_head_cert* cert,
+                    uint32_t* flags, hipStream_t st, const __half* k_new, const __half* v_new, bool* launched);
 inline uint32_t* ladder_raised(Cache* c) { return c->ladder_counts + 2; }
 inline uint32_t next_ladder_tag(Cache* c) {
   c->ladder_seq = c->ladder_seq == 0xFFFFFFFFu ? 1u : c->ladder_seq + 1u;

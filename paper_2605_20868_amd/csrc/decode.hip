@@ -545,7 +545,7 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
                          cqa_head_cert* cert, uint32_t* flags, uint32_t* flags_mirror,
                          uint32_t mirror_tag, float* blk_logmass, hipStream_t st,
                          const __half* k_new, const __half* v_new, int pstride, float* eta_out,
-                         float* partials, uint32_t* raised, uint32_t raised_tag) {
+                         float* partials, uint32_t* raised, uint32_t raised_tag, ReduceArgs* defer) {
   const int bt = c->desc.batch, hq = c->desc.n_q_heads, hkv = c->desc.n_kv_heads;
   if (partials == nullptr) partials = c->partials;
   const int64_t len = c->length[layer];
@@ -643,6 +643,10 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     }
   }
   if (reduced) return CQA_OK;
+  if (defer != nullptr && nsplit > 1 && nsplit <= FINISH_SETS && (int64_t)bt * hq <= FINISH_ROWS) {
+    *defer = ra;
+    return CQA_OK;
+  }
   // one wave per workgroup: each head's wave gets a compute unit's load path to itself
   // (measured 2 us faster at 32 heads than four heads per workgroup).  Sets per trip by the number
   // there are: a trip of 64 issues 64 loads per lane also for two sets (1K: 5.0 -> 4.1 us, 8K: 4.7 -> 4.4 us)
@@ -654,6 +658,17 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     hipLaunchKernelGGL(certified_reduce_kernel<64>, dim3(hq, bt), dim3(64), 0, st, ra);
   CQA_HIP(hipGetLastError());
   return CQA_OK;
+}
+
+int32_t launch_step(Cache* c, int layer, const __half* q, const cqa_tolerances& tol, float* O, cqa_head_cert* cert,
+                    uint32_t* flags, hipStream_t st, const __half* k_new, const __half* v_new, bool* launched) {
+  const uint32_t tag = next_ladder_tag(c);
+  ReduceArgs ra{};
+  const int32_t rc = launch_certified(c, layer, q, tol, O, cert, flags, nullptr, 0u, nullptr, st, k_new, v_new, 0, nullptr,
+                                      nullptr, ladder_raised(c), tag, &ra);
+  if (launched != nullptr) *launched = rc == CQA_OK;
+  if (rc != CQA_OK) return rc;
+  return launch_dense_ladder(c, layer, q, tol.rung4_min_groups, O, cert, flags, tag, st, ra.nsplit > 0 ? &ra : nullptr);
 }
 
 }  // namespace cqa

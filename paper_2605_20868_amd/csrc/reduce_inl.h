@@ -344,9 +344,16 @@ __device__ __forceinline__ void load_trail(const ReduceArgs& a, int b, int hq, c
   }
 }
 
-// Attends the trailing tokens, evaluates the certificate and writes the row.
-__device__ __forceinline__ void finish_head(const ReduceArgs& a, int b, int hq, const HeadState& hs, const TrailRegs& tr,
-                                            const AdaptiveIn* ad) {
+// The result of one (batch, query head): certificate and flag word in every lane, out = channels 2l, 2l + 1 of lane l.
+struct HeadRow {
+  cqa_head_cert ct;
+  uint32_t fl;
+  float2 out;
+};
+
+// Attends the trailing tokens and evaluates the certificate.
+__device__ __forceinline__ HeadRow finish_row(const ReduceArgs& a, const HeadState& hs, const TrailRegs& tr,
+                                              const AdaptiveIn* ad) {
   const int l = threadIdx.x & 63;
   const float inv_sqrt_d = 0.08838834764831845f;
   float M = hs.M, L = hs.L, EV = hs.EV, EVM = hs.EVM, VM = hs.VM;
@@ -404,74 +411,81 @@ __device__ __forceinline__ void finish_head(const ReduceArgs& a, int b, int hq, 
     M = M2;
   }
 
-  const float out0 = o2.x / L, out1 = o2.y / L;
-  reinterpret_cast<float2*>(a.O + ((int64_t)b * a.n_q + hq) * D)[l] = make_float2(out0, out1);
-  const bool bad = __any(!isfinite(out0) || !isfinite(out1));
+  HeadRow row;
+  row.out = make_float2(o2.x / L, o2.y / L);
+  const bool bad = __any(!isfinite(row.out.x) || !isfinite(row.out.y));
 
+  // certificate scalars in FP32 (a handful of operations; their rounding is ~1e-7 relative)
+  const float e_val = EV / L;
+  const float lse = M + logf(L);
+  const float maxc = EVM / L;
+  const float alpha_hat = ad != nullptr ? ad->alpha : L_sealed / L;
+  const float delta = ad != nullptr ? ad->delta : DM;
+  const float vmax = VM;
+  // No cap on the exponents: beyond the binary32 range the factors are +inf, the tail form of
+  // the key term with them, and a non-finite key term raises PRECOND below (in the default
+  // mode the tanh form, at most 1, still wins the min).
+  float t_tail = 0.0f;
+  if (alpha_hat > 0.0f && delta != 0.0f) {
+    const float grow = expf((float)a.tol.mass_exp * delta);
+    const float widen = expm1f(2.0f * delta);
+    t_tail = fminf(1.0f, grow * alpha_hat) * widen;
+  }
+  const float t_full = tanhf(delta);
+  const float tv = a.tol.key_bound_mode == 0 ? fminf(t_full, t_tail) : (a.tol.key_bound_mode == 1 ? t_tail : t_full);
+  const float e_key = 2.0f * vmax * tv;
+  float margin = a.nb >= 2 ? T1 - T2 : INFINITY;
+  float rho_top = a.nb >= 1 ? expf(T1 - lse) : 0.0f;
+  bool rank_flag = a.tol.rank_depth >= 1 && a.nb >= 2 && rho_top >= a.tol.rank_min_mass &&
+                   margin <= 2.0f * delta + a.tol.eps_guard;
+  if (ad != nullptr) {
+    const bool any = ad->top_block >= 0;
+    margin = any ? ad->kth_fp16 - ad->tail_ub : INFINITY;
+    rho_top = any ? expf(ad->top_fp16 - lse) : 0.0f;
+    rank_flag = a.tol.rank_depth >= 1 && any && rho_top >= a.tol.rank_min_mass && ad->rank_fail != 0;
+    I1 = ad->top_block;
+  }
+
+  uint32_t fl = 0;
+  if (e_key > a.tol.eps_key) fl |= CQA_FLAG_KEY;
+  if (e_val > a.tol.eps_val || maxc > a.tol.v_tol) fl |= CQA_FLAG_VAL;
+  if (rank_flag) fl |= CQA_FLAG_RANK;
+  if (ad != nullptr && ad->precond != 0) fl |= CQA_FLAG_PRECOND;
+  if (bad || !isfinite(e_key) || !isfinite(e_val) || !isfinite(delta) || !isfinite(vmax) || !isfinite(lse))
+    fl |= CQA_FLAG_PRECOND;
+  if (e_key + e_val > a.tol.eps_total) fl |= CQA_FLAG_TOTAL;
+  fl |= a.tol.force_flags;
+
+  row.ct.E_key = e_key;
+  row.ct.E_val = e_val;
+  row.ct.delta_h = delta;
+  row.ct.v_max = VM;
+  row.ct.alpha_tail_hat = alpha_hat;
+  row.ct.lse = lse;
+  row.ct.max_block_contrib = maxc;
+  row.ct.rank_margin = margin;
+  row.ct.top_block = I1;
+  row.ct.served_rung = 0;
+  row.fl = fl;
+  return row;
+}
+
+// Attends the trailing tokens, evaluates the certificate and writes the row.
+__device__ __forceinline__ void finish_head(const ReduceArgs& a, int b, int hq, const HeadState& hs, const TrailRegs& tr,
+                                            const AdaptiveIn* ad) {
+  const int l = threadIdx.x & 63;
+  const HeadRow row = finish_row(a, hs, tr, ad);
+  const int64_t r = (int64_t)b * a.n_q + hq;
+  reinterpret_cast<float2*>(a.O + r * D)[l] = row.out;
   if (l == 0) {
-    // certificate scalars in FP32 (a handful of operations; their rounding is ~1e-7 relative)
-    const float e_val = EV / L;
-    const float lse = M + logf(L);
-    const float maxc = EVM / L;
-    const float alpha_hat = ad != nullptr ? ad->alpha : L_sealed / L;
-    const float delta = ad != nullptr ? ad->delta : DM;
-    const float vmax = VM;
-    // No cap on the exponents: beyond the binary32 range the factors are +inf, the tail form of
-    // the key term with them, and a non-finite key term raises PRECOND below (in the default
-    // mode the tanh form, at most 1, still wins the min).
-    float t_tail = 0.0f;
-    if (alpha_hat > 0.0f && delta != 0.0f) {
-      const float grow = expf((float)a.tol.mass_exp * delta);
-      const float widen = expm1f(2.0f * delta);
-      t_tail = fminf(1.0f, grow * alpha_hat) * widen;
-    }
-    const float t_full = tanhf(delta);
-    const float tv = a.tol.key_bound_mode == 0 ? fminf(t_full, t_tail)
-                                               : (a.tol.key_bound_mode == 1 ? t_tail : t_full);
-    const float e_key = 2.0f * vmax * tv;
-    float margin = a.nb >= 2 ? T1 - T2 : INFINITY;
-    float rho_top = a.nb >= 1 ? expf(T1 - lse) : 0.0f;
-    bool rank_flag = a.tol.rank_depth >= 1 && a.nb >= 2 && rho_top >= a.tol.rank_min_mass &&
-                     margin <= 2.0f * delta + a.tol.eps_guard;
-    if (ad != nullptr) {
-      const bool any = ad->top_block >= 0;
-      margin = any ? ad->kth_fp16 - ad->tail_ub : INFINITY;
-      rho_top = any ? expf(ad->top_fp16 - lse) : 0.0f;
-      rank_flag = a.tol.rank_depth >= 1 && any && rho_top >= a.tol.rank_min_mass && ad->rank_fail != 0;
-      I1 = ad->top_block;
-    }
-
-    uint32_t fl = 0;
-    if (e_key > a.tol.eps_key) fl |= CQA_FLAG_KEY;
-    if (e_val > a.tol.eps_val || maxc > a.tol.v_tol) fl |= CQA_FLAG_VAL;
-    if (rank_flag) fl |= CQA_FLAG_RANK;
-    if (ad != nullptr && ad->precond != 0) fl |= CQA_FLAG_PRECOND;
-    if (bad || !isfinite(e_key) || !isfinite(e_val) || !isfinite(delta) || !isfinite(vmax) ||
-        !isfinite(lse))
-      fl |= CQA_FLAG_PRECOND;
-    if (e_key + e_val > a.tol.eps_total) fl |= CQA_FLAG_TOTAL;
-    fl |= a.tol.force_flags;
-
-    cqa_head_cert ct;
-    ct.E_key = e_key;
-    ct.E_val = e_val;
-    ct.delta_h = delta;
-    ct.v_max = VM;
-    ct.alpha_tail_hat = alpha_hat;
-    ct.lse = lse;
-    ct.max_block_contrib = maxc;
-    ct.rank_margin = margin;
-    ct.top_block = I1;
-    ct.served_rung = 0;
-    a.cert[(int64_t)b * a.n_q + hq] = ct;
-    a.flags[(int64_t)b * a.n_q + hq] = fl;
-    if (a.raised != nullptr && (fl & CQA_FLAG_ANY) != 0u) *a.raised = a.raised_tag;
+    a.cert[r] = row.ct;
+    a.flags[r] = row.fl;
+    if (a.raised != nullptr && (row.fl & CQA_FLAG_ANY) != 0u) *a.raised = a.raised_tag;
     // last store of this head: a host thread polling the mirror may take the tagged word as
     // "this head's row, certificate and flags have been issued" (device consumers rely on
     // stream order, not on this word)
     if (a.flags_mirror != nullptr)
-      __hip_atomic_store(a.flags_mirror + (int64_t)b * a.n_q + hq, fl | a.mirror_tag,
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(a.flags_mirror + r, row.fl | a.mirror_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 

@@ -283,3 +283,51 @@ def test_random_small_shapes_against_oracle():
             O, cert, flags = enqueue(gc, q, to_gpu_tol(cqa, tol), k[:, :, n:], v[:, :, n:])
             assert gc.length() == n + 1
             compare_all(gc, ref, O, cert, flags, ("case", case, bt, hkv, group, n))
+
+
+@pytest.mark.parametrize("bt,hkv,g,n", [(1, 1, 4, 16 * 40 + 3), (1, 1, 1, 16 * 100), (2, 2, 2, 16 * 64 + 15), (1, 8, 1, 16 * 36 + 1),
+                                        (1, 2, 4, 16 * 120), (1, 3, 4, 16 * 50 + 2), (1, 1, 2, 16 * 200 + 9)])
+def test_reduction_and_ladder_in_one_launch_for_few_rows(bt, hkv, g, n):
+    """Up to eight (batch, query head) rows with two to eight partial sets are reduced and served by one launch; more
+    rows (3 x 4) and more sets (3200 tokens) take two.  Every rung against the oracle, and against the host-resolved step."""
+    say(f"few rows: Bt={bt} Hkv={hkv} G={g} N={n}")
+    import torch
+    rng = np.random.default_rng(n + g)
+    hq = hkv * g
+    k = rng.standard_normal((bt, hkv, n, 128)).astype(np.float16)
+    v = rng.standard_normal((bt, hkv, n, 128)).astype(np.float16)
+    q = rng.standard_normal((bt, hq, 128)).astype(np.float16)
+    oc = oracle.OracleLayerCache(bt, hkv)
+    oc.append(k, v)
+    tot = np.sort([r["E_key"] + r["E_val"] for r in oc.certified_decode(q, oracle.Tolerances())])
+    mid = 0.5 * (tot[-1] + tot[-2]) if len(tot) > 1 else 0.5 * tot[-1]
+    with GpuLayerCache(bt, hq, hkv, n + 64) as gc:
+        gc.append(k, v)
+        qd = gc.to_dev(q)
+        served3 = served4 = 0
+        for tol in (oracle.Tolerances(), oracle.Tolerances(eps_total=float(np.float32(mid))),
+                    oracle.Tolerances(force_flags=oracle.FLAG_TOTAL), oracle.Tolerances(force_flags=oracle.FLAG_PRECOND),
+                    oracle.Tolerances(eps_total=float(np.float32(mid)), rung4_min_groups=1), oracle.Tolerances()):
+            gc.O.fill_(float("nan"))
+            gc.cqa.cqa_decode_step_enqueue(gc.h, 0, None, None, qd, to_gpu_tol(gc.cqa, tol), gc.O, gc.cert, gc.flags)
+            O, cert, flags = [x.copy() for x in gc.results()]
+            ref = oc.decode_step(q, tol)
+            for i, r in enumerate(ref):
+                b, h = divmod(i, hq)
+                assert_head_matches(r, O[b, h], cert[b, h], flags[b, h], (tol.eps_total, tol.force_flags, b, h))
+            rung = max(r["served_rung"] for r in ref)
+            served3 += rung == 3
+            served4 += rung == 4
+            _, O2, cert2, flags2 = gc.decode_step(q, to_gpu_tol(gc.cqa, tol))
+            certified = cert["served_rung"] == 0
+            assert np.array_equal(flags, flags2) and np.array_equal(O[certified], O2[certified])
+        assert gc.cqa.cqa_ladder_counts(gc.h) == (served3, served4)
+        # a token that rides on the step, attended by the same launch
+        ks, vs = (rng.standard_normal((bt, hkv, 1, 128)).astype(np.float16) for _ in range(2))
+        oc.append(ks, vs)
+        gc.cqa.cqa_decode_step_enqueue(gc.h, 0, gc.to_dev(ks), gc.to_dev(vs), qd, gc.cqa.Tolerances(), gc.O, gc.cert, gc.flags)
+        O, cert, flags = gc.results()
+        for i, r in enumerate(oc.decode_step(q, oracle.Tolerances())):
+            b, h = divmod(i, hq)
+            assert_head_matches(r, O[b, h], cert[b, h], flags[b, h], ("riding token", b, h))
+        torch.cuda.synchronize()
