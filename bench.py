@@ -448,8 +448,8 @@ def main() -> int:
         torch.cuda.synchronize()
         tf0 = time.perf_counter()
         for i in range(n_fb):
-            cqa.cqa_certified_decode(h, 0, qp + i * q_stride, tol, Op, certp, flagsp, None, stream)
-            cqa.cqa_dense_fallback(h, 0, qp + i * q_stride, sel, 0, 3, Op, certp, flagsp, stream)
+            cqa.cqa_certified_decode(h, 0, qp + (i % n_in) * q_stride, tol, Op, certp, flagsp, None, stream)
+            cqa.cqa_dense_fallback(h, 0, qp + (i % n_in) * q_stride, sel, 0, 3, Op, certp, flagsp, stream)
         torch.cuda.synchronize()
         fb_ms = (time.perf_counter() - tf0) * 1e3 / n_fb
 
@@ -459,12 +459,12 @@ def main() -> int:
         atol = cqa.Tolerances(rank_depth=1, rank_min_mass=0.25)
         n_ad = 20
         for i in range(3):
-            cqa.cqa_adaptive_step_enqueue(h, 0, qp + i * q_stride, atol, sel, Op, certp, flagsp, stream)
+            cqa.cqa_adaptive_step_enqueue(h, 0, qp + (i % n_in) * q_stride, atol, sel, Op, certp, flagsp, stream)
         torch.cuda.synchronize()
         lc0 = cqa.cqa_ladder_counts(h)
         ta0 = time.perf_counter()
         for i in range(n_ad):
-            cqa.cqa_adaptive_step_enqueue(h, 0, qp + (W + i) * q_stride, atol, sel, Op, certp, flagsp, stream)
+            cqa.cqa_adaptive_step_enqueue(h, 0, qp + ((W + i) % n_in) * q_stride, atol, sel, Op, certp, flagsp, stream)
         torch.cuda.synchronize()
         ad_ms = (time.perf_counter() - ta0) * 1e3 / n_ad
         lc1 = cqa.cqa_ladder_counts(h)
@@ -475,11 +475,11 @@ def main() -> int:
         vsel = cqa.Selector(0.995, 2, 128, 128, v_limit=128)
         vtol = cqa.Tolerances(rank_depth=1, rank_min_mass=0.25, v_tol=0.05)
         for i in range(3):
-            cqa.cqa_adaptive_step_enqueue(h, 0, qp + i * q_stride, vtol, vsel, Op, certp, flagsp, stream)
+            cqa.cqa_adaptive_step_enqueue(h, 0, qp + (i % n_in) * q_stride, vtol, vsel, Op, certp, flagsp, stream)
         torch.cuda.synchronize()
         tv0 = time.perf_counter()
         for i in range(n_ad):
-            cqa.cqa_adaptive_step_enqueue(h, 0, qp + (W + i) * q_stride, vtol, vsel, Op, certp, flagsp, stream)
+            cqa.cqa_adaptive_step_enqueue(h, 0, qp + ((W + i) % n_in) * q_stride, vtol, vsel, Op, certp, flagsp, stream)
         torch.cuda.synchronize()
         adv_ms = (time.perf_counter() - tv0) * 1e3 / n_ad
         vstate = cqa.cqa_adaptive_state(h, 0, sh.batch, sh.n_q_heads, sh.n_kv_heads)
@@ -490,7 +490,7 @@ def main() -> int:
             torch.cuda.synchronize()
             tt = time.perf_counter()
             for i in range(n_ad):
-                cqa.cqa_adaptive_step_enqueue(h, 0, qp + (first + i) * q_stride, tl, sl, Op, certp, flagsp, stream)
+                cqa.cqa_adaptive_step_enqueue(h, 0, qp + ((first + i) % n_in) * q_stride, tl, sl, Op, certp, flagsp, stream)
             torch.cuda.synchronize()
             return (time.perf_counter() - tt) * 1e3 / n_ad
         # the paper's default promoted sets (every head its own selection) against the per-group union
