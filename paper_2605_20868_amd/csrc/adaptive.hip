@@ -11,7 +11,7 @@
 //
 // Sequence on one stream (launch_adaptive): the certified pass over all sealed blocks in INT8 /
 // INT4 (it emits the block log-masses, eta_b and the usual partial sets, and its reduction the
-// total log-mass, Delta_h and V_max the selector needs) -> select_kernel (per head) ->
+// total log-mass, Delta_h and V_max the selector needs) -> select_kernel (per head and ranking: keys, values) ->
 // compact_kernel (per group: union bit mask -> per-block flags and ordered list) -> promoted-block
 // pass over the listed blocks only: positive partial sets computed with the originals the flags ask
 // for (read straight from the pinned Tier-2 arrays over the host link) and negated sets computed as

@@ -204,7 +204,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   // address arithmetic.  The prefetch issued by a wave's last iteration is never used: it is
   // aimed at one record per head that every wave shares (the head's first), which stays in L2, so
   // it costs no HBM traffic.  A ragged last quad of the head reads the not yet sealed blocks of
-  // its record, which hold zeros and are masked out.
+  // its record, whose metadata is zero, and masks them out.
   // The prefetch is unconditional on purpose: guarding it with a branch makes every prefetched
   // register a phi and costs dozens of spilled VGPRs.
   //   K codes : block i, channel half cq; lane (token n, kg) takes bytes [16 l, +16) of each KB
@@ -486,8 +486,8 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
     }
 
     // ---- block statistics and online softmax of head kg; this lane is token n of each block.
-    //      Branch-free.  Blocks past the end of the head (only in its last quad) hold zeros --
-    //      unsealed memory is cleared -- so their eta, nu and Delta_b are already zero; giving
+    //      Branch-free.  Blocks past the end of the head (only in its last quad) have zero
+    //      metadata -- the seal clears it -- so their eta, nu and Delta_b are already zero; giving
     //      their scores a huge negative value makes every weight and mass they produce vanish.
     float mbv[4], ptv[4], sbv[4];
     float mq = -INFINITY;

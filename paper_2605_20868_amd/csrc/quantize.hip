@@ -367,7 +367,7 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
   }
 }
 
-// An append that completes no block: its tokens join the trailing block and, for short appends with
+// An append that completes no block: its tokens join the trailing block and, with
 // Tier 2, the FP16 originals go straight into the pinned arrays (device stores to mapped host
 // memory: a decode-time append of one token per head is one small launch).  16 lanes per token row.
 // dst_first: slot of the first new token; n_new < 16.  t2_k / t2_v: null = Tier-2 handled elsewhere.
