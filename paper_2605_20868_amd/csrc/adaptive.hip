@@ -1108,7 +1108,7 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   ra.n_kv = hkv;
   DecodeArgs a{};   // every field starts null / zero
   a.t1 = c->t1 + layer_head0 * c->nq_cap * QUAD_BYTES;
-  a.sigmax = layer_sigmax(c, layer, false);
+  a.sigmax = c->sigmax + layer_head0;
   a.q = q;
   a.partials = c->partials;
   a.blk_logmass = w.lmx;

@@ -142,8 +142,6 @@ static void release(cqa_cache* h) {
   }
   delete[] c->prof_ms;
   delete[] c->length;
-  delete[] c->sigmax_half;
-  delete[] c->sealed;
   delete h;
 }
 
@@ -213,7 +211,7 @@ int32_t cqa_workspace_bytes(const cqa_cache_desc* desc, int64_t* device_bytes,
   const int64_t groups = (int64_t)desc->batch * desc->n_kv_heads;
   if (device_bytes) {
     // every device allocation of create_cache, in its order ...
-    int64_t n = s.t1 + 2 * s.heads * 4 + 2 * s.trail + s.partials + 2 * s.dense_ws + s.select;
+    int64_t n = s.t1 + s.heads * 4 + 2 * s.trail + s.partials + 2 * s.dense_ws + s.select;
     if (t2) {
       n += 3 * s.ad_lm + 2 * s.ad_sel + 4 * s.ad_head + 2 * s.ad_mask + s.ad_slot + s.ad_group + s.ad_ulist +
            s.ad_eta + 8;
@@ -252,20 +250,11 @@ static int32_t create_cache(const cqa_cache_desc* desc, __half* caller_k, __half
   c->desc = *desc;
   c->t2_borrowed = caller_k != nullptr;
   c->length = new (std::nothrow) int64_t[desc->n_layers];
-  c->sigmax_half = new (std::nothrow) uint8_t[desc->n_layers];
-  c->sealed = new (std::nothrow) bool[desc->n_layers];
-  if (c->length == nullptr || c->sigmax_half == nullptr || c->sealed == nullptr) {
-    delete[] c->length;
-    delete[] c->sigmax_half;
-    delete[] c->sealed;
+  if (c->length == nullptr) {
     delete h;
     return CQA_ERR_INVALID_ARG;
   }
-  for (int i = 0; i < desc->n_layers; ++i) {
-    c->length[i] = 0;
-    c->sigmax_half[i] = 0;
-    c->sealed[i] = false;
-  }
+  for (int i = 0; i < desc->n_layers; ++i) c->length[i] = 0;
   // from here on release() frees whatever has been set, and the handle itself
   CQA_TRY(hipGetDevice(&c->device));
   CQA_TRY(hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, c->device));
@@ -279,8 +268,8 @@ static int32_t create_cache(const cqa_cache_desc* desc, __half* caller_k, __half
   // the metadata of blocks that are not sealed yet must read as zeros: the decode pass loads whole
   // records and only masks the scores of the unsealed blocks of a head's last record
   CQA_TRY(hipMemset(c->t1, 0, (size_t)s.t1));
-  CQA_ALLOC_DEV(c->sigmax, 2 * s.heads * 4);
-  CQA_TRY(hipMemset(c->sigmax, 0, (size_t)(2 * s.heads) * 4));
+  CQA_ALLOC_DEV(c->sigmax, s.heads * 4);
+  CQA_TRY(hipMemset(c->sigmax, 0, (size_t)s.heads * 4));
   CQA_ALLOC_DEV(c->trail_k, s.trail);
   CQA_ALLOC_DEV(c->trail_v, s.trail);
   CQA_ALLOC_DEV(c->partials, s.partials);
@@ -419,13 +408,8 @@ int32_t cqa_cache_reset(cqa_cache* h, int32_t layer) {
   Cache* c = &h->impl;
   CQA_HIP(hipDeviceSynchronize());
   // Nothing of Tier-1 is cleared here: the next seal clears what the decode pass reads beyond its last
-  // block, and the running maxima of sigma switch to the half that the first seal since the
-  // last reset has cleared.  (Clearing the layer's records took 22 us at 64K tokens x 8 heads, and each
-  // of the two memsets a wait on the host.)
-  if (c->sealed[layer]) {
-    c->sigmax_half[layer] ^= 1;
-    c->sealed[layer] = false;
-  }
+  // block, and the running maxima of sigma start afresh with the first seal.  (Clearing the layer's
+  // records took 22 us at 64K tokens x 8 heads, and each of the two memsets a wait on the host.)
   if (c->ad.sc_map != nullptr) {
     // the layer's blocks are gone: nothing of it stays in the FP16 scratch
     const int64_t h0 = head_index(c, layer, 0, 0), nh = (int64_t)c->desc.batch * c->desc.n_kv_heads;

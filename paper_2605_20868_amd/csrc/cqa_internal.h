@@ -159,10 +159,8 @@ struct Cache {
   uint32_t* ladder_tickets;
   uint32_t* ladder_counts;   // [2] steps served by Rung 3 / 4, [1] word of the last step that raised a flag
   uint32_t ladder_seq;       // host: number of the last enqueue-only step, never 0
-  float* sigmax;             // [2][heads_total] running max of sigma (non-negative: ordered as ints); a layer uses
-                             // one of the two until it is reset, see layer_sigmax
-  uint8_t* sigmax_half;      // host, per layer: the half in use
-  bool* sealed;              // host, per layer: a block has been sealed since the last reset
+  float* sigmax;             // [heads_total] running max of sigma (non-negative: ordered as ints) over the sealed
+                             // blocks; a sequence's first seal sets it, so it holds nothing while there are none
   // trailing FP16 partial blocks [heads_total][16][128]
   __half* trail_k;
   __half* trail_v;
@@ -239,12 +237,6 @@ struct DecodeArgs {
 
 inline int64_t head_index(const Cache* c, int layer, int b, int kvh) {
   return ((int64_t)layer * c->desc.batch + b) * c->desc.n_kv_heads + kvh;
-}
-
-// The layer's running maxima of sigma, [batch][n_kv_heads]: the ones in use, or (next) the ones it uses
-// after its next reset.  The first seal after a reset clears the next ones, so a reset only switches.
-inline float* layer_sigmax(const Cache* c, int layer, bool next) {
-  return c->sigmax + (int64_t)(c->sigmax_half[layer] ^ (next ? 1 : 0)) * c->heads_total + head_index(c, layer, 0, 0);
 }
 
 extern thread_local int g_last_hip_error;

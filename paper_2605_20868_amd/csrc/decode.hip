@@ -577,7 +577,7 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
   if (nb > 0) {
     DecodeArgs a{};   // every field starts null / zero
     a.t1 = c->t1 + layer_head0 * c->nq_cap * QUAD_BYTES;
-    a.sigmax = layer_sigmax(c, layer, false);
+    a.sigmax = c->sigmax + layer_head0;
     a.q = q;
     a.partials = partials;
     a.blk_logmass = blk_logmass;

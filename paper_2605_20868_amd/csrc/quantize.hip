@@ -26,7 +26,6 @@ struct SealArgs {
   __half* trail_v;
   uint8_t* t1;          // Tier-1 quad records
   float* sigmax;        // [Bt][Hkv] running max of sigma of the layer's sequences
-  float* sigmax_next;   // [Bt][Hkv] the one the layer uses after its next reset: cleared by the first seal
   int64_t nq_cap;
   int64_t nb_old;       // sealed blocks before this append
   int64_t n_new;
@@ -234,13 +233,14 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
 #pragma unroll
     for (int m = 1; m < 64; m <<= 1) smax = fmaxf(smax, __shfl_xor(smax, m));
     // thousands of blocks of one head would queue up on the same word: the running maximum is
-    // read first (it only grows, so a stale value merely costs a redundant atomic) and the atomic
-    // is issued only by a workgroup that raises it
+    // read first (within a launch it only grows, so a stale value merely costs a redundant atomic) and the
+    // atomic is issued only by a workgroup that raises it
     if (l == 0) {
-      if (__float_as_int(smax) > __hip_atomic_load(reinterpret_cast<int*>(a.sigmax + grp), __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT))
-        atomicMax(reinterpret_cast<int*>(a.sigmax + grp), __float_as_int(smax));
-      if (blockIdx.x == 0 && a.nb_old == 0) a.sigmax_next[grp] = 0.0f;
+      int* const word = reinterpret_cast<int*>(a.sigmax + grp);
+      if (a.nb_old == 0 && gridDim.x == 1)
+        *word = __float_as_int(smax);   // the sequence's first blocks, and no other workgroup has any: starts afresh
+      else if (__float_as_int(smax) > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(word, __float_as_int(smax));
     }
   } else {
     // ---- values
@@ -367,6 +367,15 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
   }
 }
 
+// The running maxima of sigma start afresh with the first blocks of a sequence.  The device does it, in stream
+// order, at the one address that they always have: a decode, or an append, that was recorded into a graph and is
+// replayed after a reset then reads what an eager call would.  One small launch ahead of a first seal of
+// several workgroups (a single workgroup per head simply stores its maximum).
+__global__ __launch_bounds__(256) void clear_sigmax_kernel(float* sigmax, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) sigmax[i] = 0.0f;
+}
+
 // An append that completes no block: its tokens join the trailing block and, with
 // Tier 2, the FP16 originals go straight into the pinned arrays (device stores to mapped host
 // memory: a decode-time append of one token per head is one small launch).  16 lanes per token row.
@@ -403,8 +412,7 @@ int32_t launch_seal(Cache* c, int layer, const __half* k_in, const __half* v_in,
     a.trail_k = c->trail_k;
     a.trail_v = c->trail_v;
     a.t1 = c->t1;
-    a.sigmax = layer_sigmax(c, layer, false);
-    a.sigmax_next = layer_sigmax(c, layer, true);
+    a.sigmax = c->sigmax + head_index(c, layer, 0, 0);
     a.nq_cap = c->nq_cap;
     a.nb_old = len_before / BLK;
     a.n_new = n_new;
@@ -422,9 +430,14 @@ int32_t launch_seal(Cache* c, int layer, const __half* k_in, const __half* v_in,
     a.n_seal = (int)n_seal;
     a.per = (int)std::min<int64_t>(std::max<int64_t>(n_seal * hkv * bt / 2048, 1), 8);
     // grid.x is limited to 2^31-1 blocks; n_seal <= nb_cap is far below that
-    hipLaunchKernelGGL(seal_kernel, dim3((unsigned)((n_seal + a.per - 1) / a.per), hkv, bt), dim3(128), 0, st, a);
+    const unsigned runs = (unsigned)((n_seal + a.per - 1) / a.per);
+    if (a.nb_old == 0 && runs > 1) {
+      const int n = bt * hkv;
+      hipLaunchKernelGGL(clear_sigmax_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a.sigmax, n);
+      CQA_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(seal_kernel, dim3(runs, hkv, bt), dim3(128), 0, st, a);
     CQA_HIP(hipGetLastError());
-    c->sealed[layer] = true;
     return CQA_OK;
   }
   hipLaunchKernelGGL(trail_kernel, dim3(hkv, bt), dim3(256), 0, st, k_in, v_in, c->trail_k, c->trail_v, (int)n_new, r,

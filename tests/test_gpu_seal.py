@@ -96,7 +96,7 @@ def test_a_reset_cache_equals_a_fresh_one(first, second, int8_query):
     with GpuLayerCache(2, 8, 2, 512) as fresh:
         want = fill(fresh)
     with GpuLayerCache(2, 8, 2, 512) as gc:
-        for rounds in range(3):                     # the maxima of sigma alternate between two halves
+        for rounds in range(3):
             kx, vx = kv[0].copy(), kv[1].copy()
             if rounds == 1:
                 kx[..., 7], vx[..., 40] = np.inf, np.nan        # what is left behind is not even finite
