@@ -14,6 +14,7 @@ namespace cqa {
 constexpr int DP_FLOATS = 4 + D;  // m (base 2), l, pad, pad, o[128]
 constexpr int DENSE_WAVES = 8;    // waves per workgroup of the dense pass
 constexpr int DENSE_WG_TARGET = 256;  // one workgroup of eight waves on each of the compute units
+constexpr int PAGED_WG = 16;      // a paged KV group with fewer workgroups is attended by single waves
 constexpr int DENSE_TILE = 32;    // tokens a wave takes per iteration
 // ... when the ladder reads the pinned originals, where the host link is the bound and more requests in
 // flight only make the workgroups' shares of it uneven.  One group of 131072 tokens: 8 tokens 1213 us,
@@ -65,9 +66,9 @@ struct DenseSmem {
   float ms[W][G][2];
 };
 
-// The W waves of a workgroup attend tiles [t0, t1) of 32 tokens of k, v ([n_tokens][128], device or
-// mapped host memory) for the G heads of one KV group, dealt round-robin; on return (after a
-// workgroup barrier) each wave's state is in LDS.
+// Wave w of W attends its tiles of [t0, t1), dealt round-robin, of k, v ([n_tokens][128], device or
+// mapped host memory) for G heads of one KV group, and leaves its state at mo [G][mo_stride] (the channels)
+// and ms [G][ms_stride] (maximum in base 2, sum).  AHEAD: tiles whose loads are in flight.
 // Bound by the memory stream.  Every load covers 1 KB of consecutive memory: a row of 16 lanes
 // holds one token, a lane 8 channels of it, so a wave's four rows take tokens r, 4 + r, 8 + r, ...
 // of a tile.  A score is 8 products per head and a row sum on DPP; after it every lane of the row
@@ -76,12 +77,12 @@ struct DenseSmem {
 // of 32 tokens 16 KB in flight per wave, 128 KB per compute unit.  Measured on 16 groups of 32775
 // tokens, 268 MB, four heads per group: 46.4 us = 5.8 TB/s (plain loads, tiles of 32: 85 us with the
 // reduction; the non-temporal hint: 49; one launch pair per group before: 2074).
-template <int G, int W, int TILE, bool NT>
-__device__ __forceinline__ void dense_split_work(const __half* __restrict__ q, const __half* __restrict__ k,
-                                                 const __half* __restrict__ v, int64_t n_tokens, int64_t t0,
-                                                 int64_t t1, DenseSmem<G, W>& sm) {
+template <int G, int W, int TILE, bool NT, int AHEAD = 1>
+__device__ __forceinline__ void dense_wave_work(const __half* __restrict__ q, const __half* __restrict__ k,
+                                                const __half* __restrict__ v, int64_t n_tokens, int64_t t0,
+                                                int64_t t1, int w, float* mo, int mo_stride, float* ms, int ms_stride) {
   constexpr int T = TILE / 4;   // tokens per row and tile
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int l = threadIdx.x & 63;
   const int c8 = l & 15, row = l >> 4;
   const float scale = 0.08838834764831845f * 1.4426950408889634f;   // 1 / sqrt(128), in base-2 units
 
@@ -98,7 +99,7 @@ __device__ __forceinline__ void dense_split_work(const __half* __restrict__ q, c
     for (int j = 0; j < 8; ++j) acc[j][h] = 0.0f;
   }
 
-  uint4 kr[T], vr[T];
+  uint4 kr[AHEAD][T], vr[AHEAD][T];
   // address = the tile's wave-uniform base + a 32-bit lane offset; tokens past the end read the last
   // token's row, their scores are masked.  The request of a wave's last iteration is not used:
   // it is aimed at the first query row, in cache, and costs no memory traffic.
@@ -110,65 +111,71 @@ __device__ __forceinline__ void dense_split_work(const __half* __restrict__ q, c
       DST[i] = ld_dense<NT>(base__ + (uint32_t)(min(i * 4 + row, last__) * (D * 2) + c8 * 16)); \
   }
   int64_t tile = t0 + __builtin_amdgcn_readfirstlane(w);
-  if (tile < t1) {
-    CQA_DENSE_LOAD(kr, k, tile, true)
-    CQA_DENSE_LOAD(vr, v, tile, true)
-  }
-  for (; tile < t1; tile += W) {
-    const int64_t nxt = tile + W;
-    const int live = (int)min((int64_t)TILE, n_tokens - tile * TILE);
-    float s[T][G];
 #pragma unroll
-    for (int i = 0; i < T; ++i) {
-      const __half2* kh = reinterpret_cast<const __half2*>(&kr[i]);
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const __half2* qh = reinterpret_cast<const __half2*>(&qr[h]);
-        float d = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          d = fmaf(__low2float(qh[j]), __low2float(kh[j]), d);
-          d = fmaf(__high2float(qh[j]), __high2float(kh[j]), d);
-        }
-        s[i][h] = d;
-      }
+  for (int u = 0; u < AHEAD; ++u)
+    if (tile + u * W < t1) {
+      CQA_DENSE_LOAD(kr[u], k, tile + u * W, true)
+      CQA_DENSE_LOAD(vr[u], v, tile + u * W, true)
     }
-    CQA_DENSE_LOAD(kr, k, nxt, nxt < t1)
+  while (tile < t1) {
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      float m_new = m_run[h];
+    for (int u = 0; u < AHEAD; ++u, tile += W) {
+      if (u > 0 && tile >= t1) break;
+      const int64_t nxt = tile + AHEAD * W;
+      const int live = (int)min((int64_t)TILE, n_tokens - tile * TILE);
+      float s[T][G];
 #pragma unroll
       for (int i = 0; i < T; ++i) {
-        const float sum16 = row_sum(s[i][h]);
-        s[i][h] = i * 4 + row < live ? sum16 * scale : -INFINITY;
-        m_new = fmaxf(m_new, s[i][h]);
-      }
-      const float alpha = __builtin_amdgcn_exp2f(m_run[h] - m_new);
-      float sum = 0.0f;
-#pragma unroll
-      for (int i = 0; i < T; ++i) {
-        s[i][h] = __builtin_amdgcn_exp2f(s[i][h] - m_new);
-        sum += s[i][h];
-      }
-      l_run[h] = fmaf(l_run[h], alpha, sum);
-      m_run[h] = m_new;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j][h] *= alpha;
-    }
-#pragma unroll
-    for (int i = 0; i < T; ++i) {
-      const __half2* vh = reinterpret_cast<const __half2*>(&vr[i]);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float v0 = __low2float(vh[j]), v1 = __high2float(vh[j]);
+        const __half2* kh = reinterpret_cast<const __half2*>(&kr[u][i]);
 #pragma unroll
         for (int h = 0; h < G; ++h) {
-          acc[2 * j][h] = fmaf(s[i][h], v0, acc[2 * j][h]);
-          acc[2 * j + 1][h] = fmaf(s[i][h], v1, acc[2 * j + 1][h]);
+          const __half2* qh = reinterpret_cast<const __half2*>(&qr[h]);
+          float d = 0.0f;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            d = fmaf(__low2float(qh[j]), __low2float(kh[j]), d);
+            d = fmaf(__high2float(qh[j]), __high2float(kh[j]), d);
+          }
+          s[i][h] = d;
         }
       }
+      CQA_DENSE_LOAD(kr[u], k, nxt, nxt < t1)
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        float m_new = m_run[h];
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+          const float sum16 = row_sum(s[i][h]);
+          s[i][h] = i * 4 + row < live ? sum16 * scale : -INFINITY;
+          m_new = fmaxf(m_new, s[i][h]);
+        }
+        const float alpha = __builtin_amdgcn_exp2f(m_run[h] - m_new);
+        float sum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+          s[i][h] = __builtin_amdgcn_exp2f(s[i][h] - m_new);
+          sum += s[i][h];
+        }
+        l_run[h] = fmaf(l_run[h], alpha, sum);
+        m_run[h] = m_new;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j][h] *= alpha;
+      }
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        const __half2* vh = reinterpret_cast<const __half2*>(&vr[u][i]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float v0 = __low2float(vh[j]), v1 = __high2float(vh[j]);
+#pragma unroll
+          for (int h = 0; h < G; ++h) {
+            acc[2 * j][h] = fmaf(s[i][h], v0, acc[2 * j][h]);
+            acc[2 * j + 1][h] = fmaf(s[i][h], v1, acc[2 * j + 1][h]);
+          }
+        }
+      }
+      CQA_DENSE_LOAD(vr[u], v, nxt, nxt < t1)
     }
-    CQA_DENSE_LOAD(vr, v, nxt, nxt < t1)
   }
 #undef CQA_DENSE_LOAD
 
@@ -182,29 +189,52 @@ __device__ __forceinline__ void dense_split_work(const __half* __restrict__ q, c
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] = sum_x32(sum_x16(acc[j][h] * f));
     if (row == 0) {
-      *reinterpret_cast<float4*>(&sm.mo[w][h][c8 * 8]) = make_float4(x[0], x[1], x[2], x[3]);
-      *reinterpret_cast<float4*>(&sm.mo[w][h][c8 * 8 + 4]) = make_float4(x[4], x[5], x[6], x[7]);
-      sm.ms[w][h][0] = M;
-      sm.ms[w][h][1] = L;
+      *reinterpret_cast<float4*>(&mo[h * mo_stride + c8 * 8]) = make_float4(x[0], x[1], x[2], x[3]);
+      *reinterpret_cast<float4*>(&mo[h * mo_stride + c8 * 8 + 4]) = make_float4(x[4], x[5], x[6], x[7]);
+      ms[h * ms_stride] = M;
+      ms[h * ms_stride + 1] = L;
     }
   }
+}
+
+// The W waves of a workgroup attend tiles [t0, t1) for the G heads of one KV group; on return (after a
+// workgroup barrier) each wave's state is in LDS.
+template <int G, int W, int TILE, bool NT>
+__device__ __forceinline__ void dense_split_work(const __half* __restrict__ q, const __half* __restrict__ k,
+                                                 const __half* __restrict__ v, int64_t n_tokens, int64_t t0,
+                                                 int64_t t1, DenseSmem<G, W>& sm) {
+  const int w = threadIdx.x >> 6;
+  dense_wave_work<G, W, TILE, NT>(q, k, v, n_tokens, t0, t1, w, sm.mo[w][0], D, sm.ms[w][0], 2);
   __syncthreads();
 }
 
-// (m, l, o[c]) of head h over the workgroup's waves, from LDS
-template <int G, int W>
-__device__ __forceinline__ void dense_wg_merge(const DenseSmem<G, W>& sm, int h, int c, float& M, float& L, float& o) {
-  M = sm.ms[0][h][0];
+// (m, l, o) of one channel over the waves of a split
+template <int W>
+__device__ __forceinline__ void dense_wave_merge(const float (&m)[W], const float (&l)[W], const float (&x)[W], float& M,
+                                                 float& L, float& o) {
+  M = m[0];
 #pragma unroll
-  for (int w = 1; w < W; ++w) M = fmaxf(M, sm.ms[w][h][0]);
+  for (int w = 1; w < W; ++w) M = fmaxf(M, m[w]);
   L = 0.0f;
   o = 0.0f;
 #pragma unroll
   for (int w = 0; w < W; ++w) {
-    const float f = __builtin_amdgcn_exp2f(sm.ms[w][h][0] - M);
-    L = fmaf(f, sm.ms[w][h][1], L);
-    o = fmaf(f, sm.mo[w][h][c], o);
+    const float f = __builtin_amdgcn_exp2f(m[w] - M);
+    L = fmaf(f, l[w], L);
+    o = fmaf(f, x[w], o);
   }
+}
+// ... of head h, channel c over the workgroup's waves, from LDS
+template <int G, int W>
+__device__ __forceinline__ void dense_wg_merge(const DenseSmem<G, W>& sm, int h, int c, float& M, float& L, float& o) {
+  float m[W], l[W], x[W];
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    m[w] = sm.ms[w][h][0];
+    l[w] = sm.ms[w][h][1];
+    x[w] = sm.mo[w][h][c];
+  }
+  dense_wave_merge<W>(m, l, x, M, L, o);
 }
 
 // this workgroup's partial sets: ws[h][split]
@@ -249,6 +279,29 @@ __device__ __forceinline__ float dense_merge_row(const float* part, int nsplit, 
   return o / L;
 }
 
+// ... where the waves of a split have left their states one by one (dense_paged_kernel): nsplit * DENSE_WAVES sets
+__device__ __forceinline__ float dense_merge_row_of_waves(const float* part, int nsplit, int c) {
+  float M = M_EMPTY;
+  const int sets = nsplit * DENSE_WAVES;
+  for (int s = 0; s < sets; s += 64) M = fmaxf(M, part[(int64_t)min(s + (int)(threadIdx.x & 63), sets - 1) * DP_FLOATS]);
+  M = wave_max(M);
+  float L = 0.0f, o = 0.0f;
+  for (int s = 0; s < nsplit; ++s, part += DENSE_WAVES * DP_FLOATS) {
+    float m[DENSE_WAVES], l[DENSE_WAVES], x[DENSE_WAVES], Ms, Ls, os;
+#pragma unroll
+    for (int w = 0; w < DENSE_WAVES; ++w) {
+      m[w] = part[w * DP_FLOATS];
+      l[w] = part[w * DP_FLOATS + 1];
+      x[w] = part[w * DP_FLOATS + 4 + c];
+    }
+    dense_wave_merge<DENSE_WAVES>(m, l, x, Ms, Ls, os);
+    const float f = __builtin_amdgcn_exp2f(Ms - M);
+    L = fmaf(f, Ls, L);
+    o = fmaf(f, os, o);
+  }
+  return o / L;
+}
+
 __device__ __forceinline__ void dense_mark_served(cqa_head_cert* cert, uint32_t* flags, int64_t row, int rung) {
   if (cert != nullptr) {
     cert[row].E_key = 0.0f;
@@ -264,7 +317,8 @@ struct DenseArgs {
   const __half* v;
   int64_t n_tokens;
   int nsplit, tiles_per_split;
-  float* ws;                // [groups][G][nsplit][DP_FLOATS], unused with one split
+  int by_wave;              // 1: the partial sets are those of the single waves, nsplit * DENSE_WAVES of them
+  float* ws;                // [groups][G][partial sets][DP_FLOATS], unused with one
   float* O;                 // [groups][G][128]
   const uint32_t* select;   // [groups][G] or null = all: rows that are written
   cqa_head_cert* cert;      // or null
@@ -297,6 +351,24 @@ __global__ __launch_bounds__(64 * DENSE_WAVES, 2) void dense_split_kernel(DenseA
   }
 }
 
+// One paged KV group of a layer that has many: the dense call gives such a group fewer than PAGED_WG workgroups, often
+// one, but here it is alone on the chip.  Every (split, wave, head) is a workgroup of one wave, so the group spreads
+// over 8 x heads as many compute units; the arithmetic of a head is that of dense_split_kernel, and
+// dense_merge_row_of_waves merges in the same order, so the rows are bit-equal to the dense call's.
+// Bound by the chain of a wave's tiles: 0.8 us each with two requested ahead, 1.05 with one.
+// One group of 32768 tokens in a layer of 136 or more groups: this kernel and the merge 116 us against 452 for one
+// workgroup; the fallback call with its copies (295) 812 -> 470 us.
+__global__ __launch_bounds__(64) void dense_paged_kernel(DenseArgs a) {
+  const int h = blockIdx.y, unit = blockIdx.x;   // unit = split * DENSE_WAVES + wave
+  if (a.select != nullptr && a.select[h] == 0) return;
+  const int split = unit / DENSE_WAVES;
+  const int64_t tiles = (a.n_tokens + DENSE_TILE - 1) / DENSE_TILE;
+  const int64_t t0 = (int64_t)split * a.tiles_per_split;
+  const int64_t t1 = min(t0 + (int64_t)a.tiles_per_split, tiles);
+  float* p = a.ws + ((int64_t)h * a.nsplit * DENSE_WAVES + unit) * DP_FLOATS;
+  dense_wave_work<1, DENSE_WAVES, DENSE_TILE, false, 2>(a.q + h * D, a.k, a.v, a.n_tokens, t0, t1, unit % DENSE_WAVES, p + 4, 0, p, 0);
+}
+
 // One workgroup of 128 threads per row.  (Before: one thread per channel walked all splits twice,
 // one load in flight: 112 us for 256 splits of one group, which made it 16 times 125 us for the
 // 268 MB call.)
@@ -304,7 +376,8 @@ __global__ __launch_bounds__(128) void dense_reduce_kernel(DenseArgs a) {
   const int64_t row = blockIdx.x;
   if (a.select != nullptr && a.select[row] == 0) return;
   const int c = threadIdx.x;
-  a.O[row * D + c] = dense_merge_row(a.ws + row * a.nsplit * DP_FLOATS, a.nsplit, c);
+  a.O[row * D + c] = a.by_wave ? dense_merge_row_of_waves(a.ws + row * a.nsplit * DENSE_WAVES * DP_FLOATS, a.nsplit, c)
+                               : dense_merge_row(a.ws + row * a.nsplit * DP_FLOATS, a.nsplit, c);
   if (c == 0) dense_mark_served(a.cert, a.flags, row, a.rung);
 }
 
@@ -549,16 +622,25 @@ int32_t launch_dense(const __half* q, const __half* k, const __half* v, int grou
   a.cert = cert;
   a.flags = flags;
   a.rung = rung;
+  // by single waves: where a workgroup per split would leave most of the chip idle, it has more than a tile per wave to
+  // do, and the workspace of one group (dense_ws_units sets per head) holds the waves' states.  One group of 32768
+  // tokens with its copies, a workgroup per split and by waves: 4 splits 470, 383 us; 2 582, 410; 1 812, 470 (16
+  // splits, a workgroup each: 385).  4107 tokens, every group of 32: 77 -> 70 us a group.
+  a.by_wave = groups == 1 && a.nsplit < PAGED_WG && a.tiles_per_split > DENSE_WAVES &&
+              a.nsplit * DENSE_WAVES <= dense_ws_units(n_tokens);
   if (groups * std::max(a.nsplit, group) > 0x7FFFFFFF) return CQA_ERR_UNSUPPORTED;   // one grid dimension
   const dim3 grid((unsigned)(groups * a.nsplit));
-  switch (group) {
+  if (a.by_wave) {
+    if (group != 1 && group != 2 && group != 4) return CQA_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(dense_paged_kernel, dim3((unsigned)(a.nsplit * DENSE_WAVES), (unsigned)group), dim3(64), 0, st, a);
+  } else switch (group) {
     case 1: hipLaunchKernelGGL(dense_split_kernel<1>, grid, dim3(64 * DENSE_WAVES), 0, st, a); break;
     case 2: hipLaunchKernelGGL(dense_split_kernel<2>, grid, dim3(64 * DENSE_WAVES), 0, st, a); break;
     case 4: hipLaunchKernelGGL(dense_split_kernel<4>, grid, dim3(64 * DENSE_WAVES), 0, st, a); break;
     default: return CQA_ERR_UNSUPPORTED;
   }
   CQA_HIP(hipGetLastError());
-  if (a.nsplit > 1) {
+  if (a.nsplit > 1 || a.by_wave) {
     hipLaunchKernelGGL(dense_reduce_kernel, dim3((unsigned)(groups * group)), dim3(128), 0, st, a);
     CQA_HIP(hipGetLastError());
   }

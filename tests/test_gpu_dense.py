@@ -37,3 +37,79 @@ def test_dense_attention_at_the_edges_of_its_geometry(batch, hq, hkv, n):
         # ~1e-6 in practice, and a weight by the same factor; 1e-5 of the largest value that is averaged
         assert np.abs(got[b, h] - ref).max() <= 1e-5 * np.abs(v[b, h // g].astype(np.float64)).max()
     assert np.isfinite(got).all()
+
+
+# (batch, kv heads, group, tokens): layers of so many KV groups that the dense call has one or a few workgroups per group,
+# with a last split or last rounds of a wave that are short, and sizes on both sides of the single-wave rule
+@pytest.mark.parametrize("bt,hkv,g,n", [(17, 8, 4, 1350), (9, 8, 4, 7003), (33, 8, 1, 2100), (3, 7, 2, 5000), (5, 8, 1, 20000), (6, 8, 2, 9000),
+                                        (1, 8, 4, 3000), (9, 1, 4, 3090), (20, 8, 2, 880), (1, 16, 4, 33000)])
+def test_fallback_rows_equal_the_dense_call_in_large_layers(bt, hkv, g, n):
+    """The fallback attends one KV group at a time, by single waves where the dense call gives a group few workgroups, and
+    merges them in the same order."""
+    import torch
+
+    from helpers import GpuLayerCache
+    print("fallback", bt, hkv, g, n, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    k, v = (torch.randn((bt, hkv, n, 128), generator=gen, device="cuda", dtype=torch.float32).half() for _ in range(2))
+    q = torch.randn((bt, hkv * g, 128), generator=gen, device="cuda", dtype=torch.float32).half()
+    with GpuLayerCache(bt, hkv * g, hkv, n + 16) as gc:
+        cqa = gc.cqa
+        gc.append(k, v)
+        need = cqa.cqa_dense_workspace_bytes(bt, hkv * g, n)
+        ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        dense = torch.empty((bt, hkv * g, 128), dtype=torch.float32, device="cuda")
+        cqa.cqa_dense_attention(q, k, v, bt, hkv * g, hkv, n, dense, ws)
+        gc.O.fill_(float("nan"))
+        cqa.cqa_dense_fallback(gc.h, 0, q, None, 1, 4, gc.O)
+        torch.cuda.synchronize()
+        assert (ws[need:] == 0x5A).all()
+        assert torch.equal(gc.O, dense)
+        sel = np.zeros((bt, hkv * g), dtype=np.uint32)
+        sel[bt - 1, 1] = sel[bt // 2, hkv * g - 1] = 1
+        gc.O.fill_(7.0)
+        cqa.cqa_dense_fallback(gc.h, 0, q, sel, 0, 3, gc.O)
+        torch.cuda.synchronize()
+        on = torch.from_numpy(sel != 0)
+        assert torch.equal(gc.O.cpu()[on], dense.cpu()[on]) and (gc.O.cpu()[~on] == 7.0).all()
+        for b, h in ((0, 0), (bt - 1, hkv * g - 1)):
+            kk, vv = k[b, h // g].cpu().numpy(), v[b, h // g].cpu().numpy()
+            ref = oracle.softmax_attention(q[b, h].cpu().numpy(), kk, vv)
+            # as above: 1e-5 of the largest value that is averaged
+            assert np.abs(dense[b, h].cpu().numpy().astype(np.float64) - ref).max() <= 1e-5 * np.abs(vv.astype(np.float64)).max()
+
+
+def test_a_paged_group_of_a_large_layer_takes_no_longer_than_one_of_a_small_layer():
+    """One head of one KV group falls back, in a layer of 8 groups and in one of 136: the same bytes of the same pinned
+    arrays over the host link, and the same attention.  372 and 470 us; 814 us for the large layer with the dense
+    call's one workgroup per group."""
+    import time
+
+    import torch
+
+    from helpers import load_binding
+    print("fallback time", flush=True)
+    cqa = load_binding()
+    n, most, took = 32768, 17, []
+    t2 = [torch.empty(most * 8 * n * 128, dtype=torch.float16, pin_memory=True) for _ in range(2)]
+    for bt in (1, most):
+        h = cqa.cqa_cache_create_caller_tier2(1, bt, 32, 8, n, t2[0], t2[1], t2[0].numel() * 2)
+        try:
+            k = torch.randn((bt, 8, n, 128), device="cuda", dtype=torch.float16)
+            q = torch.randn((bt, 32, 128), device="cuda", dtype=torch.float16)
+            O = torch.empty((bt, 32, 128), device="cuda", dtype=torch.float32)
+            cqa.cqa_cache_append(h, 0, k, k, n)
+            sel = np.zeros((bt, 32), dtype=np.uint32)
+            sel[0, 5] = 1
+            times = []
+            for _ in range(12):
+                torch.cuda.synchronize()
+                t0 = time.perf_counter()
+                cqa.cqa_dense_fallback(h, 0, q, sel, 0, 3, O)
+                torch.cuda.synchronize()
+                times.append(time.perf_counter() - t0)
+            took.append(min(times))
+        finally:
+            cqa.cqa_cache_destroy(h)
+    assert took[1] <= 1.6 * took[0], took
