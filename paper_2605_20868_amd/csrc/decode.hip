@@ -615,6 +615,12 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     a.int8_query = tol.int8_query;
     a.wpb = wpb;
     a.keep_sets = pstride > 0 ? 1 : 0;
+    // With a mirror of the flag words in host memory the four waves that finish a group of four heads store neighbouring
+    // words at the same moment, and such stores wait for one another: from there on a launch of its own is
+    // the cheaper place.  A step of 4 heads per group, this launch finishing the rows and the reduction: 32 rows
+    // 18.0, 20.5 us; 64 20.0, 21.3; 128 23.3, 22.2; 256 27.5, 23.1; 1280 55.7, 45.9.  One or two heads per
+    // group gain at any number: 720 rows 31.0, 34.6; 1440 36.3, 41.0.
+    a.finish = nsplit == 1 && (flags_mirror == nullptr || hq / hkv < 4 || bt * hq <= 64) ? 1 : 0;
     // the quantised-query scoring exists in the matrix-core pass (and in the promoted-block pass of
     // the adaptive calls), not in the vector-ALU cross-check kernel
     if (tol.int8_query != 0 && c->variant != 0) return CQA_ERR_UNSUPPORTED;
@@ -627,7 +633,7 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
       // one-dimensional grid: the kernel decodes (head, partial set) from the linear index
       const int32_t rc = launch_split_mfma(a, ra, hq / hkv, dim3((unsigned)nsplit * hkv * bt), ev0, ev1, st);
       if (rc != CQA_OK) return rc;
-      reduced = nsplit == 1;
+      reduced = a.finish != 0;
     } else {
       switch (hq / hkv) {
         case 1: hipLaunchKernelGGL((certified_split_kernel<1, false>), grid, dim3(256), 0, st, a); break;

@@ -657,7 +657,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   //      to arrive finishing the rows (agent-scope stores, a ticket, agent-scope loads) measured
   //      8.9 -> 15.8 us for this launch at 1K and 11.7 -> 18.2 us at 8K, against a reduction of 4.7 us.
   const int hq0 = kvh * G;
-  const bool finish = a.nsplit == 1;
+  const bool finish = a.finish != 0;
   TrailRegs tr;
   if (finish && w < G) {
     __builtin_amdgcn_s_setprio(2);

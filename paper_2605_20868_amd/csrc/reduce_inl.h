@@ -283,6 +283,9 @@ __device__ __forceinline__ HeadState reduce_sets(const float* part, int n_sets, 
 // ms + i * ms_stride, channels at mo + i * mo_stride.  Waves that saw no block hold zeros and a maximum of
 // -infinity; the result of only such waves is one more of the kind.
 __device__ __forceinline__ HeadState reduce_lds(const float* ms, int ms_stride, const float* mo, int mo_stride, int n) {
+  // A product fused into the first addition of a sum over lanes would round differently in the two lanes of a pair:
+  // every lane holds the same bits, those that a partial set carries, whichever launch finishes the row.
+#pragma clang fp contract(off)
   const int l = threadIdx.x & 63;
   const bool on = l < n;
   const float* m = ms + (on ? l : 0) * ms_stride;

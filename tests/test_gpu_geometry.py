@@ -44,3 +44,28 @@ def test_results_do_not_depend_on_the_launch_geometry(bt, hkv, g, n, splits):
         O2, cert2, _ = gc.certified_decode(q)
         assert np.abs(O2 - O).max() <= 1e-4 * np.abs(O).max()
         assert np.allclose(cert2["lse"], cert["lse"], rtol=5e-6, atol=0)
+
+
+@pytest.mark.parametrize("bt,hkv,g,n", [(2, 8, 4, 125), (17, 1, 4, 125), (9, 2, 4, 70), (40, 8, 4, 333), (40, 8, 2, 125), (33, 8, 1, 200)])
+def test_steps_of_one_split_give_the_same_rows_on_both_routes(bt, hkv, g, n):
+    """A sequence of one workgroup is finished by the split pass, or, when many rows mirror their flags to the host, by the
+    reduction: the host-resolved step, with its mirror, and the plain call bit for bit, either side of 64 rows."""
+    print("one split", bt, hkv, g, n, flush=True)
+    rng = np.random.default_rng(n + bt)
+    k = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    v = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    q = rng.standard_normal((bt, hkv * g, 128)).astype(np.float16)
+    oc = oracle.OracleLayerCache(1, hkv)
+    oc.append(k[-1:], v[-1:])
+    ref = oc.certified_decode(q[-1:], oracle.Tolerances())
+    with GpuLayerCache(bt, hkv * g, hkv, n + 16) as gc:
+        gc.append(k, v)
+        assert gc.cqa.cqa_decode_splits(gc.h, 0) == 1
+        O, cert, flags = [x.copy() for x in gc.certified_decode(q)]
+        for h, r in enumerate(ref):
+            assert_head_matches(r, O[-1, h], cert[-1, h], flags[-1, h], (bt, hkv, g, h))
+        for _ in range(2):
+            gc.O.fill_(float("nan"))
+            rung, O2, cert2, flags2 = gc.decode_step(q)
+            assert rung == 0
+            assert np.array_equal(O, O2) and cert.tobytes() == cert2.tobytes() and (flags == flags2).all()
