@@ -304,6 +304,8 @@ struct LadderArgs {
   const uint32_t* raised;   // equals raised_tag when some head of this step requests a fallback (it may
   uint32_t raised_tag;      // do so without one: a recorded step that is replayed keeps its number)
   int groups;               // Bt * Hkv
+  int many_items;           // more served (KV group, split) items than this are walked by many_walkers workgroups
+  int many_walkers;
   float* O;
   cqa_head_cert* cert;
   uint32_t* flags;

@@ -381,14 +381,17 @@ __global__ __launch_bounds__(128) void dense_reduce_kernel(DenseArgs a) {
   if (c == 0) dense_mark_served(a.cert, a.flags, row, a.rung);
 }
 
-// The (KV group, split) items of the groups that a rung serves, walked by the launch's workgroups of W waves.
+// The (KV group, split) items of the groups that a rung serves, walked by the first `walkers` of the launch's workgroups
+// of W waves.
 // flagged(row): whether a row asked for the fallback (uniform in the wave).  mark: also rewrite the
 // served rows' certificates and rung bits.
 template <int G, int W, typename F>
-__device__ __forceinline__ void ladder_serve(const LadderArgs& a, int rung, F flagged, bool mark, DenseSmem<G, W>& sm) {
+__device__ __forceinline__ void ladder_serve(const LadderArgs& a, int rung, int walkers, F flagged, bool mark,
+                                             DenseSmem<G, W>& sm) {
   __shared__ int s_last;
   const int64_t items = (int64_t)a.groups * a.nsplit;
-  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+  if ((int)blockIdx.x >= walkers) return;
+  for (int64_t item = blockIdx.x; item < items; item += walkers) {
     const int64_t grp = item / a.nsplit;
     const int split = (int)(item - grp * a.nsplit);
     const int64_t row0 = grp * G;
@@ -440,7 +443,7 @@ __device__ __forceinline__ void ladder_serve(const LadderArgs& a, int rung, F fl
 template <int G>
 __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
   if (*a.raised != a.raised_tag) return;
-  __shared__ int s_rung;
+  __shared__ int s_rung, s_walkers;
   __shared__ int s_cnt[4], s_pre[4];
   {
     // each wave takes every fourth chunk of 64 flag words (a group's heads never straddle a
@@ -477,6 +480,12 @@ __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
       int rung = cnt > 0 ? 3 : 0;
       if (rung != 0 && (pre || (a.rung4_min_groups > 0 && cnt >= a.rung4_min_groups))) rung = 4;
       s_rung = rung;
+      // Few items: a workgroup each, wherever they lie in the layer.  Many: the link is kept busy by fewer workgroups,
+      // each with its own run of tokens to read, and runs better on fewer runs at a time.  Layers of 264 groups of 500
+      // tokens, 320 of 300 and 512 of 1000, all served, on 512 workgroups and on 128: 1447 -> 1321, 1301 -> 987 and
+      // 5451 -> 4853 us (a workgroup per item: 1427, 1133, 5191).  128 items on 128 as well: 333 -> 362.
+      s_walkers = (int64_t)(rung == 4 ? a.groups : cnt) * a.nsplit > a.many_items ? min((int)gridDim.x, a.many_walkers)
+                                                                                 : (int)gridDim.x;
       if (rung != 0 && blockIdx.x == 0) atomicAdd(a.counts + (rung - 3), 1u);
     }
   }
@@ -486,7 +495,7 @@ __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
 
   __shared__ __align__(16) DenseSmem<G, 4> sm;
   // (the rung bits that a finished group's rows get do not touch the bits looked at here)
-  ladder_serve<G, 4>(a, rung, [&](int64_t row) { return (a.flags[row] & CQA_FLAG_ANY) != 0u; }, true, sm);
+  ladder_serve<G, 4>(a, rung, s_walkers, [&](int64_t row) { return (a.flags[row] & CQA_FLAG_ANY) != 0u; }, true, sm);
 }
 
 // Reduction and ladder of a short step of few rows (at most FINISH_ROWS heads with at most FINISH_SETS partial sets
@@ -535,7 +544,7 @@ __global__ __launch_bounds__(64 * FINISH_ROWS) void finish_ladder_kernel(ReduceA
   }
   if (rung == 0) return;
   __shared__ __align__(16) DenseSmem<G, FINISH_ROWS> sm;
-  ladder_serve<G, FINISH_ROWS>(a, rung, [&](int64_t i) { return ((any >> (int)i) & 1u) != 0u; }, false, sm);
+  ladder_serve<G, FINISH_ROWS>(a, rung, (int)gridDim.x, [&](int64_t i) { return ((any >> (int)i) & 1u) != 0u; }, false, sm);
 }
 
 int ladder_splits(const Cache* c, int64_t n_tokens) {
@@ -578,6 +587,8 @@ int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_
   a.raised = ladder_raised(c);
   a.raised_tag = raised_tag;
   a.groups = bt * hkv;
+  a.many_items = c->n_cu;
+  a.many_walkers = std::max(c->n_cu / 2, 1);
   a.O = O;
   a.cert = cert;
   a.flags = flags;

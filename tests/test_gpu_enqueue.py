@@ -331,3 +331,33 @@ def test_reduction_and_ladder_in_one_launch_for_few_rows(bt, hkv, g, n):
             b, h = divmod(i, hq)
             assert_head_matches(r, O[b, h], cert[b, h], flags[b, h], ("riding token", b, h))
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("bt,hkv,g,n", [(33, 8, 4, 500), (40, 8, 1, 77), (9, 8, 2, 1500), (4, 8, 4, 1000)])
+def test_ladder_that_serves_more_items_than_workgroups_walk(bt, hkv, g, n):
+    """All heads, about half and about one in thirty of them served, in layers where that is more and less than one
+    (KV group, split) item per compute unit: served rows dense, the others bit-identical to the certified pass."""
+    say(f"many served groups: Bt={bt} Hkv={hkv} G={g} N={n}")
+    cqa = load_binding()
+    rng = np.random.default_rng(n)
+    hq = hkv * g
+    k = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    v = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    q = rng.standard_normal((bt, hq, 128)).astype(np.float16)
+    with GpuLayerCache(bt, hq, hkv, n + 8) as gc:
+        gc.append(k, v)
+        Oq, certq, _ = [x.copy() for x in gc.certified_decode(q)]
+        tot = (certq["E_key"].astype(np.float64) + certq["E_val"]).ravel()
+        order = np.sort(tot)[::-1]
+        for served in (len(tot), len(tot) // 2, max(1, len(tot) // 30)):
+            eps = -1.0 if served == len(tot) else float(np.float32(0.5 * (order[served - 1] + order[served])))
+            for rung4 in (0, 1):
+                gc.O.fill_(float("nan"))
+                O, cert, flags = enqueue(gc, q, cqa.Tolerances(eps_total=eps, rung4_min_groups=rung4))
+                rung = 4 if rung4 else 3
+                want = np.ones((bt, hq), bool) if rung4 else (certq["E_key"] + certq["E_val"]) > np.float32(eps)
+                assert ((cert["served_rung"] == rung) == want).all() and (cert["served_rung"][~want] == 0).all()
+                assert np.array_equal(O[~want], Oq[~want]) and np.isfinite(O).all()
+                for b, h in np.argwhere(want)[:: max(1, int(want.sum()) // 12)]:
+                    dense = oracle.softmax_attention(q[b, h], k[b, h // g], v[b, h // g])
+                    assert np.linalg.norm(O[b, h] - dense) <= 1e-3 * np.linalg.norm(dense) + 1e-6, (b, h)
