@@ -639,16 +639,31 @@ int32_t launch_dense(const __half* q, const __half* k, const __half* v, int grou
   // splits, a workgroup each: 385).  4107 tokens, every group of 32: 77 -> 70 us a group.
   a.by_wave = groups == 1 && a.nsplit < PAGED_WG && a.tiles_per_split > DENSE_WAVES &&
               a.nsplit * DENSE_WAVES <= dense_ws_units(n_tokens);
-  if (groups * std::max(a.nsplit, group) > 0x7FFFFFFF) return CQA_ERR_UNSUPPORTED;   // one grid dimension
-  const dim3 grid((unsigned)(groups * a.nsplit));
   if (a.by_wave) {
     if (group != 1 && group != 2 && group != 4) return CQA_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(dense_paged_kernel, dim3((unsigned)(a.nsplit * DENSE_WAVES), (unsigned)group), dim3(64), 0, st, a);
-  } else switch (group) {
-    case 1: hipLaunchKernelGGL(dense_split_kernel<1>, grid, dim3(64 * DENSE_WAVES), 0, st, a); break;
-    case 2: hipLaunchKernelGGL(dense_split_kernel<2>, grid, dim3(64 * DENSE_WAVES), 0, st, a); break;
-    case 4: hipLaunchKernelGGL(dense_split_kernel<4>, grid, dim3(64 * DENSE_WAVES), 0, st, a); break;
-    default: return CQA_ERR_UNSUPPORTED;
+  } else {
+    // a grid dimension holds fewer than 2^32 threads: 8388607 workgroups a launch (as many KV groups: with so many of
+    // them a group is one workgroup, which finishes its rows)
+    const int64_t most = 0xFFFFFFFFll / (64 * DENSE_WAVES * a.nsplit);
+    for (int64_t g0 = 0; g0 < groups; g0 += most) {
+      DenseArgs part = a;
+      part.q += g0 * group * D;
+      part.k += g0 * n_tokens * D;
+      part.v += g0 * n_tokens * D;
+      part.O += g0 * group * D;
+      if (part.select != nullptr) part.select += g0 * group;
+      if (part.cert != nullptr) part.cert += g0 * group;
+      if (part.flags != nullptr) part.flags += g0 * group;
+      if (a.nsplit > 1) part.ws += g0 * group * a.nsplit * DP_FLOATS;
+      const dim3 grid((unsigned)(std::min(most, groups - g0) * a.nsplit));
+      switch (group) {
+        case 1: hipLaunchKernelGGL(dense_split_kernel<1>, grid, dim3(64 * DENSE_WAVES), 0, st, part); break;
+        case 2: hipLaunchKernelGGL(dense_split_kernel<2>, grid, dim3(64 * DENSE_WAVES), 0, st, part); break;
+        case 4: hipLaunchKernelGGL(dense_split_kernel<4>, grid, dim3(64 * DENSE_WAVES), 0, st, part); break;
+        default: return CQA_ERR_UNSUPPORTED;
+      }
+    }
   }
   CQA_HIP(hipGetLastError());
   if (a.nsplit > 1 || a.by_wave) {

@@ -113,3 +113,20 @@ def test_a_paged_group_of_a_large_layer_takes_no_longer_than_one_of_a_small_laye
         finally:
             cqa.cqa_cache_destroy(h)
     assert took[1] <= 1.6 * took[0], took
+
+
+def test_more_kv_groups_than_one_launch_holds():
+    """A grid dimension holds fewer than 2^32 threads, 8388607 workgroups of 512; one more group of one token each.  The
+    softmax of a single score is 1 and the sum of one value that value: exact."""
+    import torch
+
+    from helpers import load_binding
+    print("dense launches", flush=True)
+    cqa = load_binding()
+    groups = 8388608 + 5
+    v = torch.randn((groups, 128), device="cuda", dtype=torch.float16)
+    O = torch.full((groups, 128), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(cqa.cqa_dense_workspace_bytes(1, groups, 1), dtype=torch.uint8, device="cuda")
+    cqa.cqa_dense_attention(v, v, v, 1, groups, groups, 1, O, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(O, v.float())
