@@ -25,6 +25,9 @@
  * wait for the device (as do the test hooks of cqa_test.h); cqa_decode_step_enqueue and
  * cqa_adaptive_step_enqueue never do.
  *
+ * Alignment: the FP16 inputs q, k and v may start at any address an FP16 value may
+ * have (2 bytes); O, cert, flags, blk_logmass and workspaces need 16.
+ *
  * Concurrency: the decode calls of one handle share its workspaces (split
  * partials, fallback partials and arrival counters, selector state), whatever
  * the layer.  Calls on one handle must therefore be ordered -- issue them on one

@@ -240,6 +240,20 @@ inline int64_t head_index(const Cache* c, int layer, int b, int kvh) {
   return ((int64_t)layer * c->desc.batch + b) * c->desc.n_kv_heads + kvh;
 }
 
+// Reads of the caller's q, k and v, which need no more than the alignment of an FP16 number: the device reads a
+// lane's 4 or 16 bytes at any address with the same instruction, the compiler only has to be told.
+typedef uint32_t u32_any __attribute__((aligned(2)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ uint32_t ld4_any(const __half* p) { return *reinterpret_cast<const u32_any*>(p); }
+__device__ __forceinline__ uint4 ld16_any(const __half* p) {
+  const u32x4_any v = *reinterpret_cast<const u32x4_any*>(p);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ __half2 ld_half2_any(const __half* p) {
+  const uint32_t x = ld4_any(p);
+  return __builtin_bit_cast(__half2, x);
+}
+
 extern thread_local int g_last_hip_error;
 #define CQA_HIP(expr)                                   \
   do {                                                  \

@@ -58,8 +58,7 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a) {
   float qv[G][2];
 #pragma unroll
   for (int h = 0; h < G; ++h) {
-    const __half2 t = reinterpret_cast<const __half2*>(
-        a.q + ((int64_t)b * a.n_q + kvh * G + h) * D)[l];
+    const __half2 t = ld_half2_any(a.q + ((int64_t)b * a.n_q + kvh * G + h) * D + 2 * l);
     qv[h][0] = __low2float(t);
     qv[h][1] = __high2float(t);
   }

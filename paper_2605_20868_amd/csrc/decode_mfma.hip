@@ -175,8 +175,8 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   // trailing tokens, runs after this launch has completed.
   if (a.ap_k_new != nullptr && split == 0 && w == 0) {
     const int64_t grp = (int64_t)b * a.n_kv + kvh;
-    const uint32_t kx = reinterpret_cast<const uint32_t*>(a.ap_k_new + grp * D)[l];
-    const uint32_t vx = reinterpret_cast<const uint32_t*>(a.ap_v_new + grp * D)[l];
+    const uint32_t kx = ld4_any(a.ap_k_new + grp * D + 2 * l);
+    const uint32_t vx = ld4_any(a.ap_v_new + grp * D + 2 * l);
     reinterpret_cast<uint32_t*>(a.ap_trail_k + (grp * BLK + a.ap_slot) * D)[l] = kx;
     reinterpret_cast<uint32_t*>(a.ap_trail_v + (grp * BLK + a.ap_slot) * D)[l] = vx;
     if (a.ap_t2_k != nullptr) {
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   // order, so the row arrives first and the set-up below does not wait for a whole quad.
   __half2 q_in = __floats2half2_rn(0.0f, 0.0f);
   if (w < G)
-    q_in = *reinterpret_cast<const __half2*>(a.q + ((int64_t)b * a.n_q + kvh * G + w) * D + 2 * l);
+    q_in = ld_half2_any(a.q + ((int64_t)b * a.n_q + kvh * G + w) * D + 2 * l);
   const float sigmax_head = a.sigmax[(int64_t)b * a.n_kv + kvh];
 
   // Loads of one quad = one Tier-1 record.  Every address is the record's wave-uniform base plus

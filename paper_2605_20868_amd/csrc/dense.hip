@@ -52,11 +52,10 @@ static int dense_splits(int group, int64_t groups, int64_t n_tokens) {
   return (int)((tiles + tps - 1) / tps);
 }
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 template <bool NT>
 __device__ __forceinline__ uint4 ld_dense(const char* p) {
-  const u32x4* x = reinterpret_cast<const u32x4*>(p);
-  const u32x4 v = NT ? __builtin_nontemporal_load(x) : *x;
+  const u32x4_any* x = reinterpret_cast<const u32x4_any*>(p);
+  const u32x4_any v = NT ? __builtin_nontemporal_load(x) : *x;
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
@@ -88,7 +87,7 @@ __device__ __forceinline__ void dense_wave_work(const __half* __restrict__ q, co
 
   uint4 qr[G];
 #pragma unroll
-  for (int h = 0; h < G; ++h) qr[h] = *reinterpret_cast<const uint4*>(q + h * D + c8 * 8);
+  for (int h = 0; h < G; ++h) qr[h] = ld16_any(q + h * D + c8 * 8);
 
   float m_run[G], l_run[G], acc[8][G];
 #pragma unroll

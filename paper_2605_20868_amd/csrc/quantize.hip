@@ -107,7 +107,7 @@ __device__ __forceinline__ void store_originals(const __half* in, __half* t2, in
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int64_t i = first + r * 4 + (l >> 4);
-    if (i >= 0) x[r] = reinterpret_cast<const uint4*>(in + i * D)[l & 15];
+    if (i >= 0) x[r] = ld16_any(in + i * D + 8 * (l & 15));
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -156,9 +156,9 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
     // channels (2 l, 2 l + 1) of each token of the block in work and of the next one.  Token i of this
     // append is one of the r waiting ones, or new token i - r.
     uint32_t kx[BLK], kn[BLK];
-    const uint32_t* const kin = reinterpret_cast<const uint32_t*>(a.k_in + (in_head - a.r) * D);
+    const u32_any* const kin = reinterpret_cast<const u32_any*>(a.k_in + (in_head - a.r) * D);
     if (j == 0 && a.r > 0) {            // the first block of an append that finds tokens waiting
-      const uint32_t* ktr = reinterpret_cast<const uint32_t*>(a.trail_k + head * BLK * D);
+      const u32_any* ktr = reinterpret_cast<const u32_any*>(a.trail_k + head * BLK * D);
 #pragma unroll
       for (int t = 0; t < BLK; ++t) kn[t] = (t < a.r ? ktr : kin)[t * (D / 2) + l];
     } else {
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
     {
       const __half* row = (int64_t)j * BLK + t < a.r ? a.trail_v + (head * BLK + t) * D : vin + (int64_t)j * (BLK * D);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) nxt[k >> 1][k & 1] = reinterpret_cast<const uint4*>(row)[8 * (k >> 1) + 2 * p + (k & 1)];
+      for (int k = 0; k < 4; ++k) nxt[k >> 1][k & 1] = ld16_any(row + 8 * (8 * (k >> 1) + 2 * p + (k & 1)));
     }
     for (; j < j1; ++j) {
       const int64_t blk = a.nb_old + j;
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
       if (j + 1 < j1) {
         const __half* row = vin + (int64_t)(j + 1) * (BLK * D);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) nxt[k >> 1][k & 1] = reinterpret_cast<const uint4*>(row)[8 * (k >> 1) + 2 * p + (k & 1)];
+        for (int k = 0; k < 4; ++k) nxt[k >> 1][k & 1] = ld16_any(row + 8 * (8 * (k >> 1) + 2 * p + (k & 1)));
       }
       double e2 = 0.0, n2 = 0.0;
 #pragma unroll
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
     __half* t2 = w == 0 ? a.t2_k : a.t2_v;
     for (int t = l >> 4; t < a.r_new; t += 4) {
       const int64_t src = a.n_new - a.r_new + t;
-      const uint4 x = reinterpret_cast<const uint4*>(in + (in_head + src) * D)[l & 15];
+      const uint4 x = ld16_any(in + (in_head + src) * D + 8 * (l & 15));
       reinterpret_cast<uint4*>(tr + (head * BLK + t) * D)[l & 15] = x;
       if (t2 != nullptr) reinterpret_cast<uint4*>(t2 + (head * a.t2_cap + a.len_before + src) * D)[l & 15] = x;
     }
@@ -390,8 +390,8 @@ __global__ __launch_bounds__(256) void trail_kernel(const __half* k_in, const __
   const int64_t head = ((int64_t)layer * batch + b) * n_kv + kvh;
   const int64_t in_head = ((int64_t)b * n_kv + kvh) * n_new;
   if (t >= n_new) return;
-  const uint4 k = reinterpret_cast<const uint4*>(k_in + (in_head + t) * D)[c];
-  const uint4 v = reinterpret_cast<const uint4*>(v_in + (in_head + t) * D)[c];
+  const uint4 k = ld16_any(k_in + (in_head + t) * D + 8 * c);
+  const uint4 v = ld16_any(v_in + (in_head + t) * D + 8 * c);
   reinterpret_cast<uint4*>(trail_k + (head * BLK + dst_first + t) * D)[c] = k;
   reinterpret_cast<uint4*>(trail_v + (head * BLK + dst_first + t) * D)[c] = v;
   if (t2_k != nullptr) {

@@ -335,15 +335,15 @@ __device__ __forceinline__ void load_trail(const ReduceArgs& a, int b, int hq, c
   const __half* qp = a.q + ((int64_t)b * a.n_q + hq) * D + cpart * 32;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    t.kq[i] = reinterpret_cast<const uint4*>(kp)[i];
-    t.vq[i] = reinterpret_cast<const uint4*>(vp)[i];
-    t.qq[i] = reinterpret_cast<const uint4*>(qp)[i];
+    t.kq[i] = ld16_any(kp + 8 * i);
+    t.vq[i] = ld16_any(vp + 8 * i);
+    t.qq[i] = ld16_any(qp + 8 * i);
   }
 #pragma unroll
   for (int i = 0; i < BLK - 1; ++i) {
     const int j = min(i, last);
     const __half* row = new_v != nullptr && j == last ? new_v + grp * D : tv + j * D;
-    t.vt[i] = reinterpret_cast<const __half2*>(row)[l];
+    t.vt[i] = ld_half2_any(row + 2 * l);
   }
 }
 

@@ -266,6 +266,58 @@ def test_fallback_equals_dense_kernel_bit_for_bit():
         assert cert["served_rung"][1, 5] == 3 and cert["served_rung"].sum() == 3
 
 
+@pytest.mark.parametrize("off", [1, 2, 5])
+@pytest.mark.parametrize("bt,hkv,g,n", [(1, 2, 4, 16 * 7 + 9), (2, 1, 2, 16 * 40 + 3), (1, 8, 4, 16 * 130 + 13)])
+def test_inputs_need_no_more_than_fp16_alignment(bt, hkv, g, n, off):
+    """q, k and v as views that start 2, 4 and 10 bytes behind a 16-byte boundary: every entry point that reads them, on
+    the one-workgroup and the several-workgroup route, bit for bit as with aligned ones."""
+    say(f"alignment: off={off} Bt={bt} Hkv={hkv} G={g} N={n}")
+    import torch
+    rng = np.random.default_rng(n)
+    hq = hkv * g
+    k, v = (rng.standard_normal((bt, hkv, n, 128)).astype(np.float16) for _ in range(2))
+    q = rng.standard_normal((bt, hq, 128)).astype(np.float16)
+
+    def view(x, o):
+        buf = torch.empty(x.size + 8, dtype=torch.float16, device="cuda")
+        y = buf[o:o + x.size].view(x.shape)
+        y.copy_(torch.from_numpy(np.ascontiguousarray(x)))
+        assert y.data_ptr() % 16 == 2 * o
+        return y
+
+    def program(o):
+        out = []
+        with GpuLayerCache(bt, hq, hkv, n + 64) as gc:
+            cqa, qd = gc.cqa, view(q, o)
+            for a, b in ((0, 5), (5, 21), (21, 40), (40, n)):          # trailing block, seals of one and more blocks
+                gc.append(view(k[:, :, a:b], o), view(v[:, :, a:b], o))
+            tol = cqa.Tolerances()
+            forced = cqa.Tolerances(force_flags=cqa.FLAG_TOTAL)
+            sel = cqa.Selector(0.995, 2, 64, 64, v_limit=8)
+            step = lambda t, nk, nv: cqa.cqa_decode_step_enqueue(gc.h, 0, nk, nv, qd, t, gc.O, gc.cert, gc.flags)
+            calls = [lambda: cqa.cqa_certified_decode(gc.h, 0, qd, tol, gc.O, gc.cert, gc.flags, None),
+                     lambda: step(tol, view(k[:, :, :1], o), view(v[:, :, :1], o)),      # rides on the split launch
+                     lambda: step(forced, None, None),
+                     lambda: cqa.cqa_decode_step(gc.h, 0, qd, forced, gc.O, gc.cert, gc.flags, None),
+                     lambda: cqa.cqa_adaptive_decode(gc.h, 0, qd, cqa.Tolerances(v_tol=1e-3), sel, gc.O, gc.cert, gc.flags)]
+            for call in calls:
+                gc.O.fill_(float("nan"))
+                call()
+                out.append([x.copy() for x in gc.results()])
+            cqa.cqa_set_kernel_variant(gc.h, 1)                        # the vector-ALU pass
+            out.append([x.copy() for x in gc.certified_decode(q)])
+            kd, vd = view(k, o), view(v, o)
+            ws = torch.empty(cqa.cqa_dense_workspace_bytes(bt, hq, n), dtype=torch.uint8, device="cuda")
+            cqa.cqa_dense_attention(qd, kd, vd, bt, hq, hkv, n, gc.O, ws)
+            out.append([gc.results()[0].copy()])
+            out.append([np.array(x) for blk in (0, n // 16 - 1) for x in gc.export(bt - 1, hkv - 1, blk)])
+        return out
+
+    for a, b in zip(program(0), program(off)):
+        for x, y in zip(a, b):
+            assert x.tobytes() == y.tobytes()
+
+
 # ------------------------------------------------------------------ config 2: 8K, 64 steps
 
 def test_l8k_sixty_four_steps():
