@@ -842,8 +842,9 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
     for (int i = t; i < n_list; i += ASCAN) {
       if (i != t) blk = ulist[i];
       if (blk < 0 || blk >= ra.nb || !(slot[blk] & kbit)) continue;
-      best_merge(best_x, ix, lx[blk], blk);
-      best_merge(best_8, i8, l8[blk], blk);
+      const float vx = lx[blk], v8 = l8[blk];
+      if (vx > -INFINITY) best_merge(best_x, ix, vx, blk);   // a block without a log-mass (not a number, for a
+      if (v8 > -INFINITY) best_merge(best_8, i8, v8, blk);   // query that is none) tops no ranking
     }
     // reduce over each wave, then (below) over the waves' results
     wave_best(best_x, ix);

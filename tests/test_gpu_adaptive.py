@@ -829,3 +829,34 @@ def test_selector_where_its_histogram_is_crowded_empty_or_tied(nblocks, kmax, kl
                     assert abs(len(vs) - len(got)) <= 1, (h, len(vs), len(got))
                 else:
                     assert len(vs) == len(got)
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("depth,v_limit", [(1, 0), (3, 16)])
+def test_a_query_that_is_not_finite_tops_no_ranking(bad, depth, v_limit):
+    """No block of such a head has a log-mass: PRECOND, no top block, no margin to state (+inf), as on a cache without
+    promoted blocks.  The group's other heads are what they are without it."""
+    say(f"adaptive, query element {bad}, depth {depth}, v_limit {v_limit}")
+    rng = np.random.default_rng(4)
+    bt, hkv, g, n = 1, 2, 4, 16 * 40 + 5
+    k, v = (rng.standard_normal((bt, hkv, n, 128)).astype(np.float16) for _ in range(2))
+    q = rng.standard_normal((bt, hkv * g, 128)).astype(np.float16)
+    with GpuLayerCache(bt, hkv * g, hkv, n + 16) as gc:
+        cqa = gc.cqa
+        gc.append(k, v)
+        tol = cqa.Tolerances(rank_depth=depth, rank_min_mass=0.25, v_tol=0.01 if v_limit else np.inf)
+        sel = cqa.Selector(0.995, 2, 16, 32, v_limit=v_limit, per_head=True)
+        out = []
+        for x in (q, q.copy()):
+            if out:
+                x[0, 1, 3] = bad
+            cqa.cqa_adaptive_decode(gc.h, 0, gc.to_dev(x), tol, sel, gc.O, gc.cert, gc.flags)
+            out.append([y.copy() for y in gc.results()])
+        (O0, c0, f0), (O, cert, flags) = out
+        assert flags[0, 1] & cqa.FLAG_PRECOND
+        assert cert["top_block"][0, 1] == -1 and cert["rank_margin"][0, 1] == np.inf
+        others = [0] + list(range(2, hkv * g))
+        assert (cert["top_block"][0, others] == c0["top_block"][0, others]).all() and (flags[0, others] == f0[0, others]).all()
+        # per-head sets: the others keep their own selection, so their rows agree up to the order of the listed blocks
+        for h in others:
+            assert np.linalg.norm(O[0, h] - O0[0, h]) <= 1e-3 * np.linalg.norm(O0[0, h])
