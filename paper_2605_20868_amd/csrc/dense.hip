@@ -160,16 +160,22 @@ __device__ __forceinline__ void dense_wave_work(const __half* __restrict__ q, co
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[j][h] *= alpha;
       }
+      // 16 tokens at a time: where none of them exists nothing is added, not zero weights times the last token's
+      // value, which may be infinite
 #pragma unroll
-      for (int i = 0; i < T; ++i) {
-        const __half2* vh = reinterpret_cast<const __half2*>(&vr[u][i]);
+      for (int i0 = 0; i0 < T; i0 += 4) {
+        if (i0 > 0 && i0 * 4 >= live) break;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float v0 = __low2float(vh[j]), v1 = __high2float(vh[j]);
+        for (int i = i0; i < i0 + 4 && i < T; ++i) {
+          const __half2* vh = reinterpret_cast<const __half2*>(&vr[u][i]);
 #pragma unroll
-          for (int h = 0; h < G; ++h) {
-            acc[2 * j][h] = fmaf(s[i][h], v0, acc[2 * j][h]);
-            acc[2 * j + 1][h] = fmaf(s[i][h], v1, acc[2 * j + 1][h]);
+          for (int j = 0; j < 4; ++j) {
+            const float v0 = __low2float(vh[j]), v1 = __high2float(vh[j]);
+#pragma unroll
+            for (int h = 0; h < G; ++h) {
+              acc[2 * j][h] = fmaf(s[i][h], v0, acc[2 * j][h]);
+              acc[2 * j + 1][h] = fmaf(s[i][h], v1, acc[2 * j + 1][h]);
+            }
           }
         }
       }
@@ -270,9 +276,10 @@ __device__ __forceinline__ float dense_merge_row(const float* part, int nsplit, 
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float f = s0 + i < nsplit ? __builtin_amdgcn_exp2f(m[i] - M) : 0.0f;
+      const bool in = s0 + i < nsplit;
+      const float f = in ? __builtin_amdgcn_exp2f(m[i] - M) : 0.0f;
       L = fmaf(f, l[i], L);
-      o = fmaf(f, x[i], o);
+      o = fmaf(f, in ? x[i] : 0.0f, o);   // (the last set's sum may be infinite)
     }
   }
   return o / L;

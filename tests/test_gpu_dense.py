@@ -130,3 +130,36 @@ def test_more_kv_groups_than_one_launch_holds():
     cqa.cqa_dense_attention(v, v, v, 1, groups, groups, 1, O, ws)
     torch.cuda.synchronize()
     assert torch.equal(O, v.float())
+
+
+@pytest.mark.parametrize("bt,hkv,g,n", [(1, 1, 2, 4800), (1, 1, 2, 16 * 41), (1, 2, 4, 48), (2, 1, 4, 16 * 300), (40, 8, 1, 16 * 21), (17, 8, 1, 16 * 143),
+                                        (1, 1, 4, 16)])
+def test_an_infinite_value_stays_infinite(bt, hkv, g, n):
+    """The last token's value has an infinite element: infinite in the result, through the dense call, the fallback and the
+    ladder, at whole blocks that leave tiles, splits and trips of the reduction ragged; every other channel untouched."""
+    import torch
+
+    from helpers import GpuLayerCache
+    print("infinite value", bt, hkv, g, n, flush=True)
+    rng = np.random.default_rng(n)
+    q = rng.standard_normal((bt, hkv * g, 128)).astype(np.float16)
+    k, v = (rng.standard_normal((bt, hkv, n, 128)).astype(np.float16) for _ in range(2))
+    v[:, :, n - 1, 7], v[:, :, n - 1, 70] = np.inf, -np.inf
+    with GpuLayerCache(bt, hkv * g, hkv, n + 16) as gc:
+        cqa = gc.cqa
+        gc.append(k, v)
+        qd, kd, vd = (gc.to_dev(x) for x in (q, k, v))
+        ws = torch.empty(cqa.cqa_dense_workspace_bytes(bt, hkv * g, n), dtype=torch.uint8, device="cuda")
+        outs = []
+        cqa.cqa_dense_attention(qd, kd, vd, bt, hkv * g, hkv, n, gc.O, ws)
+        outs.append(gc.results()[0])
+        cqa.cqa_dense_fallback(gc.h, 0, qd, None, 1, 4, gc.O)
+        outs.append(gc.results()[0])
+        cqa.cqa_decode_step_enqueue(gc.h, 0, None, None, qd, cqa.Tolerances(force_flags=cqa.FLAG_PRECOND), gc.O, gc.cert, gc.flags)
+        outs.append(gc.results()[0])
+        finite = [c for c in range(128) if c not in (7, 70)]
+        for o in outs:
+            assert (o[..., 7] == np.inf).all() and (o[..., 70] == -np.inf).all()
+            for b, h in ((0, 0), (bt - 1, hkv * g - 1)):
+                ref = oracle.softmax_attention(q[b, h], k[b, h // g], v[b, h // g][:, finite])
+                assert np.linalg.norm(o[b, h][finite] - ref) <= 1e-3 * np.linalg.norm(ref) + 1e-6
