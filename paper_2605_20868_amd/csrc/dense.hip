@@ -507,8 +507,9 @@ __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
 // Reduction and ladder of a short step of few rows (at most FINISH_ROWS heads with at most FINISH_SETS partial sets
 // each) in one launch: every workgroup merges all rows, one per wave, and so knows every flag
 // without waiting for another one; the first one writes the rows, leaving out the outputs that a
-// rung replaces, and the others leave unless a head asks for a fallback.  1029 tokens, 4 heads: a step 18.4 ->
-// 14.2 us.  (32 rows, two per wave of 16: 13 -> 23 us, the workgroups' copies of the work get in each other's way.)
+// rung replaces, and the others leave unless a head asks for a fallback.  A step in two launches and in one:
+// 4 rows 14.3, 12.3 us at 3 to 8 sets; 8 rows 14.4, 14.1 at 3 sets and 14.3, 13.5 at 8.  (32 rows, two per wave of
+// 16: 13 -> 23 us, the workgroups' copies of the work get in each other's way.)
 template <int G>
 __global__ __launch_bounds__(64 * FINISH_ROWS) void finish_ladder_kernel(ReduceArgs ra, LadderArgs a) {
   const int r = threadIdx.x >> 6, l = threadIdx.x & 63;   // this wave's row
@@ -599,8 +600,10 @@ int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_
   a.cert = cert;
   a.flags = flags;
   if (reduce != nullptr) {
-    // each of the workgroups merges the rows: no more of them than keep the host link busy when a rung serves
-    const dim3 fgrid((unsigned)std::min<int64_t>((int64_t)a.nsplit * a.groups, 64));
+    // Each of the workgroups merges the rows: no more of them than keep the host link busy when a rung serves.  Eight
+    // groups of one head, all served, on 64, 128, 256 and 512 workgroups: 600 tokens 121, 111, 116, 119 us, 1100
+    // tokens 165, 146, 162, 188, 2000 tokens 242, 250, 277, 278 (without a flag all four take 13.1 - 14.2; 512 16).
+    const dim3 fgrid((unsigned)std::min<int64_t>((int64_t)a.nsplit * a.groups, std::max(c->n_cu / 2, 1)));
     switch (g) {
       case 1: hipLaunchKernelGGL(finish_ladder_kernel<1>, fgrid, dim3(64 * FINISH_ROWS), 0, st, *reduce, a); break;
       case 2: hipLaunchKernelGGL(finish_ladder_kernel<2>, fgrid, dim3(64 * FINISH_ROWS), 0, st, *reduce, a); break;
