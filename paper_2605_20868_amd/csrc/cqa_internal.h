@@ -95,9 +95,9 @@ constexpr int MAX_K_LIMIT = 512;            // blocks one head may promote (Rung
 constexpr int MAX_UNION = 8 * MAX_K_LIMIT;  // blocks one KV group may promote (keys and values, <= 4 heads each)
 constexpr int PROM_SPLITS = 16;             // workgroups (= partial sets) per KV group of each half of the promoted-block
                                             // pass: 64 waves, about two blocks per wave for a group that promotes K_max = 128.
-                                            // With the 32 sets of the pass over all blocks the adaptive reduction then merges
-                                            // 64 sets, one trip of its head wave (measured: 32 per half, two trips, 3.6 us slower;
-                                            // 8 per half, 3.5 us slower: too few waves for the large unions)
+                                            // An adaptive step with 8, 16 and 32 per half: one group of 8000 tokens 85, 70, 71 us
+                                            // (too few waves for large unions); 32K 152, 151, 154; 128K 122, 124, 126; 4 x 20000
+                                            // 640, 635, 651; 16 x 4000 2105, 2103, 2155 (more sets to merge than the waves gain)
 
 // Workspace of the adaptive path, shared by all layers (one decode step at a time).
 struct AdaptiveWs {
@@ -302,7 +302,8 @@ int64_t dense_ws_floats(int group, int64_t n_tokens);
 
 // Device-resolved fallback ladder (dense_ladder_kernel).
 constexpr int LADDER_MAX_SPLITS = 64;
-// Steps that finish_ladder_kernel reduces as well: up to this many (batch, q-head) rows and partial sets per row.
+// Steps that finish_ladder_kernel reduces as well: up to this many (batch, q-head) rows and partial sets per row (the
+// times at these limits stand beside it).
 constexpr int FINISH_ROWS = 8, FINISH_SETS = 8;
 struct LadderArgs {
   const __half* q;          // [Bt][Hq][128]
