@@ -217,8 +217,8 @@ def test_caller_provided_tier2():
         cert = torch.zeros((bt * hq, cqa.CERT_BYTES), dtype=torch.uint8, device=dev)
         flags = torch.zeros((bt * hq,), dtype=torch.int32, device=dev)
         kd, vd, qd = (torch.from_numpy(x).to(dev) for x in (k, v, q))
-        cqa.cqa_cache_append(h, 0, kd[:, :, :600].contiguous(), vd[:, :, :600].contiguous(), 600)   # copy engines
-        for t in range(600, n):                                                                  # kernel stores
+        cqa.cqa_cache_append(h, 0, kd[:, :, :600].contiguous(), vd[:, :, :600].contiguous(), 600)   # the seal launch stores
+        for t in range(600, n):                                                                  # the step's launches store
             cqa.cqa_decode_step_enqueue(h, 0, kd[:, :, t:t + 1].contiguous(), vd[:, :, t:t + 1].contiguous(), qd,
                                         cqa.Tolerances(), O, cert, flags)
         torch.cuda.synchronize()
@@ -245,6 +245,37 @@ def test_caller_provided_tier2():
         cqa.cqa_cache_destroy(h)
     # the arrays are the caller's: still there, still holding the originals
     assert (t2k.numpy().reshape(bt, hkv, cap, 128)[:, :, :n].view(np.uint16) == k.view(np.uint16)).all()
+
+
+@pytest.mark.parametrize("lengths", [(9, 60, 2300, 3, 45), (2101, 17), (31, 2049, 16)])
+def test_stored_originals_byte_for_byte(lengths):
+    """Appends that find 0 to 15 waiting tokens and leave some: up to 32 MB of originals are stored by the seal launch (or
+    the trailing one), more by the copy engines.  32 sequences: 2048 tokens are 32 MB."""
+    say(f"stored originals: appends of {lengths} tokens")
+    import torch
+    cqa = load_binding()
+    bt, hkv, n = 4, 8, sum(lengths)
+    cap = n + 7
+    shape = (bt, hkv, cap, 128)
+    elems = bt * hkv * cap * 128
+    t2k = torch.zeros(elems, dtype=torch.float16, pin_memory=True)
+    t2v = torch.zeros(elems, dtype=torch.float16, pin_memory=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    k, v = (torch.randn((bt, hkv, n, 128), generator=gen, device="cuda", dtype=torch.float32).half() for _ in range(2))
+    h = cqa.cqa_cache_create_caller_tier2(1, bt, hkv, hkv, cap, t2k, t2v, elems * 2)
+    try:
+        at = 0
+        for m in lengths:
+            cqa.cqa_cache_append(h, 0, k[:, :, at:at + m].contiguous(), v[:, :, at:at + m].contiguous(), m)
+            torch.cuda.synchronize()
+            at += m
+            for t2, x in ((t2k, k), (t2v, v)):
+                got = t2.numpy().view(np.uint16).reshape(shape)
+                assert np.array_equal(got[:, :, :at], x[:, :, :at].cpu().numpy().view(np.uint16)), (lengths, at)
+                assert not got[:, :, at:].any(), (lengths, at)
+    finally:
+        cqa.cqa_cache_destroy(h)
 
 
 def test_random_small_shapes_against_oracle():

@@ -91,6 +91,13 @@ def test_a_reset_cache_equals_a_fresh_one(first, second, int8_query):
         rung, O, cert, flags = gc.decode_step(q, gc.cqa.Tolerances(force_flags=gc.cqa.FLAG_TOTAL))
         assert rung == 3
         out.append([O.copy(), cert.copy(), flags.copy()])
+        # every head served from the stored originals: the dense result over the tokens themselves
+        kk = np.concatenate([kv[2], *step[0]], axis=2)
+        vv = np.concatenate([kv[3], *step[1]], axis=2)
+        for b in range(2):
+            for h in range(8):
+                dense = oracle.softmax_attention(q[b, h], kk[b, h // 4], vv[b, h // 4])
+                assert np.linalg.norm(O[b, h] - dense) <= 1e-3 * np.linalg.norm(dense) + 1e-6, (b, h)
         return out
 
     with GpuLayerCache(2, 8, 2, 512) as fresh:
