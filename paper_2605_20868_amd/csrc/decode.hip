@@ -484,7 +484,8 @@ void split_geometry(const Cache* c, int64_t n_blocks, int* nsplit, int* wpb) {
 // 70 us a pass against 75); beyond it the hinted loads stream faster: 278 MB 81 -> 76 us, 303 MB
 // 64 -> 58.5 us a step when three caches take turns (INT8 x INT8 scoring 63.6 -> 58.4), 606 MB 109 -> 98 us.
 // The price is paid where one layer of that size is read over and over, which a stack of layers never is: 303 MB 51.2
-// -> 51.7 us a pass (INT8 x INT8 51.0 -> 51.4; up to 1.5 us on other boxes), the step the same 57.4.
+// -> 51.7 us a pass, up to 1.5 us more on other boxes, the step the same 57.4 (INT8 x INT8 51.0 -> 51.4; with a token
+// appended each step 53.3 -> 55.7).
 int stream_nt(const Cache* c, int64_t n_blocks) {
   if (c->stream_hint == 1) return 0;
   if (c->stream_hint == 2) return 1;
