@@ -372,7 +372,8 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
 // replayed after a reset then reads what an eager call would.  One small launch, 2 - 3 us, ahead of a first seal of
 // several workgroups (a single workgroup per head simply stores its maximum).  (Instead of it, an epoch in pinned
 // memory that a reset raises and every workgroup puts above its maximum: a prompt of 65549 tokens 140 -> 435 us,
-// reads of one host word are served one after the other.)
+// reads of one host word are served one after the other.  A word per workgroup, all set by the first seal and
+// reduced by every decode: nothing for the prompt, but 0.1 us for each short step and 101.0 -> 102.2 for 64 x 4107 tokens.)
 __global__ __launch_bounds__(256) void clear_sigmax_kernel(float* sigmax, int n) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < n) sigmax[i] = 0.0f;
