@@ -69,3 +69,31 @@ def test_steps_of_one_split_give_the_same_rows_on_both_routes(bt, hkv, g, n):
             rung, O2, cert2, flags2 = gc.decode_step(q)
             assert rung == 0
             assert np.array_equal(O, O2) and cert.tobytes() == cert2.tobytes() and (flags == flags2).all()
+
+
+@pytest.mark.parametrize("int8", [False, True])
+@pytest.mark.parametrize("bt,hkv,g,n,splits", [
+    (1, 8, 4, 64 * 32 - 5, 8),        # every wave exactly one quad, the last one short of a block
+    (1, 8, 2, 64 * 32 + 16, 9),       # ... and a ninth workgroup with a single quad of one block
+    (2, 4, 1, 64 * 9 + 40, 3),        # two waves of the last workgroup without one
+])
+def test_contexts_of_one_quad_per_wave(bt, hkv, g, n, splits, int8):
+    """Short contexts, where no wave of the split pass takes a second quad, in both scoring modes."""
+    import torch
+    print("one quad", bt, hkv, g, n, int8, flush=True)
+    rng = np.random.default_rng(n + bt)
+    k = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    v = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    q = rng.standard_normal((bt, hkv * g, 128)).astype(np.float16)
+    oc = oracle.OracleLayerCache(bt, hkv)
+    oc.append(k, v)
+    ref = oc.certified_decode(q, oracle.Tolerances(int8_query=int8))
+    with GpuLayerCache(bt, hkv * g, hkv, n + 16, tier2=False) as gc:
+        gc.append(k, v)
+        if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+            assert gc.cqa.cqa_decode_splits(gc.h, 0) == splits
+        O, cert, flags, lm = gc.certified_decode(q, gc.cqa.Tolerances(int8_query=int8), want_logmass=True)
+        for i, r in enumerate(ref):
+            at = divmod(i, hkv * g)
+            assert_head_matches(r, O[at], cert[at], flags[at], (bt, hkv, g, at, int8))
+            assert np.abs(lm[at] - r["blk_logmass"]).max() <= 1e-4
