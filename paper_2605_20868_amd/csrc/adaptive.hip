@@ -800,9 +800,10 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
   AdaptiveIn ad;
   ad.pos_set0 = a.pos_set0;
   ad.pos_set1 = a.pos_set1;
-  HeadState hs;
+  OctState st{};
+  float2 o2 = make_float2(0.0f, 0.0f);
   if (tid < 64) {
-    hs = reduce_sets<16>(ra.partials + row * ra.pstride * PART_FLOATS, ra.nsplit, &ad);
+    st = merge_sets(ra.partials + row * ra.pstride * PART_FLOATS, 0, 8, ra.nsplit, ad.pos_set0, ad.pos_set1, o2);
   } else {
     const int t = tid - 64;
     const int n_list = min(a.ucount[grp], MAX_UNION);
@@ -868,7 +869,7 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
     }
   }
   TrailRegs tr;
-  if (tid < 64) load_trail(ra, b, hq, nullptr, nullptr, tr);
+  if (tid < 64 && ra.r > 0) load_trail(ra, b, hq, nullptr, nullptr, tr);
   __syncthreads();
   if (tid < 64) {
     const bool on = tid >= 1 && tid < NW;    // one scanning wave's results per lane
@@ -990,7 +991,9 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
   ad.maxc8 = s_top[3];
   ad.lse8 = lse8;
   if (tid == 0) a.alpha_out[row] = ad.alpha;
-  finish_head(ra, b, hq, hs, tr, &ad);
+  TrailState ts{};
+  if (ra.r > 0) ts = trail_state(ra, tr);
+  finish_head(ra, b, hq, head_state(st, o2), ts, key_terms(ra, delta), &ad);
 }
 
 }  // namespace

@@ -675,23 +675,23 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   TrailRegs tr;
   if (finish && w < G) {
     __builtin_amdgcn_s_setprio(2);
-    load_trail(ra, b, hq0 + w, a.ap_k_new, a.ap_v_new, tr);
+    if (ra.r > 0) load_trail(ra, b, hq0 + w, a.ap_k_new, a.ap_v_new, tr);
   }
   __syncthreads();
-  // one wave per head merges the waves' states (lane = wave; with a thread per channel and one per head's
-  // scalars walking the waves, this tail took 3000 cycles instead of 900)
+  // one wave per head merges the waves' states
   if (w < G) {
-    const HeadState hs = reduce_lds(ms[0][w], G * 12, mo[0][w], G * D, W);
+    float2 o2;
+    const OctState st = merge_lds(ms[0][w], G * 12, mo[0][w], G * D, W, o2);
     if (!finish || a.keep_sets) {
       float* pp = a.partials + (((int64_t)b * a.n_q + hq0 + w) * a.pstride + split) * PART_FLOATS;
-      *reinterpret_cast<float2*>(pp + P_O + 2 * l) = hs.o2;
-      if (l == 0) {
-        *reinterpret_cast<float4*>(pp) = make_float4(hs.M, hs.L, hs.EV, hs.EVM);
-        *reinterpret_cast<float4*>(pp + P_DMAX) = make_float4(hs.DM, hs.VM, hs.T1, hs.T2);
-        pp[P_I1] = __int_as_float(hs.I1);
-      }
+      store_state(st, o2, pp, pp + P_O);
     }
-    if (finish) finish_head(ra, b, hq0 + w, hs, tr, nullptr);
+    if (finish) {
+      TrailState ts{};
+      if (ra.r > 0) ts = trail_state(ra, tr);
+      const HeadState hs = head_state(st, o2);
+      finish_head(ra, b, hq0 + w, hs, ts, key_terms(ra, hs.DM), nullptr);
+    }
   }
 }
 

@@ -114,6 +114,17 @@ __device__ __forceinline__ float max_x32(float x) {
 // all-reduce over the 64 lanes of the wave: the row step on DPP, two cross-row exchanges
 __device__ __forceinline__ float wave_sum(float v) { return sum_x32(sum_x16(row_sum(v))); }
 __device__ __forceinline__ float wave_max(float v) { return max_x32(max_x16(row_max(v))); }
+// ... of values that the four lanes of a quad have in common, each counted once
+__device__ __forceinline__ float quads_sum(float x) {
+  x += dpp_mov<0x141>(x);
+  x += dpp_mov<0x140>(x);
+  return sum_x32(sum_x16(x));
+}
+__device__ __forceinline__ float quads_max(float x) {
+  x = fmaxf(x, dpp_mov<0x141>(x));
+  x = fmaxf(x, dpp_mov<0x140>(x));
+  return max_x32(max_x16(x));
+}
 __device__ __forceinline__ double pack_d(uint32_t lo, uint32_t hi) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
@@ -136,35 +147,6 @@ __device__ __forceinline__ double wave_sum_d(double x) {
   swap32((uint32_t)u, al, bl);
   swap32((uint32_t)(u >> 32), ah, bh);
   return pack_d(al, ah) + pack_d(bl, bh);
-}
-template <int CTRL>
-__device__ __forceinline__ void top2_step_dpp(float& t1, int& i1, float& t2) {
-  const float u1 = dpp_mov<CTRL>(t1), u2 = dpp_mov<CTRL>(t2);
-  const int j1 = dpp_movi<CTRL>(i1);
-  top2_merge(t1, i1, t2, u1, j1, u2);
-}
-__device__ __forceinline__ void wave_top2(float& t1, int& i1, float& t2) {
-  top2_step_dpp<0xB1>(t1, i1, t2);
-  top2_step_dpp<0x4E>(t1, i1, t2);
-  top2_step_dpp<0x141>(t1, i1, t2);
-  top2_step_dpp<0x140>(t1, i1, t2);
-#pragma unroll
-  for (int step = 0; step < 2; ++step) {
-    uint32_t a1, b1, a2, b2, ai, bi;
-    if (step == 0) {
-      swap16(__float_as_uint(t1), a1, b1);
-      swap16(__float_as_uint(t2), a2, b2);
-      swap16((uint32_t)i1, ai, bi);
-    } else {
-      swap32(__float_as_uint(t1), a1, b1);
-      swap32(__float_as_uint(t2), a2, b2);
-      swap32((uint32_t)i1, ai, bi);
-    }
-    t1 = __uint_as_float(a1);
-    t2 = __uint_as_float(a2);
-    i1 = (int)ai;
-    top2_merge(t1, i1, t2, __uint_as_float(b1), (int)bi, __uint_as_float(b2));
-  }
 }
 // larger value wins; equal values: the lower index (-1 = nothing seen loses)
 __device__ __forceinline__ void best_merge(float& v, int& i, float ov, int oi) {
@@ -226,90 +208,148 @@ __device__ __forceinline__ float lane_of(float x, int lane) {
   return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), lane));
 }
 
-// Merges the n_sets partial sets of one head (set s at part + s * PART_FLOATS), CH per trip.
-// All 64 lanes of the wave must call.  This code runs on the critical tail of a launch: it is
-// written for few dependent memory round trips (all loads of a trip are issued before anything is
-// consumed) and short cross-lane chains, not for few instructions.
-template <int CH>
-__device__ __forceinline__ HeadState reduce_sets(const float* part, int n_sets, const AdaptiveIn* ad) {
-  const int l = threadIdx.x & 63;
-  HeadState r;
-  r.M = -INFINITY;
-  r.L = r.EV = r.EVM = r.DM = r.VM = 0.0f;
-  r.T1 = r.T2 = -INFINITY;
-  r.I1 = -1;
-  r.o2 = make_float2(0.0f, 0.0f);
-  for (int s0 = 0; s0 < n_sets; s0 += CH) {
-    // scalars of set s0 + l (one set per lane) and, for my two channels, the outputs of all sets
-    const int s = s0 + l;
-    const bool on = l < CH && s < n_sets;
-    const float* ps = part + (int64_t)(on ? s : n_sets - 1) * PART_FLOATS;
-    float2 sc[5];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) sc[i] = *reinterpret_cast<const float2*>(ps + 2 * i);   // (P_M P_L) (P_EV P_EVMAX) (P_DMAX P_VMAX) (P_T1 P_T2) (P_I1 -)
-    float2 x[CH];
-#pragma unroll
-    for (int i = 0; i < CH; ++i)
-      x[i] = *reinterpret_cast<const float2*>(part + (int64_t)min(s0 + i, n_sets - 1) * PART_FLOATS + P_O + 2 * l);
+// ---- merging states.  A state is nine scalars (in the order of the partial set's) and 128 channels.
+// max, sum, smallest unsigned over the eight lanes of a half row, in each of them
+__device__ __forceinline__ float oct_max(float x) {
+  x = fmaxf(x, dpp_mov<0xB1>(x));
+  x = fmaxf(x, dpp_mov<0x4E>(x));
+  return fmaxf(x, dpp_mov<0x141>(x));
+}
+__device__ __forceinline__ float oct_sum(float x) {
+  x += dpp_mov<0xB1>(x);
+  x += dpp_mov<0x4E>(x);
+  return x + dpp_mov<0x141>(x);
+}
+__device__ __forceinline__ uint32_t oct_minu(uint32_t x) {
+  x = min(x, (uint32_t)dpp_movi<0xB1>((int)x));
+  x = min(x, (uint32_t)dpp_movi<0x4E>((int)x));
+  return min(x, (uint32_t)dpp_movi<0x141>((int)x));
+}
 
-    const float m = on ? sc[0].x : -INFINITY;
-    const float Mn = fmaxf(r.M, wave_max(m));
-    const float fo = __expf(r.M - Mn);        // rescales what earlier trips accumulated
-    const float f = on ? __expf(m - Mn) : 0.0f;
-    const float fc = (ad == nullptr || (s >= ad->pos_set0 && s < ad->pos_set1)) ? f : 0.0f;
-    r.L = r.L * fo + wave_sum(fc * sc[0].y);
-    r.EV = r.EV * fo + wave_sum(fc * sc[1].x);
-    r.EVM = fmaxf(r.EVM * fo, wave_max(fc * sc[1].y));
-    r.DM = fmaxf(r.DM, wave_max(on ? sc[2].x : 0.0f));
-    r.VM = fmaxf(r.VM, wave_max(on ? sc[2].y : 0.0f));
-    float u1 = on ? sc[3].x : -INFINITY, u2 = on ? sc[3].y : -INFINITY;
-    int j1 = on ? __float_as_int(sc[4].x) : -1;
-    wave_top2(u1, j1, u2);
-    top2_merge(r.T1, r.I1, r.T2, u1, j1, u2);
-    r.M = Mn;
-    r.o2.x *= fo;
-    r.o2.y *= fo;
+// The scalars of up to eight merged states: lane 8 j + i holds scalar j (P_M .. P_T2) of the result.
+struct OctState {
+  float x;
+  float M, T1;   // scalars P_M and P_T1, in every lane
+  int i1;        // P_I1, in every lane
+};
+// Merges up to eight states.  Lane 8 j + i brings scalar j of state i (v) and the state's m, t1, t2, i1; on: there is a
+// state i; sums: its mass and value term count.  f: the factor of state i's channels.
+// One wave-wide reduction per scalar, six steps each and a long chain for the two largest log-masses, made this
+// 2700 cycles of a lone wave; with a lane per scalar and state all scalars share three steps.
+// Products and sums are kept apart: fused, the lanes of a pair would round differently, and every lane holds the bits
+// that a partial set carries, whichever launch finishes the row.
+__device__ __forceinline__ OctState merge_oct(float v, float m, float t1, float t2, int i1, bool on, bool sums, float& f) {
+#pragma clang fp contract(off)
+  const int j = (threadIdx.x & 63) >> 3;
+  OctState r;
+  r.M = oct_max(on ? m : -INFINITY);
+  f = on ? __expf(m - (r.M == -INFINITY ? 0.0f : r.M)) : 0.0f;
+  r.T1 = oct_max(on ? t1 : -INFINITY);
+  const bool top = on && t1 == r.T1;
+  const uint32_t best = oct_minu(top ? (uint32_t)i1 : 0xFFFFFFFFu);   // equal log-masses: the lower index (-1, none, is the largest)
+  r.i1 = (int)best;
+  const float second = top && (uint32_t)i1 == best ? t2 : t1;
+  const float scaled = (sums ? f : 0.0f) * v;
+  float x = j >= P_L && j <= P_EVMAX ? scaled : (j == P_T2 ? second : v);
+  if (!on) x = j >= P_L && j <= P_VMAX ? 0.0f : -INFINITY;
+  const float sum = oct_sum(x), mx = oct_max(x);
+  r.x = j == P_M ? r.M : (j <= P_EV ? sum : mx);
+  return r;
+}
+// ... of two results of it; fa, fb: the factors of their channels
+__device__ __forceinline__ OctState merge_two(const OctState& a, const OctState& b, float& fa, float& fb) {
+#pragma clang fp contract(off)
+  const int j = (threadIdx.x & 63) >> 3;
+  OctState r;
+  r.M = fmaxf(a.M, b.M);
+  const float base = r.M == -INFINITY ? 0.0f : r.M;
+  fa = __expf(a.M - base);
+  fb = __expf(b.M - base);
+  r.T1 = fmaxf(a.T1, b.T1);
+  r.i1 = a.T1 > b.T1 || (a.T1 == b.T1 && (uint32_t)a.i1 <= (uint32_t)b.i1) ? a.i1 : b.i1;
+  const bool scaled = j >= P_L && j <= P_EVMAX;
+  const float xa = scaled ? fa * a.x : a.x, xb = scaled ? fb * b.x : b.x;
+  const float mx = fmaxf(xa, xb);
+  r.x = j == P_M ? r.M : (j <= P_EV ? xa + xb : (j == P_T2 ? fmaxf(mx, fminf(a.T1, b.T1)) : mx));
+  return r;
+}
+__device__ __forceinline__ HeadState head_state(const OctState& m, float2 o2) {
+  HeadState r;
+  r.M = m.M;
+  r.L = lane_of(m.x, 8 * P_L);
+  r.EV = lane_of(m.x, 8 * P_EV);
+  r.EVM = lane_of(m.x, 8 * P_EVMAX);
+  r.DM = lane_of(m.x, 8 * P_DMAX);
+  r.VM = lane_of(m.x, 8 * P_VMAX);
+  r.T1 = m.T1;
+  r.T2 = lane_of(m.x, 8 * P_T2);
+  r.I1 = m.i1;
+  r.o2 = o2;
+  return r;
+}
+
+// Merges partial sets first, first + 1, ..., first + 7, first + jump, ... of one head's n_sets (set s at part +
+// s * PART_FLOATS); of sets outside [pos0, pos1) only the channels (and maxima) count.  o2: channels 2l, 2l + 1.
+// All loads of a trip are issued before anything is consumed.
+__device__ __forceinline__ OctState merge_sets(const float* part, int first, int jump, int n_sets, int pos0, int pos1, float2& o2) {
+  const int l = threadIdx.x & 63;
+  OctState r;
+  r.M = r.T1 = -INFINITY;
+  r.i1 = -1;
+  r.x = (l >> 3) >= P_L && (l >> 3) <= P_VMAX ? 0.0f : -INFINITY;
+  o2 = make_float2(0.0f, 0.0f);
+  for (int s0 = first; s0 < n_sets; s0 += jump) {
+    const int s = s0 + (l & 7);
+    const float* ps = part + (int64_t)min(s, n_sets - 1) * PART_FLOATS;
+    const float v = ps[l >> 3], m = ps[P_M], t1 = ps[P_T1], t2 = ps[P_T2], i1 = ps[P_I1];
+    float2 x[8];
 #pragma unroll
-    for (int i = 0; i < CH; ++i) {
+    for (int i = 0; i < 8; ++i)
+      x[i] = *reinterpret_cast<const float2*>(part + (int64_t)min(s0 + i, n_sets - 1) * PART_FLOATS + P_O + 2 * l);
+    float f;
+    const OctState t = merge_oct(v, m, t1, t2, __float_as_int(i1), s < n_sets, s >= pos0 && s < pos1, f);
+    float2 o = make_float2(0.0f, 0.0f);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
       const float fi = lane_of(f, i);            // zero for sets past the end
-      r.o2.x = fmaf(fi, x[i].x, r.o2.x);
-      r.o2.y = fmaf(fi, x[i].y, r.o2.y);
+      o.x = fmaf(fi, x[i].x, o.x);
+      o.y = fmaf(fi, x[i].y, o.y);
+    }
+    if (s0 == first) {
+      r = t;
+      o2 = o;
+    } else {
+      float fa, fb;
+      r = merge_two(r, t, fa, fb);
+      o2.x = fmaf(fa, o2.x, fb * o.x);
+      o2.y = fmaf(fa, o2.y, fb * o.y);
     }
   }
   return r;
 }
 
-// Merges the states of n waves kept in LDS: scalars (in the order of the partial set's) at
-// ms + i * ms_stride, channels at mo + i * mo_stride.  Waves that saw no block hold zeros and a maximum of
-// -infinity; the result of only such waves is one more of the kind.
-__device__ __forceinline__ HeadState reduce_lds(const float* ms, int ms_stride, const float* mo, int mo_stride, int n) {
-  // A product fused into the first addition of a sum over lanes would round differently in the two lanes of a pair:
-  // every lane holds the same bits, those that a partial set carries, whichever launch finishes the row.
-#pragma clang fp contract(off)
-  const int l = threadIdx.x & 63;
-  const bool on = l < n;
-  const float* m = ms + (on ? l : 0) * ms_stride;
-  HeadState r;
-  const float mx = on ? m[P_M] : -INFINITY;
-  r.M = wave_max(mx);
-  const float f = on ? __expf(mx - (r.M == -INFINITY ? 0.0f : r.M)) : 0.0f;
-  r.L = wave_sum(f * m[P_L]);
-  r.EV = wave_sum(f * m[P_EV]);
-  r.EVM = wave_max(f * m[P_EVMAX]);
-  r.DM = wave_max(on ? m[P_DMAX] : 0.0f);
-  r.VM = wave_max(on ? m[P_VMAX] : 0.0f);
-  r.T1 = on ? m[P_T1] : -INFINITY;
-  r.T2 = on ? m[P_T2] : -INFINITY;
-  r.I1 = on ? __float_as_int(m[P_I1]) : -1;
-  wave_top2(r.T1, r.I1, r.T2);
-  r.o2 = make_float2(0.0f, 0.0f);
-  for (int i = 0; i < n; ++i) {
-    const float fi = lane_of(f, i);
-    const float2 x = *reinterpret_cast<const float2*>(mo + i * mo_stride + 2 * l);
-    r.o2.x = fmaf(fi, x.x, r.o2.x);
-    r.o2.y = fmaf(fi, x.y, r.o2.y);
+// Merges the states of n <= 8 waves kept in LDS: scalars at ms + i * ms_stride, channels at mo + i * mo_stride.
+// Waves that saw no block hold zeros and a maximum of -infinity; the result of only such waves is one more of the kind.
+__device__ __forceinline__ OctState merge_lds(const float* ms, int ms_stride, const float* mo, int mo_stride, int n, float2& o2) {
+  const int l = threadIdx.x & 63, i = l & 7;
+  const float* m = ms + (i < n ? i : 0) * ms_stride;
+  float f;
+  const OctState r = merge_oct(m[l >> 3], m[P_M], m[P_T1], m[P_T2], __float_as_int(m[P_I1]), i < n, true, f);
+  o2 = make_float2(0.0f, 0.0f);
+  for (int k = 0; k < n; ++k) {
+    const float fk = lane_of(f, k);
+    const float2 x = *reinterpret_cast<const float2*>(mo + k * mo_stride + 2 * l);
+    o2.x = fmaf(fk, x.x, o2.x);
+    o2.y = fmaf(fk, x.y, o2.y);
   }
   return r;
+}
+// a state as merge_lds reads it / as a partial set
+__device__ __forceinline__ void store_state(const OctState& m, float2 o2, float* ms, float* mo) {
+  const int l = threadIdx.x & 63;
+  if ((l & 7) == 0) ms[l >> 3] = m.x;
+  if (l == 1) ms[P_I1] = __int_as_float(m.i1);
+  *reinterpret_cast<float2*>(mo + 2 * l) = o2;
 }
 
 // Trailing FP16 tokens of one head (at most 15), requested before the partial sets and used after them.
@@ -354,11 +394,63 @@ struct HeadRow {
   float2 out;
 };
 
-// Attends the trailing tokens and evaluates the certificate.
-__device__ __forceinline__ HeadRow finish_row(const ReduceArgs& a, const HeadState& hs, const TrailRegs& tr,
-                                              const AdaptiveIn* ad) {
+// The trailing tokens as a state of their own: exact keys and values, eta = 0, no contribution to Delta_h.
+struct TrailState {
+  float M, L, V;   // maximum, mass, largest value norm; in every lane
+  float2 o;
+};
+__device__ __forceinline__ TrailState trail_state(const ReduceArgs& a, const TrailRegs& tr) {
   const int l = threadIdx.x & 63;
   const float inv_sqrt_d = 0.08838834764831845f;
+  float dot = 0.0f, n2 = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const __half2* kh = reinterpret_cast<const __half2*>(&tr.kq[i]);
+    const __half2* vh = reinterpret_cast<const __half2*>(&tr.vq[i]);
+    const __half2* qh = reinterpret_cast<const __half2*>(&tr.qq[i]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      dot = fmaf(__low2float(qh[e]), __low2float(kh[e]), dot);
+      dot = fmaf(__high2float(qh[e]), __high2float(kh[e]), dot);
+      n2 = fmaf(__low2float(vh[e]), __low2float(vh[e]), n2);
+      n2 = fmaf(__high2float(vh[e]), __high2float(vh[e]), n2);
+    }
+  }
+  dot += dpp_mov<0xB1>(dot);      // the four parts of a token are one quad of lanes
+  dot += dpp_mov<0x4E>(dot);
+  n2 += dpp_mov<0xB1>(n2);
+  n2 += dpp_mov<0x4E>(n2);
+  const bool live = (l >> 2) < a.r;
+  const float st = live ? dot * inv_sqrt_d : -INFINITY;
+  TrailState t;
+  t.M = quads_max(st);
+  t.V = quads_max(live ? sqrtf(n2) : 0.0f);
+  const float pt = live ? __expf(st - (t.M == -INFINITY ? 0.0f : t.M)) : 0.0f;
+  t.L = quads_sum(pt);
+  t.o = make_float2(0.0f, 0.0f);
+#pragma unroll
+  for (int i = 0; i < BLK - 1; ++i) {
+    const float p = lane_of(pt, 4 * i);       // zero for tokens past the last
+    t.o.x = fmaf(p, __low2float(tr.vt[i]), t.o.x);
+    t.o.y = fmaf(p, __high2float(tr.vt[i]), t.o.y);
+  }
+  return t;
+}
+
+// What the key term takes from Delta_h alone.  No cap on the exponents: beyond the binary32 range the factors are +inf, the
+// tail form of the key term with them, and a non-finite key term raises PRECOND (in the default
+// mode the tanh form, at most 1, still wins the min).
+struct KeyTerms {
+  float full, grow, widen;   // tanh Delta_h, e^{c Delta_h}, e^{2 Delta_h} - 1
+};
+__device__ __forceinline__ KeyTerms key_terms(const ReduceArgs& a, float delta) {
+  return KeyTerms{tanhf(delta), expf((float)a.tol.mass_exp * delta), expm1f(2.0f * delta)};
+}
+
+// Joins the sealed blocks' state and the trailing tokens' and evaluates the certificate.
+__device__ __forceinline__ HeadRow finish_row(const ReduceArgs& a, const HeadState& hs, const TrailState& ts,
+                                              const KeyTerms& kt, const AdaptiveIn* ad) {
+#pragma clang fp contract(off)
   float M = hs.M, L = hs.L, EV = hs.EV, EVM = hs.EVM, VM = hs.VM;
   const float DM = hs.DM, T1 = hs.T1, T2 = hs.T2;
   int I1 = hs.I1;
@@ -371,46 +463,16 @@ __device__ __forceinline__ HeadRow finish_row(const ReduceArgs& a, const HeadSta
     EVM = fmaxf(EVM, g8 * ad->maxc8);
   }
   float L_sealed = L;
-
-  // ---- trailing FP16 tokens: exact keys and values, eta = 0
   if (a.r > 0) {
-    float dot = 0.0f, n2 = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const __half2* kh = reinterpret_cast<const __half2*>(&tr.kq[i]);
-      const __half2* vh = reinterpret_cast<const __half2*>(&tr.vq[i]);
-      const __half2* qh = reinterpret_cast<const __half2*>(&tr.qq[i]);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        dot = fmaf(__low2float(qh[e]), __low2float(kh[e]), dot);
-        dot = fmaf(__high2float(qh[e]), __high2float(kh[e]), dot);
-        n2 = fmaf(__low2float(vh[e]), __low2float(vh[e]), n2);
-        n2 = fmaf(__high2float(vh[e]), __high2float(vh[e]), n2);
-      }
-    }
-    dot += dpp_mov<0xB1>(dot);      // the four parts of a token are one quad of lanes
-    dot += dpp_mov<0x4E>(dot);
-    n2 += dpp_mov<0xB1>(n2);
-    n2 += dpp_mov<0x4E>(n2);
-    const bool live = (l >> 2) < a.r;
-    const float st = live ? dot * inv_sqrt_d : -INFINITY;
-    const float M2 = fmaxf(M, wave_max(st));
-    VM = fmaxf(VM, wave_max(live ? sqrtf(n2) : 0.0f));
-    const float fs = __expf(M - M2);
-    const float pt = live ? __expf(st - M2) : 0.0f;
-    L *= fs;
-    o2.x *= fs;
-    o2.y *= fs;
+    const float M2 = fmaxf(M, ts.M);
+    const float fs = __expf(M - M2), ft = __expf(ts.M - M2);
+    VM = fmaxf(VM, ts.V);
     EV *= fs;
     EVM *= fs;
-    L_sealed = L;
-    L += wave_sum(pt) * 0.25f;      // every token is held by four lanes
-#pragma unroll
-    for (int t = 0; t < BLK - 1; ++t) {
-      const float p = lane_of(pt, 4 * t);       // zero for t >= r
-      o2.x = fmaf(p, __low2float(tr.vt[t]), o2.x);
-      o2.y = fmaf(p, __high2float(tr.vt[t]), o2.y);
-    }
+    L_sealed = L * fs;
+    L = fmaf(ft, ts.L, L_sealed);
+    o2.x = fmaf(ft, ts.o.x, o2.x * fs);
+    o2.y = fmaf(ft, ts.o.y, o2.y * fs);
     M = M2;
   }
 
@@ -425,16 +487,9 @@ __device__ __forceinline__ HeadRow finish_row(const ReduceArgs& a, const HeadSta
   const float alpha_hat = ad != nullptr ? ad->alpha : L_sealed / L;
   const float delta = ad != nullptr ? ad->delta : DM;
   const float vmax = VM;
-  // No cap on the exponents: beyond the binary32 range the factors are +inf, the tail form of
-  // the key term with them, and a non-finite key term raises PRECOND below (in the default
-  // mode the tanh form, at most 1, still wins the min).
   float t_tail = 0.0f;
-  if (alpha_hat > 0.0f && delta != 0.0f) {
-    const float grow = expf((float)a.tol.mass_exp * delta);
-    const float widen = expm1f(2.0f * delta);
-    t_tail = fminf(1.0f, grow * alpha_hat) * widen;
-  }
-  const float t_full = tanhf(delta);
+  if (alpha_hat > 0.0f && delta != 0.0f) t_tail = fminf(1.0f, kt.grow * alpha_hat) * kt.widen;
+  const float t_full = kt.full;
   const float tv = a.tol.key_bound_mode == 0 ? fminf(t_full, t_tail) : (a.tol.key_bound_mode == 1 ? t_tail : t_full);
   const float e_key = 2.0f * vmax * tv;
   float margin = a.nb >= 2 ? T1 - T2 : INFINITY;
@@ -473,11 +528,11 @@ __device__ __forceinline__ HeadRow finish_row(const ReduceArgs& a, const HeadSta
   return row;
 }
 
-// Attends the trailing tokens, evaluates the certificate and writes the row.
-__device__ __forceinline__ void finish_head(const ReduceArgs& a, int b, int hq, const HeadState& hs, const TrailRegs& tr,
-                                            const AdaptiveIn* ad) {
+// ... and writes the row.
+__device__ __forceinline__ void finish_head(const ReduceArgs& a, int b, int hq, const HeadState& hs, const TrailState& ts,
+                                            const KeyTerms& kt, const AdaptiveIn* ad) {
   const int l = threadIdx.x & 63;
-  const HeadRow row = finish_row(a, hs, tr, ad);
+  const HeadRow row = finish_row(a, hs, ts, kt, ad);
   const int64_t r = (int64_t)b * a.n_q + hq;
   reinterpret_cast<float2*>(a.O + r * D)[l] = row.out;
   if (l == 0) {
@@ -490,17 +545,6 @@ __device__ __forceinline__ void finish_head(const ReduceArgs& a, int b, int hq, 
     if (a.flags_mirror != nullptr)
       __hip_atomic_store(a.flags_mirror + r, row.fl | a.mirror_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
-}
-
-// One head by one wave: all its partial sets (written by earlier launches), the trailing tokens, the row.
-// CH: sets per trip; a trip costs CH loads whether or not there are as many sets.
-template <int CH>
-__device__ __forceinline__ void reduce_head_wave(const ReduceArgs& a, int b, int hq) {
-  TrailRegs tr;
-  load_trail(a, b, hq, nullptr, nullptr, tr);
-  const float* part = a.partials + ((int64_t)b * a.n_q + hq) * (a.pstride > 0 ? a.pstride : a.nsplit) * PART_FLOATS;
-  const HeadState hs = reduce_sets<CH>(part, a.nsplit, nullptr);
-  finish_head(a, b, hq, hs, tr, nullptr);
 }
 
 }  // namespace cqa
