@@ -10,12 +10,13 @@
 // or, with cqa_selector.per_head, per query head over the head's own promoted set (its default).
 //
 // Sequence on one stream (launch_adaptive): the certified pass over all sealed blocks in INT8 /
-// INT4 (it emits the block log-masses, eta_b and the usual partial sets, and its reduction the
-// total log-mass, Delta_h and V_max the selector needs) -> select_kernel (per head and ranking: keys, values) ->
-// compact_kernel (per group: union bit mask -> per-block flags and ordered list) -> promoted-block
-// pass over the listed blocks only: positive partial sets computed with the originals the flags ask
+// INT4 (it emits the block log-masses, eta_b and the usual partial sets) -> select_kernel (per head and ranking: keys, values; it
+// reduces the head's partial sets for the total log-mass, Delta_h and V_max) -> promoted-block
+// pass over the listed blocks only (each workgroup makes its share of the list from the selection masks):
+// positive partial sets computed with the originals the flags ask
 // for (read straight from the pinned Tier-2 arrays over the host link) and negated sets computed as
-// the first pass did, so that the merge replaces those blocks' contribution -> adaptive_reduce_kernel.
+// the first pass did, so that the merge replaces those blocks' contribution; beside it, a workgroup per head sums up what
+// is left in INT8 -> adaptive_reduce_kernel.
 // Tier-1 is read once per step; the paper's two passes (score, then attend) become one pass plus a
 // correction for a few dozen blocks.
 #include <algorithm>
@@ -26,7 +27,7 @@
 namespace cqa {
 
 // defined in decode.hip
-int32_t launch_promoted_pass(const DecodeArgs& a, int group, dim3 grid, hipStream_t st);
+int32_t launch_promoted_pass(const DecodeArgs& a, const PromArgs& p, int group, dim3 grid, hipStream_t st);
 
 namespace {
 
@@ -51,7 +52,12 @@ struct SelectArgs {
   const float* lm8;            // [Bt][Hq][nb]: log-masses of the pass over all blocks
   const float* eta_blk;        // [Bt][Hkv][nb] (values)
   float* contrib;              // [Bt][Hq][nb]: estimated contributions p_b eta_b, written here (values)
-  const cqa_head_cert* cert;   // first pass: lse, delta_h, v_max
+  ReduceArgs ra;               // reduction of the pass over all blocks
+  float* first;                // [Bt][Hq][4]: lse, delta_h, v_max of that pass, written here
+  int32_t* slot;               // [Bt][Hkv][slot_stride]: the flag words of the previous call's list are taken back here
+  int64_t slot_stride;
+  const int32_t* ulist;        // [Bt][Hkv][MAX_UNION]
+  const int32_t* ucount;       // [Bt][Hkv]
   float v_tol, eps_val;        // value selection: local threshold and budget
   float* score_dev;            // [Bt][Hq] canary output, cleared here (null = no canary)
   int v_greedy;
@@ -62,24 +68,8 @@ struct SelectArgs {
   int mass_exp, key_bound_mode;
 };
 
-// Strided pass over a row in batches: all loads of a batch are issued before anything is consumed
-// (a plain strided loop has one load in flight per thread and is bound by its latency).
 constexpr int ST = 1024;          // threads of the selector workgroup
-constexpr int SBATCH = 8;
-#define CQA_ROW_PASS(ROW, N, TID, BODY)                                           \
-  for (int base__ = 0; base__ < (N); base__ += ST * SBATCH) {                      \
-    float val__[SBATCH];                                                            \
-    _Pragma("unroll") for (int j__ = 0; j__ < SBATCH; ++j__) {                      \
-      const int i__ = base__ + j__ * ST + (TID);                                  \
-      val__[j__] = i__ < (N) ? (ROW)[i__] : 0.0f;                                  \
-    }                                                                              \
-    _Pragma("unroll") for (int j__ = 0; j__ < SBATCH; ++j__) {                      \
-      const int i = base__ + j__ * ST + (TID);                                    \
-      const float x = val__[j__];                                                  \
-      const bool in = i < (N);                                                     \
-      BODY                                                                         \
-    }                                                                              \
-  }
+constexpr int SBATCH = 8;         // loads in flight per thread
 
 // The selector walks its row of log-masses several times.  Rows of up to LDS_KEYS blocks are read
 // from memory once, as order-preserving integer keys kept in LDS; longer rows are re-read.
@@ -131,52 +121,6 @@ __device__ __forceinline__ void hist_add(uint32_t* hist, uint32_t bin, bool pred
   if (pred) atomicAdd(&hist[bin], 1u);
 }
 
-// v plus the lane that DPP control CTRL points at (0 where there is none, or where ROWS masks the row out)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, true);
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t scan_step(uint32_t v) { return v + dpp_or_zero<CTRL, ROWS>(v); }
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int scan_step(int v) { return v + (int)dpp_or_zero<CTRL, ROWS>((uint32_t)v); }
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double scan_step(double v) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  return v + pack_d(dpp_or_zero<CTRL, ROWS>((uint32_t)u), dpp_or_zero<CTRL, ROWS>((uint32_t)(u >> 32)));
-}
-__device__ __forceinline__ uint32_t row_total(uint32_t v) {
-  v += (uint32_t)dpp_movi<0xB1>((int)v);
-  v += (uint32_t)dpp_movi<0x4E>((int)v);
-  v += (uint32_t)dpp_movi<0x141>((int)v);
-  return v + (uint32_t)dpp_movi<0x140>((int)v);
-}
-__device__ __forceinline__ int row_total(int v) { return (int)row_total((uint32_t)v); }
-__device__ __forceinline__ double row_total(double v) {
-  v += dpp_mov_d<0xB1>(v);
-  v += dpp_mov_d<0x4E>(v);
-  v += dpp_mov_d<0x141>(v);
-  return v + dpp_mov_d<0x140>(v);
-}
-// Inclusive scan over the threads of a workgroup with two barriers: DPP shifts inside each row of
-// 16 lanes, the totals of the preceding rows by DPP broadcasts, then the preceding waves' totals.
-// `tot` = one word of LDS scratch per wave.
-template <typename T>
-__device__ __forceinline__ T block_scan_incl(T v, T* tot, int tid) {
-  const int l = tid & 63, w = tid >> 6;
-  v = scan_step<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8
-  v = scan_step<0x112, 0xf>(v);
-  v = scan_step<0x114, 0xf>(v);
-  v = scan_step<0x118, 0xf>(v);
-  v = scan_step<0x142, 0xa>(v);   // row_bcast 15 into rows 1 and 3
-  v = scan_step<0x143, 0xc>(v);   // row_bcast 31 into rows 2 and 3
-  __syncthreads();            // protects `tot` against the previous use
-  if (l == 63) tot[w] = v;
-  __syncthreads();
-  // at most 16 waves: every row of lanes adds up the totals of the waves before this one
-  return v + row_total((l & 15) < w ? tot[l & 15] : T(0));
-}
-
 // Histogram bin of a value in the selector's first pass: not decreasing with the value (the order the
 // selection keeps), 1024 bins where the KL-th best can lie -- log-masses by their distance below the total
 // log-mass, 1/32 apart up to 16 (diffuse heads), 1/8 up to 64, 1 beyond (heads with a few dominant blocks);
@@ -206,7 +150,8 @@ __device__ __forceinline__ int select_bin(float x, float lse) {
 // more than KL, are rank-sorted as they are.  Only when that bin is crowded (equal
 // or nearly equal values) a radix selection narrows them down to KL.
 // 128K, 32 heads: 18.9 -> 14.6 us (four radix passes before).  4 x 32K, keys and values in one launch: 9.9 us
-// (16.1 + 15.1 in two launches and 4.8 for one that formed the contributions, before).
+// (16.1 + 15.1 in two launches and 4.8 for one that formed the contributions, before).  The reduction at its head, under
+// which the row's first loads come in, adds 2.5 us and saves a launch of 4.8 us.
 constexpr int CAND_SLACK = 256;   // blocks beyond KL that the rank sort takes rather than another pass
 
 struct SelectSmem {
@@ -214,7 +159,10 @@ struct SelectSmem {
   unsigned long long sorted[MAX_K_LIMIT];   // the winners, best first: (key, ~index)
   double pm[MAX_K_LIMIT];                   // prefix sums of their masses
   uint32_t hist[ST];
-  uint32_t keys[LDS_KEYS];
+  union {
+    uint32_t keys[LDS_KEYS];
+    ReduceSmem red;                         // (before there are keys)
+  };
 };
 
 template <bool VALUES>
@@ -242,54 +190,79 @@ __device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm)
   __shared__ uint32_t s_idx_prefix, s_idx_want;
   __shared__ int s_k, s_first, s_bin, s_found, s_done;
 
-  const float lse_f = a.cert[row].lse;
-  const double lse = (double)lse_f;
-  if (!VALUES && tid == 0 && a.score_dev != nullptr) a.score_dev[row] = 0.0f;
-  if (KL == 0) {
-    if (tid == 0) side.kstar[row] = 0;
-    return;
+  // ---- the first blocks of the row are requested, the head's partial sets are reduced meanwhile, and what the previous
+  //      call left behind is taken back: the head's mask, and by one head the flag words of the group's list
+  float v[SBATCH], e[SBATCH];
+#pragma unroll
+  for (int j = 0; j < SBATCH; ++j) {
+    const int i = j * ST + tid;
+    v[j] = i < nb ? lm[i] : 0.0f;
+    e[j] = VALUES && i < nb ? eta[i] : 0.0f;
   }
-
-  // ---- the one pass over memory: keys to LDS, the estimated mass of the sealed blocks (single-
-  //      precision exponentials, accumulated in double; the rest of 1 is the exact trailing tokens), histogram
+  uint32_t* const um = side.umask + row * a.mask_words;
+  for (int i = tid; i < ((nb + 31) >> 5); i += ST) um[i] = 0u;
+  const int g = a.n_q / a.n_kv;
+  if (!VALUES && hq % g == 0) {
+    const int64_t grp = (int64_t)b * a.n_kv + hq / g;
+    const int n_prev = min(a.ucount[grp], MAX_UNION);
+    for (int i = tid; i < n_prev; i += ST) {
+      const int blk = a.ulist[grp * MAX_UNION + i];
+      if (blk >= 0 && blk < a.slot_stride) a.slot[grp * a.slot_stride + blk] = 0;
+    }
+  }
   hist[tid] = 0u;
+  __shared__ float s_lse, s_delta, s_vmax;
+  {
+    HeadRow hr;
+    if (reduce_row(a.ra, b, hq, min((a.ra.nsplit + 7) / 8, RED_WAVES) + 2, sm.red, hr) && tid == 0) {
+      s_lse = hr.ct.lse;
+      s_delta = hr.ct.delta_h;
+      s_vmax = hr.ct.v_max;
+      if (!VALUES) *reinterpret_cast<float4*>(a.first + row * 4) = make_float4(hr.ct.lse, hr.ct.delta_h, hr.ct.v_max, 0.0f);
+    }
+  }
   if (tid == 0) {
     s_cnt = 0u;
     s_first = MAX_K_LIMIT + 1;
     s_bin = 0;
     s_found = nb;
   }
+  if (!VALUES && tid == 0 && a.score_dev != nullptr) a.score_dev[row] = 0.0f;
+  if (KL == 0) {
+    if (tid == 0) side.kstar[row] = 0;
+    return;
+  }
   __syncthreads();
+  const float lse_f = s_lse;
+  const double lse = (double)lse_f;
+
+  // ---- the one pass over memory: keys to LDS, the estimated mass of the sealed blocks (single-
+  //      precision exponentials, accumulated in double; the rest of 1 is the exact trailing tokens), histogram
   double part = 0.0;
-  if (VALUES) {
-    for (int base = 0; base < nb; base += ST * SBATCH) {
-      float v[SBATCH], e[SBATCH];
+  for (int base = 0; base < nb; base += ST * SBATCH) {
+    if (base > 0) {
 #pragma unroll
       for (int j = 0; j < SBATCH; ++j) {
         const int i = base + j * ST + tid;
         v[j] = i < nb ? lm[i] : 0.0f;
-        e[j] = i < nb ? eta[i] : 0.0f;
-      }
-#pragma unroll
-      for (int j = 0; j < SBATCH; ++j) {
-        const int i = base + j * ST + tid;
-        if (i < nb) {
-          const float x = __expf(v[j] - lse_f) * e[j];
-          contrib[i] = x;
-          part += (double)x;
-          if (cached) keys[i] = ord32(x);
-          atomicAdd(&hist[select_bin<true>(x, lse_f)], 1u);
-        }
+        e[j] = VALUES && i < nb ? eta[i] : 0.0f;
       }
     }
-  } else {
-    CQA_ROW_PASS(lm, nb, tid, {
-      if (in) {
-        part += (double)__expf(x - lse_f);
-        if (cached) keys[i] = ord32(x);
-        atomicAdd(&hist[select_bin<false>(x, lse_f)], 1u);
+#pragma unroll
+    for (int j = 0; j < SBATCH; ++j) {
+      const int i = base + j * ST + tid;
+      if (i < nb) {
+        float x = __expf(v[j] - lse_f);
+        if (VALUES) {
+          x *= e[j];
+          contrib[i] = x;
+        }
+        part += (double)x;
+        const float ranks = VALUES ? x : v[j];
+        if (cached) keys[i] = ord32(ranks);
+        atomicAdd(&hist[select_bin<VALUES>(ranks, lse_f)], 1u);
       }
-    })
+    }
   }
   part = wave_sum_d(part);
   if ((tid & 63) == 0) dsum[tid >> 6] = part;
@@ -432,7 +405,7 @@ __device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm)
       k = min(k, nb);
       k = min(k, n);
       // Rung 1 (an infinite threshold is never exceeded: its test, a chain of double-precision functions, is skipped)
-      const double delta = (double)a.cert[row].delta_h, vmax = (double)a.cert[row].v_max;
+      const double delta = (double)s_delta, vmax = (double)s_vmax;
       const int cap = a.eps_key == INFINITY ? 0 : min(max(side.k_limit, side.k_max), n);
       while (k < cap) {
         const double tail = total - (k > 0 ? pm[k - 1] : 0.0);
@@ -467,7 +440,6 @@ __device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm)
   }
   __syncthreads();
   const int k = s_k;
-  uint32_t* um = side.umask + row * a.mask_words;
   for (int i = tid; i < k; i += ST) {
     const int idx = (int)(0xFFFFFFFFu - (uint32_t)(sorted[i] & 0xFFFFFFFFull));
     side.sel[row * MAX_K_LIMIT + i] = idx;
@@ -483,22 +455,11 @@ __global__ __launch_bounds__(ST) void select_kernel(SelectArgs a) {
     select_rows<true>(a, sm);
 }
 
-// The exploration draw: 32-bit multiply-xorshift mixer over (block, KV group, seed).
-__device__ __forceinline__ uint32_t explore_mix(uint32_t blk, uint32_t grp, uint32_t seed) {
-  uint32_t x = blk * 0x9E3779B1u ^ grp * 0x85EBCA77u ^ seed * 0xC2B2AE3Du;
-  x ^= x >> 16;
-  x *= 0x7FEB352Du;
-  x ^= x >> 15;
-  x *= 0x846CA68Bu;
-  x ^= x >> 16;
-  return x;
-}
-
 struct CompactArgs {
   uint32_t explore_threshold;   // a block is explored (key-promoted) when its draw is below this; 0 = off
   uint32_t explore_seed;
-  uint32_t* vmask;     // [Bt][Hq][mask_words] value selections per head (null = none); cleared likewise
-  uint32_t* umask;     // [Bt][Hq][mask_words] key selections per head; cleared on the way out
+  const uint32_t* vmask;   // [Bt][Hq][mask_words] value selections per head (null = none)
+  const uint32_t* umask;   // [Bt][Hq][mask_words] key selections per head
   int64_t mask_words;
   int group;           // query heads per KV group
   int per_head;        // 1: a head's promoted sets are its own selections; 0: the group's unions
@@ -518,31 +479,23 @@ struct CompactArgs {
   uint32_t sc_step;    // stamp of this step (larger than every stamp before it, never 0)
 };
 
+// With the FP16 scratch in use (otherwise the promoted-block pass reads the masks itself: a launch less).
 // One workgroup per KV group: the heads' bit masks (FP16 keys, FP16 values) -> per-block flags
 // (bit 0: some head scores the block with FP16 keys, bit 1: some head attends its FP16 values,
 // bits 24-27 / 28-31: which heads; 0 = neither) and the ascending list of blocks with any flag.
-// Per-group promotion gives every head the union's bits.  Clears the masks.
+// Per-group promotion gives every head the union's bits.
 __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
   const int tid = threadIdx.x;
   const int64_t grp = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  uint32_t* um = a.umask + grp * a.group * a.mask_words;        // the group's heads are consecutive rows
-  uint32_t* vm = a.vmask != nullptr ? a.vmask + grp * a.group * a.mask_words : nullptr;
+  const uint32_t* um = a.umask + grp * a.group * a.mask_words;        // the group's heads are consecutive rows
+  const uint32_t* vm = a.vmask != nullptr ? a.vmask + grp * a.group * a.mask_words : nullptr;
   int32_t* slot = a.slot + grp * a.slot_stride;
   int32_t* ulist = a.ulist + grp * MAX_UNION;
   const int words = (a.nb + 31) >> 5;
   __shared__ int itot_c[4];
   __shared__ int s_base;
-  // The flag words of the previous call are taken back through its list (the words of all other
-  // blocks are zero already: at creation every word is, and only listed blocks are ever set), so
-  // a call touches a few dozen words per group instead of one per block.
-  {
-    const int n_prev = min(a.ucount[grp], MAX_UNION);
-    for (int i = tid; i < n_prev; i += 256) {
-      const int blk = ulist[i];
-      if (blk >= 0 && blk < a.slot_stride) slot[blk] = 0;
-    }
-  }
-  __syncthreads();                       // (with its fence) before the same words are set again
+  // (every flag word is zero: only listed blocks' words are ever set, and the selector has taken those of the
+  // previous call's list back)
   // thread t owns the contiguous run of mask words [t wpt, (t + 1) wpt): the list comes out ascending
   constexpr int WPT_MAX = 8;             // up to 256 x 8 x 32 blocks (1M tokens) in one sweep
   const int wpt = (words + 255) >> 8;
@@ -559,11 +512,9 @@ __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
       if (u < wpt_here && w < words) {
         for (int i = 0; i < a.group; ++i) {
           kh[i] = um[i * a.mask_words + w];
-          if (kh[i] != 0u) um[i * a.mask_words + w] = 0u;
           kbits |= kh[i];
           if (vm != nullptr) {
             vh[i] = vm[i * a.mask_words + w];
-            if (vh[i] != 0u) vm[i * a.mask_words + w] = 0u;
             vbits |= vh[i];
           }
         }
@@ -756,25 +707,39 @@ struct AdaptiveReduceArgs {
   const float* lmx;      // [Bt][Hq][nb]
   const int32_t* slot;   // [Bt][Hkv][slot_stride]
   int64_t slot_stride;
+  const float* first;    // [Bt][Hq][4]
+  const float* scan;     // [Bt][Hq][8]
   float* alpha_out;      // [Bt][Hq]
   const float* score_dev;  // [Bt][Hq] canary deviations, or null
-  const float* eta;      // [Bt][Hkv][nb] value annotations eta_b written by the pass over all blocks
   int pos_set0, pos_set1;  // the promoted-block pass's positive partial sets
-  const int32_t* ulist;  // [Bt][Hkv][MAX_UNION] listed blocks of the group (ranking depth > 1)
+  const int32_t* ulist;  // [Bt][Hkv][MAX_UNION] listed blocks of the group
   const int32_t* ucount; // [Bt][Hkv]
 };
 
-// One workgroup per (batch, query head).  Its first wave merges the partial sets of the pass over all blocks
-// and of the promoted-block pass while the others scan the block log-masses (estimated mass left in INT8, best
-// unpromoted block) and the list of the promoted ones (best under either ranking); then the first wave
-// finalises the certificate with these substituted.
-// Bound by latency: 128K, 32 heads 13.6 -> 9.5 us (scan and merge one after the other, the FP16 log-mass of
-// every block requested, before).
-constexpr int ART = 1024;                // threads of the adaptive reduction
-constexpr int ASCAN = ART - 64;          // ... of which scan: 8192 blocks in one trip of nine
-constexpr int ABATCH = 9;
+// One workgroup per (batch, query head): eight waves merge the partial sets of the pass over all blocks and of the
+// promoted-block pass, one attends the trailing tokens, one prepares the key term, all of them look through the list of promoted blocks for
+// the best under either ranking, and the first joins the results.  (What the other blocks add up to has been summed
+// beside the promoted-block pass.)
+// Bound by latency: 128K, 32 heads 9.3 -> 6.4 us, 4K 8.2 -> 6.7 (with the scan over all log-masses in this launch, before).
+constexpr int AR_WAVES = RED_WAVES + 2;
+constexpr int ART = 64 * AR_WAVES;
+struct RankBest {
+  float x[AR_WAVES], e[AR_WAVES];   // by FP16 / by INT8 log-mass
+  int ix[AR_WAVES], ie[AR_WAVES];
+};
+// the best of the waves' results, in every lane of a wave
+__device__ __forceinline__ void rank_join(const RankBest& r, float& x, int& ix, float& e, int& ie) {
+  const int l = threadIdx.x & 63;
+  const bool on = l < AR_WAVES;
+  x = on ? r.x[l] : -INFINITY;
+  e = on ? r.e[l] : -INFINITY;
+  ix = on ? r.ix[l] : -1;
+  ie = on ? r.ie[l] : -1;
+  wave_best(x, ix);
+  wave_best(e, ie);
+}
 __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs a) {
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, l = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hq = blockIdx.x, b = blockIdx.y;
   const ReduceArgs& ra = a.ra;
   const int64_t row = (int64_t)b * ra.n_q + hq;
@@ -782,147 +747,85 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
   const float* l8 = a.lm8 + row * ra.nb;
   const float* lx = a.lmx + row * ra.nb;
   const int32_t* slot = a.slot + grp * a.slot_stride;
-  // the first pass left its certificate in the caller's array; read what is needed before
-  // the first wave overwrites it
-  const float lse8 = ra.cert[row].lse;
-  const float delta = ra.cert[row].delta_h;
+  const int32_t* ulist = a.ulist + grp * MAX_UNION;
   const int kbit = 1 << (SLOT_HK_SHIFT + hq % (ra.n_q / ra.n_kv));   // this head scores the block with FP16 keys
+  const float lse8 = a.first[row * 4], delta = a.first[row * 4 + 1];
+  const int n_list = min(a.ucount[grp], MAX_UNION);
+  int blk = ulist[tid];                    // valid for tid < n_list
 
-  constexpr int NW = ART / 64;
-  __shared__ float s_bx[ART], s_b8[ART];     // (for the deeper places of the ranking below)
-  __shared__ int s_ix[ART], s_i8[ART];
-  __shared__ float w_bx[NW], w_b8[NW], w_tm[NW], w_mc[NW];
-  __shared__ int w_ix[NW], w_i8[NW];
-  __shared__ double w_mass[NW], w_l8u[NW], w_ev8u[NW];
-  __shared__ float s_top[4];
-  __shared__ int s_topi[2];
-  __shared__ double s_sum[3];
-  AdaptiveIn ad;
-  ad.pos_set0 = a.pos_set0;
-  ad.pos_set1 = a.pos_set1;
-  OctState st{};
-  float2 o2 = make_float2(0.0f, 0.0f);
-  if (tid < 64) {
-    st = merge_sets(ra.partials + row * ra.pstride * PART_FLOATS, 0, 8, ra.nsplit, ad.pos_set0, ad.pos_set1, o2);
+  __shared__ __align__(16) ReduceSmem sm;
+  __shared__ RankBest rb;
+  if (w < RED_WAVES) {
+    float2 o2;
+    const OctState st = merge_sets(ra.partials + row * ra.pstride * PART_FLOATS, 8 * w, 8 * RED_WAVES, ra.nsplit, a.pos_set0,
+                                   a.pos_set1, o2);
+    store_state(st, o2, sm.sc[w], sm.o[w]);
+  } else if (w == RED_WAVES) {
+    if (ra.r > 0) {
+      TrailRegs tr;
+      load_trail(ra, b, hq, nullptr, nullptr, tr);
+      const TrailState ts = trail_state(ra, tr);
+      *reinterpret_cast<float2*>(&sm.trail_o[2 * l]) = ts.o;
+      if (l == 0) {
+        sm.trail[0] = ts.M;
+        sm.trail[1] = ts.L;
+        sm.trail[2] = ts.V;
+      }
+    }
   } else {
-    const int t = tid - 64;
-    const int n_list = min(a.ucount[grp], MAX_UNION);
-    const int32_t* ulist = a.ulist + grp * MAX_UNION;
-    int blk = ulist[t];                      // valid for t < n_list
-    const float* eta = a.eta + grp * ra.nb;
-    float best_x = -INFINITY, best_8 = -INFINITY, tail_max = -INFINITY, maxc8 = 0.0f;
-    int ix = -1, i8 = -1;
-    double tail_mass = 0.0, l8u = 0.0, ev8u = 0.0;
-    for (int base = 0; base < ra.nb; base += ASCAN * ABATCH) {
-      float b8[ABATCH], be[ABATCH];
-      int bs[ABATCH];
-#pragma unroll
-      for (int j = 0; j < ABATCH; ++j) {       // all loads of the batch first
-        const int i = base + j * ASCAN + t;
-        const bool in = i < ra.nb;
-        b8[j] = in ? l8[i] : 0.0f;
-        bs[j] = in ? slot[i] : kbit;
-        be[j] = in ? eta[i] : 0.0f;
-      }
-#pragma unroll
-      for (int j = 0; j < ABATCH; ++j) {
-        if (bs[j] & kbit) continue;            // key-promoted for this head (or past the end)
-        const float v8 = b8[j];
-        const float mass = expf(v8 - lse8);
-        tail_max = fmaxf(tail_max, v8);
-        tail_mass += (double)mass;
-        if (bs[j] == 0) {
-          // not listed: the promoted-block pass does not revisit it, it keeps its INT8 mass
-          // and its eta_b
-          l8u += (double)mass;
-          ev8u += (double)(mass * be[j]);
-          maxc8 = fmaxf(maxc8, mass * be[j]);
-        }
-      }
-    }
-    for (int i = t; i < n_list; i += ASCAN) {
-      if (i != t) blk = ulist[i];
-      if (blk < 0 || blk >= ra.nb || !(slot[blk] & kbit)) continue;
-      const float vx = lx[blk], v8 = l8[blk];
-      if (vx > -INFINITY) best_merge(best_x, ix, vx, blk);   // a block without a log-mass (not a number, for a
-      if (v8 > -INFINITY) best_merge(best_8, i8, v8, blk);   // query that is none) tops no ranking
-    }
-    // reduce over each wave, then (below) over the waves' results
-    wave_best(best_x, ix);
-    wave_best(best_8, i8);
-    tail_max = wave_max(tail_max);
-    maxc8 = wave_max(maxc8);
-    tail_mass = wave_sum_d(tail_mass);
-    l8u = wave_sum_d(l8u);
-    ev8u = wave_sum_d(ev8u);
-    if ((tid & 63) == 0) {
-      const int w = tid >> 6;
-      w_bx[w] = best_x;
-      w_ix[w] = ix;
-      w_b8[w] = best_8;
-      w_i8[w] = i8;
-      w_tm[w] = tail_max;
-      w_mc[w] = maxc8;
-      w_mass[w] = tail_mass;
-      w_l8u[w] = l8u;
-      w_ev8u[w] = ev8u;
+    const KeyTerms kt = key_terms(ra, delta);
+    if (l == 0) {
+      sm.key[0] = kt.full;
+      sm.key[1] = kt.grow;
+      sm.key[2] = kt.widen;
     }
   }
-  TrailRegs tr;
-  if (tid < 64 && ra.r > 0) load_trail(ra, b, hq, nullptr, nullptr, tr);
-  __syncthreads();
-  if (tid < 64) {
-    const bool on = tid >= 1 && tid < NW;    // one scanning wave's results per lane
-    float bx = on ? w_bx[tid] : -INFINITY, b8 = on ? w_b8[tid] : -INFINITY;
-    int jx = on ? w_ix[tid] : -1, j8 = on ? w_i8[tid] : -1;
-    wave_best(bx, jx);
-    wave_best(b8, j8);
-    const float tm = wave_max(on ? w_tm[tid] : -INFINITY), mc = wave_max(on ? w_mc[tid] : 0.0f);
-    const double ms = wave_sum_d(on ? w_mass[tid] : 0.0), lu = wave_sum_d(on ? w_l8u[tid] : 0.0),
-                 eu = wave_sum_d(on ? w_ev8u[tid] : 0.0);
-    if (tid == 0) {
-      s_top[0] = bx;
-      s_top[1] = b8;
-      s_top[2] = tm;
-      s_top[3] = mc;
-      s_topi[0] = jx;
-      s_topi[1] = j8;
-      s_sum[0] = ms;
-      s_sum[1] = lu;
-      s_sum[2] = eu;
-    }
+  float best_x = -INFINITY, best_8 = -INFINITY;
+  int ix = -1, i8 = -1;
+  for (int i = tid; i < n_list; i += ART) {
+    if (i != tid) blk = ulist[i];
+    if (blk < 0 || blk >= ra.nb || !(slot[blk] & kbit)) continue;
+    const float vx = lx[blk], v8 = l8[blk];
+    if (vx > -INFINITY) best_merge(best_x, ix, vx, blk);   // a block without a log-mass (not a number, for a
+    if (v8 > -INFINITY) best_merge(best_8, i8, v8, blk);   // query that is none) tops no ranking
+  }
+  wave_best(best_x, ix);
+  wave_best(best_8, i8);
+  if (l == 0) {
+    rb.x[w] = best_x;
+    rb.ix[w] = ix;
+    rb.e[w] = best_8;
+    rb.ie[w] = i8;
   }
   __syncthreads();
   // ---- ranking check (the paper's "Ranking-Consistency Check" with its boundary verification)
   //      at depth r: the r best promoted blocks under the FP16 and under the INT8 log-masses must
   //      be the same blocks in the same order, and no unpromoted block may reach the r-th FP16
-  //      log-mass with its upper-bounded one.  Depth 1 is what the scan has found; each further
+  //      log-mass with its upper-bounded one.  Depth 1 is what the look through the list has found; each further
   //      place is one more arg-max over the group's listed blocks (a few dozen, held in registers),
   //      restricted to what comes after the previous place in the order (larger log-mass first,
   //      equal log-masses by lower index).  Fewer promoted blocks than r: the depth is their number.
-  const float top_x = s_top[0], top_8 = s_top[1];
-  const int top_ix = s_topi[0], top_i8 = s_topi[1];
+  float top_x, top_8;
+  int top_ix, top_i8;
+  rank_join(rb, top_x, top_ix, top_8, top_i8);
   bool disagree = top_ix >= 0 && top_ix != top_i8;
   float kth_x = top_x;
   const int depth = min(ra.tol.rank_depth, MAX_RANK_DEPTH);
   if (depth > 1 && top_ix >= 0) {          // uniform over the workgroup
-    constexpr int CAND = MAX_UNION / ART;
+    constexpr int CAND = (MAX_UNION + ART - 1) / ART;
     float cx[CAND], c8[CAND];
     int cb[CAND];
-    const int n = min(a.ucount[grp], MAX_UNION);
-    const int32_t* ulist = a.ulist + grp * MAX_UNION;
 #pragma unroll
     for (int j = 0; j < CAND; ++j) {
       const int i = j * ART + tid;
-      const int blk = i < n ? ulist[i] : -1;
-      const bool keyp = blk >= 0 && blk < ra.nb && (slot[blk] & kbit);
-      cb[j] = keyp ? blk : -1;
-      cx[j] = keyp ? lx[blk] : 0.0f;
-      c8[j] = keyp ? l8[blk] : 0.0f;
+      const int c = i < n_list ? ulist[i] : -1;
+      const bool keyp = c >= 0 && c < ra.nb && (slot[c] & kbit);
+      cb[j] = keyp ? c : -1;
+      cx[j] = keyp ? lx[c] : 0.0f;
+      c8[j] = keyp ? l8[c] : 0.0f;
     }
     float px = top_x, p8 = top_8;
     int pix = top_ix, pi8 = top_i8;
-    __syncthreads();                        // every thread has read the depth-1 results
     for (int k = 1; k < depth; ++k) {
       float bx = -INFINITY, b8 = -INFINITY;
       int jx = -1, j8 = -1;
@@ -940,31 +843,19 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
           j8 = cb[j];
         }
       }
-      s_bx[tid] = bx;
-      s_ix[tid] = jx;
-      s_b8[tid] = b8;
-      s_i8[tid] = j8;
-      __syncthreads();
-      for (int st = ART / 2; st > 0; st >>= 1) {
-        if (tid < st) {
-          const float ox = s_bx[tid + st];
-          const int oix = s_ix[tid + st];
-          if (oix >= 0 && (s_ix[tid] < 0 || ox > s_bx[tid] || (ox == s_bx[tid] && oix < s_ix[tid]))) {
-            s_bx[tid] = ox;
-            s_ix[tid] = oix;
-          }
-          const float o8 = s_b8[tid + st];
-          const int oi8 = s_i8[tid + st];
-          if (oi8 >= 0 && (s_i8[tid] < 0 || o8 > s_b8[tid] || (o8 == s_b8[tid] && oi8 < s_i8[tid]))) {
-            s_b8[tid] = o8;
-            s_i8[tid] = oi8;
-          }
-        }
-        __syncthreads();
+      wave_best(bx, jx);
+      wave_best(b8, j8);
+      __syncthreads();                      // the previous place has been read
+      if (l == 0) {
+        rb.x[w] = bx;
+        rb.ix[w] = jx;
+        rb.e[w] = b8;
+        rb.ie[w] = j8;
       }
-      const float nx = s_bx[0], n8 = s_b8[0];
-      const int nix = s_ix[0], ni8 = s_i8[0];
-      __syncthreads();                      // read before the next round overwrites
+      __syncthreads();
+      float nx, n8;
+      int nix, ni8;
+      rank_join(rb, nx, nix, n8, ni8);
       if (nix < 0) break;                   // fewer promoted blocks than the depth (uniform)
       disagree = disagree || nix != ni8;
       kth_x = nx;
@@ -974,26 +865,29 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
       pi8 = ni8;
     }
   }
-  if (tid >= 64) return;
-  ad.alpha = (float)s_sum[0];
+  if (w != 0) return;
+  const float* sc = a.scan + row * 8;
+  const float tmax = sc[S_TOP];
+  const bool has_tail = tmax > -INFINITY;
+  AdaptiveIn ad;
+  ad.alpha = sc[S_ALPHA];
   ad.delta = delta;
   ad.top_block = top_ix;
   ad.top_fp16 = top_ix >= 0 ? top_x : -INFINITY;
   ad.kth_fp16 = top_ix >= 0 ? kth_x : -INFINITY;
-  const float tmax = s_top[2];
-  const bool has_tail = tmax > -INFINITY;
   ad.tail_ub = has_tail ? tmax + delta : -INFINITY;
   const bool boundary = top_ix >= 0 && has_tail && tmax + delta + ra.tol.eps_guard > kth_x;
   ad.rank_fail = (disagree || boundary) ? 1 : 0;
   ad.precond = (a.score_dev != nullptr && a.score_dev[row] > delta + ra.tol.eps_guard) ? 1 : 0;
-  ad.L8u = (float)s_sum[1];
-  ad.EV8u = (float)s_sum[2];
-  ad.maxc8 = s_top[3];
+  ad.L8u = sc[S_L8U];
+  ad.EV8u = sc[S_EV8U];
+  ad.maxc8 = sc[S_MAXC8];
   ad.lse8 = lse8;
-  if (tid == 0) a.alpha_out[row] = ad.alpha;
-  TrailState ts{};
-  if (ra.r > 0) ts = trail_state(ra, tr);
-  finish_head(ra, b, hq, head_state(st, o2), ts, key_terms(ra, delta), &ad);
+  if (l == 0) a.alpha_out[row] = ad.alpha;
+  float2 o2;
+  const OctState st = merge_lds(sm.sc[0], 12, sm.o[0], D, RED_WAVES, o2);
+  const TrailState ts{sm.trail[0], sm.trail[1], sm.trail[2], *reinterpret_cast<const float2*>(&sm.trail_o[2 * l])};
+  finish_head(ra, b, hq, head_state(st, o2), ts, KeyTerms{sm.key[0], sm.key[1], sm.key[2]}, &ad);
 }
 
 }  // namespace
@@ -1028,8 +922,9 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
     return launch_certified(c, layer, q, tol, O, cert, flags, flags_mirror, mirror_tag, nullptr, st, nullptr, nullptr, 0,
                             nullptr, nullptr, raised, raised_tag);
   }
+  ReduceArgs first{};   // its reduction is left to the selector
   int32_t rc = launch_certified(c, layer, q, loose, O, cert, flags, nullptr, 0u, w.lm8, st, nullptr, nullptr,
-                                total, w.eta_blk);
+                                total, w.eta_blk, nullptr, nullptr, 0u, &first, true);
   if (rc != CQA_OK) return rc;
 
   // ---- 2. selection per head (+ Rung 1), union bit mask per group
@@ -1040,7 +935,12 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   sa.lm8 = w.lm8;
   sa.eta_blk = w.eta_blk;
   sa.contrib = w.contrib;
-  sa.cert = cert;
+  sa.ra = first;
+  sa.first = w.first;
+  sa.slot = w.slot;
+  sa.slot_stride = c->nq_cap * 4;
+  sa.ulist = w.ulist;
+  sa.ucount = w.ucount;
   sa.mask_words = w.mask_words;
   sa.nb = (int)nb;
   sa.n_q = hq;
@@ -1056,13 +956,12 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   hipLaunchKernelGGL(select_kernel, dim3(hq, bt, values ? 2 : 1), dim3(ST), 0, st, sa);
   CQA_HIP(hipGetLastError());
 
-  // ---- 3. slot map and ordered list per group
+  // ---- 3. with the FP16 scratch, flag words and ordered list per group
+  const double thr = (double)sel.explore_frac * 4294967296.0;
+  const uint32_t explore_threshold = sel.explore_frac > 0.0f ? (uint32_t)std::min(thr, 4294967295.0) : 0u;
   CompactArgs ca{};
-  {
-    const double thr = (double)sel.explore_frac * 4294967296.0;
-    ca.explore_threshold = sel.explore_frac > 0.0f ? (uint32_t)std::min(thr, 4294967295.0) : 0u;
-    ca.explore_seed = sel.explore_seed;
-  }
+  ca.explore_threshold = explore_threshold;
+  ca.explore_seed = sel.explore_seed;
   ca.vmask = values ? w.vmask : nullptr;
   ca.umask = w.umask;
   ca.group = g;
@@ -1085,9 +984,9 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
     ca.sc_stats = w.sc_stats;
     ca.sc_cap = w.sc_cap;
     ca.sc_step = w.sc_step;
+    hipLaunchKernelGGL(compact_kernel, dim3(hkv, bt), dim3(256), 0, st, ca);
+    CQA_HIP(hipGetLastError());
   }
-  hipLaunchKernelGGL(compact_kernel, dim3(hkv, bt), dim3(256), 0, st, ca);
-  CQA_HIP(hipGetLastError());
 
   // ---- 4. promoted-block pass: the listed blocks once more with the originals their flags ask
   //         for (positive sets) and once as the first pass saw them (negated sets)
@@ -1122,12 +1021,9 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   a.pstride = total;
   a.n_q = hq;
   a.n_kv = hkv;
-  a.slot = w.slot;
   a.sc_k = w.sc_slots > 0 ? w.sc_k + layer_head0 * w.sc_cap * BLK * D : nullptr;
   a.sc_v = w.sc_slots > 0 ? w.sc_v + layer_head0 * w.sc_cap * BLK * D : nullptr;
   a.sc_cap = w.sc_cap;
-  a.ulist = w.ulist;
-  a.ucount = w.ucount;
   a.t2_k = c->t2_k + layer_head0 * c->desc.max_tokens * D;
   a.t2_v = c->t2_v + layer_head0 * c->desc.max_tokens * D;
   a.eta_out = nullptr;
@@ -1135,7 +1031,21 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   a.int8_query = tol.int8_query;
   a.max_tokens = c->desc.max_tokens;
   a.split0 = nsplit;
-  rc = launch_promoted_pass(a, g, dim3(2 * PROM_SPLITS, hkv, bt), st);
+  PromArgs pa{};
+  pa.umask = w.sc_slots > 0 ? nullptr : w.umask;
+  pa.vmask = values ? w.vmask : nullptr;
+  pa.mask_words = w.mask_words;
+  pa.per_head = sel.per_head;
+  pa.explore_threshold = explore_threshold;
+  pa.explore_seed = sel.explore_seed;
+  pa.slot = w.slot;
+  pa.ulist = w.ulist;
+  pa.ucount = w.ucount;
+  pa.lm8 = w.lm8;
+  pa.eta = w.eta_blk;
+  pa.first = w.first;
+  pa.scan = w.scan;
+  rc = launch_promoted_pass(a, pa, g, dim3(2 * PROM_SPLITS + g, hkv, bt), st);
   if (rc != CQA_OK) return rc;
 
   // ---- 5. merge, certificate with the achieved tail, ranking check
@@ -1147,7 +1057,8 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   ar.slot_stride = c->nq_cap * 4;
   ar.alpha_out = w.alpha;
   ar.score_dev = sel.canary ? w.score_dev : nullptr;
-  ar.eta = w.eta_blk;
+  ar.first = w.first;
+  ar.scan = w.scan;
   ar.pos_set0 = nsplit;
   ar.pos_set1 = nsplit + PROM_SPLITS;
   ar.ulist = w.ulist;

@@ -116,6 +116,8 @@ struct AdaptiveWs {
   float* score_dev;  // [Bt][Hq]              canary: largest |s_fp16 - s_int8| on key-promoted tokens
   int32_t* ucount;   // [Bt][Hkv]             promoted blocks of the group
   int32_t* ulist;    // [Bt][Hkv][MAX_UNION]  their indices, ascending
+  float* first;      // [Bt][Hq][4]           lse, Delta_h, V_max of the pass over all blocks
+  float* scan;       // [Bt][Hq][8]           what the blocks its group left in INT8 add up to (S_* below)
   int64_t mask_words;
   // FP16 scratch (the paper's VRAM scratch cache of promoted originals, LRU): per (layer, batch,
   // kv-head) `sc_cap` slots of one block each, a key half and a value half.  sc_map: block ->
@@ -133,6 +135,9 @@ struct AdaptiveWs {
   uint32_t sc_step;  // stamp of the last adaptive step
 };
 
+// AdaptiveWs::scan: over the blocks that are not key-promoted for the head, the estimated mass and the largest log-mass;
+// over those that are not listed at all, relative to lse, the mass, the value term and the largest share of it
+constexpr int S_ALPHA = 0, S_TOP = 1, S_L8U = 2, S_EV8U = 3, S_MAXC8 = 4;
 constexpr int MAX_RANK_DEPTH = 8;   // largest depth r of the ranking check (adaptive path)
 constexpr int SC_MAX_SLOTS = 1024;
 // per-block word of AdaptiveWs::slot: bit 0 FP16 keys, bit 1 FP16 values, bit 2 / bit 3 the keys /
@@ -208,13 +213,10 @@ struct DecodeArgs {
   int finish;          // matrix-core pass: 1 = it finishes the rows of a single split itself
   int keep_sets;       // matrix-core pass: 1 = the partial sets are read by a later launch too
   int wpb;             // matrix-core pass: waves per workgroup, 8 or 4 (split_geometry)
-  // promoted-block pass of the adaptive decode (null slot = not that pass)
-  const int32_t* slot;      // [Bt][Hkv][4 nq_cap]: bit 0 = FP16 keys, bit 1 = FP16 values, 0 = neither
+  // promoted-block pass of the adaptive decode
   __half* sc_k;             // layer base of the FP16 scratch's key halves [Bt * Hkv][sc_cap][16][128], or null
   __half* sc_v;             // ... and of its value halves (null exactly when sc_k is)
   int sc_cap;
-  const int32_t* ulist;     // [Bt][Hkv][MAX_UNION]: promoted blocks of the group, ascending
-  const int32_t* ucount;    // [Bt][Hkv]
   const __half* t2_k;       // pinned FP16 key originals of the layer: [Bt * Hkv][max_tokens][128]
   const __half* t2_v;       // value originals, same layout
   int64_t max_tokens;
@@ -235,6 +237,24 @@ struct DecodeArgs {
   int64_t ap_pos, ap_max_tokens;
 };
 
+
+// The promoted-block pass's part of the adaptive step besides DecodeArgs.
+struct PromArgs {
+  const uint32_t* umask;    // [Bt][Hq][mask_words] key selections per head, or null: the list and the flag words are
+                            // there already (compact_kernel, which looks after the FP16 scratch)
+  const uint32_t* vmask;    // value selections, or null
+  int64_t mask_words;
+  int per_head;             // 1: a head's promoted sets are its own selections; 0: the group's unions
+  uint32_t explore_threshold;   // a block is explored (key-promoted) when its draw is below this; 0 = off
+  uint32_t explore_seed;
+  int32_t* slot;            // written from the masks: the flag words of the listed blocks, ...
+  int32_t* ulist;           // ... the list, ascending, ...
+  int32_t* ucount;          // ... its length
+  const float* lm8;         // [Bt][Hq][nb]
+  const float* eta;         // [Bt][Hkv][nb]
+  const float* first;       // [Bt][Hq][4]
+  float* scan;              // [Bt][Hq][8], written
+};
 
 inline int64_t head_index(const Cache* c, int layer, int b, int kvh) {
   return ((int64_t)layer * c->desc.batch + b) * c->desc.n_kv_heads + kvh;
@@ -275,7 +295,8 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
                          const __half* v_new = nullptr, int pstride = 0, float* eta_out = nullptr,
                          float* partials = nullptr,   // null = the cache's own split workspace
                          uint32_t* raised = nullptr, uint32_t raised_tag = 0u,
-                         ReduceArgs* defer = nullptr);   // nsplit set > 0: the reduction is left to the caller
+                         ReduceArgs* defer = nullptr,    // nsplit set > 0: the reduction is left to the caller,
+                         bool always = false);           // ... not only where the ladder's launch takes it
 int32_t static_scratch(int device, void** out);
 int pick_splits(const Cache* c, int64_t n_blocks);
 int stream_nt(const Cache* c, int64_t n_blocks);

@@ -27,8 +27,195 @@ namespace cqa {
 //               block is attended from its FP16 values and counts with eta_b = 0; both kinds of
 //               originals are read by the device straight from the pinned Tier-2 arrays over the
 //               host link.  Writes partial sets split0 + blockIdx.x.
+// Promotion bits of one word (32 blocks) of a KV group, from its heads' masks: key bits kh and value bits vh per head;
+// explored blocks are key-promoted for every head, and with per-group promotion every head has the unions.
+struct PromBits {
+  uint32_t kh[4], vh[4], k, v;
+};
+__device__ __forceinline__ PromBits prom_bits(const DecodeArgs& a, const PromArgs& p, int64_t grp, int group, int word, uint32_t only) {
+  PromBits r;
+  r.k = r.v = 0u;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int64_t at = (grp * group + i) * p.mask_words + word;
+    r.kh[i] = i < group ? p.umask[at] & only : 0u;
+    r.vh[i] = i < group && p.vmask != nullptr ? p.vmask[at] & only : 0u;
+    r.k |= r.kh[i];
+    r.v |= r.vh[i];
+  }
+  if (p.explore_threshold != 0u) {
+    uint32_t x = 0u;
+    for (uint32_t m = only; m != 0u; m &= m - 1u) {
+      const int j = __ffs((int)m) - 1;
+      if (explore_mix((uint32_t)(word * 32 + j), (uint32_t)grp, p.explore_seed) < p.explore_threshold) x |= 1u << j;
+    }
+    r.k |= x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.kh[i] |= x;
+  }
+  const uint32_t in = word * 32 + 32 <= a.nb ? ~0u : (1u << (a.nb & 31)) - 1u;   // nothing past nb
+  r.k &= in;
+  r.v &= in;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    r.kh[i] = i < group ? (p.per_head ? r.kh[i] & in : r.k) : 0u;
+    r.vh[i] = i < group ? (p.per_head ? r.vh[i] & in : r.v) : 0u;
+  }
+  return r;
+}
+
+// The share of workgroup psplit in its KV group's list of promoted blocks, which is dealt in fours: positions 4 psplit .. + 3, and
+// every 4 * PROM_SPLITS further, to s_blk (block) and s_pf (flag word); returns the list's length.  The list comes from the
+// selection masks (every workgroup walks them, one, `write`, also stores list and flag words for the reduction),
+// or, when the FP16 scratch is in use, is there already.  As a launch of its own this took 5 - 10 us.
+constexpr int PROM_SHARE = MAX_UNION / PROM_SPLITS;
+__device__ __forceinline__ int prom_list(const DecodeArgs& a, const PromArgs& p, int64_t grp, int group, int psplit, bool write,
+                                         int* s_blk, int* s_pf) {
+  const int tid = threadIdx.x;
+  int32_t* const slot = p.slot + grp * (a.nq_cap * 4);
+  int32_t* const ulist = p.ulist + grp * MAX_UNION;
+  if (p.umask == nullptr) {
+    const int n = min(p.ucount[grp], MAX_UNION);
+    const int pos = (tid >> 2) * (4 * PROM_SPLITS) + psplit * 4 + (tid & 3);
+    if (pos < n) {
+      const int blk = ulist[pos];
+      s_blk[tid] = blk;
+      s_pf[tid] = blk >= 0 && blk < a.nb ? slot[blk] : 0;
+    }
+    __syncthreads();
+    return n;
+  }
+  __shared__ int s_tot[4], s_base;
+  const int words = (a.nb + 31) >> 5;
+  // a thread takes a word, or a half, a quarter, an eighth of one while there are threads: set bits are walked one by one
+  int per = 0;                          // log2 of the pieces per word
+  while (per < 3 && (words << (per + 1)) <= 256) ++per;
+  const int bits = 32 >> per, pieces = words << per;
+  int total = 0;
+  for (int p0 = 0; p0 < pieces; p0 += 256) {
+    const int piece = p0 + tid, word = piece >> per, off = (piece & ((1 << per) - 1)) * bits;
+    PromBits m;
+    m.k = m.v = 0u;
+    if (piece < pieces) m = prom_bits(a, p, grp, group, word, (bits == 32 ? ~0u : (1u << bits) - 1u) << off);
+    uint32_t any = m.k | m.v;
+    const int cnt = __popc(any);
+    const int upto = total + block_scan_incl<int>(cnt, s_tot, tid);
+    if (tid == 255) s_base = upto;
+    // the list cannot overflow (4 heads x MAX_K_LIMIT for keys and as many for values) but by explored
+    // blocks; one that does not fit stays unpromoted
+    for (int pos = upto - cnt; any != 0u; any &= any - 1u, ++pos) {
+      const bool mine = ((pos >> 2) & (PROM_SPLITS - 1)) == psplit;
+      if (pos >= MAX_UNION || !(mine || write)) continue;
+      const int j = __ffs((int)any) - 1, blk = word * 32 + j;
+      uint32_t f = ((m.k >> j) & 1u) | (((m.v >> j) & 1u) << 1);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        f |= (((m.kh[i] >> j) & 1u) << (SLOT_HK_SHIFT + i)) | (((m.vh[i] >> j) & 1u) << (SLOT_HV_SHIFT + i));
+      if (mine) {
+        const int at = (pos / (4 * PROM_SPLITS)) * 4 + (pos & 3);
+        s_blk[at] = blk;
+        s_pf[at] = (int)f;
+      }
+      if (write) {
+        slot[blk] = (int)f;
+        ulist[pos] = blk;
+      }
+    }
+    __syncthreads();
+    total = s_base;
+  }
+  total = min(total, MAX_UNION);
+  if (write && tid == 0) p.ucount[grp] = total;
+  return total;
+}
+
+// What the blocks left in INT8 add up to for one head (AdaptiveWs::scan), by one workgroup beside the promoted-block pass.
+__device__ __forceinline__ void prom_scan(const DecodeArgs& a, const PromArgs& p, int64_t grp, int group, int h, int64_t row) {
+  const int tid = threadIdx.x;
+  const int32_t* const slot = p.slot + grp * (a.nq_cap * 4);
+  const float* l8 = p.lm8 + row * a.nb;
+  const float* eta = p.eta + grp * a.nb;
+  const float lse8 = p.first[row * 4];
+  const int kbit = 1 << (SLOT_HK_SHIFT + h);
+  __shared__ uint32_t s_key[256], s_any[256];   // key-promoted for the head, listed: 8192 blocks at a time
+  __shared__ double s_sum[4][3];
+  __shared__ float s_max[4][2];
+  __shared__ int s_scan[4], s_total;
+  int listed = 0;
+  float tail_max = -INFINITY, maxc8 = 0.0f;
+  double tail_mass = 0.0, l8u = 0.0, ev8u = 0.0;
+  for (int b0 = 0; b0 < a.nb; b0 += 8192) {
+    if (p.umask != nullptr) {
+      PromBits m;
+      m.k = m.v = m.kh[h] = 0u;
+      if (b0 + tid * 32 < a.nb) m = prom_bits(a, p, grp, group, (b0 >> 5) + tid, ~0u);
+      uint32_t any = m.k | m.v;
+      const int upto = listed + block_scan_incl<int>(__popc(any), s_scan, tid);
+      if (tid == 255) s_total = upto;
+      // what does not fit the list stays unpromoted: the highest blocks
+      for (int over = upto - MAX_UNION; over > 0 && any != 0u; --over) any &= ~(0x80000000u >> __clz((int)any));
+      s_key[tid] = m.kh[h] & any;
+      s_any[tid] = any;
+      __syncthreads();
+      listed = s_total;
+    }
+    for (int base = b0; base < min(b0 + 8192, a.nb); base += 256 * 8) {
+      float b8[8], be[8];
+      int bs[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int i = base + j * 256 + tid;
+        const bool in = i < a.nb;
+        b8[j] = in ? l8[i] : 0.0f;
+        be[j] = in ? eta[i] : 0.0f;
+        if (p.umask != nullptr) {
+          const int wd = in ? (i - b0) >> 5 : 0;
+          bs[j] = !in || ((s_key[wd] >> (i & 31)) & 1u) ? kbit : (int)((s_any[wd] >> (i & 31)) & 1u);
+        } else {
+          bs[j] = in ? slot[i] : kbit;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        if (bs[j] & kbit) continue;            // key-promoted for this head (or past the end)
+        const float mass = expf(b8[j] - lse8);
+        tail_max = fmaxf(tail_max, b8[j]);
+        tail_mass += (double)mass;
+        if (bs[j] == 0) {
+          // not listed: the promoted-block pass does not revisit it, it keeps its INT8 mass and its eta_b
+          l8u += (double)mass;
+          ev8u += (double)(mass * be[j]);
+          maxc8 = fmaxf(maxc8, mass * be[j]);
+        }
+      }
+    }
+  }
+  const int w = tid >> 6;
+  tail_mass = wave_sum_d(tail_mass);
+  l8u = wave_sum_d(l8u);
+  ev8u = wave_sum_d(ev8u);
+  tail_max = wave_max(tail_max);
+  maxc8 = wave_max(maxc8);
+  if ((tid & 63) == 0) {
+    s_sum[w][0] = tail_mass;
+    s_sum[w][1] = l8u;
+    s_sum[w][2] = ev8u;
+    s_max[w][0] = tail_max;
+    s_max[w][1] = maxc8;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    float* out = p.scan + row * 8;
+    out[S_ALPHA] = (float)(s_sum[0][0] + s_sum[1][0] + s_sum[2][0] + s_sum[3][0]);
+    out[S_L8U] = (float)(s_sum[0][1] + s_sum[1][1] + s_sum[2][1] + s_sum[3][1]);
+    out[S_EV8U] = (float)(s_sum[0][2] + s_sum[1][2] + s_sum[2][2] + s_sum[3][2]);
+    out[S_TOP] = fmaxf(fmaxf(s_max[0][0], s_max[1][0]), fmaxf(s_max[2][0], s_max[3][0]));
+    out[S_MAXC8] = fmaxf(fmaxf(s_max[0][1], s_max[1][1]), fmaxf(s_max[2][1], s_max[3][1]));
+  }
+}
+
 template <int G, bool PROM>
-__global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a, PromArgs p) {
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int tok = l & 15, kg = l >> 4;              // roles in the score phase
   const int vn = l & 15, vgh = (l >> 4) & 1, vo = l >> 5;  // roles in the value phase
@@ -36,16 +223,23 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a) {
   const int64_t head_rec = ((int64_t)b * a.n_kv + kvh) * a.nq_cap;
   // blocks are dealt evenly over the splits (every split gets at least one: nsplit <= nb)
   const int64_t grp = (int64_t)b * a.n_kv + kvh;
-  // PROM: positions split * 4 + w, + 4 * gridDim.x, ... of the group's list; else a block range
+  // PROM: positions psplit * 4 + w, + 4 * PROM_SPLITS, ... of the group's list; else a block range
   // PROM: the second half of the workgroups (neg) walks the same list with INT8 keys and INT4
   // values whatever the flags say and writes its partial set negated: it takes back what the one
   // pass over all sealed blocks added for the listed blocks, the first half adds them again with
-  // the originals the flags ask for.
-  const bool neg = PROM && split >= (int)gridDim.x / 2;
-  const int psplit = PROM ? (neg ? split - (int)gridDim.x / 2 : split) : split;
+  // the originals the flags ask for.  One more workgroup per head sums up the blocks left in INT8.
+  if (PROM && split >= 2 * PROM_SPLITS) {
+    const int h = split - 2 * PROM_SPLITS;
+    prom_scan(a, p, grp, G, h, (int64_t)b * a.n_q + kvh * G + h);
+    return;
+  }
+  const bool neg = PROM && split >= PROM_SPLITS;
+  const int psplit = PROM ? split & (PROM_SPLITS - 1) : split;
+  __shared__ int s_blk[PROM ? PROM_SHARE : 1], s_pf[PROM ? PROM_SHARE : 1];
+  const int n_list = PROM ? prom_list(a, p, grp, G, psplit, split == PROM_SPLITS, s_blk, s_pf) : 0;
   const int b0 = PROM ? psplit * 4 : (int)(((int64_t)split * a.nb) / a.nsplit);
-  const int b1 = PROM ? min(a.ucount[grp], MAX_UNION) : (int)(((int64_t)(split + 1) * a.nb) / a.nsplit);
-  const int bstep = PROM ? 2 * (int)gridDim.x : 4;   // PROM: 4 waves x gridDim.x / 2 workgroups
+  const int b1 = PROM ? n_list : (int)(((int64_t)(split + 1) * a.nb) / a.nsplit);
+  const int bstep = PROM ? 4 * PROM_SPLITS : 4;
   const int out_split = PROM ? a.split0 + split : split;
   const float inv_sqrt_d = 0.08838834764831845f;  // 1 / sqrt(128)
 
@@ -84,19 +278,17 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a) {
     for (int gq = 0; gq < 4; ++gq) acc[gq][h] = 0.0f;
   }
 
-  // the list entry of the next iteration is requested one iteration ahead
-  int blk_next = (PROM && b0 + w < b1) ? a.ulist[grp * MAX_UNION + b0 + w] : b0 + w;
-  for (int pos = b0 + w; pos < b1; pos += bstep) {
+  int at = w;   // PROM: this wave's entry of the share
+  for (int pos = b0 + w; pos < b1; pos += bstep, at += 4) {
     // every index is bounded on the way in: a list entry outside [0, nb) is skipped
-    const int blk = blk_next;
-    blk_next = (PROM && pos + bstep < b1) ? a.ulist[grp * MAX_UNION + pos + bstep] : pos + bstep;
+    const int blk = PROM ? __builtin_amdgcn_readfirstlane(s_blk[at]) : pos;
     if (PROM && (blk < 0 || blk >= a.nb)) continue;
     // Every load of the block is requested here, before anything is consumed: the block sits at
     // an address nothing else in this launch touches, so each dependent load costs a full
     // memory (and page-walk) latency.  First everything whose address follows from blk alone
     // (flags, INT8 codes, key and value metadata, INT4 codes), then the originals the flags ask
     // for.
-    const int pf = PROM ? a.slot[grp * (a.nq_cap * 4) + blk] : 0;   // bit 0: FP16 keys, bit 1: FP16 values
+    const int pf = PROM ? __builtin_amdgcn_readfirstlane(s_pf[at]) : 0;   // bit 0: FP16 keys, bit 1: FP16 values
     const float* kmb = reinterpret_cast<const float*>(a.t1 + t1_offset(head_rec, blk, Q_KM, KM_BYTES));
     const float2 sg8 = reinterpret_cast<const float2*>(kmb)[l];
     const float2 zz8 = reinterpret_cast<const float2*>(kmb + D)[l];
@@ -416,56 +608,11 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a) {
   }
 }
 
-// Stand-alone cross-split reduction: one workgroup per (batch, query head).  It runs on the critical tail of a step, alone on the
-// chip, and is bound by the length of its instruction chain, so the chain is cut into parts that run side by side: up to RED_WAVES
-// waves merge eight partial sets a trip each, one attends the trailing tokens, one takes Delta_h through the
-// key term's functions; the first then joins their results.  Where one wave per head did all this in turn (8500 cycles), a step of 8 KV
-// heads, four layers: 8229 tokens 64.4 -> 57.7 us, 3000 tokens 59.6 -> 50.6.
-constexpr int RED_WAVES = 8;
-struct ReduceSmem {
-  float sc[RED_WAVES][12];
-  float o[RED_WAVES][D];
-  float trail_o[D];
-  float trail[4], key[4];
-};
+// Stand-alone cross-split reduction.
 __global__ __launch_bounds__(64 * (RED_WAVES + 2)) void certified_reduce_kernel(ReduceArgs a) {
-  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nw = (int)(blockDim.x >> 6) - 2;     // waves that merge sets
-  const int hq = blockIdx.x, b = blockIdx.y;
   __shared__ __align__(16) ReduceSmem sm;
-  const float* part = a.partials + ((int64_t)b * a.n_q + hq) * (a.pstride > 0 ? a.pstride : a.nsplit) * PART_FLOATS;
-  OctState st{};
-  float2 o2 = make_float2(0.0f, 0.0f);
-  if (w < nw) {
-    st = merge_sets(part, 8 * w, 8 * nw, a.nsplit, 0, a.nsplit, o2);
-    if (nw > 1) store_state(st, o2, sm.sc[w], sm.o[w]);
-  } else if (w == nw) {
-    if (a.r > 0) {
-      TrailRegs tr;
-      load_trail(a, b, hq, nullptr, nullptr, tr);
-      const TrailState ts = trail_state(a, tr);
-      *reinterpret_cast<float2*>(&sm.trail_o[2 * l]) = ts.o;
-      if (l == 0) {
-        sm.trail[0] = ts.M;
-        sm.trail[1] = ts.L;
-        sm.trail[2] = ts.V;
-      }
-    }
-  } else {
-    float delta = 0.0f;
-    for (int s = l; s < a.nsplit; s += 64) delta = fmaxf(delta, part[(int64_t)s * PART_FLOATS + P_DMAX]);
-    const KeyTerms kt = key_terms(a, wave_max(delta));
-    if (l == 0) {
-      sm.key[0] = kt.full;
-      sm.key[1] = kt.grow;
-      sm.key[2] = kt.widen;
-    }
-  }
-  __syncthreads();
-  if (w != 0) return;
-  if (nw > 1) st = merge_lds(sm.sc[0], 12, sm.o[0], D, nw, o2);
-  const TrailState ts{sm.trail[0], sm.trail[1], sm.trail[2], *reinterpret_cast<const float2*>(&sm.trail_o[2 * l])};
-  finish_head(a, b, hq, head_state(st, o2), ts, KeyTerms{sm.key[0], sm.key[1], sm.key[2]}, nullptr);
+  HeadRow row;
+  if (reduce_row(a, blockIdx.y, blockIdx.x, (int)(blockDim.x >> 6), sm, row)) store_row(a, blockIdx.y, blockIdx.x, row);
 }
 
 // Workgroups ("splits") per (batch, kv-head) and waves per workgroup of the matrix-core split pass.
@@ -543,14 +690,13 @@ int pick_splits(const Cache* c, int64_t n_blocks) {
 }
 
 // Promoted-block pass of the adaptive decode (see certified_split_kernel).
-int32_t launch_promoted_pass(const DecodeArgs& a, int group, dim3 grid, hipStream_t st) {
-  if (a.ulist == nullptr || a.ucount == nullptr || a.slot == nullptr || a.t2_k == nullptr ||
-      a.t2_v == nullptr)
+int32_t launch_promoted_pass(const DecodeArgs& a, const PromArgs& p, int group, dim3 grid, hipStream_t st) {
+  if (p.ulist == nullptr || p.ucount == nullptr || p.slot == nullptr || a.t2_k == nullptr || a.t2_v == nullptr)
     return CQA_ERR_INVALID_ARG;
   switch (group) {
-    case 1: hipLaunchKernelGGL((certified_split_kernel<1, true>), grid, dim3(256), 0, st, a); break;
-    case 2: hipLaunchKernelGGL((certified_split_kernel<2, true>), grid, dim3(256), 0, st, a); break;
-    case 4: hipLaunchKernelGGL((certified_split_kernel<4, true>), grid, dim3(256), 0, st, a); break;
+    case 1: hipLaunchKernelGGL((certified_split_kernel<1, true>), grid, dim3(256), 0, st, a, p); break;
+    case 2: hipLaunchKernelGGL((certified_split_kernel<2, true>), grid, dim3(256), 0, st, a, p); break;
+    case 4: hipLaunchKernelGGL((certified_split_kernel<4, true>), grid, dim3(256), 0, st, a, p); break;
     default: return CQA_ERR_UNSUPPORTED;
   }
   CQA_HIP(hipGetLastError());
@@ -589,7 +735,7 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
                          cqa_head_cert* cert, uint32_t* flags, uint32_t* flags_mirror,
                          uint32_t mirror_tag, float* blk_logmass, hipStream_t st,
                          const __half* k_new, const __half* v_new, int pstride, float* eta_out,
-                         float* partials, uint32_t* raised, uint32_t raised_tag, ReduceArgs* defer) {
+                         float* partials, uint32_t* raised, uint32_t raised_tag, ReduceArgs* defer, bool always) {
   const int bt = c->desc.batch, hq = c->desc.n_q_heads, hkv = c->desc.n_kv_heads;
   if (partials == nullptr) partials = c->partials;
   const int64_t len = c->length[layer];
@@ -629,9 +775,6 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     a.nb = (int)nb;
     a.nsplit = nsplit;
     a.pstride = pstride > 0 ? pstride : nsplit;
-    a.slot = nullptr;
-    a.ulist = nullptr;
-    a.ucount = nullptr;
     a.t2_k = nullptr;
     a.t2_v = nullptr;
     a.eta_out = nullptr;
@@ -664,7 +807,7 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     // the cheaper place.  A step of 4 heads per group, this launch finishing the rows and the reduction: 32 rows
     // 18.0, 20.5 us; 64 20.0, 21.3; 128 23.3, 22.2; 256 27.5, 23.1; 1280 55.7, 45.9.  One or two heads per
     // group gain at any number: 720 rows 31.0, 34.6; 1440 36.3, 41.0.
-    a.finish = nsplit == 1 && (flags_mirror == nullptr || hq / hkv < 4 || bt * hq <= 64) ? 1 : 0;
+    a.finish = nsplit == 1 && !always && (flags_mirror == nullptr || hq / hkv < 4 || bt * hq <= 64) ? 1 : 0;
     // the quantised-query scoring exists in the matrix-core pass (and in the promoted-block pass of
     // the adaptive calls), not in the vector-ALU cross-check kernel
     if (tol.int8_query != 0 && c->variant != 0) return CQA_ERR_UNSUPPORTED;
@@ -680,9 +823,9 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
       reduced = a.finish != 0;
     } else {
       switch (hq / hkv) {
-        case 1: hipLaunchKernelGGL((certified_split_kernel<1, false>), grid, dim3(256), 0, st, a); break;
-        case 2: hipLaunchKernelGGL((certified_split_kernel<2, false>), grid, dim3(256), 0, st, a); break;
-        case 4: hipLaunchKernelGGL((certified_split_kernel<4, false>), grid, dim3(256), 0, st, a); break;
+        case 1: hipLaunchKernelGGL((certified_split_kernel<1, false>), grid, dim3(256), 0, st, a, PromArgs{}); break;
+        case 2: hipLaunchKernelGGL((certified_split_kernel<2, false>), grid, dim3(256), 0, st, a, PromArgs{}); break;
+        case 4: hipLaunchKernelGGL((certified_split_kernel<4, false>), grid, dim3(256), 0, st, a, PromArgs{}); break;
         default: return CQA_ERR_UNSUPPORTED;
       }
     }
@@ -693,7 +836,7 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     }
   }
   if (reduced) return CQA_OK;
-  if (defer != nullptr && nsplit > 1 && nsplit <= FINISH_SETS && (int64_t)bt * hq <= FINISH_ROWS) {
+  if (defer != nullptr && (always || (nsplit > 1 && nsplit <= FINISH_SETS && (int64_t)bt * hq <= FINISH_ROWS))) {
     *defer = ra;
     return CQA_OK;
   }

@@ -1,0 +1,104 @@
+"""The list of promoted blocks as the promoted-block pass makes it from the selection masks, against the list of a cache
+whose FP16 scratch is in use (a launch of its own) and against the oracle's exploration draw, where the pieces of
+a mask word change size, in the last, partial word, and where the list is full; and merges of many partial sets."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from oracle import adaptive as ad
+from helpers import GpuLayerCache, assert_head_matches
+
+pytestmark = pytest.mark.gpu
+
+
+def run(gc, q, tol, sel):
+    gc.cqa.cqa_adaptive_decode(gc.h, 0, gc.to_dev(q), tol, sel, gc.O, gc.cert, gc.flags)
+    O, cert, flags = [x.copy() for x in gc.results()]
+    st = gc.cqa.cqa_adaptive_state(gc.h, 0, gc.bt, gc.hq, gc.hkv)
+    return O, cert, flags, st
+
+
+# blocks: 8, 4, 2 or 1 pieces a word (up to 32, 64, 128 words), one and several sweeps of 256 words
+@pytest.mark.parametrize("blocks", [1, 31, 33, 32 * 32, 32 * 33 + 1, 32 * 64 + 7, 32 * 129 + 3, 8192 + 40])
+@pytest.mark.parametrize("hkv,g,per_head,values", [(2, 4, True, 24), (1, 1, False, 0)])
+def test_the_list_from_the_masks_is_the_list_of_the_scratch_path(blocks, hkv, g, per_head, values):
+    n = blocks * 16 + 5
+    rng = np.random.Generator(np.random.Philox(blocks))
+    k, v = workloads.student_t3_f16(rng, (1, hkv, n, 128)), workloads.normal_f16(rng, (1, hkv, n, 128))
+    qs = [workloads.normal_f16(rng, (1, hkv * g, 128)) for _ in range(2)]
+    print("list", blocks, hkv, g, flush=True)
+    got = []
+    for slots in (0, 16):
+        with GpuLayerCache(1, hkv * g, hkv, n + 16) as gc:
+            gc.append(k, v)
+            gc.cqa.cqa_set_scratch_slots(gc.h, min(slots, 1 << max(0, (blocks - 1).bit_length())))
+            tol = gc.cqa.Tolerances(rank_depth=3, v_tol=0.02 if values else float("inf"))
+            sel = gc.cqa.Selector(0.995, 2, 40, 48, v_limit=values, canary=True, explore_frac=0.03, explore_seed=5, per_head=per_head)
+            got.append([run(gc, q, tol, sel) for q in qs])     # the second call takes the first one's list back
+    for a, b, q in zip(got[0], got[1], qs):
+        assert np.array_equal(a[0], b[0]) and a[1].tobytes() == b[1].tobytes() and (a[2] == b[2]).all()
+        for i in (0, 2, 3, 4, 8):                              # K*, flags, both log-masses, deviations
+            assert np.array_equal(a[3][i], b[3][i]), i
+        prom = a[3][2]
+        par = ad.SelectorParams(explore_frac=0.03, explore_seed=5)
+        for grp in range(hkv):
+            drawn = np.asarray(ad.explored_blocks(blocks, grp, par), dtype=bool)
+            assert (prom[0, grp, :blocks][drawn] & 1).all()
+
+
+@pytest.mark.parametrize("blocks", [4096, 4200, 9000])
+def test_a_full_list_leaves_the_last_blocks_in_int8(blocks):
+    """Exploration of every block: 4096 fit the list, the rest stays unpromoted and keeps its INT8 mass."""
+    n = blocks * 16
+    rng = np.random.Generator(np.random.Philox(blocks))
+    k, v = workloads.normal_f16(rng, (1, 1, n, 128)), workloads.normal_f16(rng, (1, 1, n, 128))
+    q = workloads.normal_f16(rng, (1, 2, 128))
+    print("full list", blocks, flush=True)
+    with GpuLayerCache(1, 2, 1, n + 16) as gc:
+        gc.append(k, v)
+        sel = gc.cqa.Selector(0.995, 2, 16, 16, explore_frac=1.0, explore_seed=1)
+        O, cert, flags, st = run(gc, q, gc.cqa.Tolerances(), sel)
+        keys = st[2][0, 0, :blocks] & 1
+        assert keys[:4096].all() and not keys[4096:].any()
+        s8, _, _, lm = gc.certified_decode(q, want_logmass=True)
+        kd, vd, qd = k[0, 0].astype(np.float64), v[0, 0].astype(np.float64), q[0].astype(np.float64)
+        for h in range(2):
+            # the mass left in INT8, from the first pass's log-masses (binary32 exponentials: 1e-5)
+            l8 = lm[0, h, :blocks].astype(np.float64)
+            tail = np.exp(l8[4096:] - np.logaddexp.reduce(l8)).sum()
+            assert abs(cert[0, h]["alpha_tail_hat"] - tail) <= 1e-5 * tail + 1e-12
+            if blocks == 4096:      # everything promoted: FP16 scores, values as the plain pass has them
+                s = kd @ qd[h] / np.sqrt(128.0)
+                m = s.max()
+                assert abs(cert[0, h]["lse"] - (m + np.log(np.exp(s - m).sum()))) <= 1e-4
+
+
+@pytest.mark.parametrize("splits", [1, 8, 9, 17, 64, 65, 130, 200])
+def test_merging_any_number_of_partial_sets(splits):
+    """A wave merges eight sets a trip, eight waves share a head's sets: up to 64 in one trip, more in several."""
+    n = 16 * 4 * 4 * 210 + 7
+    rng = np.random.default_rng(splits)
+    k = rng.standard_normal((1, 1, n, 128), dtype=np.float32).astype(np.float16)
+    v = rng.standard_normal((1, 1, n, 128), dtype=np.float32).astype(np.float16)
+    q = rng.standard_normal((1, 4, 128)).astype(np.float16)
+    print("sets", splits, flush=True)
+    oc = oracle.OracleLayerCache(1, 1)
+    oc.append(k, v)
+    ref = oc.certified_decode(q, oracle.Tolerances())
+    with GpuLayerCache(1, 4, 1, n + 16) as gc:
+        gc.append(k, v)
+        gc.cqa.cqa_set_splits(gc.h, splits)
+        O, cert, flags = gc.certified_decode(q)
+        for h, r in enumerate(ref):
+            assert_head_matches(r, O[0, h], cert[0, h], flags[0, h], (splits, h))
+        # the adaptive reduction merges 32 sets more
+        sel = gc.cqa.Selector(0.995, 2, 16, 16)
+        O2, cert2, _, st = run(gc, q, gc.cqa.Tolerances(), sel)
+        gc.cqa.cqa_set_splits(gc.h, 1)
+        O3, cert3, _, st3 = run(gc, q, gc.cqa.Tolerances(), sel)
+        if np.array_equal(st[2], st3[2]):
+            # split counts move the rounding of the value weights (2^-17 each, 1e-4 of a row's largest channel) and, since
+            # the listed blocks are subtracted and added again, that of sums as large as V_max (4e-6 of it)
+            assert np.abs(O2 - O3).max() <= 1e-4 * np.abs(O3).max() + 4e-6 * cert3["v_max"].max()
+            assert np.allclose(cert2["lse"], cert3["lse"], rtol=5e-6, atol=0)
