@@ -254,6 +254,8 @@ struct PromArgs {
   const float* eta;         // [Bt][Hkv][nb]
   const float* first;       // [Bt][Hq][4]
   float* scan;              // [Bt][Hq][8], written
+  int groups;               // Bt * Hkv
+  int sums_last;            // 1: the workgroups that sum up the blocks left in INT8 come behind all others
 };
 
 inline int64_t head_index(const Cache* c, int layer, int b, int kvh) {

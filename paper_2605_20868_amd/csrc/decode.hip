@@ -219,7 +219,24 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a, Prom
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int tok = l & 15, kg = l >> 4;              // roles in the score phase
   const int vn = l & 15, vgh = (l >> 4) & 1, vo = l >> 5;  // roles in the value phase
-  const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+  int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+  if (PROM) {   // one index: per KV group its workgroups one after the other, the summing ones among them or last of all
+    const int L = (int)(blockIdx.y * gridDim.x + blockIdx.x), passes = 2 * PROM_SPLITS * p.groups;
+    int g;
+    if (L >= (2 * PROM_SPLITS + G) * p.groups) return;
+    if (!p.sums_last) {
+      g = L / (2 * PROM_SPLITS + G);
+      split = L % (2 * PROM_SPLITS + G);
+    } else if (L < passes) {
+      g = L / (2 * PROM_SPLITS);
+      split = L % (2 * PROM_SPLITS);
+    } else {
+      g = (L - passes) / G;
+      split = 2 * PROM_SPLITS + (L - passes) % G;
+    }
+    b = g / a.n_kv;
+    kvh = g - b * a.n_kv;
+  }
   const int64_t head_rec = ((int64_t)b * a.n_kv + kvh) * a.nq_cap;
   // blocks are dealt evenly over the splits (every split gets at least one: nsplit <= nb)
   const int64_t grp = (int64_t)b * a.n_kv + kvh;
