@@ -122,16 +122,18 @@ __device__ __forceinline__ void hist_add(uint32_t* hist, uint32_t bin, bool pred
 }
 
 // Histogram bin of a value in the selector's first pass: not decreasing with the value (the order the
-// selection keeps), 1024 bins where the KL-th best can lie -- log-masses by their distance below the total
-// log-mass, 1/32 apart up to 16 (diffuse heads), 1/8 up to 64, 1 beyond (heads with a few dominant blocks);
+// selection keeps), 1024 bins where the KL-th best can lie -- log-masses by their distance below the largest
+// one, 1/32 apart up to 16 (diffuse heads), 1/8 up to 64, 1 beyond (heads with a few dominant blocks; a distance below the
+// total log-mass would put all blocks into the last bin where the trailing tokens hold nearly all of it: 128K, such a head
+// 23 us against 10);
 // contributions by octave eighths of the binary representation.
 template <bool VALUES>
-__device__ __forceinline__ int select_bin(float x, float lse) {
+__device__ __forceinline__ int select_bin(float x, float top) {
   if (VALUES) {
     const int i = (int)(__float_as_uint(x) >> 20) - 18;
     return __float_as_uint(x) >> 31 ? 0 : min(max(i, 0), ST - 1);
   }
-  const float d = lse - x;
+  const float d = top - x;
   const float t = d < 16.0f ? d * 32.0f : (d < 64.0f ? fmaf(d - 16.0f, 8.0f, 512.0f) : 832.0f + d);
   return ST - 1 - (int)fminf(fmaxf(t, 0.0f), (float)(ST - 1));
 }
@@ -151,7 +153,8 @@ __device__ __forceinline__ int select_bin(float x, float lse) {
 // or nearly equal values) a radix selection narrows them down to KL.
 // 128K, 32 heads: 18.9 -> 14.6 us (four radix passes before).  4 x 32K, keys and values in one launch: 9.9 us
 // (16.1 + 15.1 in two launches and 4.8 for one that formed the contributions, before).  The reduction at its head, under
-// which the row's first loads come in, adds 2.5 us and saves a launch of 4.8 us.
+// which the row's first loads come in, adds 2.5 us and saves a launch of 4.8 us.  Places handed out per wave instead of per lane,
+// the first covering place by ballot, bins below the largest log-mass: 128K step 102.7 -> 99.6 us.
 constexpr int CAND_SLACK = 256;   // blocks beyond KL that the rank sort takes rather than another pass
 
 struct SelectSmem {
@@ -159,6 +162,7 @@ struct SelectSmem {
   unsigned long long sorted[MAX_K_LIMIT];   // the winners, best first: (key, ~index)
   double pm[MAX_K_LIMIT];                   // prefix sums of their masses
   uint32_t hist[ST];
+  uint16_t bins[LDS_KEYS];                  // histogram bins of the keys
   union {
     uint32_t keys[LDS_KEYS];
     ReduceSmem red;                         // (before there are keys)
@@ -192,32 +196,41 @@ __device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm)
 
   // ---- the first blocks of the row are requested, the head's partial sets are reduced meanwhile, and what the previous
   //      call left behind is taken back: the head's mask, and by one head the flag words of the group's list
+  //      (The waves that reduce ask for their sets first.)
   float v[SBATCH], e[SBATCH];
+  const auto load_row = [&](int base) {
 #pragma unroll
-  for (int j = 0; j < SBATCH; ++j) {
-    const int i = j * ST + tid;
-    v[j] = i < nb ? lm[i] : 0.0f;
-    e[j] = VALUES && i < nb ? eta[i] : 0.0f;
-  }
+    for (int j = 0; j < SBATCH; ++j) {
+      const int i = base + j * ST + tid;
+      v[j] = i < nb ? lm[i] : 0.0f;
+      e[j] = VALUES && i < nb ? eta[i] : 0.0f;
+    }
+  };
+  const int reducing = min((a.ra.nsplit + 7) / 8, RED_WAVES) + 2;   // waves
   uint32_t* const um = side.umask + row * a.mask_words;
-  for (int i = tid; i < ((nb + 31) >> 5); i += ST) um[i] = 0u;
-  const int g = a.n_q / a.n_kv;
-  if (!VALUES && hq % g == 0) {
-    const int64_t grp = (int64_t)b * a.n_kv + hq / g;
-    const int n_prev = min(a.ucount[grp], MAX_UNION);
-    for (int i = tid; i < n_prev; i += ST) {
-      const int blk = a.ulist[grp * MAX_UNION + i];
-      if (blk >= 0 && blk < a.slot_stride) a.slot[grp * a.slot_stride + blk] = 0;
+  if ((tid >> 6) >= reducing) {
+    load_row(0);
+    const int t = tid - 64 * reducing, step = ST - 64 * reducing;
+    for (int i = t; i < ((nb + 31) >> 5); i += step) um[i] = 0u;
+    const int g = a.n_q / a.n_kv;
+    if (!VALUES && hq % g == 0) {
+      const int64_t grp = (int64_t)b * a.n_kv + hq / g;
+      const int n_prev = min(a.ucount[grp], MAX_UNION);
+      for (int i = t; i < n_prev; i += step) {
+        const int blk = a.ulist[grp * MAX_UNION + i];
+        if (blk >= 0 && blk < a.slot_stride) a.slot[grp * a.slot_stride + blk] = 0;
+      }
     }
   }
   hist[tid] = 0u;
-  __shared__ float s_lse, s_delta, s_vmax;
+  __shared__ float s_lse, s_delta, s_vmax, s_top;
   {
     HeadRow hr;
-    if (reduce_row(a.ra, b, hq, min((a.ra.nsplit + 7) / 8, RED_WAVES) + 2, sm.red, hr) && tid == 0) {
+    if (reduce_row(a.ra, b, hq, reducing, sm.red, hr) && tid == 0) {
       s_lse = hr.ct.lse;
       s_delta = hr.ct.delta_h;
       s_vmax = hr.ct.v_max;
+      s_top = hr.top;
       if (!VALUES) *reinterpret_cast<float4*>(a.first + row * 4) = make_float4(hr.ct.lse, hr.ct.delta_h, hr.ct.v_max, 0.0f);
     }
   }
@@ -227,27 +240,21 @@ __device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm)
     s_bin = 0;
     s_found = nb;
   }
+  if ((tid >> 6) < reducing) load_row(0);
   if (!VALUES && tid == 0 && a.score_dev != nullptr) a.score_dev[row] = 0.0f;
   if (KL == 0) {
     if (tid == 0) side.kstar[row] = 0;
     return;
   }
   __syncthreads();
-  const float lse_f = s_lse;
+  const float lse_f = s_lse, top = s_top;
   const double lse = (double)lse_f;
 
   // ---- the one pass over memory: keys to LDS, the estimated mass of the sealed blocks (single-
   //      precision exponentials, accumulated in double; the rest of 1 is the exact trailing tokens), histogram
   double part = 0.0;
   for (int base = 0; base < nb; base += ST * SBATCH) {
-    if (base > 0) {
-#pragma unroll
-      for (int j = 0; j < SBATCH; ++j) {
-        const int i = base + j * ST + tid;
-        v[j] = i < nb ? lm[i] : 0.0f;
-        e[j] = VALUES && i < nb ? eta[i] : 0.0f;
-      }
-    }
+    if (base > 0) load_row(base);
 #pragma unroll
     for (int j = 0; j < SBATCH; ++j) {
       const int i = base + j * ST + tid;
@@ -259,8 +266,12 @@ __device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm)
         }
         part += (double)x;
         const float ranks = VALUES ? x : v[j];
-        if (cached) keys[i] = ord32(ranks);
-        atomicAdd(&hist[select_bin<VALUES>(ranks, lse_f)], 1u);
+        const int bin = select_bin<VALUES>(ranks, top);
+        if (cached) {
+          keys[i] = ord32(ranks);
+          sm.bins[i] = (uint16_t)bin;
+        }
+        atomicAdd(&hist[bin], 1u);
       }
     }
   }
@@ -281,16 +292,56 @@ __device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm)
   double total = 0.0;
   for (int w = 0; w < ST / 64; ++w) total += dsum[w];
 
+  // s_first = the smallest thread (= place) for which `hit` holds; a wave's lanes are settled by ballot (an LDS minimum over
+  // lanes of different values is walked lane by lane: 2.5 us where a head's first blocks cover everything)
+  const auto first_of = [&](bool hit) {
+    const unsigned long long m = __ballot(hit);
+    if (m != 0ull && (tid & 63) == __ffsll((long long)m) - 1) atomicMin(&s_first, tid);
+  };
+  // Candidates into LDS in any order.  (Short code on purpose: it runs once per launch and has to be fetched first.)
+  const auto collect = [&](int most, auto wanted) {
+#pragma unroll 1
+    for (int i = tid; (i & ~63) < nb; i += ST) {
+      const unsigned long long m = __ballot(i < nb && wanted(i));
+      if (m == 0ull) continue;
+      int at = 0;
+      if ((tid & 63) == 0) at = (int)atomicAdd(&s_cnt, (uint32_t)__popcll(m));
+      at = __builtin_amdgcn_readfirstlane(at);
+      const int pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)at));
+      if (((m >> (tid & 63)) & 1ull) && pos < most) {
+        const uint32_t k = cached ? keys[i] : ord32(ranked[i]);
+        cand[pos] = ((unsigned long long)k << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)i);
+      }
+    }
+  };
+  // ... those of bin `bin` and up: a place per wave and eight passes, not one per wave and pass
+  const auto collect_bins = [&](int bin) {
+    for (int base = 0; base < nb; base += ST * SBATCH) {
+      uint32_t mine = 0u;
+#pragma unroll
+      for (int j = 0; j < SBATCH; ++j) {
+        const int i = base + j * ST + tid;
+        mine |= i < nb && (int)sm.bins[min(i, LDS_KEYS - 1)] >= bin ? 1u << j : 0u;
+      }
+      if (__ballot(mine != 0u) == 0ull) continue;
+      const uint32_t n = (uint32_t)__popc(mine), upto = wave_scan_incl(n);
+      uint32_t at = 0u;
+      if ((tid & 63) == 63) at = atomicAdd(&s_cnt, upto);
+      at = (uint32_t)__builtin_amdgcn_readlane((int)at, 63) + upto - n;
+      for (; mine != 0u; mine &= mine - 1u, ++at) {
+        const int i = base + (__ffs((int)mine) - 1) * ST + tid;
+        if (at < (uint32_t)(MAX_K_LIMIT + CAND_SLACK))
+          cand[at] = ((unsigned long long)keys[i] << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)i);
+      }
+    }
+  };
   if (s_found <= KL + CAND_SLACK) {
     // ---- every block from that bin up is a candidate
     const int bin = s_bin;
-    CQA_KEY_PASS(ranked, nb, tid, cached, keys, {
-      if (in && select_bin<VALUES>(from_ord32(k), lse_f) >= bin) {
-        const uint32_t pos = atomicAdd(&s_cnt, 1u);
-        if (pos < (uint32_t)(MAX_K_LIMIT + CAND_SLACK))
-          cand[pos] = ((unsigned long long)k << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)i);
-      }
-    })
+    if (cached)
+      collect_bins(bin);
+    else
+      collect(MAX_K_LIMIT + CAND_SLACK, [&](int i) { return select_bin<VALUES>(ranked[i], top) >= bin; });
   } else {
     // ---- radix selection of the KL-th largest key, 8 bits at a time from the top
     if (tid == 0) {
@@ -353,13 +404,10 @@ __device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm)
     __syncthreads();
     const uint32_t Tidx = s_idx_prefix;            // largest index taken among the ties
     // ---- collect the KL winners as composite keys (log-mass order, then lower index first)
-    CQA_KEY_PASS(ranked, nb, tid, cached, keys, {
-      if (in && (k > T || (k == T && (uint32_t)i <= Tidx))) {
-        const uint32_t pos = atomicAdd(&s_cnt, 1u);
-        if (pos < (uint32_t)MAX_K_LIMIT)
-          cand[pos] = ((unsigned long long)k << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)i);
-      }
-    })
+    collect(MAX_K_LIMIT, [&](int i) {
+      const uint32_t k = cached ? keys[i] : ord32(ranked[i]);
+      return k > T || (k == T && (uint32_t)i <= Tidx);
+    });
   }
   __syncthreads();
   const int nc = (int)min(s_cnt, (uint32_t)(MAX_K_LIMIT + CAND_SLACK));
@@ -394,10 +442,7 @@ __device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm)
     //      the search stops there; then clamps and Rung-1 growth
     const double rho_trail = 1.0 - total;
     const int look = min(n, side.k_max);
-    for (int kk = tid; kk <= look; kk += ST) {
-      const double covered = rho_trail + (kk > 0 ? pm[kk - 1] : 0.0);
-      if (covered >= (double)a.tau_cov) atomicMin(&s_first, kk);
-    }
+    first_of(tid <= look && rho_trail + (tid > 0 ? pm[min(tid, n) - 1] : 0.0) >= (double)a.tau_cov);
     __syncthreads();
     if (tid == 0) {
       int k = s_first <= look ? s_first : nb;             // no prefix up to k_max covers tau_cov
@@ -422,13 +467,9 @@ __device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm)
     __shared__ int s_over;
     if (tid == 0) s_over = 0;
     __syncthreads();
-    if (tid < n && val0 > a.v_tol) atomicAdd(&s_over, 1);
-    if (a.v_greedy) {
-      for (int kk = tid; kk <= n; kk += ST) {
-        const double left = total - (kk > 0 ? pm[kk - 1] : 0.0);
-        if (left <= (double)a.eps_val) atomicMin(&s_first, kk);
-      }
-    }
+    const int over = __popcll(__ballot(tid < n && val0 > a.v_tol));
+    if ((tid & 63) == 0 && over > 0) atomicAdd(&s_over, over);
+    if (a.v_greedy) first_of(tid <= n && total - (tid > 0 ? pm[min(tid, n) - 1] : 0.0) <= (double)a.eps_val);
     __syncthreads();
     if (tid == 0) {
       int k = s_over;

@@ -175,18 +175,23 @@ __device__ __forceinline__ double row_total(double v) {
   v += dpp_mov_d<0x141>(v);
   return v + dpp_mov_d<0x140>(v);
 }
+// Inclusive scan over the lanes of a wave.
+template <typename T>
+__device__ __forceinline__ T wave_scan_incl(T v) {
+  v = scan_step<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8
+  v = scan_step<0x112, 0xf>(v);
+  v = scan_step<0x114, 0xf>(v);
+  v = scan_step<0x118, 0xf>(v);
+  v = scan_step<0x142, 0xa>(v);   // row_bcast 15 into rows 1 and 3
+  return scan_step<0x143, 0xc>(v);   // row_bcast 31 into rows 2 and 3
+}
 // Inclusive scan over the threads of a workgroup with two barriers: DPP shifts inside each row of
 // 16 lanes, the totals of the preceding rows by DPP broadcasts, then the preceding waves' totals.
 // `tot` = one word of LDS scratch per wave.
 template <typename T>
 __device__ __forceinline__ T block_scan_incl(T v, T* tot, int tid) {
   const int l = tid & 63, w = tid >> 6;
-  v = scan_step<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8
-  v = scan_step<0x112, 0xf>(v);
-  v = scan_step<0x114, 0xf>(v);
-  v = scan_step<0x118, 0xf>(v);
-  v = scan_step<0x142, 0xa>(v);   // row_bcast 15 into rows 1 and 3
-  v = scan_step<0x143, 0xc>(v);   // row_bcast 31 into rows 2 and 3
+  v = wave_scan_incl(v);
   __syncthreads();            // protects `tot` against the previous use
   if (l == 63) tot[w] = v;
   __syncthreads();
@@ -436,6 +441,7 @@ __device__ __forceinline__ void load_trail(const ReduceArgs& a, int b, int hq, c
 // The result of one (batch, query head): certificate and flag word in every lane, out = channels 2l, 2l + 1 of lane l.
 struct HeadRow {
   cqa_head_cert ct;
+  float top;      // largest block log-mass
   uint32_t fl;
   float2 out;
 };
@@ -572,6 +578,7 @@ __device__ __forceinline__ HeadRow finish_row(const ReduceArgs& a, const HeadSta
   row.ct.top_block = I1;
   row.ct.served_rung = 0;
   row.fl = fl;
+  row.top = T1;
   return row;
 }
 
