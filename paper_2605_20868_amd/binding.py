@@ -164,14 +164,17 @@ _lib, EXPORTED = _load()
 
 
 def _ptr(x):
-    if x is None:
-        return None
+    # A step takes seven of these, on the host's critical path where the device has little to do: a tensor's address goes to
+    # ctypes as the number it is (a c_void_p object per argument and two attribute look-ups: 2.7 us more a call).
+    if x is None or x.__class__ is int:
+        return x
+    f = getattr(x, "data_ptr", None)
+    if f is not None:
+        return f()
     if isinstance(x, int):
-        return C.c_void_p(x)
-    if hasattr(x, "data_ptr"):
-        return C.c_void_p(x.data_ptr())
+        return int(x)
     if hasattr(x, "ctypes"):
-        return C.c_void_p(x.ctypes.data)
+        return x.ctypes.data
     return x
 
 
