@@ -644,8 +644,9 @@ __global__ __launch_bounds__(64 * (RED_WAVES + 2)) void certified_reduce_kernel(
 //     all waves dispatched in one sweep: 200 of 5000: 66.9 against 72.1 us), four-wave ones where they
 //     divide better (130 of 8000: 74.3 against 81.3 us; 152 of 7000: 73.3 against 75.8 us), and where a quad
 //     per wave needs no more of them than there are compute units: a wave that has its SIMD to itself is
-//     through its only quad 0.9 us earlier (1 sequence of 1029: 13.9 -> 13.3 us, 8 of 1000: 14.4 -> 13.8), as
-//     long as the reduction still takes its sets in one trip of 32.  Up to eight quads are one workgroup,
+//     through its only quad 0.9 us earlier (1 sequence of 1029: 13.9 -> 13.3 us, 8 of 1000: 14.4 -> 13.8; 1 of 10000, 20
+//     and 40 sets: 10.75, 9.1; 4 of 16384, 32 and 64: 12.3, 11.8; 1 of 30000, 59 and 118: 12.9, 11.6), up to 128 sets,
+//     which the reduction takes in two trips (1 of 60000, 118 and 235: 14.1, 14.2).  Up to eight quads are one workgroup,
 //     which finishes the rows itself: 300 tokens 12.8 -> 11.6 us, 520 12.9 -> 12.1 (with 16 quads the second
 //     round costs more than the reduction's launch: 13.0 against 14.9).
 //   More sequences than compute units: four-wave workgroups, up to four splits where a last
@@ -675,7 +676,7 @@ void split_geometry(const Cache* c, int64_t n_blocks, int* nsplit, int* wpb) {
     consider(*wpb, c->forced_splits);
   } else if (heads <= c->n_cu) {
     if (quads <= 8) consider(8, 1);
-    if (heads * ((quads + 3) / 4) <= c->n_cu && quads <= 4 * 32) consider(4, (quads + 3) / 4);
+    if (heads * ((quads + 3) / 4) <= c->n_cu && quads <= 4 * 128) consider(4, (quads + 3) / 4);
     consider(8, c->n_cu / heads);
     consider(4, 2 * c->n_cu / heads);
   } else {

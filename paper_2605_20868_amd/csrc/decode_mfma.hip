@@ -120,11 +120,12 @@ constexpr int P_HEAD = 4 * BLK + 16;    // floats per head in the probability bu
 //     and scored against the stored key codes by mfma_i32_16x16x64_i8; the block's score bound
 //     grows by the explicit term (128 / sqrt d) sum_c |q~_c - s_q T_c|.
 // W: waves per workgroup, 8 (one workgroup per compute unit) or 4 (two); either way a SIMD holds two waves.
-// ONE: no wave takes a second quad (four-wave workgroups, short contexts).  Such a wave usually has its SIMD to itself, so
+// ONE: no wave takes a second quad (short contexts).  Such a wave often has its SIMD to itself, so
 //     nothing hides its latencies: no loads are requested that it would not use, the rescaling of empty accumulators
 //     goes, and the fences that keep the loop's registers down go too, so that the metadata of all channel
-//     slices is read from LDS ahead of the products (152 registers instead of 242).  8 KV heads: 3000 tokens a step 15.3
-//     -> 14.9 us, a prompt of 1000 tokens with 24 steps 418 -> 408.
+//     slices is read from LDS ahead of the products (152 registers instead of 242).  Four-wave workgroups, 8 KV heads: 3000
+//     tokens a step 15.3 -> 14.9 us, a prompt of 1000 tokens with 24 steps 418 -> 408.  Eight-wave ones: 8 KV heads of 8229
+//     tokens 13.4 -> 12.9 us a call, 16 x 8 of 250 9.6 -> 8.8, of 500 11.1 -> 10.3.
 template <int G, bool LM, bool NT, bool Q8, int W, bool ONE>
 __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(DecodeArgs a, ReduceArgs ra) {
   const int l = threadIdx.x & 63;
@@ -751,7 +752,7 @@ int32_t launch_stream_read(const uint8_t* t1, int64_t nq_cap, int nb, dim3 grid,
 int32_t launch_split_mfma(const DecodeArgs& a, const ReduceArgs& ra, int group, dim3 grid, hipEvent_t ev0,
                           hipEvent_t ev1, hipStream_t st) {
   const bool lm = a.blk_logmass != nullptr;
-  const bool one = 4 * a.nsplit >= (a.nb + 3) / 4;   // no wave takes a second quad
+  const bool one = a.wpb * a.nsplit >= (a.nb + 3) / 4;   // no wave takes a second quad
   if (a.wpb != 4 && a.wpb != 8) return CQA_ERR_INVALID_ARG;
 // The launch that takes events costs the host 2.3 us more than the plain one (a step of three launches 10.8, 8.4 us), which
 // short steps wait for, so it is used for timing only.
@@ -764,9 +765,11 @@ int32_t launch_split_mfma(const DecodeArgs& a, const ReduceArgs& ra, int group, 
 #define CQA_LAUNCH_W(GG, NTV, Q8V, WV, ONEV)                                                       \
   if (lm) { CQA_LAUNCH_LM(GG, true, NTV, Q8V, WV, ONEV) } else { CQA_LAUNCH_LM(GG, false, NTV, Q8V, WV, ONEV) }
 #define CQA_LAUNCH_Q(GG, NTV, Q8V)                                                                 \
-  if (a.wpb == 8) { CQA_LAUNCH_W(GG, NTV, Q8V, 8, false) }                                         \
-  else if (one) { CQA_LAUNCH_W(GG, NTV, Q8V, 4, true) }                                            \
-  else { CQA_LAUNCH_W(GG, NTV, Q8V, 4, false) }
+  if (a.wpb == 8) {                                                                                \
+    if (one) { CQA_LAUNCH_W(GG, NTV, Q8V, 8, true) } else { CQA_LAUNCH_W(GG, NTV, Q8V, 8, false) } \
+  } else {                                                                                         \
+    if (one) { CQA_LAUNCH_W(GG, NTV, Q8V, 4, true) } else { CQA_LAUNCH_W(GG, NTV, Q8V, 4, false) } \
+  }
 #define CQA_LAUNCH_NT(GG, NTV)                                                                     \
   if (a.int8_query) { CQA_LAUNCH_Q(GG, NTV, true) } else { CQA_LAUNCH_Q(GG, NTV, false) }
 #define CQA_LAUNCH(GG)                                                                             \

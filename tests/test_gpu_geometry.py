@@ -76,6 +76,10 @@ def test_steps_of_one_split_give_the_same_rows_on_both_routes(bt, hkv, g, n):
     (1, 8, 4, 64 * 32 - 5, 8),        # every wave exactly one quad, the last one short of a block
     (1, 8, 2, 64 * 32 + 16, 9),       # ... and a ninth workgroup with a single quad of one block
     (2, 4, 1, 64 * 9 + 40, 3),        # two waves of the last workgroup without one
+    (1, 1, 4, 64 * 130, 33),          # more sets than one trip of four merging waves holds
+    (1, 1, 2, 64 * 512, 128),         # the most sets of four-wave workgroups ...
+    (1, 1, 2, 64 * 512 + 3 * 16, 65), # ... one quad more: eight waves
+    (8, 8, 4, 64 * 5 + 20, 1),        # eight waves, finished by the pass itself
 ])
 def test_contexts_of_one_quad_per_wave(bt, hkv, g, n, splits, int8):
     """Short contexts, where no wave of the split pass takes a second quad, in both scoring modes."""
