@@ -324,6 +324,8 @@ struct DenseArgs {
   int64_t n_tokens;
   int nsplit, tiles_per_split;
   int by_wave;              // 1: the partial sets are those of the single waves, nsplit * DENSE_WAVES of them
+  int units;                // KV groups, or parts of them (below)
+  int per_group;            // parts, of G heads each, that a KV group's heads are served in
   float* ws;                // [groups][G][partial sets][DP_FLOATS], unused with one
   float* O;                 // [groups][G][128]
   const uint32_t* select;   // [groups][G] or null = all: rows that are written
@@ -332,15 +334,29 @@ struct DenseArgs {
   int rung;
 };
 
-template <int G>
+// SPREAD: the heads of a KV group are served in parts, each by workgroups of its own, where a workgroup per group and split would
+// leave half of the chip or more idle: the caller's workspace allows few splits then (it is sized for one group at a time), and
+// the vector ALU of the few compute units is the bound.  The parts of one (group, split) lie eight workgroups apart, so on one die
+// as a rule, and read the same keys and values from its cache, without the non-temporal hint.  A head's arithmetic
+// does not depend on the part it is in.  8 KV heads x 4: 200 tokens 7.8 -> 5.1 us, 1000 18.2 -> 7.9, 4000 21.7 -> 11.2; 16 x 4 of 4000
+// 35.6 -> 16.2, of 16000 (in halves) 40.3 -> 32.0; 32 x 2 of 4000 26.6 -> 17.6.
+template <int G, bool SPREAD>
 __global__ __launch_bounds__(64 * DENSE_WAVES, 2) void dense_split_kernel(DenseArgs a) {
   __shared__ __align__(16) DenseSmem<G, DENSE_WAVES> sm;
-  const int64_t grp = blockIdx.x / a.nsplit;
-  const int split = (int)(blockIdx.x - grp * a.nsplit);
+  int64_t grp = blockIdx.x / a.nsplit, kv = grp;   // grp: the unit
+  int split = (int)(blockIdx.x - grp * a.nsplit);
+  if (SPREAD) {
+    const int eight = (int)blockIdx.x >> 3, part = eight % a.per_group;
+    const int item = (eight / a.per_group) * 8 + ((int)blockIdx.x & 7);
+    kv = item / a.nsplit;
+    split = item - (int)kv * a.nsplit;
+    grp = kv * a.per_group + part;
+    if (grp >= a.units) return;
+  }
   const int64_t tiles = (a.n_tokens + DENSE_TILE - 1) / DENSE_TILE;
   const int64_t t0 = (int64_t)split * a.tiles_per_split;
   const int64_t t1 = min(t0 + (int64_t)a.tiles_per_split, tiles);
-  dense_split_work<G, DENSE_WAVES, DENSE_TILE, true>(a.q + grp * G * D, a.k + grp * a.n_tokens * D, a.v + grp * a.n_tokens * D,
+  dense_split_work<G, DENSE_WAVES, DENSE_TILE, !SPREAD>(a.q + grp * G * D, a.k + kv * a.n_tokens * D, a.v + kv * a.n_tokens * D,
                                    a.n_tokens, t0, t1, sm);
   if (a.nsplit > 1) {
     dense_store_partials<G, DENSE_WAVES>(sm, a.ws + grp * G * a.nsplit * DP_FLOATS, a.nsplit, split);
@@ -658,22 +674,33 @@ int32_t launch_dense(const __half* q, const __half* k, const __half* v, int grou
   } else {
     // a grid dimension holds fewer than 2^32 threads: 8388607 workgroups a launch (as many KV groups: with so many of
     // them a group is one workgroup, which finishes its rows)
+    int part = group;            // heads per workgroup: halved while twice the workgroups are still one to a compute unit
+    while (part > 1 && groups * a.nsplit * (group / part) * 2 <= DENSE_WG_TARGET) part /= 2;
+    if (part < group) {
+      a.per_group = group / part;
+      a.units = (int)groups * a.per_group;
+      const dim3 grid((unsigned)((groups * a.nsplit + 7) / 8 * 8 * a.per_group));
+      if (part == 1)
+        hipLaunchKernelGGL((dense_split_kernel<1, true>), grid, dim3(64 * DENSE_WAVES), 0, st, a);
+      else
+        hipLaunchKernelGGL((dense_split_kernel<2, true>), grid, dim3(64 * DENSE_WAVES), 0, st, a);
+    }
     const int64_t most = 0xFFFFFFFFll / (64 * DENSE_WAVES * a.nsplit);
-    for (int64_t g0 = 0; g0 < groups; g0 += most) {
-      DenseArgs part = a;
-      part.q += g0 * group * D;
-      part.k += g0 * n_tokens * D;
-      part.v += g0 * n_tokens * D;
-      part.O += g0 * group * D;
-      if (part.select != nullptr) part.select += g0 * group;
-      if (part.cert != nullptr) part.cert += g0 * group;
-      if (part.flags != nullptr) part.flags += g0 * group;
-      if (a.nsplit > 1) part.ws += g0 * group * a.nsplit * DP_FLOATS;
+    for (int64_t g0 = part < group ? groups : 0; g0 < groups; g0 += most) {
+      DenseArgs chunk = a;
+      chunk.q += g0 * group * D;
+      chunk.k += g0 * n_tokens * D;
+      chunk.v += g0 * n_tokens * D;
+      chunk.O += g0 * group * D;
+      if (chunk.select != nullptr) chunk.select += g0 * group;
+      if (chunk.cert != nullptr) chunk.cert += g0 * group;
+      if (chunk.flags != nullptr) chunk.flags += g0 * group;
+      if (a.nsplit > 1) chunk.ws += g0 * group * a.nsplit * DP_FLOATS;
       const dim3 grid((unsigned)(std::min(most, groups - g0) * a.nsplit));
       switch (group) {
-        case 1: hipLaunchKernelGGL(dense_split_kernel<1>, grid, dim3(64 * DENSE_WAVES), 0, st, part); break;
-        case 2: hipLaunchKernelGGL(dense_split_kernel<2>, grid, dim3(64 * DENSE_WAVES), 0, st, part); break;
-        case 4: hipLaunchKernelGGL(dense_split_kernel<4>, grid, dim3(64 * DENSE_WAVES), 0, st, part); break;
+        case 1: hipLaunchKernelGGL((dense_split_kernel<1, false>), grid, dim3(64 * DENSE_WAVES), 0, st, chunk); break;
+        case 2: hipLaunchKernelGGL((dense_split_kernel<2, false>), grid, dim3(64 * DENSE_WAVES), 0, st, chunk); break;
+        case 4: hipLaunchKernelGGL((dense_split_kernel<4, false>), grid, dim3(64 * DENSE_WAVES), 0, st, chunk); break;
         default: return CQA_ERR_UNSUPPORTED;
       }
     }

@@ -90,7 +90,7 @@ def test_a_paged_group_of_a_large_layer_takes_no_longer_than_one_of_a_small_laye
 
     from helpers import load_binding
     print("fallback time", flush=True)
-    cqa = load_binding()
+    from paper_2605_20868_amd import binding as cqa
     n, most, took = 32768, 17, []
     t2 = [torch.empty(most * 8 * n * 128, dtype=torch.float16, pin_memory=True) for _ in range(2)]
     for bt in (1, most):
@@ -122,7 +122,7 @@ def test_more_kv_groups_than_one_launch_holds():
 
     from helpers import load_binding
     print("dense launches", flush=True)
-    cqa = load_binding()
+    from paper_2605_20868_amd import binding as cqa
     groups = 8388608 + 5
     v = torch.randn((groups, 128), device="cuda", dtype=torch.float16)
     O = torch.full((groups, 128), float("nan"), dtype=torch.float32, device="cuda")
@@ -163,3 +163,35 @@ def test_an_infinite_value_stays_infinite(bt, hkv, g, n):
             for b, h in ((0, 0), (bt - 1, hkv * g - 1)):
                 ref = oracle.softmax_attention(q[b, h], k[b, h // g], v[b, h // g][:, finite])
                 assert np.linalg.norm(o[b, h][finite] - ref) <= 1e-3 * np.linalg.norm(ref) + 1e-6
+
+
+@pytest.mark.parametrize("bt,hkv,g,n", [
+    (1, 1, 4, 1),          # one item in a row of eight workgroups
+    (3, 3, 4, 33),         # nine items, the last row of eight nearly empty; one split
+    (1, 5, 2, 700),        # heads one by one, several splits
+    (8, 8, 4, 130),        # 64 workgroups: all four heads apart
+    (13, 5, 4, 130),       # 65: in halves
+    (16, 8, 4, 40),        # 128: the last size in halves
+    (43, 3, 4, 40),        # 129: together
+    (2, 8, 4, 4000),       # the workspace allows two splits
+])
+def test_heads_of_a_group_in_parts(bt, hkv, g, n):
+    """Few workgroups: the heads of a KV group are served by workgroups of their own."""
+    import torch
+    from paper_2605_20868_amd import binding as cqa
+    print("parts", bt, hkv, g, n, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n + bt)
+    k, v = (torch.randn((bt, hkv, n, 128), generator=gen, device="cuda").half() for _ in range(2))
+    q = torch.randn((bt, hkv * g, 128), generator=gen, device="cuda").half()
+    guard = 64
+    O = torch.full((bt * hkv * g * 128 + guard,), float("nan"), device="cuda")
+    nb = cqa.cqa_dense_workspace_bytes(bt, hkv * g, n)
+    ws = torch.full((nb + guard,), 0x5A, dtype=torch.uint8, device="cuda")
+    cqa.cqa_dense_attention(q, k, v, bt, hkv * g, hkv, n, O, ws)
+    torch.cuda.synchronize()
+    assert torch.isnan(O[-guard:]).all() and (ws[nb:] == 0x5A).all()
+    s = torch.einsum("bhgd,bhnd->bhgn", q.view(bt, hkv, g, 128).cpu().double(), k.cpu().double()) / 128 ** 0.5
+    ref = torch.einsum("bhgn,bhnd->bhgd", torch.softmax(s, -1), v.cpu().double()).reshape(bt, hkv * g, 128)
+    got = O[:-guard].view(bt, hkv * g, 128).cpu().double()
+    # binary32 throughout: 128 products per score, n weights, each rounded once (1e-7 relative)
+    assert (got - ref).norm() <= 3e-6 * ref.norm() and (got - ref).abs().max() <= 1e-5 * ref.abs().max()
