@@ -112,9 +112,7 @@ static void release(cqa_cache* h) {
   (void)hipFree(c->ad.contrib);
   (void)hipFree(c->ad.vsel);
   (void)hipFree(c->ad.vcount);
-  (void)hipFree(c->ad.score_dev);
   (void)hipFree(c->ad.first);
-  (void)hipFree(c->ad.scan);
   (void)hipFree(c->ad.sc_k);
   (void)hipFree(c->ad.sc_v);
   (void)hipFree(c->ad.sc_have);
@@ -292,9 +290,9 @@ static int32_t create_cache(const cqa_cache_desc* desc, __half* caller_k, __half
     CQA_ALLOC_DEV(c->ad.contrib, s.ad_lm);
     CQA_ALLOC_DEV(c->ad.vsel, s.ad_sel);
     CQA_ALLOC_DEV(c->ad.vcount, s.ad_head);
-    CQA_ALLOC_DEV(c->ad.score_dev, s.ad_head);
-    CQA_ALLOC_DEV(c->ad.first, 4 * s.ad_head);
-    CQA_ALLOC_DEV(c->ad.scan, 8 * s.ad_head);
+    CQA_ALLOC_DEV(c->ad.first, 13 * s.ad_head);   // with `scan` and `score_dev` behind it
+    c->ad.scan = c->ad.first + s.ad_head;         // (ad_head: bytes of one word per row)
+    c->ad.score_dev = c->ad.scan + 2 * s.ad_head;
     CQA_TRY(hipMemset(c->ad.score_dev, 0, (size_t)s.ad_head));
     c->ad.mask_words = s.ad_mask_words;
     CQA_TRY(hipMemset(c->ad.umask, 0, (size_t)s.ad_mask));       // the selector ORs into it
