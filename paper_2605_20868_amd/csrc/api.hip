@@ -112,7 +112,7 @@ static void release(cqa_cache* h) {
   (void)hipFree(c->ad.contrib);
   (void)hipFree(c->ad.vsel);
   (void)hipFree(c->ad.vcount);
-  (void)hipFree(c->ad.first);
+  (void)hipFree(c->ad.score_dev);
   (void)hipFree(c->ad.sc_k);
   (void)hipFree(c->ad.sc_v);
   (void)hipFree(c->ad.sc_have);
@@ -213,7 +213,7 @@ int32_t cqa_workspace_bytes(const cqa_cache_desc* desc, int64_t* device_bytes,
     // every device allocation of create_cache, in its order ...
     int64_t n = s.t1 + s.heads * 4 + 2 * s.trail + s.partials + 2 * s.dense_ws + s.select;
     if (t2) {
-      n += 3 * s.ad_lm + 2 * s.ad_sel + 16 * s.ad_head + 2 * s.ad_mask + s.ad_slot + s.ad_group + s.ad_ulist +
+      n += 3 * s.ad_lm + 2 * s.ad_sel + 19 * s.ad_head + 2 * s.ad_mask + s.ad_slot + s.ad_group + s.ad_ulist +
            s.ad_eta + 8;
       n += 4 * s.stage + s.ladder_ws + groups * 4 + 12;
       // ... and what the first cqa_set_scratch_slots(n > 0) adds: key and value halves, map, three words per slot
@@ -290,9 +290,10 @@ static int32_t create_cache(const cqa_cache_desc* desc, __half* caller_k, __half
     CQA_ALLOC_DEV(c->ad.contrib, s.ad_lm);
     CQA_ALLOC_DEV(c->ad.vsel, s.ad_sel);
     CQA_ALLOC_DEV(c->ad.vcount, s.ad_head);
-    CQA_ALLOC_DEV(c->ad.first, 13 * s.ad_head);   // with `scan` and `score_dev` behind it
-    c->ad.scan = c->ad.first + s.ad_head;         // (ad_head: bytes of one word per row)
-    c->ad.score_dev = c->ad.scan + 2 * s.ad_head;
+    // with `first` and `scan` behind it, on 16-byte boundaries (ad_head: bytes of one word per row)
+    CQA_ALLOC_DEV(c->ad.score_dev, 16 * s.ad_head);
+    c->ad.first = c->ad.score_dev + s.ad_head;
+    c->ad.scan = c->ad.first + s.ad_head;
     CQA_TRY(hipMemset(c->ad.score_dev, 0, (size_t)s.ad_head));
     c->ad.mask_words = s.ad_mask_words;
     CQA_TRY(hipMemset(c->ad.umask, 0, (size_t)s.ad_mask));       // the selector ORs into it
