@@ -632,6 +632,10 @@ __global__ __launch_bounds__(64 * (RED_WAVES + 2)) void certified_reduce_kernel(
   if (reduce_row(a, blockIdx.y, blockIdx.x, (int)(blockDim.x >> 6), sm, row)) store_row(a, blockIdx.y, blockIdx.x, row);
 }
 
+__global__ __launch_bounds__(64) void certified_reduce_wave_kernel(ReduceArgs a) {
+  store_row(a, blockIdx.y, blockIdx.x, reduce_row_wave(a, blockIdx.y, blockIdx.x));
+}
+
 // Workgroups ("splits") per (batch, kv-head) and waves per workgroup of the matrix-core split pass.
 // A compute unit holds eight of its waves: one workgroup of eight, or two of four.  The quads of a
 // head are dealt evenly over its waves, so a workgroup takes ceil(quads / (waves * splits)) rounds of
@@ -860,7 +864,14 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
   }
   // a wave per eight sets, while there are waves
   const int nw = std::min(std::max((nsplit + 7) / 8, 1), RED_WAVES);
-  hipLaunchKernelGGL(certified_reduce_kernel, dim3(hq, bt), dim3(64 * (nw + 2)), 0, st, ra);
+  // With a mirror and more than four rows per compute unit, one wave per row: a row's waves side by side bring the stores
+  // to the mirror closer together, where they wait for one another.  A host-resolved step of 4 heads per group, three waves a row and
+  // one: 640 rows 25.2, 26.4 us; 1024 31.8, 32.1; 1152 35.4, 32.4; 2048 44.0, 40.3; 4096 79.3, 67.3; two sets, 2240 rows
+  // 97.7, 91.7.  (Two heads per group: 1152 rows 70.4, 69.8; 1280 56.8, 57.0.)
+  if (flags_mirror != nullptr && (int64_t)bt * hq > 4 * (int64_t)c->n_cu && nsplit <= 8)
+    hipLaunchKernelGGL(certified_reduce_wave_kernel, dim3(hq, bt), dim3(64), 0, st, ra);
+  else
+    hipLaunchKernelGGL(certified_reduce_kernel, dim3(hq, bt), dim3(64 * (nw + 2)), 0, st, ra);
   CQA_HIP(hipGetLastError());
   return CQA_OK;
 }

@@ -532,16 +532,7 @@ __global__ __launch_bounds__(64 * FINISH_ROWS) void finish_ladder_kernel(ReduceA
   __shared__ uint32_t s_fl[FINISH_ROWS];
   HeadRow row;
   row.fl = 0u;
-  if (r < a.n_rows) {
-    TrailRegs tr;
-    TrailState ts{};
-    if (ra.r > 0) load_trail(ra, r / ra.n_q, r % ra.n_q, nullptr, nullptr, tr);
-    float2 o2;
-    const OctState st = merge_sets(ra.partials + (int64_t)r * ra.nsplit * PART_FLOATS, 0, 8, ra.nsplit, 0, ra.nsplit, o2);
-    if (ra.r > 0) ts = trail_state(ra, tr);
-    const HeadState hs = head_state(st, o2);
-    row = finish_row(ra, hs, ts, key_terms(ra, hs.DM), nullptr);
-  }
+  if (r < a.n_rows) row = reduce_row_wave(ra, r / ra.n_q, r % ra.n_q);
   if (l == 0) s_fl[r] = row.fl;
   __syncthreads();
   const uint32_t f = l < FINISH_ROWS ? s_fl[l] : 0u;

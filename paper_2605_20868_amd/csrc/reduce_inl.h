@@ -654,6 +654,19 @@ __device__ __forceinline__ bool reduce_row(const ReduceArgs& a, int b, int hq, i
   return true;
 }
 
+// ... by one wave, its parts one after the other.
+__device__ __forceinline__ HeadRow reduce_row_wave(const ReduceArgs& a, int b, int hq) {
+  TrailRegs tr;
+  TrailState ts{};
+  if (a.r > 0) load_trail(a, b, hq, nullptr, nullptr, tr);
+  float2 o2;
+  const OctState st = merge_sets(a.partials + ((int64_t)b * a.n_q + hq) * (a.pstride > 0 ? a.pstride : a.nsplit) * PART_FLOATS,
+                                 0, 8, a.nsplit, 0, a.nsplit, o2);
+  if (a.r > 0) ts = trail_state(a, tr);
+  const HeadState hs = head_state(st, o2);
+  return finish_row(a, hs, ts, key_terms(a, hs.DM), nullptr);
+}
+
 // The exploration draw: 32-bit multiply-xorshift mixer over (block, KV group, seed).
 __device__ __forceinline__ uint32_t explore_mix(uint32_t blk, uint32_t grp, uint32_t seed) {
   uint32_t x = blk * 0x9E3779B1u ^ grp * 0x85EBCA77u ^ seed * 0xC2B2AE3Du;

@@ -71,6 +71,31 @@ def test_steps_of_one_split_give_the_same_rows_on_both_routes(bt, hkv, g, n):
             assert np.array_equal(O, O2) and cert.tobytes() == cert2.tobytes() and (flags == flags2).all()
 
 
+@pytest.mark.parametrize("bt,hkv,g,n", [(70, 8, 2, 64 * 16 + 2), (70, 8, 4, 64 * 16), (72, 8, 2, 64 * 24 + 5)])
+def test_many_rows_of_several_splits_give_the_same_rows_on_both_routes(bt, hkv, g, n):
+    """More than 1024 rows are reduced by one wave each where their flags are mirrored to the host and by several waves
+    otherwise: bit for bit the same, with and without trailing tokens."""
+    print("several splits", bt, hkv, g, n, flush=True)
+    rng = np.random.default_rng(n + bt)
+    k = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    v = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    q = rng.standard_normal((bt, hkv * g, 128)).astype(np.float16)
+    oc = oracle.OracleLayerCache(1, hkv)
+    oc.append(k[-1:], v[-1:])
+    ref = oc.certified_decode(q[-1:], oracle.Tolerances())
+    with GpuLayerCache(bt, hkv * g, hkv, n + 16, tier2=False) as gc:
+        gc.append(k, v)
+        assert 2 <= gc.cqa.cqa_decode_splits(gc.h, 0) <= 8
+        O, cert, flags = [x.copy() for x in gc.certified_decode(q)]
+        for h, r in enumerate(ref):
+            assert_head_matches(r, O[-1, h], cert[-1, h], flags[-1, h], (bt, hkv, g, h))
+        for _ in range(2):
+            gc.O.fill_(float("nan"))
+            rung, O2, cert2, flags2 = gc.decode_step(q)
+            assert rung == 0
+            assert np.array_equal(O, O2) and cert.tobytes() == cert2.tobytes() and (flags == flags2).all()
+
+
 @pytest.mark.parametrize("int8", [False, True])
 @pytest.mark.parametrize("bt,hkv,g,n,splits", [
     (1, 8, 4, 64 * 32 - 5, 8),        # every wave exactly one quad, the last one short of a block
