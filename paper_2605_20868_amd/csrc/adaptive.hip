@@ -749,7 +749,8 @@ struct AdaptiveReduceArgs {
   const int32_t* slot;   // [Bt][Hkv][slot_stride]
   int64_t slot_stride;
   const float* first;    // [Bt][Hq][4]
-  const float* scan;     // [Bt][Hq][8]
+  const ScanPart* scan;  // [Bt][Hq][parts]
+  int parts;
   float* alpha_out;      // [Bt][Hq]
   const float* score_dev;  // [Bt][Hq] canary deviations, or null
   int pos_set0, pos_set1;  // the promoted-block pass's positive partial sets
@@ -758,7 +759,7 @@ struct AdaptiveReduceArgs {
 };
 
 // One workgroup per (batch, query head): eight waves merge the partial sets of the pass over all blocks and of the
-// promoted-block pass, one attends the trailing tokens, one prepares the key term, all of them look through the list of promoted blocks for
+// promoted-block pass, one attends the trailing tokens, one prepares the key term and adds up the sums' parts, all of them look through the list of promoted blocks for
 // the best under either ranking, and the first joins the results.  (What the other blocks add up to has been summed
 // beside the promoted-block pass.)
 // Bound by latency: 128K, 32 heads 9.3 -> 6.4 us, 4K 8.2 -> 6.7 (with the scan over all log-masses in this launch, before).
@@ -796,6 +797,7 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
 
   __shared__ __align__(16) ReduceSmem sm;
   __shared__ RankBest rb;
+  __shared__ ScanPart sums;
   if (w < RED_WAVES) {
     float2 o2;
     const OctState st = merge_sets(ra.partials + row * ra.pstride * PART_FLOATS, 8 * w, 8 * RED_WAVES, ra.nsplit, a.pos_set0,
@@ -820,6 +822,23 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
       sm.key[1] = kt.grow;
       sm.key[2] = kt.widen;
     }
+    ScanPart t{0.0, 0.0, 0.0, -INFINITY, 0.0f};
+    for (int i = l; i < a.parts; i += 64) {
+      const ScanPart x = a.scan[row * a.parts + i];
+      t.alpha += x.alpha;
+      t.l8u += x.l8u;
+      t.ev8u += x.ev8u;
+      t.top = fmaxf(t.top, x.top);
+      t.maxc8 = fmaxf(t.maxc8, x.maxc8);
+    }
+    if (a.parts > 1) {
+      t.alpha = wave_sum_d(t.alpha);
+      t.l8u = wave_sum_d(t.l8u);
+      t.ev8u = wave_sum_d(t.ev8u);
+      t.top = wave_max(t.top);
+      t.maxc8 = wave_max(t.maxc8);
+    }
+    if (l == 0) sums = t;
   }
   float best_x = -INFINITY, best_8 = -INFINITY;
   int ix = -1, i8 = -1;
@@ -907,11 +926,10 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
     }
   }
   if (w != 0) return;
-  const float* sc = a.scan + row * 8;
-  const float tmax = sc[S_TOP];
+  const float tmax = sums.top;
   const bool has_tail = tmax > -INFINITY;
   AdaptiveIn ad;
-  ad.alpha = sc[S_ALPHA];
+  ad.alpha = (float)sums.alpha;
   ad.delta = delta;
   ad.top_block = top_ix;
   ad.top_fp16 = top_ix >= 0 ? top_x : -INFINITY;
@@ -920,9 +938,9 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
   const bool boundary = top_ix >= 0 && has_tail && tmax + delta + ra.tol.eps_guard > kth_x;
   ad.rank_fail = (disagree || boundary) ? 1 : 0;
   ad.precond = (a.score_dev != nullptr && a.score_dev[row] > delta + ra.tol.eps_guard) ? 1 : 0;
-  ad.L8u = sc[S_L8U];
-  ad.EV8u = sc[S_EV8U];
-  ad.maxc8 = sc[S_MAXC8];
+  ad.L8u = (float)sums.l8u;
+  ad.EV8u = (float)sums.ev8u;
+  ad.maxc8 = sums.maxc8;
   ad.lse8 = lse8;
   if (l == 0) a.alpha_out[row] = ad.alpha;
   float2 o2;
@@ -1087,13 +1105,14 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   pa.first = w.first;
   pa.scan = w.scan;
   pa.groups = bt * hkv;
+  pa.parts = (int)scan_parts(nb);
   // The summing workgroups keep the link idle while they hold a place that a workgroup with originals to fetch could
   // have, so where not all are resident at once (two to a compute unit) they come last: 128 groups of 4000 tokens 2291 -> 2263 us
   // a step; 8 groups, all resident: 128K 102.3 us with them in between, 104.8 last, 107.6 first.
-  const int wgs = (2 * PROM_SPLITS + g) * pa.groups;
+  const int64_t wgs = (int64_t)(2 * PROM_SPLITS + g * pa.parts) * pa.groups;
   pa.sums_last = wgs > 2 * c->n_cu ? 1 : 0;
-  const unsigned gx = (unsigned)std::min(wgs, 1 << 22);   // (a grid dimension holds fewer than 2^32 threads)
-  rc = launch_promoted_pass(a, pa, g, dim3(gx, (unsigned)((wgs + (int64_t)gx - 1) / gx)), st);
+  const unsigned gx = (unsigned)std::min<int64_t>(wgs, 1 << 22);   // (a grid dimension holds fewer than 2^32 threads)
+  rc = launch_promoted_pass(a, pa, g, dim3(gx, (unsigned)((wgs + gx - 1) / gx)), st);
   if (rc != CQA_OK) return rc;
 
   // ---- 5. merge, certificate with the achieved tail, ranking check
@@ -1107,6 +1126,7 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   ar.score_dev = sel.canary ? w.score_dev : nullptr;
   ar.first = w.first;
   ar.scan = w.scan;
+  ar.parts = pa.parts;
   ar.pos_set0 = nsplit;
   ar.pos_set1 = nsplit + PROM_SPLITS;
   ar.ulist = w.ulist;

@@ -35,7 +35,7 @@ static int32_t check_desc(const cqa_cache_desc* d) {
 
 struct Sizes {
   int64_t nb_cap, nq_cap, heads, t1, trail, t2, partials, dense_ws, stage, select, ladder_ws;
-  int64_t ad_lm, ad_sel, ad_head, ad_mask_words, ad_mask, ad_slot, ad_group, ad_ulist, ad_eta;
+  int64_t ad_lm, ad_sel, ad_head, ad_sums, ad_mask_words, ad_mask, ad_slot, ad_group, ad_ulist, ad_eta;
   int64_t sc_k, sc_map, sc_tag;
   int sc_cap;
   int max_splits;
@@ -67,6 +67,7 @@ static Sizes compute_sizes(const cqa_cache_desc* d, int n_cu) {
   s.ad_lm = ad ? rows * s.nb_cap * 4 : 0;
   s.ad_sel = ad ? rows * MAX_K_LIMIT * 4 : 0;
   s.ad_head = ad ? rows * 4 : 0;
+  s.ad_sums = ad ? rows * (4 * 4 + 4 * 4 + scan_parts(s.nb_cap) * (int64_t)sizeof(ScanPart)) : 0;
   s.ad_mask_words = (s.nb_cap + 31) / 32;
   s.ad_mask = ad ? rows * s.ad_mask_words * 4 : 0;
   s.ad_slot = ad ? groups * s.nq_cap * 4 * 4 : 0;
@@ -213,7 +214,7 @@ int32_t cqa_workspace_bytes(const cqa_cache_desc* desc, int64_t* device_bytes,
     // every device allocation of create_cache, in its order ...
     int64_t n = s.t1 + s.heads * 4 + 2 * s.trail + s.partials + 2 * s.dense_ws + s.select;
     if (t2) {
-      n += 3 * s.ad_lm + 2 * s.ad_sel + 19 * s.ad_head + 2 * s.ad_mask + s.ad_slot + s.ad_group + s.ad_ulist +
+      n += 3 * s.ad_lm + 2 * s.ad_sel + 3 * s.ad_head + s.ad_sums + 2 * s.ad_mask + s.ad_slot + s.ad_group + s.ad_ulist +
            s.ad_eta + 8;
       n += 4 * s.stage + s.ladder_ws + groups * 4 + 12;
       // ... and what the first cqa_set_scratch_slots(n > 0) adds: key and value halves, map, three words per slot
@@ -291,9 +292,9 @@ static int32_t create_cache(const cqa_cache_desc* desc, __half* caller_k, __half
     CQA_ALLOC_DEV(c->ad.vsel, s.ad_sel);
     CQA_ALLOC_DEV(c->ad.vcount, s.ad_head);
     // with `first` and `scan` behind it, on 16-byte boundaries (ad_head: bytes of one word per row)
-    CQA_ALLOC_DEV(c->ad.score_dev, 16 * s.ad_head);
+    CQA_ALLOC_DEV(c->ad.score_dev, s.ad_sums);
     c->ad.first = c->ad.score_dev + s.ad_head;
-    c->ad.scan = c->ad.first + s.ad_head;
+    c->ad.scan = reinterpret_cast<ScanPart*>(c->ad.first + s.ad_head);
     CQA_TRY(hipMemset(c->ad.score_dev, 0, (size_t)s.ad_head));
     c->ad.mask_words = s.ad_mask_words;
     CQA_TRY(hipMemset(c->ad.umask, 0, (size_t)s.ad_mask));       // the selector ORs into it

@@ -100,6 +100,16 @@ constexpr int PROM_SPLITS = 16;             // workgroups (= partial sets) per K
                                             // 640, 635, 651; 16 x 4000 2105, 2103, 2155 (more sets to merge than the waves gain)
 
 // Workspace of the adaptive path, shared by all layers (one decode step at a time).
+// What a run of up to SCAN_PART blocks left in INT8 adds up to for one head: over the blocks that are not key-promoted for
+// the head, the estimated mass and the largest log-mass; over those that are not listed at all, relative to lse, the mass,
+// the value term and the largest share of it.
+struct ScanPart {
+  double alpha, l8u, ev8u;
+  float top, maxc8;
+};
+constexpr int SCAN_PART = 8192;
+inline int64_t scan_parts(int64_t n_blocks) { return (n_blocks + SCAN_PART - 1) / SCAN_PART; }
+
 struct AdaptiveWs {
   float* lm8;        // [Bt][Hq][nb_cap]      INT8 block log-masses of the pass over all blocks
   float* lmx;        // [Bt][Hq][nb_cap]      log-masses of the listed blocks as the promoted-block pass computed them (FP16 keys where promoted)
@@ -117,7 +127,7 @@ struct AdaptiveWs {
   int32_t* ucount;   // [Bt][Hkv]             promoted blocks of the group
   int32_t* ulist;    // [Bt][Hkv][MAX_UNION]  their indices, ascending
   float* first;      // [Bt][Hq][4]           lse, Delta_h, V_max of the pass over all blocks
-  float* scan;       // [Bt][Hq][8]           what the blocks its group left in INT8 add up to (S_* below)
+  ScanPart* scan;    // [Bt][Hq][parts]       what the blocks its group left in INT8 add up to
   int64_t mask_words;
   // FP16 scratch (the paper's VRAM scratch cache of promoted originals, LRU): per (layer, batch,
   // kv-head) `sc_cap` slots of one block each, a key half and a value half.  sc_map: block ->
@@ -135,9 +145,6 @@ struct AdaptiveWs {
   uint32_t sc_step;  // stamp of the last adaptive step
 };
 
-// AdaptiveWs::scan: over the blocks that are not key-promoted for the head, the estimated mass and the largest log-mass;
-// over those that are not listed at all, relative to lse, the mass, the value term and the largest share of it
-constexpr int S_ALPHA = 0, S_TOP = 1, S_L8U = 2, S_EV8U = 3, S_MAXC8 = 4;
 constexpr int MAX_RANK_DEPTH = 8;   // largest depth r of the ranking check (adaptive path)
 constexpr int SC_MAX_SLOTS = 1024;
 // per-block word of AdaptiveWs::slot: bit 0 FP16 keys, bit 1 FP16 values, bit 2 / bit 3 the keys /
@@ -253,7 +260,8 @@ struct PromArgs {
   const float* lm8;         // [Bt][Hq][nb]
   const float* eta;         // [Bt][Hkv][nb]
   const float* first;       // [Bt][Hq][4]
-  float* scan;              // [Bt][Hq][8], written
+  ScanPart* scan;           // [Bt][Hq][parts], written
+  int parts;                // workgroups that sum up the blocks left in INT8, per head
   int groups;               // Bt * Hkv
   int sums_last;            // 1: the workgroups that sum up the blocks left in INT8 come behind all others
 };

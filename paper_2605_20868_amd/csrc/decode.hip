@@ -129,64 +129,76 @@ __device__ __forceinline__ int prom_list(const DecodeArgs& a, const PromArgs& p,
   return total;
 }
 
-// What the blocks left in INT8 add up to for one head (AdaptiveWs::scan), by one workgroup beside the promoted-block pass.
-__device__ __forceinline__ void prom_scan(const DecodeArgs& a, const PromArgs& p, int64_t grp, int group, int h, int64_t row) {
+// What blocks SCAN_PART part .. + SCAN_PART - 1 left in INT8 add up to for one head, by one workgroup beside the promoted-block
+// pass: 128K tokens are one part, which runs under the pass's own time.  (One workgroup per head at any length was the
+// longest thing in the launch beyond that: 1 KV head of 1M tokens 67 us where the pass takes 5, the step 162.7 -> 107.2 us
+// with the sums in parts; 4 x 4 heads of 512K 173.1 -> 149.5.)
+__device__ __forceinline__ void prom_scan(const DecodeArgs& a, const PromArgs& p, int64_t grp, int group, int h, int part, int64_t row) {
   const int tid = threadIdx.x;
   const int32_t* const slot = p.slot + grp * (a.nq_cap * 4);
   const float* l8 = p.lm8 + row * a.nb;
   const float* eta = p.eta + grp * a.nb;
   const float lse8 = p.first[row * 4];
   const int kbit = 1 << (SLOT_HK_SHIFT + h);
-  __shared__ uint32_t s_key[256], s_any[256];   // key-promoted for the head, listed: 8192 blocks at a time
+  __shared__ uint32_t s_key[SCAN_PART / 32], s_any[SCAN_PART / 32];   // key-promoted for the head, listed
   __shared__ double s_sum[4][3];
   __shared__ float s_max[4][2];
   __shared__ int s_scan[4], s_total;
-  int listed = 0;
-  float tail_max = -INFINITY, maxc8 = 0.0f;
-  double tail_mass = 0.0, l8u = 0.0, ev8u = 0.0;
-  for (int b0 = 0; b0 < a.nb; b0 += 8192) {
-    if (p.umask != nullptr) {
-      PromBits m;
-      m.k = m.v = m.kh[h] = 0u;
-      if (b0 + tid * 32 < a.nb) m = prom_bits(a, p, grp, group, (b0 >> 5) + tid, ~0u);
-      uint32_t any = m.k | m.v;
-      const int upto = listed + block_scan_incl<int>(__popc(any), s_scan, tid);
+  const int b0 = part * SCAN_PART, b1 = min(b0 + SCAN_PART, a.nb);
+  if (p.umask != nullptr) {
+    // blocks listed before this part: they matter only where the list can overflow, which takes explored blocks
+    int listed = 0;
+    if (p.explore_threshold != 0u && part > 0) {
+      int mine = 0;
+      for (int w0 = tid; w0 < b0 >> 5; w0 += 256) {
+        const PromBits m = prom_bits(a, p, grp, group, w0, ~0u);
+        mine += __popc(m.k | m.v);
+      }
+      const int upto = block_scan_incl<int>(mine, s_scan, tid);
       if (tid == 255) s_total = upto;
-      // what does not fit the list stays unpromoted: the highest blocks
-      for (int over = upto - MAX_UNION; over > 0 && any != 0u; --over) any &= ~(0x80000000u >> __clz((int)any));
-      s_key[tid] = m.kh[h] & any;
-      s_any[tid] = any;
       __syncthreads();
       listed = s_total;
     }
-    for (int base = b0; base < min(b0 + 8192, a.nb); base += 256 * 8) {
-      float b8[8], be[8];
-      int bs[8];
+    PromBits m;
+    m.k = m.v = m.kh[h] = 0u;
+    if (b0 + tid * 32 < b1) m = prom_bits(a, p, grp, group, (b0 >> 5) + tid, ~0u);
+    uint32_t any = m.k | m.v;
+    const int upto = listed + block_scan_incl<int>(__popc(any), s_scan, tid);
+    // what does not fit the list stays unpromoted: the highest blocks
+    for (int over = upto - MAX_UNION; over > 0 && any != 0u; --over) any &= ~(0x80000000u >> __clz((int)any));
+    s_key[tid] = m.kh[h] & any;
+    s_any[tid] = any;
+    __syncthreads();
+  }
+  float tail_max = -INFINITY, maxc8 = 0.0f;
+  double tail_mass = 0.0, l8u = 0.0, ev8u = 0.0;
+  for (int base = b0; base < b1; base += 256 * 8) {
+    float b8[8], be[8];
+    int bs[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int i = base + j * 256 + tid;
-        const bool in = i < a.nb;
-        b8[j] = in ? l8[i] : 0.0f;
-        be[j] = in ? eta[i] : 0.0f;
-        if (p.umask != nullptr) {
-          const int wd = in ? (i - b0) >> 5 : 0;
-          bs[j] = !in || ((s_key[wd] >> (i & 31)) & 1u) ? kbit : (int)((s_any[wd] >> (i & 31)) & 1u);
-        } else {
-          bs[j] = in ? slot[i] : kbit;
-        }
+    for (int j = 0; j < 8; ++j) {
+      const int i = base + j * 256 + tid;
+      const bool in = i < b1;
+      b8[j] = in ? l8[i] : 0.0f;
+      be[j] = in ? eta[i] : 0.0f;
+      if (p.umask != nullptr) {
+        const int wd = in ? (i - b0) >> 5 : 0;
+        bs[j] = !in || ((s_key[wd] >> (i & 31)) & 1u) ? kbit : (int)((s_any[wd] >> (i & 31)) & 1u);
+      } else {
+        bs[j] = in ? slot[i] : kbit;
       }
+    }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        if (bs[j] & kbit) continue;            // key-promoted for this head (or past the end)
-        const float mass = expf(b8[j] - lse8);
-        tail_max = fmaxf(tail_max, b8[j]);
-        tail_mass += (double)mass;
-        if (bs[j] == 0) {
-          // not listed: the promoted-block pass does not revisit it, it keeps its INT8 mass and its eta_b
-          l8u += (double)mass;
-          ev8u += (double)(mass * be[j]);
-          maxc8 = fmaxf(maxc8, mass * be[j]);
-        }
+    for (int j = 0; j < 8; ++j) {
+      if (bs[j] & kbit) continue;            // key-promoted for this head (or past the end)
+      const float mass = expf(b8[j] - lse8);
+      tail_max = fmaxf(tail_max, b8[j]);
+      tail_mass += (double)mass;
+      if (bs[j] == 0) {
+        // not listed: the promoted-block pass does not revisit it, it keeps its INT8 mass and its eta_b
+        l8u += (double)mass;
+        ev8u += (double)(mass * be[j]);
+        maxc8 = fmaxf(maxc8, mass * be[j]);
       }
     }
   }
@@ -205,12 +217,13 @@ __device__ __forceinline__ void prom_scan(const DecodeArgs& a, const PromArgs& p
   }
   __syncthreads();
   if (tid == 0) {
-    float* out = p.scan + row * 8;
-    out[S_ALPHA] = (float)(s_sum[0][0] + s_sum[1][0] + s_sum[2][0] + s_sum[3][0]);
-    out[S_L8U] = (float)(s_sum[0][1] + s_sum[1][1] + s_sum[2][1] + s_sum[3][1]);
-    out[S_EV8U] = (float)(s_sum[0][2] + s_sum[1][2] + s_sum[2][2] + s_sum[3][2]);
-    out[S_TOP] = fmaxf(fmaxf(s_max[0][0], s_max[1][0]), fmaxf(s_max[2][0], s_max[3][0]));
-    out[S_MAXC8] = fmaxf(fmaxf(s_max[0][1], s_max[1][1]), fmaxf(s_max[2][1], s_max[3][1]));
+    ScanPart t;
+    t.alpha = s_sum[0][0] + s_sum[1][0] + s_sum[2][0] + s_sum[3][0];
+    t.l8u = s_sum[0][1] + s_sum[1][1] + s_sum[2][1] + s_sum[3][1];
+    t.ev8u = s_sum[0][2] + s_sum[1][2] + s_sum[2][2] + s_sum[3][2];
+    t.top = fmaxf(fmaxf(s_max[0][0], s_max[1][0]), fmaxf(s_max[2][0], s_max[3][0]));
+    t.maxc8 = fmaxf(fmaxf(s_max[0][1], s_max[1][1]), fmaxf(s_max[2][1], s_max[3][1]));
+    p.scan[row * p.parts + part] = t;
   }
 }
 
@@ -221,18 +234,18 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a, Prom
   const int vn = l & 15, vgh = (l >> 4) & 1, vo = l >> 5;  // roles in the value phase
   int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
   if (PROM) {   // one index: per KV group its workgroups one after the other, the summing ones among them or last of all
-    const int L = (int)(blockIdx.y * gridDim.x + blockIdx.x), passes = 2 * PROM_SPLITS * p.groups;
+    const int L = (int)(blockIdx.y * gridDim.x + blockIdx.x), passes = 2 * PROM_SPLITS * p.groups, sums = G * p.parts;
     int g;
-    if (L >= (2 * PROM_SPLITS + G) * p.groups) return;
+    if (L >= (2 * PROM_SPLITS + sums) * p.groups) return;
     if (!p.sums_last) {
-      g = L / (2 * PROM_SPLITS + G);
-      split = L % (2 * PROM_SPLITS + G);
+      g = L / (2 * PROM_SPLITS + sums);
+      split = L % (2 * PROM_SPLITS + sums);
     } else if (L < passes) {
       g = L / (2 * PROM_SPLITS);
       split = L % (2 * PROM_SPLITS);
     } else {
-      g = (L - passes) / G;
-      split = 2 * PROM_SPLITS + (L - passes) % G;
+      g = (L - passes) / sums;
+      split = 2 * PROM_SPLITS + (L - passes) % sums;
     }
     b = g / a.n_kv;
     kvh = g - b * a.n_kv;
@@ -244,10 +257,10 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a, Prom
   // PROM: the second half of the workgroups (neg) walks the same list with INT8 keys and INT4
   // values whatever the flags say and writes its partial set negated: it takes back what the one
   // pass over all sealed blocks added for the listed blocks, the first half adds them again with
-  // the originals the flags ask for.  One more workgroup per head sums up the blocks left in INT8.
+  // the originals the flags ask for.  Further ones, per head and part, sum up the blocks left in INT8.
   if (PROM && split >= 2 * PROM_SPLITS) {
-    const int h = split - 2 * PROM_SPLITS;
-    prom_scan(a, p, grp, G, h, (int64_t)b * a.n_q + kvh * G + h);
+    const int part = (split - 2 * PROM_SPLITS) / G, h = (split - 2 * PROM_SPLITS) % G;
+    prom_scan(a, p, grp, G, h, part, (int64_t)b * a.n_q + kvh * G + h);
     return;
   }
   const bool neg = PROM && split >= PROM_SPLITS;

@@ -47,31 +47,46 @@ def test_the_list_from_the_masks_is_the_list_of_the_scratch_path(blocks, hkv, g,
             assert (prom[0, grp, :blocks][drawn] & 1).all()
 
 
-@pytest.mark.parametrize("blocks", [4096, 4200, 9000])
-def test_a_full_list_leaves_the_last_blocks_in_int8(blocks):
-    """Exploration of every block: 4096 fit the list, the rest stays unpromoted and keeps its INT8 mass."""
+# the list full within the first part of 8192 blocks, within the second, and nowhere
+@pytest.mark.parametrize("blocks,frac", [(4096, 1.0), (4200, 1.0), (9000, 1.0), (2 * 8192 + 33, 0.3), (2 * 8192 + 33, 0.01), (8192, 0.0), (8193, 0.0)])
+@pytest.mark.parametrize("slots", [0, 16])
+def test_a_full_list_leaves_the_last_blocks_in_int8(blocks, frac, slots):
+    """Explored blocks beyond the 4096 that fit the list stay unpromoted and keep their INT8 mass, which is summed in parts
+    of 8192 blocks."""
     n = blocks * 16
     rng = np.random.Generator(np.random.Philox(blocks))
     k, v = workloads.normal_f16(rng, (1, 1, n, 128)), workloads.normal_f16(rng, (1, 1, n, 128))
     q = workloads.normal_f16(rng, (1, 2, 128))
-    print("full list", blocks, flush=True)
+    print("full list", blocks, frac, slots, flush=True)
     with GpuLayerCache(1, 2, 1, n + 16) as gc:
         gc.append(k, v)
-        sel = gc.cqa.Selector(0.995, 2, 16, 16, explore_frac=1.0, explore_seed=1)
+        gc.cqa.cqa_set_scratch_slots(gc.h, slots)
+        sel = gc.cqa.Selector(0.995, 2, 16, 16, explore_frac=frac, explore_seed=1)
         O, cert, flags, st = run(gc, q, gc.cqa.Tolerances(), sel)
-        keys = st[2][0, 0, :blocks] & 1
-        assert keys[:4096].all() and not keys[4096:].any()
+        keys = (st[2][0, 0, :blocks] & 1).astype(bool)
+        wanted = np.asarray(ad.explored_blocks(blocks, 0, ad.SelectorParams(explore_frac=frac, explore_seed=1)), dtype=bool)
+        last = np.flatnonzero(keys)[-1]
+        assert keys.sum() <= 4096 and keys[:last + 1][wanted[:last + 1]].all()
+        if wanted.sum() >= 4096:
+            assert keys.sum() == 4096
+        else:
+            assert keys[wanted].all()
         s8, _, _, lm = gc.certified_decode(q, want_logmass=True)
         kd, vd, qd = k[0, 0].astype(np.float64), v[0, 0].astype(np.float64), q[0].astype(np.float64)
         for h in range(2):
             # the mass left in INT8, from the first pass's log-masses (binary32 exponentials: 1e-5)
             l8 = lm[0, h, :blocks].astype(np.float64)
-            tail = np.exp(l8[4096:] - np.logaddexp.reduce(l8)).sum()
+            tail = np.exp(l8[~keys] - np.logaddexp.reduce(l8)).sum()
             assert abs(cert[0, h]["alpha_tail_hat"] - tail) <= 1e-5 * tail + 1e-12
-            if blocks == 4096:      # everything promoted: FP16 scores, values as the plain pass has them
-                s = kd @ qd[h] / np.sqrt(128.0)
-                m = s.max()
-                assert abs(cert[0, h]["lse"] - (m + np.log(np.exp(s - m).sum()))) <= 1e-4
+            # the best block left, against the best promoted one
+            if not keys.all():
+                lx = st[4][0, h, :blocks][keys].max()
+                assert abs(cert[0, h]["rank_margin"] - (lx - (l8[~keys].max() + cert[0, h]["delta_h"]))) <= 1e-4
+            # listed blocks with FP16 scores, all others with the first pass's log-masses
+            s = kd @ qd[h] / np.sqrt(128.0)
+            m = s.max()
+            l16 = np.log(np.exp(s - m).reshape(blocks, 16).sum(1)) + m
+            assert abs(cert[0, h]["lse"] - np.logaddexp.reduce(np.where(keys, l16, l8))) <= 1e-4
 
 
 @pytest.mark.parametrize("splits", [1, 8, 9, 17, 64, 65, 130, 200])
