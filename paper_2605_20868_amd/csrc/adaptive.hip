@@ -1106,11 +1106,17 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   pa.scan = w.scan;
   pa.groups = bt * hkv;
   pa.parts = (int)scan_parts(nb);
-  // The summing workgroups keep the link idle while they hold a place that a workgroup with originals to fetch could
-  // have, so where not all are resident at once (two to a compute unit) they come last: 128 groups of 4000 tokens 2291 -> 2263 us
-  // a step; 8 groups, all resident: 128K 102.3 us with them in between, 104.8 last, 107.6 first.
+  // Order of the workgroups.  Where not all are resident at once (taking two to a compute unit), the summing ones would keep the
+  // link idle while they hold a place that a workgroup with originals to fetch could have, so they come last: 128 groups of
+  // 4000 tokens 2291 -> 2263 us a step.  With somewhat more than one to a compute unit, a few compute units get two.  Group by
+  // group that is, on some, two that fetch originals, which take the longer the more they fetch; so the order wraps
+  // round: the surplus are negated sets, sharing with negated sets.  Steps of 20000 tokens, group by group, wrapped, sums last,
+  // 4 heads per group: 8 groups, 512 blocks a head 714.6, 692.1, 692.7; 9 groups 789.1, 773.4, 796.7; 11 groups
+  // 941.1, 939.1, 942.5; 14 groups 1172.9, 1186.2, 1174.6; 8 groups of 128K, 128 blocks a head 386.5, 377.0, 376.2, few
+  // blocks 86.5, 86.8, 89.7; 14 groups, few blocks 265.6, 267.6, 269.6.
   const int64_t wgs = (int64_t)(2 * PROM_SPLITS + g * pa.parts) * pa.groups;
-  pa.sums_last = wgs > 2 * c->n_cu ? 1 : 0;
+  pa.order = wgs > 2 * c->n_cu ? PROM_SUMS_LAST : (2 * wgs > 3 * c->n_cu || wgs <= c->n_cu ? PROM_BY_GROUP : PROM_WRAPPED);
+  pa.ahead = (int)std::min<int64_t>(std::max<int64_t>(wgs - c->n_cu, 0), (int64_t)PROM_SPLITS * pa.groups);
   const unsigned gx = (unsigned)std::min<int64_t>(wgs, 1 << 22);   // (a grid dimension holds fewer than 2^32 threads)
   rc = launch_promoted_pass(a, pa, g, dim3(gx, (unsigned)((wgs + gx - 1) / gx)), st);
   if (rc != CQA_OK) return rc;

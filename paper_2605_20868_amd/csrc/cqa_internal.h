@@ -245,7 +245,10 @@ struct DecodeArgs {
 };
 
 
-// The promoted-block pass's part of the adaptive step besides DecodeArgs.
+// The promoted-block pass's part of the adaptive step besides DecodeArgs.  Orders of its workgroups: per KV group those of the
+// positive sets, of the negated sets and of the sums; all passes and then all sums; the positive sets and the sums per
+// KV group, then the negated sets, the last `ahead` of them moved to the front.
+constexpr int PROM_BY_GROUP = 0, PROM_SUMS_LAST = 1, PROM_WRAPPED = 2;
 struct PromArgs {
   const uint32_t* umask;    // [Bt][Hq][mask_words] key selections per head, or null: the list and the flag words are
                             // there already (compact_kernel, which looks after the FP16 scratch)
@@ -263,7 +266,8 @@ struct PromArgs {
   ScanPart* scan;           // [Bt][Hq][parts], written
   int parts;                // workgroups that sum up the blocks left in INT8, per head
   int groups;               // Bt * Hkv
-  int sums_last;            // 1: the workgroups that sum up the blocks left in INT8 come behind all others
+  int order;                // of the workgroups, PROM_* below
+  int ahead;                // PROM_WRAPPED: so many of the negated sets' workgroups come first
 };
 
 inline int64_t head_index(const Cache* c, int layer, int b, int kvh) {

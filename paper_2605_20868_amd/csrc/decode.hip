@@ -233,19 +233,24 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a, Prom
   const int tok = l & 15, kg = l >> 4;              // roles in the score phase
   const int vn = l & 15, vgh = (l >> 4) & 1, vo = l >> 5;  // roles in the value phase
   int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-  if (PROM) {   // one index: per KV group its workgroups one after the other, the summing ones among them or last of all
-    const int L = (int)(blockIdx.y * gridDim.x + blockIdx.x), passes = 2 * PROM_SPLITS * p.groups, sums = G * p.parts;
-    int g;
-    if (L >= (2 * PROM_SPLITS + sums) * p.groups) return;
-    if (!p.sums_last) {
+  if (PROM) {   // one index: (KV group, split), splits 0 .. 15 the positive sets, .. 31 the negated ones, then the sums
+    int L = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+    const int sums = G * p.parts, all = (2 * PROM_SPLITS + sums) * p.groups;
+    int g, passes;
+    if (L >= all) return;
+    if (p.order == PROM_BY_GROUP) {
       g = L / (2 * PROM_SPLITS + sums);
       split = L % (2 * PROM_SPLITS + sums);
-    } else if (L < passes) {
-      g = L / (2 * PROM_SPLITS);
-      split = L % (2 * PROM_SPLITS);
+    } else if (p.order == PROM_SUMS_LAST) {
+      passes = 2 * PROM_SPLITS * p.groups;
+      g = L < passes ? L / (2 * PROM_SPLITS) : (L - passes) / sums;
+      split = L < passes ? L % (2 * PROM_SPLITS) : 2 * PROM_SPLITS + (L - passes) % sums;
     } else {
-      g = (L - passes) / sums;
-      split = 2 * PROM_SPLITS + (L - passes) % sums;
+      L = L < p.ahead ? L + all - p.ahead : L - p.ahead;
+      passes = (PROM_SPLITS + sums) * p.groups;
+      g = L < passes ? L / (PROM_SPLITS + sums) : (L - passes) / PROM_SPLITS;
+      split = L < passes ? L % (PROM_SPLITS + sums) : PROM_SPLITS + (L - passes) % PROM_SPLITS;
+      if (L < passes && split >= PROM_SPLITS) split += PROM_SPLITS;
     }
     b = g / a.n_kv;
     kvh = g - b * a.n_kv;

@@ -89,6 +89,33 @@ def test_a_full_list_leaves_the_last_blocks_in_int8(blocks, frac, slots):
             assert abs(cert[0, h]["lse"] - np.logaddexp.reduce(np.where(keys, l16, l8))) <= 1e-4
 
 
+# (batch, kv heads, group, blocks): up to one workgroup per compute unit, somewhat more, two and more, with sums in one part
+# and in two; short lists, which reach few of a group's workgroups
+@pytest.mark.parametrize("bt,hkv,g,blocks", [(1, 7, 2, 300), (1, 8, 4, 300), (2, 5, 4, 130), (1, 8, 2, 8200), (1, 12, 4, 90), (2, 10, 4, 65),
+                                             (4, 8, 4, 3), (3, 7, 2, 28), (2, 8, 4, 29), (1, 9, 1, 25)])
+def test_rows_do_not_depend_on_the_order_of_the_workgroups(bt, hkv, g, blocks):
+    """Every KV group's rows are bit for bit those of a cache of its own, whose workgroups all lie one after another."""
+    n = blocks * 16 + 3
+    rng = np.random.Generator(np.random.Philox(blocks * 100 + hkv))
+    k, v = workloads.student_t3_f16(rng, (bt, hkv, n, 128)), workloads.normal_f16(rng, (bt, hkv, n, 128))
+    q = workloads.normal_f16(rng, (bt, hkv * g, 128))
+    print("order", bt, hkv, g, blocks, flush=True)
+    for b, h in [(slice(None), slice(None))] + [(i, j) for i in range(bt) for j in range(hkv)][::3]:
+        whole = isinstance(b, slice)
+        kk, vv, qq = (k, v, q) if whole else (k[b:b + 1, h:h + 1], v[b:b + 1, h:h + 1], q[b:b + 1, h * g:(h + 1) * g])
+        with GpuLayerCache(kk.shape[0], kk.shape[1] * g, kk.shape[1], n + 16) as gc:
+            gc.append(kk, vv)
+            gc.cqa.cqa_set_splits(gc.h, 2)
+            tol = gc.cqa.Tolerances(rank_depth=2, v_tol=0.02)
+            O, cert, flags, st = run(gc, qq, tol, gc.cqa.Selector(0.995, 2, 40, 40, v_limit=16, canary=True))
+        if whole:
+            all_O, all_cert, all_flags, all_st = O, cert, flags, st
+            continue
+        rows = slice(h * g, (h + 1) * g)
+        assert np.array_equal(all_O[b, rows], O[0]) and all_cert[b, rows].tobytes() == cert[0].tobytes()
+        assert (all_flags[b, rows] == flags[0]).all() and np.array_equal(all_st[2][b, h], st[2][0, 0])
+
+
 @pytest.mark.parametrize("splits", [1, 8, 9, 17, 64, 65, 130, 200])
 def test_merging_any_number_of_partial_sets(splits):
     """A wave merges eight sets a trip, eight waves share a head's sets: up to 64 in one trip, more in several."""
