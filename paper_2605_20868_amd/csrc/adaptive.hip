@@ -1116,6 +1116,12 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   // blocks 86.5, 86.8, 89.7; 14 groups, few blocks 265.6, 267.6, 269.6.
   const int64_t wgs = (int64_t)(2 * PROM_SPLITS + g * pa.parts) * pa.groups;
   pa.order = wgs > 2 * c->n_cu ? PROM_SUMS_LAST : (2 * wgs > 3 * c->n_cu || wgs <= c->n_cu ? PROM_BY_GROUP : PROM_WRAPPED);
+  // Lists that reach fewer than eight of a group's workgroups leave dies of the chip without any (a group has a multiple of
+  // eight, so the same splits of all groups lie on the same die), so each group's list starts as many workgroups
+  // away as it can reach.  64 x 8 groups, 4 heads, of 50 tokens 381.6 -> 218.7 us a step, of 120 442.3 -> 401.6, of 250 704.1 -> 681.4,
+  // of 400 1149.9 -> 1058.3, of 460 1221.3 -> 1189.0 (but 32 x 16 of 200 559.8 -> 565.2); 128 groups of 120 126.9 -> 114.2.  Where
+  // eight or more are reached it gains nothing: 700 tokens 1734, 1754; 850 2128, 2140.  16 groups of 400 72.1, 74.7.
+  pa.turn = nb <= 4 * 7 && pa.groups >= 32 ? (int)((nb + 3) / 4) : 0;
   pa.ahead = (int)std::min<int64_t>(std::max<int64_t>(wgs - c->n_cu, 0), (int64_t)PROM_SPLITS * pa.groups);
   const unsigned gx = (unsigned)std::min<int64_t>(wgs, 1 << 22);   // (a grid dimension holds fewer than 2^32 threads)
   rc = launch_promoted_pass(a, pa, g, dim3(gx, (unsigned)((wgs + gx - 1) / gx)), st);

@@ -268,6 +268,7 @@ struct PromArgs {
   int groups;               // Bt * Hkv
   int order;                // of the workgroups, PROM_* below
   int ahead;                // PROM_WRAPPED: so many of the negated sets' workgroups come first
+  int turn;                 // a KV group's list starts so many of its workgroups away from where the previous group's does
 };
 
 inline int64_t head_index(const Cache* c, int layer, int b, int kvh) {

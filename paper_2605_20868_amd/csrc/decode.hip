@@ -252,6 +252,7 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a, Prom
       split = L < passes ? L % (PROM_SPLITS + sums) : PROM_SPLITS + (L - passes) % PROM_SPLITS;
       if (L < passes && split >= PROM_SPLITS) split += PROM_SPLITS;
     }
+    if (split < 2 * PROM_SPLITS) split = (split & PROM_SPLITS) | ((split + p.turn * g) & (PROM_SPLITS - 1));
     b = g / a.n_kv;
     kvh = g - b * a.n_kv;
   }
