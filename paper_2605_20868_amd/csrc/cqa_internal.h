@@ -107,7 +107,7 @@ struct ScanPart {
   double alpha, l8u, ev8u;
   float top, maxc8;
 };
-constexpr int SCAN_PART = 8192;
+constexpr int SCAN_PART = 8192, SUM_WAVE_BLOCKS = 2048;
 inline int64_t scan_parts(int64_t n_blocks) { return (n_blocks + SCAN_PART - 1) / SCAN_PART; }
 
 struct AdaptiveWs {
@@ -264,7 +264,8 @@ struct PromArgs {
   const float* eta;         // [Bt][Hkv][nb]
   const float* first;       // [Bt][Hq][4]
   ScanPart* scan;           // [Bt][Hq][parts], written
-  int parts;                // workgroups that sum up the blocks left in INT8, per head
+  int parts;                // workgroups that sum up the blocks left in INT8, per head, ...
+  int sum_waves;            // ... or 1: one per KV group, a wave per head
   int groups;               // Bt * Hkv
   int order;                // of the workgroups, PROM_* below
   int ahead;                // PROM_WRAPPED: so many of the negated sets' workgroups come first

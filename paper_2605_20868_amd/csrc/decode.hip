@@ -133,14 +133,20 @@ __device__ __forceinline__ int prom_list(const DecodeArgs& a, const PromArgs& p,
 // pass: 128K tokens are one part, which runs under the pass's own time.  (One workgroup per head at any length was the
 // longest thing in the launch beyond that: 1 KV head of 1M tokens 67 us where the pass takes 5, the step 162.7 -> 107.2 us
 // with the sums in parts; 4 x 4 heads of 512K 173.1 -> 149.5.)
+// WAVES: by one wave, and one workgroup takes all heads of the group (at most SUM_WAVE_BLOCKS blocks, fewer than a list holds).
+template <bool WAVES>
 __device__ __forceinline__ void prom_scan(const DecodeArgs& a, const PromArgs& p, int64_t grp, int group, int h, int part, int64_t row) {
-  const int tid = threadIdx.x;
+  constexpr int T = WAVES ? 64 : 256;
+  static_assert(SUM_WAVE_BLOCKS <= 64 * 32 && SUM_WAVE_BLOCKS <= MAX_UNION, "a word per lane, and no list that overflows");
+  const int tid = threadIdx.x & (T - 1);
   const int32_t* const slot = p.slot + grp * (a.nq_cap * 4);
   const float* l8 = p.lm8 + row * a.nb;
   const float* eta = p.eta + grp * a.nb;
   const float lse8 = p.first[row * 4];
   const int kbit = 1 << (SLOT_HK_SHIFT + h);
-  __shared__ uint32_t s_key[SCAN_PART / 32], s_any[SCAN_PART / 32];   // key-promoted for the head, listed
+  __shared__ uint32_t s_key_all[SCAN_PART / 32], s_any_all[SCAN_PART / 32];   // key-promoted for the head, listed
+  uint32_t* const s_key = s_key_all + (WAVES ? 64 * h : 0);
+  uint32_t* const s_any = s_any_all + (WAVES ? 64 * h : 0);
   __shared__ double s_sum[4][3];
   __shared__ float s_max[4][2];
   __shared__ int s_scan[4], s_total;
@@ -148,7 +154,7 @@ __device__ __forceinline__ void prom_scan(const DecodeArgs& a, const PromArgs& p
   if (p.umask != nullptr) {
     // blocks listed before this part: they matter only where the list can overflow, which takes explored blocks
     int listed = 0;
-    if (p.explore_threshold != 0u && part > 0) {
+    if (!WAVES && p.explore_threshold != 0u && part > 0) {
       int mine = 0;
       for (int w0 = tid; w0 < b0 >> 5; w0 += 256) {
         const PromBits m = prom_bits(a, p, grp, group, w0, ~0u);
@@ -160,24 +166,27 @@ __device__ __forceinline__ void prom_scan(const DecodeArgs& a, const PromArgs& p
       listed = s_total;
     }
     PromBits m;
-    m.k = m.v = m.kh[h] = 0u;
+    m.k = m.v = m.kh[0] = m.kh[1] = m.kh[2] = m.kh[3] = 0u;
     if (b0 + tid * 32 < b1) m = prom_bits(a, p, grp, group, (b0 >> 5) + tid, ~0u);
     uint32_t any = m.k | m.v;
-    const int upto = listed + block_scan_incl<int>(__popc(any), s_scan, tid);
-    // what does not fit the list stays unpromoted: the highest blocks
-    for (int over = upto - MAX_UNION; over > 0 && any != 0u; --over) any &= ~(0x80000000u >> __clz((int)any));
-    s_key[tid] = m.kh[h] & any;
+    if (!WAVES) {
+      const int upto = listed + block_scan_incl<int>(__popc(any), s_scan, tid);
+      // what does not fit the list stays unpromoted: the highest blocks
+      for (int over = upto - MAX_UNION; over > 0 && any != 0u; --over) any &= ~(0x80000000u >> __clz((int)any));
+    }
+    const uint32_t keys = h == 0 ? m.kh[0] : (h == 1 ? m.kh[1] : (h == 2 ? m.kh[2] : m.kh[3]));
+    s_key[tid] = keys & any;
     s_any[tid] = any;
-    __syncthreads();
+    if (WAVES) wave_sync(); else __syncthreads();
   }
   float tail_max = -INFINITY, maxc8 = 0.0f;
   double tail_mass = 0.0, l8u = 0.0, ev8u = 0.0;
-  for (int base = b0; base < b1; base += 256 * 8) {
+  for (int base = b0; base < b1; base += T * 8) {
     float b8[8], be[8];
     int bs[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const int i = base + j * 256 + tid;
+      const int i = base + j * T + tid;
       const bool in = i < b1;
       b8[j] = in ? l8[i] : 0.0f;
       be[j] = in ? eta[i] : 0.0f;
@@ -202,12 +211,16 @@ __device__ __forceinline__ void prom_scan(const DecodeArgs& a, const PromArgs& p
       }
     }
   }
-  const int w = tid >> 6;
+  const int w = WAVES ? 0 : tid >> 6;
   tail_mass = wave_sum_d(tail_mass);
   l8u = wave_sum_d(l8u);
   ev8u = wave_sum_d(ev8u);
   tail_max = wave_max(tail_max);
   maxc8 = wave_max(maxc8);
+  if (WAVES) {
+    if (tid == 0) p.scan[row] = ScanPart{tail_mass, l8u, ev8u, tail_max, maxc8};
+    return;
+  }
   if ((tid & 63) == 0) {
     s_sum[w][0] = tail_mass;
     s_sum[w][1] = l8u;
@@ -235,7 +248,7 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a, Prom
   int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
   if (PROM) {   // one index: (KV group, split), splits 0 .. 15 the positive sets, .. 31 the negated ones, then the sums
     int L = (int)(blockIdx.y * gridDim.x + blockIdx.x);
-    const int sums = G * p.parts, all = (2 * PROM_SPLITS + sums) * p.groups;
+    const int sums = p.sum_waves ? 1 : G * p.parts, all = (2 * PROM_SPLITS + sums) * p.groups;
     int g, passes;
     if (L >= all) return;
     if (p.order == PROM_BY_GROUP) {
@@ -265,8 +278,12 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a, Prom
   // pass over all sealed blocks added for the listed blocks, the first half adds them again with
   // the originals the flags ask for.  Further ones, per head and part, sum up the blocks left in INT8.
   if (PROM && split >= 2 * PROM_SPLITS) {
+    if (p.sum_waves) {
+      if (w < G) prom_scan<true>(a, p, grp, G, w, 0, (int64_t)b * a.n_q + kvh * G + w);
+      return;
+    }
     const int part = (split - 2 * PROM_SPLITS) / G, h = (split - 2 * PROM_SPLITS) % G;
-    prom_scan(a, p, grp, G, h, part, (int64_t)b * a.n_q + kvh * G + h);
+    prom_scan<false>(a, p, grp, G, h, part, (int64_t)b * a.n_q + kvh * G + h);
     return;
   }
   const bool neg = PROM && split >= PROM_SPLITS;

@@ -89,10 +89,11 @@ def test_a_full_list_leaves_the_last_blocks_in_int8(blocks, frac, slots):
             assert abs(cert[0, h]["lse"] - np.logaddexp.reduce(np.where(keys, l16, l8))) <= 1e-4
 
 
-# (batch, kv heads, group, blocks): up to one workgroup per compute unit, somewhat more, two and more, with sums in one part
-# and in two; short lists, which reach few of a group's workgroups
-@pytest.mark.parametrize("bt,hkv,g,blocks", [(1, 7, 2, 300), (1, 8, 4, 300), (2, 5, 4, 130), (1, 8, 2, 8200), (1, 12, 4, 90), (2, 10, 4, 65),
-                                             (4, 8, 4, 3), (5, 7, 2, 28), (4, 9, 1, 29), (1, 9, 1, 25), (4, 8, 4, 13)])
+# (batch, kv heads, group, blocks): up to one workgroup per compute unit, somewhat more, two and more (sums by a wave each and
+# by a workgroup each), sums in one part and in two, short lists, which reach few of a group's workgroups
+@pytest.mark.parametrize("bt,hkv,g,blocks", [
+    (1, 7, 2, 300), (1, 8, 4, 300), (2, 5, 4, 130), (1, 8, 2, 8200), (1, 12, 4, 90), (2, 10, 4, 65), (4, 8, 4, 3), (4, 8, 4, 13),
+    (5, 7, 2, 28), (4, 9, 1, 29), (1, 9, 1, 25), (4, 9, 2, 513), (2, 8, 4, 2048), (2, 8, 4, 2049)])
 def test_rows_do_not_depend_on_the_order_of_the_workgroups(bt, hkv, g, blocks):
     """Every KV group's rows are bit for bit those of a cache of its own, whose workgroups all lie one after another."""
     n = blocks * 16 + 3
