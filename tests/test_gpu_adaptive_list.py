@@ -1,6 +1,8 @@
 """The list of promoted blocks as the promoted-block pass makes it from the selection masks, against the list of a cache
 whose FP16 scratch is in use (a launch of its own) and against the oracle's exploration draw, where the pieces of
 a mask word change size, in the last, partial word, and where the list is full; and merges of many partial sets."""
+import functools
+
 import numpy as np
 import pytest
 
@@ -8,6 +10,7 @@ import oracle
 import workloads
 from oracle import adaptive as ad
 from helpers import GpuLayerCache, assert_head_matches
+from test_gpu_adaptive import check_against_oracle, gpu_adaptive
 
 pytestmark = pytest.mark.gpu
 
@@ -21,7 +24,7 @@ def run(gc, q, tol, sel):
 
 # blocks: 8, 4, 2 or 1 pieces a word (up to 32, 64, 128 words), one and several sweeps of 256 words
 @pytest.mark.parametrize("blocks", [1, 31, 33, 32 * 32, 32 * 33 + 1, 32 * 64 + 7, 32 * 129 + 3, 8192 + 40])
-@pytest.mark.parametrize("hkv,g,per_head,values", [(2, 4, True, 24), (1, 1, False, 0)])
+@pytest.mark.parametrize("hkv,g,per_head,values", [(2, 4, True, 24), (2, 2, False, 24), (1, 1, False, 0)])
 def test_the_list_from_the_masks_is_the_list_of_the_scratch_path(blocks, hkv, g, per_head, values):
     n = blocks * 16 + 5
     rng = np.random.Generator(np.random.Philox(blocks))
@@ -36,6 +39,12 @@ def test_the_list_from_the_masks_is_the_list_of_the_scratch_path(blocks, hkv, g,
             tol = gc.cqa.Tolerances(rank_depth=3, v_tol=0.02 if values else float("inf"))
             sel = gc.cqa.Selector(0.995, 2, 40, 48, v_limit=values, canary=True, explore_frac=0.03, explore_seed=5, per_head=per_head)
             got.append([run(gc, q, tol, sel) for q in qs])     # the second call takes the first one's list back
+            if slots == 0 and blocks <= 32 * 33 + 1:
+                oc = oracle.OracleLayerCache(1, hkv)
+                oc.append(k, v)
+                otol = oracle.Tolerances(rank_depth=3, v_tol=0.02 if values else float("inf"))
+                osel = ad.SelectorParams(0.995, 2, 40, 48, values, False, True, 0.03, 5, per_head)
+                check_against_oracle(oc, qs[0], otol, osel, gpu_adaptive(gc, qs[0], otol, osel))
     for a, b, q in zip(got[0], got[1], qs):
         assert np.array_equal(a[0], b[0]) and a[1].tobytes() == b[1].tobytes() and (a[2] == b[2]).all()
         for i in (0, 2, 3, 4, 8):                              # K*, flags, both log-masses, deviations
@@ -117,31 +126,33 @@ def test_rows_do_not_depend_on_the_order_of_the_workgroups(bt, hkv, g, blocks):
         assert (all_flags[b, rows] == flags[0]).all() and np.array_equal(all_st[2][b, h], st[2][0, 0])
 
 
-@pytest.mark.parametrize("splits", [1, 8, 9, 17, 64, 65, 130, 200])
-def test_merging_any_number_of_partial_sets(splits):
-    """A wave merges eight sets a trip, eight waves share a head's sets: up to 64 in one trip, more in several."""
-    n = 16 * 4 * 4 * 210 + 7
-    rng = np.random.default_rng(splits)
-    k = rng.standard_normal((1, 1, n, 128), dtype=np.float32).astype(np.float16)
-    v = rng.standard_normal((1, 1, n, 128), dtype=np.float32).astype(np.float16)
+@functools.lru_cache(maxsize=1)
+def long_head():
+    """One KV head of 128K tokens with 4 query heads: 2048 quads, 256 sets of eight waves."""
+    rng = np.random.default_rng(256)
+    k, v = (rng.standard_normal((1, 1, 131072 + 7, 128), dtype=np.float32).astype(np.float16) for _ in range(2))
     q = rng.standard_normal((1, 4, 128)).astype(np.float16)
-    print("sets", splits, flush=True)
     oc = oracle.OracleLayerCache(1, 1)
     oc.append(k, v)
-    ref = oc.certified_decode(q, oracle.Tolerances())
-    with GpuLayerCache(1, 4, 1, n + 16) as gc:
+    return k, v, q, oc, oc.certified_decode(q, oracle.Tolerances())
+
+
+@pytest.mark.parametrize("splits", [1, 8, 9, 17, 64, 65, 130, 200, None])
+def test_merging_any_number_of_partial_sets(splits):
+    """A wave merges eight sets a trip, eight waves share a head's sets: up to 64 in one trip, more in several.  None: as
+    many as the launch rule gives, 256 on 256 compute units."""
+    k, v, q, oc, ref = long_head()
+    print("sets", splits, flush=True)
+    with GpuLayerCache(1, 4, 1, k.shape[2] + 16) as gc:
         gc.append(k, v)
-        gc.cqa.cqa_set_splits(gc.h, splits)
+        if splits is not None:
+            gc.cqa.cqa_set_splits(gc.h, splits)
+            assert gc.cqa.cqa_decode_splits(gc.h, 0) == splits
+        elif gc.torch.cuda.get_device_properties(0).multi_processor_count == 256:
+            assert gc.cqa.cqa_decode_splits(gc.h, 0) == 256
         O, cert, flags = gc.certified_decode(q)
         for h, r in enumerate(ref):
             assert_head_matches(r, O[0, h], cert[0, h], flags[0, h], (splits, h))
-        # the adaptive reduction merges 32 sets more
-        sel = gc.cqa.Selector(0.995, 2, 16, 16)
-        O2, cert2, _, st = run(gc, q, gc.cqa.Tolerances(), sel)
-        gc.cqa.cqa_set_splits(gc.h, 1)
-        O3, cert3, _, st3 = run(gc, q, gc.cqa.Tolerances(), sel)
-        if np.array_equal(st[2], st3[2]):
-            # split counts move the rounding of the value weights (2^-17 each, 1e-4 of a row's largest channel) and, since
-            # the listed blocks are subtracted and added again, that of sums as large as V_max (4e-6 of it)
-            assert np.abs(O2 - O3).max() <= 1e-4 * np.abs(O3).max() + 4e-6 * cert3["v_max"].max()
-            assert np.allclose(cert2["lse"], cert3["lse"], rtol=5e-6, atol=0)
+        # the selector reduces the same sets, and the adaptive reduction merges 32 more
+        tol, sel = oracle.Tolerances(), ad.SelectorParams(0.995, 2, 16, 16)
+        check_against_oracle(oc, q, tol, sel, gpu_adaptive(gc, q, tol, sel))
