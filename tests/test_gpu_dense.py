@@ -90,7 +90,7 @@ def test_a_paged_group_of_a_large_layer_takes_no_longer_than_one_of_a_small_laye
 
     from helpers import load_binding
     print("fallback time", flush=True)
-    from paper_2605_20868_amd import binding as cqa
+    cqa = load_binding()
     n, most, took = 32768, 17, []
     t2 = [torch.empty(most * 8 * n * 128, dtype=torch.float16, pin_memory=True) for _ in range(2)]
     for bt in (1, most):
@@ -122,7 +122,7 @@ def test_more_kv_groups_than_one_launch_holds():
 
     from helpers import load_binding
     print("dense launches", flush=True)
-    from paper_2605_20868_amd import binding as cqa
+    cqa = load_binding()
     groups = 8388608 + 5
     v = torch.randn((groups, 128), device="cuda", dtype=torch.float16)
     O = torch.full((groups, 128), float("nan"), dtype=torch.float32, device="cuda")
@@ -178,7 +178,9 @@ def test_an_infinite_value_stays_infinite(bt, hkv, g, n):
 def test_heads_of_a_group_in_parts(bt, hkv, g, n):
     """Few workgroups: the heads of a KV group are served by workgroups of their own."""
     import torch
-    from paper_2605_20868_amd import binding as cqa
+
+    from helpers import load_binding
+    cqa = load_binding()
     print("parts", bt, hkv, g, n, flush=True)
     gen = torch.Generator(device="cuda").manual_seed(n + bt)
     k, v = (torch.randn((bt, hkv, n, 128), generator=gen, device="cuda").half() for _ in range(2))
