@@ -509,7 +509,7 @@ struct CompactArgs {
   int32_t* ulist;      // [Bt][Hkv][MAX_UNION]
   int32_t* ucount;     // [Bt][Hkv]
   int nb;
-  // FP16 scratch of the layer (sc_slots = 0: off)
+  // FP16 scratch of the layer
   int32_t* sc_map;     // [Bt][Hkv][sc_map_stride]
   int64_t sc_map_stride;
   int32_t* sc_tag;     // [Bt][Hkv][sc_cap]
@@ -614,7 +614,6 @@ __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
   }
   const int s_base_final = base_total;
   if (tid == 0) a.ucount[grp] = min(s_base_final, MAX_UNION);
-  if (a.sc_slots <= 0) return;
 
   // ---- FP16 scratch: which listed blocks are held on the device, and where the others go.
   // A promoted block found in the map keeps its slot (stamped with this step); a half of it (keys,
@@ -753,7 +752,11 @@ struct AdaptiveReduceArgs {
   int parts;
   float* alpha_out;      // [Bt][Hq]
   const float* score_dev;  // [Bt][Hq] canary deviations, or null
-  int pos_set0, pos_set1;  // the promoted-block pass's positive partial sets
+  // The promoted-block pass's positive partial sets.  Those outside [pos_set0, pos_set1) -- the one pass over all sealed
+  // blocks and the negated sets that take the listed blocks back out of it -- contribute their output
+  // accumulators only.  A difference of two nearly equal sums would leave the certificate's
+  // scalars with the rounding of the large terms, so these come from the scan over the block log-masses.
+  int pos_set0, pos_set1;
   const int32_t* ulist;  // [Bt][Hkv][MAX_UNION] listed blocks of the group
   const int32_t* ucount; // [Bt][Hkv]
 };

@@ -218,7 +218,6 @@ struct DecodeArgs {
   int pstride;         // partial sets per (batch, q-head) row of `partials` (>= nsplit)
   int int8_query;      // matrix-core pass: 1 = INT8 x INT8 scoring of the quantised scaled query
   int finish;          // matrix-core pass: 1 = it finishes the rows of a single split itself
-  int keep_sets;       // matrix-core pass: 1 = the partial sets are read by a later launch too
   int wpb;             // matrix-core pass: waves per workgroup, 8 or 4 (split_geometry)
   // promoted-block pass of the adaptive decode
   __half* sc_k;             // layer base of the FP16 scratch's key halves [Bt * Hkv][sc_cap][16][128], or null

@@ -859,7 +859,6 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     a.stream_nt = stream_nt(c, nb);
     a.int8_query = tol.int8_query;
     a.wpb = wpb;
-    a.keep_sets = pstride > 0 ? 1 : 0;
     // With a mirror of the flag words in host memory the four waves that finish a group of four heads store neighbouring
     // words at the same moment, and such stores wait for one another: from there on a launch of its own is
     // the cheaper place.  A step of 4 heads per group, this launch finishing the rows and the reduction: 32 rows

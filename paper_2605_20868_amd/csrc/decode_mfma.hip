@@ -683,11 +683,10 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   if (w < G) {
     float2 o2;
     const OctState st = merge_lds(ms[0][w], G * 12, mo[0][w], G * D, W, o2);
-    if (!finish || a.keep_sets) {
+    if (!finish) {
       float* pp = a.partials + (((int64_t)b * a.n_q + hq0 + w) * a.pstride + split) * PART_FLOATS;
       store_state(st, o2, pp, pp + P_O);
-    }
-    if (finish) {
+    } else {
       TrailState ts{};
       if (ra.r > 0) ts = trail_state(ra, tr);
       const HeadState hs = head_state(st, o2);

@@ -237,14 +237,9 @@ struct AdaptiveIn {
   int top_block;     // the promoted block with the largest FP16 log-mass (-1 if none)
   int rank_fail;     // the two rankings disagree on the top block, or the boundary test failed
   int precond;       // the score-consistency check found a score outside its declared bound
-  // The partial sets outside [pos_set0, pos_set1) -- the one pass over all sealed blocks and the
-  // negated sets that take the listed blocks back out of it -- contribute their output
-  // accumulators only.  A difference of two nearly equal sums would leave the certificate's
-  // scalars with the rounding of the large terms, so the mass, the value term and the largest
-  // rho_b eta_b of the blocks that are NOT listed come from the scan over the block log-masses
-  // instead, relative to the first pass's lse8:  L8u = sum exp(l_b - lse8),
+  // The mass, the value term and the largest rho_b eta_b of the blocks that are NOT listed, from the scan over the
+  // block log-masses, relative to the first pass's lse8:  L8u = sum exp(l_b - lse8),
   // EV8u = sum exp(l_b - lse8) eta_b,  maxc8 = max exp(l_b - lse8) eta_b.
-  int pos_set0, pos_set1;
   float L8u, EV8u, maxc8, lse8;
 };
 
