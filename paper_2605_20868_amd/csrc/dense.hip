@@ -639,6 +639,7 @@ int32_t launch_dense(const __half* q, const __half* k, const __half* v, int grou
                      int64_t layer_groups, int64_t n_tokens, float* O, const uint32_t* select, cqa_head_cert* cert,
                      uint32_t* flags, int rung, float* ws, hipStream_t st) {
   if (n_tokens <= 0 || groups <= 0) return CQA_ERR_INVALID_ARG;
+  if (group != 1 && group != 2 && group != 4) return CQA_ERR_UNSUPPORTED;   // the kernels and the parts below are for these
   const int64_t tiles = (n_tokens + DENSE_TILE - 1) / DENSE_TILE;
   DenseArgs a{};
   a.q = q;
@@ -660,7 +661,6 @@ int32_t launch_dense(const __half* q, const __half* k, const __half* v, int grou
   a.by_wave = groups == 1 && a.nsplit < PAGED_WG && a.tiles_per_split > DENSE_WAVES &&
               a.nsplit * DENSE_WAVES <= dense_ws_units(n_tokens);
   if (a.by_wave) {
-    if (group != 1 && group != 2 && group != 4) return CQA_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(dense_paged_kernel, dim3((unsigned)(a.nsplit * DENSE_WAVES), (unsigned)group), dim3(64), 0, st, a);
   } else {
     // a grid dimension holds fewer than 2^32 threads: 8388607 workgroups a launch (as many KV groups: with so many of
@@ -691,8 +691,7 @@ int32_t launch_dense(const __half* q, const __half* k, const __half* v, int grou
       switch (group) {
         case 1: hipLaunchKernelGGL((dense_split_kernel<1, false>), grid, dim3(64 * DENSE_WAVES), 0, st, chunk); break;
         case 2: hipLaunchKernelGGL((dense_split_kernel<2, false>), grid, dim3(64 * DENSE_WAVES), 0, st, chunk); break;
-        case 4: hipLaunchKernelGGL((dense_split_kernel<4, false>), grid, dim3(64 * DENSE_WAVES), 0, st, chunk); break;
-        default: return CQA_ERR_UNSUPPORTED;
+        default: hipLaunchKernelGGL((dense_split_kernel<4, false>), grid, dim3(64 * DENSE_WAVES), 0, st, chunk); break;
       }
     }
   }

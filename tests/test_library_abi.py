@@ -70,3 +70,14 @@ def test_host_side_argument_checks_need_no_gpu():
     except cqa.CqaError as e:
         assert e.status == cqa.ERR_INVALID_ARG
     assert "Tier 2" in cqa.cqa_strerror(cqa.ERR_NO_TIER2)
+
+
+def test_the_dense_call_refuses_groups_it_has_no_kernel_for():
+    """Refused on the host, before anything is read: the addresses are not."""
+    cqa = load_binding()
+    for heads, kv, status in ((8, 1, cqa.ERR_UNSUPPORTED), (3, 1, cqa.ERR_UNSUPPORTED), (16, 2, cqa.ERR_UNSUPPORTED), (6, 4, cqa.ERR_INVALID_ARG)):
+        try:
+            cqa.cqa_dense_attention(4096, 4096, 4096, 1, heads, kv, 100, 4096, 4096)
+            assert False, "expected an error"
+        except cqa.CqaError as e:
+            assert e.status == status, (heads, kv)
