@@ -497,13 +497,8 @@ __global__ __launch_bounds__(ST) void select_kernel(SelectArgs a) {
 }
 
 struct CompactArgs {
-  uint32_t explore_threshold;   // a block is explored (key-promoted) when its draw is below this; 0 = off
-  uint32_t explore_seed;
-  const uint32_t* vmask;   // [Bt][Hq][mask_words] value selections per head (null = none)
-  const uint32_t* umask;   // [Bt][Hq][mask_words] key selections per head
-  int64_t mask_words;
+  PromMasks masks;
   int group;           // query heads per KV group
-  int per_head;        // 1: a head's promoted sets are its own selections; 0: the group's unions
   int32_t* slot;       // [Bt][Hkv][slot_stride]
   int64_t slot_stride;
   int32_t* ulist;      // [Bt][Hkv][MAX_UNION]
@@ -528,8 +523,6 @@ struct CompactArgs {
 __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
   const int tid = threadIdx.x;
   const int64_t grp = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  const uint32_t* um = a.umask + grp * a.group * a.mask_words;        // the group's heads are consecutive rows
-  const uint32_t* vm = a.vmask != nullptr ? a.vmask + grp * a.group * a.mask_words : nullptr;
   int32_t* slot = a.slot + grp * a.slot_stride;
   int32_t* ulist = a.ulist + grp * MAX_UNION;
   const int words = (a.nb + 31) >> 5;
@@ -543,55 +536,21 @@ __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
   int base_total = 0;
   for (int w00 = 0; w00 < words; w00 += 256 * WPT_MAX) {
     const int wpt_here = min(wpt, WPT_MAX);
-    uint32_t kb[WPT_MAX], vb[WPT_MAX], khh[WPT_MAX][4], vhh[WPT_MAX][4];
+    PromBits m[WPT_MAX];
     int cnt = 0;
 #pragma unroll
     for (int u = 0; u < WPT_MAX; ++u) {
       const int w = w00 + tid * wpt_here + u;
-      uint32_t kbits = 0u, vbits = 0u;
-      uint32_t kh[4] = {0u, 0u, 0u, 0u}, vh[4] = {0u, 0u, 0u, 0u};   // per head
-      if (u < wpt_here && w < words) {
-        for (int i = 0; i < a.group; ++i) {
-          kh[i] = um[i * a.mask_words + w];
-          kbits |= kh[i];
-          if (vm != nullptr) {
-            vh[i] = vm[i * a.mask_words + w];
-            vbits |= vh[i];
-          }
-        }
-        if (a.explore_threshold != 0u) {
-          uint32_t ebits = 0u;
-#pragma unroll 4
-          for (int j = 0; j < 32; ++j)
-            if (explore_mix((uint32_t)(w * 32 + j), (uint32_t)grp, a.explore_seed) < a.explore_threshold)
-              ebits |= 1u << j;
-          kbits |= ebits;                          // explored blocks are promoted for every head
-          for (int i = 0; i < a.group; ++i) kh[i] |= ebits;
-        }
-        if (w == words - 1 && (a.nb & 31)) {      // nothing past nb
-          kbits &= (1u << (a.nb & 31)) - 1u;
-          vbits &= (1u << (a.nb & 31)) - 1u;
-        }
-        for (int i = 0; i < 4; ++i) {
-          kh[i] = i < a.group ? (a.per_head ? kh[i] & kbits : kbits) : 0u;
-          vh[i] = i < a.group ? (a.per_head ? vh[i] & vbits : vbits) : 0u;
-        }
-      }
-      kb[u] = kbits;
-      vb[u] = vbits;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        khh[u][i] = kh[i];
-        vhh[u][i] = vh[i];
-      }
-      cnt += __popc(kbits | vbits);
+      m[u].k = m[u].v = 0u;
+      if (u < wpt_here && w < words) m[u] = prom_bits(a.masks, grp, a.group, w, ~0u);
+      cnt += __popc(m[u].k | m[u].v);
     }
     int pos = base_total + block_scan_incl<int>(cnt, itot_c, tid) - cnt;   // slot of my run's first promoted block
     if (tid == 255) s_base = pos + cnt;
 #pragma unroll
     for (int u = 0; u < WPT_MAX; ++u) {
       const int w = w00 + tid * wpt_here + u;
-      uint32_t bits = kb[u] | vb[u];
+      uint32_t bits = m[u].k | m[u].v;
       while (bits != 0u) {
         const int j = __ffs((int)bits) - 1;
         bits &= bits - 1u;
@@ -599,11 +558,7 @@ __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
         // the list cannot overflow (4 heads x MAX_K_LIMIT for keys and as many for values);
         // a block that did not fit would simply stay unpromoted
         if (pos < MAX_UNION) {
-          uint32_t f = ((kb[u] >> j) & 1u) | (((vb[u] >> j) & 1u) << 1);
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            f |= (((khh[u][i] >> j) & 1u) << (SLOT_HK_SHIFT + i)) | (((vhh[u][i] >> j) & 1u) << (SLOT_HV_SHIFT + i));
-          slot[blk] = (int)f;
+          slot[blk] = prom_flags(m[u], j);
           ulist[pos] = blk;
         }
         ++pos;
@@ -1021,14 +976,10 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   // ---- 3. with the FP16 scratch, flag words and ordered list per group
   const double thr = (double)sel.explore_frac * 4294967296.0;
   const uint32_t explore_threshold = sel.explore_frac > 0.0f ? (uint32_t)std::min(thr, 4294967295.0) : 0u;
+  const PromMasks masks{w.umask, values ? w.vmask : nullptr, w.mask_words, (int)nb, sel.per_head, explore_threshold, sel.explore_seed};
   CompactArgs ca{};
-  ca.explore_threshold = explore_threshold;
-  ca.explore_seed = sel.explore_seed;
-  ca.vmask = values ? w.vmask : nullptr;
-  ca.umask = w.umask;
+  ca.masks = masks;
   ca.group = g;
-  ca.per_head = sel.per_head;
-  ca.mask_words = w.mask_words;
   ca.slot = w.slot;
   ca.slot_stride = c->nq_cap * 4;
   ca.ulist = w.ulist;
@@ -1094,12 +1045,8 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   a.max_tokens = c->desc.max_tokens;
   a.split0 = nsplit;
   PromArgs pa{};
-  pa.umask = w.sc_slots > 0 ? nullptr : w.umask;
-  pa.vmask = values ? w.vmask : nullptr;
-  pa.mask_words = w.mask_words;
-  pa.per_head = sel.per_head;
-  pa.explore_threshold = explore_threshold;
-  pa.explore_seed = sel.explore_seed;
+  pa.masks = masks;
+  if (w.sc_slots > 0) pa.masks.umask = nullptr;
   pa.slot = w.slot;
   pa.ulist = w.ulist;
   pa.ucount = w.ucount;

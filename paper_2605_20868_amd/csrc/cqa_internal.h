@@ -244,18 +244,24 @@ struct DecodeArgs {
 };
 
 
+// What the selector leaves behind, and which promoted sets follow from it.
+struct PromMasks {
+  const uint32_t* umask;    // [Bt][Hq][mask_words] key selections per head
+  const uint32_t* vmask;    // value selections, or null
+  int64_t mask_words;
+  int nb;
+  int per_head;             // 1: a head's promoted sets are its own selections; 0: the group's unions
+  uint32_t explore_threshold;   // a block is explored (key-promoted) when its draw is below this; 0 = off
+  uint32_t explore_seed;
+};
+
 // The promoted-block pass's part of the adaptive step besides DecodeArgs.  Orders of its workgroups: per KV group those of the
 // positive sets, of the negated sets and of the sums; all passes and then all sums; the positive sets and the sums per
 // KV group, then the negated sets, the last `ahead` of them moved to the front.
 constexpr int PROM_BY_GROUP = 0, PROM_SUMS_LAST = 1, PROM_WRAPPED = 2;
 struct PromArgs {
-  const uint32_t* umask;    // [Bt][Hq][mask_words] key selections per head, or null: the list and the flag words are
-                            // there already (compact_kernel, which looks after the FP16 scratch)
-  const uint32_t* vmask;    // value selections, or null
-  int64_t mask_words;
-  int per_head;             // 1: a head's promoted sets are its own selections; 0: the group's unions
-  uint32_t explore_threshold;   // a block is explored (key-promoted) when its draw is below this; 0 = off
-  uint32_t explore_seed;
+  PromMasks masks;          // umask null: the list and the flag words are there already (compact_kernel, which looks after
+                            // the FP16 scratch)
   int32_t* slot;            // written from the masks: the flag words of the listed blocks, ...
   int32_t* ulist;           // ... the list, ascending, ...
   int32_t* ucount;          // ... its length

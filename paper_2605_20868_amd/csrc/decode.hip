@@ -27,43 +27,6 @@ namespace cqa {
 //               block is attended from its FP16 values and counts with eta_b = 0; both kinds of
 //               originals are read by the device straight from the pinned Tier-2 arrays over the
 //               host link.  Writes partial sets split0 + blockIdx.x.
-// Promotion bits of one word (32 blocks) of a KV group, from its heads' masks: key bits kh and value bits vh per head;
-// explored blocks are key-promoted for every head, and with per-group promotion every head has the unions.
-struct PromBits {
-  uint32_t kh[4], vh[4], k, v;
-};
-__device__ __forceinline__ PromBits prom_bits(const DecodeArgs& a, const PromArgs& p, int64_t grp, int group, int word, uint32_t only) {
-  PromBits r;
-  r.k = r.v = 0u;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t at = (grp * group + i) * p.mask_words + word;
-    r.kh[i] = i < group ? p.umask[at] & only : 0u;
-    r.vh[i] = i < group && p.vmask != nullptr ? p.vmask[at] & only : 0u;
-    r.k |= r.kh[i];
-    r.v |= r.vh[i];
-  }
-  if (p.explore_threshold != 0u) {
-    uint32_t x = 0u;
-    for (uint32_t m = only; m != 0u; m &= m - 1u) {
-      const int j = __ffs((int)m) - 1;
-      if (explore_mix((uint32_t)(word * 32 + j), (uint32_t)grp, p.explore_seed) < p.explore_threshold) x |= 1u << j;
-    }
-    r.k |= x;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r.kh[i] |= x;
-  }
-  const uint32_t in = word * 32 + 32 <= a.nb ? ~0u : (1u << (a.nb & 31)) - 1u;   // nothing past nb
-  r.k &= in;
-  r.v &= in;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    r.kh[i] = i < group ? (p.per_head ? r.kh[i] & in : r.k) : 0u;
-    r.vh[i] = i < group ? (p.per_head ? r.vh[i] & in : r.v) : 0u;
-  }
-  return r;
-}
-
 // The share of workgroup psplit in its KV group's list of promoted blocks, which is dealt in fours: positions 4 psplit .. + 3, and
 // every 4 * PROM_SPLITS further, to s_blk (block) and s_pf (flag word); returns the list's length.  The list comes from the
 // selection masks (every workgroup walks them, one, `write`, also stores list and flag words for the reduction),
@@ -74,7 +37,7 @@ __device__ __forceinline__ int prom_list(const DecodeArgs& a, const PromArgs& p,
   const int tid = threadIdx.x;
   int32_t* const slot = p.slot + grp * (a.nq_cap * 4);
   int32_t* const ulist = p.ulist + grp * MAX_UNION;
-  if (p.umask == nullptr) {
+  if (p.masks.umask == nullptr) {
     const int n = min(p.ucount[grp], MAX_UNION);
     const int pos = (tid >> 2) * (4 * PROM_SPLITS) + psplit * 4 + (tid & 3);
     if (pos < n) {
@@ -96,7 +59,7 @@ __device__ __forceinline__ int prom_list(const DecodeArgs& a, const PromArgs& p,
     const int piece = p0 + tid, word = piece >> per, off = (piece & ((1 << per) - 1)) * bits;
     PromBits m;
     m.k = m.v = 0u;
-    if (piece < pieces) m = prom_bits(a, p, grp, group, word, (bits == 32 ? ~0u : (1u << bits) - 1u) << off);
+    if (piece < pieces) m = prom_bits(p.masks, grp, group, word, (bits == 32 ? ~0u : (1u << bits) - 1u) << off);
     uint32_t any = m.k | m.v;
     const int cnt = __popc(any);
     const int upto = total + block_scan_incl<int>(cnt, s_tot, tid);
@@ -107,17 +70,14 @@ __device__ __forceinline__ int prom_list(const DecodeArgs& a, const PromArgs& p,
       const bool mine = ((pos >> 2) & (PROM_SPLITS - 1)) == psplit;
       if (pos >= MAX_UNION || !(mine || write)) continue;
       const int j = __ffs((int)any) - 1, blk = word * 32 + j;
-      uint32_t f = ((m.k >> j) & 1u) | (((m.v >> j) & 1u) << 1);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        f |= (((m.kh[i] >> j) & 1u) << (SLOT_HK_SHIFT + i)) | (((m.vh[i] >> j) & 1u) << (SLOT_HV_SHIFT + i));
+      const int f = prom_flags(m, j);
       if (mine) {
         const int at = (pos / (4 * PROM_SPLITS)) * 4 + (pos & 3);
         s_blk[at] = blk;
-        s_pf[at] = (int)f;
+        s_pf[at] = f;
       }
       if (write) {
-        slot[blk] = (int)f;
+        slot[blk] = f;
         ulist[pos] = blk;
       }
     }
@@ -151,13 +111,13 @@ __device__ __forceinline__ void prom_scan(const DecodeArgs& a, const PromArgs& p
   __shared__ float s_max[4][2];
   __shared__ int s_scan[4], s_total;
   const int b0 = part * SCAN_PART, b1 = min(b0 + SCAN_PART, a.nb);
-  if (p.umask != nullptr) {
+  if (p.masks.umask != nullptr) {
     // blocks listed before this part: they matter only where the list can overflow, which takes explored blocks
     int listed = 0;
-    if (!WAVES && p.explore_threshold != 0u && part > 0) {
+    if (!WAVES && p.masks.explore_threshold != 0u && part > 0) {
       int mine = 0;
       for (int w0 = tid; w0 < b0 >> 5; w0 += 256) {
-        const PromBits m = prom_bits(a, p, grp, group, w0, ~0u);
+        const PromBits m = prom_bits(p.masks, grp, group, w0, ~0u);
         mine += __popc(m.k | m.v);
       }
       const int upto = block_scan_incl<int>(mine, s_scan, tid);
@@ -167,7 +127,7 @@ __device__ __forceinline__ void prom_scan(const DecodeArgs& a, const PromArgs& p
     }
     PromBits m;
     m.k = m.v = m.kh[0] = m.kh[1] = m.kh[2] = m.kh[3] = 0u;
-    if (b0 + tid * 32 < b1) m = prom_bits(a, p, grp, group, (b0 >> 5) + tid, ~0u);
+    if (b0 + tid * 32 < b1) m = prom_bits(p.masks, grp, group, (b0 >> 5) + tid, ~0u);
     uint32_t any = m.k | m.v;
     if (!WAVES) {
       const int upto = listed + block_scan_incl<int>(__popc(any), s_scan, tid);
@@ -190,7 +150,7 @@ __device__ __forceinline__ void prom_scan(const DecodeArgs& a, const PromArgs& p
       const bool in = i < b1;
       b8[j] = in ? l8[i] : 0.0f;
       be[j] = in ? eta[i] : 0.0f;
-      if (p.umask != nullptr) {
+      if (p.masks.umask != nullptr) {
         const int wd = in ? (i - b0) >> 5 : 0;
         bs[j] = !in || ((s_key[wd] >> (i & 31)) & 1u) ? kbit : (int)((s_any[wd] >> (i & 31)) & 1u);
       } else {

@@ -673,4 +673,50 @@ __device__ __forceinline__ uint32_t explore_mix(uint32_t blk, uint32_t grp, uint
   return x;
 }
 
+// Promotion bits of one word (32 blocks) of a KV group, from its heads' masks: key bits kh and value bits vh per head;
+// explored blocks are key-promoted for every head, and with per-group promotion every head has the unions.
+struct PromBits {
+  uint32_t kh[4], vh[4], k, v;
+};
+__device__ __forceinline__ PromBits prom_bits(const PromMasks& p, int64_t grp, int group, int word, uint32_t only) {
+  PromBits r;
+  r.k = r.v = 0u;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int64_t at = (grp * group + i) * p.mask_words + word;
+    r.kh[i] = i < group ? p.umask[at] & only : 0u;
+    r.vh[i] = i < group && p.vmask != nullptr ? p.vmask[at] & only : 0u;
+    r.k |= r.kh[i];
+    r.v |= r.vh[i];
+  }
+  if (p.explore_threshold != 0u) {
+    uint32_t x = 0u;
+    for (uint32_t m = only; m != 0u; m &= m - 1u) {
+      const int j = __ffs((int)m) - 1;
+      if (explore_mix((uint32_t)(word * 32 + j), (uint32_t)grp, p.explore_seed) < p.explore_threshold) x |= 1u << j;
+    }
+    r.k |= x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.kh[i] |= x;
+  }
+  const uint32_t in = word * 32 + 32 <= p.nb ? ~0u : (1u << (p.nb & 31)) - 1u;   // nothing past nb
+  r.k &= in;
+  r.v &= in;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    r.kh[i] = i < group ? (p.per_head ? r.kh[i] & in : r.k) : 0u;
+    r.vh[i] = i < group ? (p.per_head ? r.vh[i] & in : r.v) : 0u;
+  }
+  return r;
+}
+// flag word of the word's block j: bit 0 some head scores it with FP16 keys, bit 1 some head attends its FP16 values, then
+// which heads
+__device__ __forceinline__ int prom_flags(const PromBits& m, int j) {
+  uint32_t f = ((m.k >> j) & 1u) | (((m.v >> j) & 1u) << 1);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    f |= (((m.kh[i] >> j) & 1u) << (SLOT_HK_SHIFT + i)) | (((m.vh[i] >> j) & 1u) << (SLOT_HV_SHIFT + i));
+  return (int)f;
+}
+
 }  // namespace cqa
