@@ -1065,11 +1065,15 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   // 941.1, 939.1, 942.5; 14 groups 1172.9, 1186.2, 1174.6; 8 groups of 128K, 128 blocks a head 386.5, 377.0, 376.2, few
   // blocks 86.5, 86.8, 89.7; 14 groups, few blocks 265.6, 267.6, 269.6.
   int64_t wgs = (int64_t)(2 * PROM_SPLITS + g * pa.parts) * pa.groups;
-  pa.order = wgs > 2 * c->n_cu ? PROM_SUMS_LAST : (2 * wgs > 3 * c->n_cu || wgs <= c->n_cu ? PROM_BY_GROUP : PROM_WRAPPED);
+  // With the FP16 scratch, originals mostly lie on the device and the sums are the longer part: last there (512
+  // slots, 8 and 9 groups of 4000 tokens: group by group 51.1, 54.3, wrapped 54.0, 54.8, last 50.2, 50.8).
+  const bool many = wgs > 2 * c->n_cu;
+  pa.order = many ? PROM_SUMS_LAST
+                  : (2 * wgs > 3 * c->n_cu || wgs <= c->n_cu ? PROM_BY_GROUP : (w.sc_slots > 0 ? PROM_SUMS_LAST : PROM_WRAPPED));
   // Sums that come last run while nothing is fetched any more, so for many groups of short contexts a workgroup takes a group's
   // heads, a wave each: 64 x 8 groups, 4 heads, of 500 tokens 1301.5 -> 1272.8 us, of 550 1421.5 -> 1389.7, of 700 1738.7 -> 1718.6,
   // of 1300 3187.0 -> 3175.5; level from 10000 tokens on, which is where a wave takes more than a trip.
-  if (pa.order == PROM_SUMS_LAST && nb <= SUM_WAVE_BLOCKS) {
+  if (many && nb <= SUM_WAVE_BLOCKS) {
     pa.sum_waves = 1;
     wgs = (int64_t)(2 * PROM_SPLITS + 1) * pa.groups;
   }

@@ -100,22 +100,25 @@ def test_a_full_list_leaves_the_last_blocks_in_int8(blocks, frac, slots):
 
 # (batch, kv heads, group, blocks): up to one workgroup per compute unit, somewhat more, two and more (sums by a wave each and
 # by a workgroup each), sums in one part and in two, short lists, which reach few of a group's workgroups
-@pytest.mark.parametrize("bt,hkv,g,blocks", [
-    (1, 7, 2, 300), (1, 8, 4, 300), (2, 5, 4, 130), (1, 8, 2, 8200), (1, 12, 4, 90), (2, 10, 4, 65), (4, 8, 4, 3), (4, 8, 4, 13),
-    (5, 7, 2, 28), (4, 9, 1, 29), (1, 9, 1, 25), (4, 9, 2, 513), (2, 8, 4, 2048), (2, 8, 4, 2049)])
-def test_rows_do_not_depend_on_the_order_of_the_workgroups(bt, hkv, g, blocks):
+# (sums last there, too, with the FP16 scratch in use)
+@pytest.mark.parametrize("bt,hkv,g,blocks,slots", [
+    (1, 7, 2, 300, 0), (1, 8, 4, 300, 0), (1, 8, 4, 300, 16), (2, 5, 4, 130, 0), (1, 8, 2, 8200, 0), (1, 12, 4, 90, 0), (2, 10, 4, 65, 0),
+    (4, 8, 4, 3, 0), (4, 8, 4, 13, 0), (5, 7, 2, 28, 0), (4, 9, 1, 29, 0), (1, 9, 1, 25, 0), (4, 9, 2, 513, 0), (4, 9, 2, 40, 16),
+    (2, 8, 4, 2048, 0), (2, 8, 4, 2049, 0)])
+def test_rows_do_not_depend_on_the_order_of_the_workgroups(bt, hkv, g, blocks, slots):
     """Every KV group's rows are bit for bit those of a cache of its own, whose workgroups all lie one after another."""
     n = blocks * 16 + 3
     rng = np.random.Generator(np.random.Philox(blocks * 100 + hkv))
     k, v = workloads.student_t3_f16(rng, (bt, hkv, n, 128)), workloads.normal_f16(rng, (bt, hkv, n, 128))
     q = workloads.normal_f16(rng, (bt, hkv * g, 128))
-    print("order", bt, hkv, g, blocks, flush=True)
+    print("order", bt, hkv, g, blocks, slots, flush=True)
     for b, h in [(slice(None), slice(None))] + [(i, j) for i in range(bt) for j in range(hkv)][::3]:
         whole = isinstance(b, slice)
         kk, vv, qq = (k, v, q) if whole else (k[b:b + 1, h:h + 1], v[b:b + 1, h:h + 1], q[b:b + 1, h * g:(h + 1) * g])
         with GpuLayerCache(kk.shape[0], kk.shape[1] * g, kk.shape[1], n + 16) as gc:
             gc.append(kk, vv)
             gc.cqa.cqa_set_splits(gc.h, 2)
+            gc.cqa.cqa_set_scratch_slots(gc.h, slots)
             tol = gc.cqa.Tolerances(rank_depth=2, v_tol=0.02)
             O, cert, flags, st = run(gc, qq, tol, gc.cqa.Selector(0.995, 2, 40, 40, v_limit=16, canary=True))
         if whole:
