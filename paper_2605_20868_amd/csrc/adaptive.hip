@@ -762,24 +762,9 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
                                    a.pos_set1, o2);
     store_state(st, o2, sm.sc[w], sm.o[w]);
   } else if (w == RED_WAVES) {
-    if (ra.r > 0) {
-      TrailRegs tr;
-      load_trail(ra, b, hq, nullptr, nullptr, tr);
-      const TrailState ts = trail_state(ra, tr);
-      *reinterpret_cast<float2*>(&sm.trail_o[2 * l]) = ts.o;
-      if (l == 0) {
-        sm.trail[0] = ts.M;
-        sm.trail[1] = ts.L;
-        sm.trail[2] = ts.V;
-      }
-    }
+    trail_part(ra, b, hq, sm);
   } else {
-    const KeyTerms kt = key_terms(ra, delta);
-    if (l == 0) {
-      sm.key[0] = kt.full;
-      sm.key[1] = kt.grow;
-      sm.key[2] = kt.widen;
-    }
+    key_part(ra, delta, sm);
     ScanPart t{0.0, 0.0, 0.0, -INFINITY, 0.0f};
     for (int i = l; i < a.parts; i += 64) {
       const ScanPart x = a.scan[row * a.parts + i];
@@ -903,8 +888,7 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
   if (l == 0) a.alpha_out[row] = ad.alpha;
   float2 o2;
   const OctState st = merge_lds(sm.sc[0], 12, sm.o[0], D, RED_WAVES, o2);
-  const TrailState ts{sm.trail[0], sm.trail[1], sm.trail[2], *reinterpret_cast<const float2*>(&sm.trail_o[2 * l])};
-  finish_head(ra, b, hq, head_state(st, o2), ts, KeyTerms{sm.key[0], sm.key[1], sm.key[2]}, &ad);
+  finish_head(ra, b, hq, head_state(st, o2), trail_of(sm), key_of(sm), &ad);
 }
 
 }  // namespace

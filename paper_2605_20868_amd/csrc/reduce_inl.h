@@ -610,6 +610,33 @@ struct ReduceSmem {
   float trail_o[D];
   float trail[4], key[4];
 };
+// the parts of the waves beside the merging ones, and what they leave, in every lane
+__device__ __forceinline__ void trail_part(const ReduceArgs& a, int b, int hq, ReduceSmem& sm) {
+  if (a.r <= 0) return;
+  const int l = threadIdx.x & 63;
+  TrailRegs tr;
+  load_trail(a, b, hq, nullptr, nullptr, tr);
+  const TrailState ts = trail_state(a, tr);
+  *reinterpret_cast<float2*>(&sm.trail_o[2 * l]) = ts.o;
+  if (l == 0) {
+    sm.trail[0] = ts.M;
+    sm.trail[1] = ts.L;
+    sm.trail[2] = ts.V;
+  }
+}
+__device__ __forceinline__ void key_part(const ReduceArgs& a, float delta, ReduceSmem& sm) {
+  const KeyTerms kt = key_terms(a, delta);
+  if ((threadIdx.x & 63) == 0) {
+    sm.key[0] = kt.full;
+    sm.key[1] = kt.grow;
+    sm.key[2] = kt.widen;
+  }
+}
+__device__ __forceinline__ TrailState trail_of(const ReduceSmem& sm) {
+  return TrailState{sm.trail[0], sm.trail[1], sm.trail[2], *reinterpret_cast<const float2*>(&sm.trail_o[2 * (threadIdx.x & 63)])};
+}
+__device__ __forceinline__ KeyTerms key_of(const ReduceSmem& sm) { return KeyTerms{sm.key[0], sm.key[1], sm.key[2]}; }
+
 __device__ __forceinline__ bool reduce_row(const ReduceArgs& a, int b, int hq, int waves, ReduceSmem& sm, HeadRow& row) {
   const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = min(waves - 2, RED_WAVES);
@@ -620,32 +647,16 @@ __device__ __forceinline__ bool reduce_row(const ReduceArgs& a, int b, int hq, i
     st = merge_sets(part, 8 * w, 8 * nw, a.nsplit, 0, a.nsplit, o2);
     if (nw > 1) store_state(st, o2, sm.sc[w], sm.o[w]);
   } else if (w == nw) {
-    if (a.r > 0) {
-      TrailRegs tr;
-      load_trail(a, b, hq, nullptr, nullptr, tr);
-      const TrailState ts = trail_state(a, tr);
-      *reinterpret_cast<float2*>(&sm.trail_o[2 * l]) = ts.o;
-      if (l == 0) {
-        sm.trail[0] = ts.M;
-        sm.trail[1] = ts.L;
-        sm.trail[2] = ts.V;
-      }
-    }
+    trail_part(a, b, hq, sm);
   } else if (w == nw + 1) {
     float delta = 0.0f;
     for (int s = l; s < a.nsplit; s += 64) delta = fmaxf(delta, part[(int64_t)s * PART_FLOATS + P_DMAX]);
-    const KeyTerms kt = key_terms(a, wave_max(delta));
-    if (l == 0) {
-      sm.key[0] = kt.full;
-      sm.key[1] = kt.grow;
-      sm.key[2] = kt.widen;
-    }
+    key_part(a, wave_max(delta), sm);
   }
   __syncthreads();
   if (w != 0) return false;
   if (nw > 1) st = merge_lds(sm.sc[0], 12, sm.o[0], D, nw, o2);
-  const TrailState ts{sm.trail[0], sm.trail[1], sm.trail[2], *reinterpret_cast<const float2*>(&sm.trail_o[2 * l])};
-  row = finish_row(a, head_state(st, o2), ts, KeyTerms{sm.key[0], sm.key[1], sm.key[2]}, nullptr);
+  row = finish_row(a, head_state(st, o2), trail_of(sm), key_of(sm), nullptr);
   return true;
 }
 
