@@ -72,8 +72,8 @@ constexpr int ST = 1024;          // threads of the selector workgroup
 constexpr int SBATCH = 8;         // loads in flight per thread
 
 // The selector walks its row of log-masses several times.  Rows of up to LDS_KEYS blocks are read
-// from memory once, as order-preserving integer keys kept in LDS; longer rows are re-read.
-constexpr int LDS_KEYS = 10240;   // 40 KB: contexts up to 160K tokens
+// from memory once, as order-preserving integer keys and their histogram bins kept in LDS; longer rows are re-read.
+constexpr int LDS_KEYS = 10240;   // 40 KB of keys, 20 KB of bins: contexts up to 160K tokens
 #define CQA_KEY_PASS(ROW, N, TID, CACHED, KEYS, BODY)                             \
   for (int base__ = 0; base__ < (N); base__ += ST * SBATCH) {                      \
     uint32_t key__[SBATCH];                                                         \
@@ -555,8 +555,8 @@ __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
         const int j = __ffs((int)bits) - 1;
         bits &= bits - 1u;
         const int blk = w * 32 + j;
-        // the list cannot overflow (4 heads x MAX_K_LIMIT for keys and as many for values);
-        // a block that did not fit would simply stay unpromoted
+        // the list cannot overflow (4 heads x MAX_K_LIMIT for keys and as many for values) but by explored blocks;
+        // one that does not fit stays unpromoted
         if (pos < MAX_UNION) {
           slot[blk] = prom_flags(m[u], j);
           ulist[pos] = blk;

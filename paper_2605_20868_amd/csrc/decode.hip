@@ -20,13 +20,6 @@
 
 namespace cqa {
 
-// PROM = false: the vector-ALU split pass over a contiguous range of sealed blocks (INT8 keys).
-// PROM = true : the promoted-block pass of the adaptive decode (gated precision): the workgroups
-//               of a KV group walk the group's list of promoted blocks.  A key-promoted block is
-//               scored from its FP16 keys (sigma = 1, z = 0, no score error), a value-promoted
-//               block is attended from its FP16 values and counts with eta_b = 0; both kinds of
-//               originals are read by the device straight from the pinned Tier-2 arrays over the
-//               host link.  Writes partial sets split0 + blockIdx.x.
 // The share of workgroup psplit in its KV group's list of promoted blocks, which is dealt in fours: positions 4 psplit .. + 3, and
 // every 4 * PROM_SPLITS further, to s_blk (block) and s_pf (flag word); returns the list's length.  The list comes from the
 // selection masks (every workgroup walks them, one, `write`, also stores list and flag words for the reduction),
@@ -200,6 +193,14 @@ __device__ __forceinline__ void prom_scan(const DecodeArgs& a, const PromArgs& p
   }
 }
 
+// PROM = false: the vector-ALU split pass over a contiguous range of sealed blocks (INT8 keys).
+// PROM = true : the promoted-block pass of the adaptive decode (gated precision): the workgroups
+//               of a KV group walk the group's list of promoted blocks.  A key-promoted block is
+//               scored from its FP16 keys (sigma = 1, z = 0, no score error), a value-promoted
+//               block is attended from its FP16 values and counts with eta_b = 0; both kinds of
+//               originals are read by the device straight from the pinned Tier-2 arrays over the
+//               host link.  Writes partial sets split0 + split, the split decoded from the
+//               workgroup's linear index.  Further workgroups sum up the blocks left in INT8.
 template <int G, bool PROM>
 __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a, PromArgs p) {
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;

@@ -1,4 +1,7 @@
-// Cross-split reduction of one (batch, query head), executed by ONE wave of 64 lanes.
+// Cross-split reduction of one (batch, query head).  Two forms: reduce_row, by a workgroup of three to ten waves with a
+// barrier (every wave calls it, the first gets the row), and reduce_row_wave, by one wave, its parts in turn; both are
+// built of merge_sets, trail_state, key_terms and finish_row, each by one wave of 64 lanes, and give the same bits for up
+// to eight sets.
 //
 // Merges the per-split partial states (m, l, o[128], value-term sums, maxima, two largest block
 // log-masses) with the usual log-sum-exp factors, attends the trailing FP16 tokens exactly
@@ -7,7 +10,8 @@
 //   E_val = sum_b rho_b eta_b,   E_key = 2 V_max min(tanh Delta_h, min{1, e^{c Delta_h} alpha_hat}(e^{2 Delta_h} - 1))
 // (key_bound_mode 1 / 2 select the second / first factor alone), the interval form of the
 // ranking test  l_(1) - l_(2) <= 2 Delta_h + eps_guard,  and the flag word.
-// Used by the reduction kernels of the one-pass and of the adaptive decode.
+// Used by the split pass (rows of one workgroup), the reduction kernels of the one-pass and of the adaptive decode, the
+// selector and the short steps' launch with the ladder.
 #pragma once
 
 #include "cqa_internal.h"
