@@ -581,7 +581,8 @@ __device__ __forceinline__ HeadRow finish_row(const ReduceArgs& a, const HeadSta
   return row;
 }
 
-__device__ __forceinline__ void store_row(const ReduceArgs& a, int b, int hq, const HeadRow& row) {
+// mirror: the row's own store of its mirrored flag word (the caller makes it otherwise, behind these stores)
+__device__ __forceinline__ void store_row(const ReduceArgs& a, int b, int hq, const HeadRow& row, bool mirror = true) {
   const int l = threadIdx.x & 63;
   const int64_t r = (int64_t)b * a.n_q + hq;
   reinterpret_cast<float2*>(a.O + r * D)[l] = row.out;
@@ -592,7 +593,7 @@ __device__ __forceinline__ void store_row(const ReduceArgs& a, int b, int hq, co
     // last store of this head: a host thread polling the mirror may take the tagged word as
     // "this head's row, certificate and flags have been issued" (device consumers rely on
     // stream order, not on this word)
-    if (a.flags_mirror != nullptr)
+    if (mirror && a.flags_mirror != nullptr)
       __hip_atomic_store(a.flags_mirror + r, row.fl | a.mirror_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }

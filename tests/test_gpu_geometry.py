@@ -71,6 +71,29 @@ def test_steps_of_one_split_give_the_same_rows_on_both_routes(bt, hkv, g, n):
             assert np.array_equal(O, O2) and cert.tobytes() == cert2.tobytes() and (flags == flags2).all()
 
 
+@pytest.mark.parametrize("bt,hkv,g,n", [(1, 1, 4, 125), (9, 2, 1, 125), (9, 2, 2, 125), (9, 2, 4, 125), (17, 1, 4, 70), (70, 8, 2, 64 * 16 + 2)])
+def test_a_host_resolved_step_serves_the_heads_that_ask(bt, hkv, g, n):
+    """The host reads every head's own flag word: a threshold between the heads' bounds, the rows over it are served and no other."""
+    print("mirror", bt, hkv, g, n, flush=True)
+    rng = np.random.default_rng(n + bt + g)
+    k = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    v = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    q = rng.standard_normal((bt, hkv * g, 128)).astype(np.float16)
+    with GpuLayerCache(bt, hkv * g, hkv, n + 16) as gc:
+        gc.append(k, v)
+        O, cert, _ = [x.copy() for x in gc.certified_decode(q)]
+        total = cert["E_key"] + cert["E_val"]
+        order = np.sort(total.ravel())
+        for i in (len(order) // 3, len(order) - 2):
+            eps = float(np.float32(0.5 * (order[i] + order[i + 1])))
+            over = total > np.float32(eps)
+            rung, O2, cert2, flags2 = gc.decode_step(q, gc.cqa.Tolerances(eps_total=eps))
+            assert rung == 3 and 0 < over.sum() < over.size
+            assert ((flags2 & gc.cqa.FLAG_TOTAL) != 0).tolist() == over.tolist()
+            assert (cert2["served_rung"] == np.where(over, 3, 0)).all()
+            assert np.array_equal(O2[~over], O[~over]) and np.isfinite(O2).all()
+
+
 @pytest.mark.parametrize("bt,hkv,g,n", [(70, 8, 2, 64 * 16 + 2), (70, 8, 4, 64 * 16), (72, 8, 2, 64 * 24 + 5)])
 def test_many_rows_of_several_splits_give_the_same_rows_on_both_routes(bt, hkv, g, n):
     """More than 1024 rows are reduced by one wave each where their flags are mirrored to the host and by several waves
