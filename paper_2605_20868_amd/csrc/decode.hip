@@ -648,8 +648,8 @@ __global__ __launch_bounds__(64) void certified_reduce_wave_kernel(ReduceArgs a)
 //     through its only quad 0.9 us earlier (1 sequence of 1029: 13.9 -> 13.3 us, 8 of 1000: 14.4 -> 13.8; 1 of 10000, 20
 //     and 40 sets: 10.75, 9.1; 4 of 16384, 32 and 64: 12.3, 11.8; 1 of 30000, 59 and 118: 12.9, 11.6), up to 128 sets,
 //     which the reduction takes in two trips (1 of 60000, 118 and 235: 14.1, 14.2).  Up to eight quads are one workgroup,
-//     which finishes the rows itself: 300 tokens 12.8 -> 11.6 us, 520 12.9 -> 12.1 (with 16 quads the second
-//     round costs more than the reduction's launch: 13.0 against 14.9).
+//     which finishes the rows itself: 1 KV head of 300 tokens 9.0 -> 7.9 us, of 520 9.2 -> 8.2 (with 16 quads the
+//     second round costs more than the reduction's launch: 8.3 against 12.2).
 //   More sequences than compute units: four-wave workgroups, up to four splits where a last
 //     generation would be nearly empty (288 of 3600: 1 split 91.2, 2 90.9, 3 78.8 us; 384 of 2700: 1
 //     78.5, 2 82.5; 560 of 1900: 1 93.4, 2 84.5, 3 85.1; 704 of 1500: 1 90.3, 2 84.4; 1104 of 950: 1 92.7, 2 95.1).
@@ -820,12 +820,10 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     a.stream_nt = stream_nt(c, nb);
     a.int8_query = tol.int8_query;
     a.wpb = wpb;
-    // With a mirror of the flag words in host memory the four waves that finish a group of four heads store neighbouring
-    // words at the same moment, and such stores wait for one another: from there on a launch of its own is
-    // the cheaper place.  A step of 4 heads per group, this launch finishing the rows and the reduction: 32 rows
-    // 18.0, 20.5 us; 64 20.0, 21.3; 128 23.3, 22.2; 256 27.5, 23.1; 1280 55.7, 45.9.  One or two heads per
-    // group gain at any number: 720 rows 31.0, 34.6; 1440 36.3, 41.0.
-    a.finish = nsplit == 1 && !always && (flags_mirror == nullptr || hq / hkv < 4 || bt * hq <= 64) ? 1 : 0;
+    // The rows of one workgroup's sequences are finished by this launch, whether their flags are mirrored to the host or not.
+    // A host-resolved step, the reduction's launch and this one finishing the rows: 4 heads per group, 32 rows 19.2, 15.9 us; 128
+    // 20.9, 16.2; 256 22.2, 16.5; 1024 27.9, 17.9; 2048 40.6, 25.3; two, 1440 rows 48.6, 35.5; one, 720 42.6, 36.0.
+    a.finish = nsplit == 1 && !always ? 1 : 0;
     // the quantised-query scoring exists in the matrix-core pass (and in the promoted-block pass of
     // the adaptive calls), not in the vector-ALU cross-check kernel
     if (tol.int8_query != 0 && c->variant != 0) return CQA_ERR_UNSUPPORTED;
@@ -862,8 +860,9 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
   const int nw = std::min(std::max((nsplit + 7) / 8, 1), RED_WAVES);
   // With a mirror and more than four rows per compute unit, one wave per row: a row's waves side by side bring the stores
   // to the mirror closer together, where they wait for one another.  A host-resolved step of 4 heads per group, three waves a row and
-  // one: 640 rows 25.2, 26.4 us; 1024 31.8, 32.1; 1152 35.4, 32.4; 2048 44.0, 40.3; 4096 79.3, 67.3; two sets, 2240 rows
-  // 97.7, 91.7.  (Two heads per group: 1152 rows 70.4, 69.8; 1280 56.8, 57.0.)
+  // one: 1152 rows of three sets 79.5, 78.9 us; 2240 of two 97.7, 91.7; 2816 102.1, 97.0.  (Two heads per group, level: 1152
+  // rows 70.4, 69.8; 1280 56.8, 57.0.)  Up to 1024 rows, and without a mirror at any number, three waves: 256 rows 10.4, 10.9 us a
+  // decode; 512 13.4, 13.9; 1152 63.1, 63.6; 2240 70.3, 71.1.
   if (flags_mirror != nullptr && (int64_t)bt * hq > 4 * (int64_t)c->n_cu && nsplit <= 8)
     hipLaunchKernelGGL(certified_reduce_wave_kernel, dim3(hq, bt), dim3(64), 0, st, ra);
   else

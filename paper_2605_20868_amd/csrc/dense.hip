@@ -524,8 +524,9 @@ __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
 // each) in one launch: every workgroup merges all rows, one per wave, and so knows every flag
 // without waiting for another one; the first one writes the rows, leaving out the outputs that a
 // rung replaces, and the others leave unless a head asks for a fallback.  A step in two launches and in one:
-// 4 rows 14.3, 12.3 us at 3 to 8 sets; 8 rows 14.4, 14.1 at 3 sets and 14.3, 13.5 at 8.  (32 rows, two per wave of
-// 16: 13 -> 23 us, the workgroups' copies of the work get in each other's way.)
+// 4 rows 12.4, 10.5 us at 3 sets and 11.8, 10.9 at 8; 8 rows of 8 KV heads 13.3, 12.3 at 3 and 13.0, 12.4 at 8, of
+// 2 KV heads level (11.9, 12.0; 12.1, 12.1).  (32 rows, two per wave of 16, with an earlier merge: 13 -> 23 us, the workgroups'
+// copies of the work get in each other's way.)
 template <int G>
 __global__ __launch_bounds__(64 * FINISH_ROWS) void finish_ladder_kernel(ReduceArgs ra, LadderArgs a) {
   const int r = threadIdx.x >> 6, l = threadIdx.x & 63;   // this wave's row

@@ -48,8 +48,8 @@ def test_results_do_not_depend_on_the_launch_geometry(bt, hkv, g, n, splits):
 
 @pytest.mark.parametrize("bt,hkv,g,n", [(2, 8, 4, 125), (17, 1, 4, 125), (9, 2, 4, 70), (40, 8, 4, 333), (40, 8, 2, 125), (33, 8, 1, 200)])
 def test_steps_of_one_split_give_the_same_rows_on_both_routes(bt, hkv, g, n):
-    """A sequence of one workgroup is finished by the split pass, or, when many rows mirror their flags to the host, by the
-    reduction: the host-resolved step, with its mirror, and the plain call bit for bit, either side of 64 rows."""
+    """A sequence of one workgroup is finished by the split pass, with or without a mirror of its flags: the host-resolved step
+    and the plain call bit for bit, few rows and many."""
     print("one split", bt, hkv, g, n, flush=True)
     rng = np.random.default_rng(n + bt)
     k = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
