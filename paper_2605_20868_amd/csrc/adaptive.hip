@@ -121,8 +121,8 @@ __device__ __forceinline__ void hist_add(uint32_t* hist, uint32_t bin, bool pred
   if (pred) atomicAdd(&hist[bin], 1u);
 }
 
-// Histogram bin of a value in the selector's first pass: not decreasing with the value (the order the
-// selection keeps), 1024 bins where the KL-th best can lie -- log-masses by their distance below the largest
+// Histogram bin of a value in the selector's first pass: not decreasing with the value in the order the
+// selection keeps (that of ord32: what is not a number, with the sign set, is last), 1024 bins where the KL-th best can lie -- log-masses by their distance below the largest
 // one, 1/32 apart up to 16 (diffuse heads), 1/8 up to 64, 1 beyond (heads with a few dominant blocks; a distance below the
 // total log-mass would put all blocks into the last bin where the trailing tokens hold nearly all of it: 128K, such a head
 // 23 us against 10);
@@ -133,6 +133,7 @@ __device__ __forceinline__ int select_bin(float x, float top) {
     const int i = (int)(__float_as_uint(x) >> 20) - 18;
     return __float_as_uint(x) >> 31 ? 0 : min(max(i, 0), ST - 1);
   }
+  if (__float_as_uint(x) > 0xFF800000u) return 0;
   const float d = top - x;
   const float t = d < 16.0f ? d * 32.0f : (d < 64.0f ? fmaf(d - 16.0f, 8.0f, 512.0f) : 832.0f + d);
   return ST - 1 - (int)fminf(fmaxf(t, 0.0f), (float)(ST - 1));

@@ -129,6 +129,27 @@ def test_rows_do_not_depend_on_the_order_of_the_workgroups(bt, hkv, g, blocks, s
         assert (all_flags[b, rows] == flags[0]).all() and np.array_equal(all_st[2][b, h], st[2][0, 0])
 
 
+@pytest.mark.parametrize("blocks,where", [(40, 39), (300, 17), (1500, 1400), (11000, 10)])
+@pytest.mark.parametrize("value", [np.inf, -np.inf])
+def test_a_block_without_a_log_mass_takes_no_place_from_one_that_has(blocks, where, value):
+    """One infinite key: its block has no log-mass, is last in the ranking, and with it no prefix of the ranking covers
+    anything, so every head selects its K_max best other blocks."""
+    n = blocks * 16 + 5
+    rng = np.random.default_rng(blocks)
+    k, v = (rng.standard_normal((1, 2, n, 128), dtype=np.float32).astype(np.float16) for _ in range(2))
+    q = rng.standard_normal((1, 8, 128)).astype(np.float16)
+    k[0, 0, where * 16 + 3, 7] = value
+    print("no log-mass", blocks, where, value, flush=True)
+    with GpuLayerCache(1, 8, 2, n + 16) as gc:
+        gc.append(k, v)
+        _, _, _, st = run(gc, q, gc.cqa.Tolerances(), gc.cqa.Selector(0.995, 2, 16, 16))
+        for h in range(4):
+            l8 = st[3][0, h]
+            assert np.flatnonzero(~np.isfinite(l8)).tolist() == [where] and st[0][0, h] == 16
+            best = np.argsort(-np.where(np.isfinite(l8), l8, -np.inf), kind="stable")[:16]
+            assert st[1][0, h, :16].tolist() == best.tolist(), h
+
+
 @functools.lru_cache(maxsize=1)
 def long_head():
     """One KV head of 128K tokens with 4 query heads: 2048 quads, 256 sets of eight waves."""
