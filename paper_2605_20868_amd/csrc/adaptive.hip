@@ -1045,16 +1045,17 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   // link idle while they hold a place that a workgroup with originals to fetch could have, so they come last: 128 groups of
   // 4000 tokens 2291 -> 2263 us a step.  With somewhat more than one to a compute unit, a few compute units get two.  Group by
   // group that is, on some, two that fetch originals, which take the longer the more they fetch; so the order wraps
-  // round: the surplus are negated sets, sharing with negated sets.  Steps of 20000 tokens, group by group, wrapped, sums last,
-  // 4 heads per group: 8 groups, 512 blocks a head 714.6, 692.1, 692.7; 9 groups 789.1, 773.4, 796.7; 11 groups
-  // 941.1, 939.1, 942.5; 14 groups 1172.9, 1186.2, 1174.6; 8 groups of 128K, 128 blocks a head 386.5, 377.0, 376.2, few
-  // blocks 86.5, 86.8, 89.7; 14 groups, few blocks 265.6, 267.6, 269.6.
+  // round: the surplus are negated sets, sharing with negated sets.  Up to one in eight more, that is; beyond, so many share
+  // that it evens out.  Steps of 20000 tokens, group by group, wrapped, sums last, 4 heads per group: 8 groups, 512 blocks a head
+  // 714.6, 692.1, 692.7, few blocks 176.2, 178.8, 177.5; 9 groups 789.1, 773.4, 796.7 and 182.5, 187.3, 187.3; 11 groups 941.1,
+  // 939.1, 942.5 and 224.8, 222.8, 227.1; 14 groups 1172.9, 1186.2, 1174.6 and 265.6, 267.6, 269.6; 8 groups of 128K, 128 blocks a
+  // head 386.5, 377.0, 376.2, few blocks 92.6, 92.5, 94.6.
   int64_t wgs = (int64_t)(2 * PROM_SPLITS + g * pa.parts) * pa.groups;
   // With the FP16 scratch, originals mostly lie on the device and the sums are the longer part: last there (512
-  // slots, 8 and 9 groups of 4000 tokens: group by group 51.1, 54.3, wrapped 54.0, 54.8, last 50.2, 50.8).
+  // slots, 8 groups of 4000 tokens: group by group 51.1, wrapped 54.0, last 50.2).
   const bool many = wgs > 2 * c->n_cu;
   pa.order = many ? PROM_SUMS_LAST
-                  : (2 * wgs > 3 * c->n_cu || wgs <= c->n_cu ? PROM_BY_GROUP : (w.sc_slots > 0 ? PROM_SUMS_LAST : PROM_WRAPPED));
+                  : (8 * wgs > 9 * (int64_t)c->n_cu || wgs <= c->n_cu ? PROM_BY_GROUP : (w.sc_slots > 0 ? PROM_SUMS_LAST : PROM_WRAPPED));
   // Sums that come last run while nothing is fetched any more, so for many groups of short contexts a workgroup takes a group's
   // heads, a wave each: 64 x 8 groups, 4 heads, of 500 tokens 1301.5 -> 1272.8 us, of 550 1421.5 -> 1389.7, of 700 1738.7 -> 1718.6,
   // of 1300 3187.0 -> 3175.5; level from 10000 tokens on, which is where a wave takes more than a trip.
