@@ -179,7 +179,7 @@ __device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm)
   const int nb = a.nb;
   float* contrib = VALUES ? a.contrib + row * nb : nullptr;
   const float* lm = a.lm8 + row * nb;
-  const float* eta = VALUES ? a.eta_blk + ((int64_t)b * a.n_kv + hq / (a.n_q / a.n_kv)) * nb : nullptr;
+  const float* eta = VALUES ? a.eta_blk + ((int64_t)b * a.n_kv + (hq >> group_shift(a.n_q, a.n_kv))) * nb : nullptr;
   const float* ranked = VALUES ? contrib : lm;         // the row as later passes re-read it
   const int KL = min(max(side.k_limit, side.k_max), min(nb, MAX_K_LIMIT));
 
@@ -207,15 +207,15 @@ __device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm)
       e[j] = VALUES && i < nb ? eta[i] : 0.0f;
     }
   };
-  const int reducing = min((a.ra.nsplit + 7) / 8, RED_WAVES) + 2;   // waves
+  const int reducing = reduce_waves(a.ra.nsplit);   // waves
   uint32_t* const um = side.umask + row * a.mask_words;
   if ((tid >> 6) >= reducing) {
     load_row(0);
     const int t = tid - 64 * reducing, step = ST - 64 * reducing;
     for (int i = t; i < ((nb + 31) >> 5); i += step) um[i] = 0u;
-    const int g = a.n_q / a.n_kv;
-    if (!VALUES && hq % g == 0) {
-      const int64_t grp = (int64_t)b * a.n_kv + hq / g;
+    const int shift = group_shift(a.n_q, a.n_kv);
+    if (!VALUES && (hq & ((1 << shift) - 1)) == 0) {
+      const int64_t grp = (int64_t)b * a.n_kv + (hq >> shift);
       const int n_prev = min(a.ucount[grp], MAX_UNION);
       for (int i = t; i < n_prev; i += step) {
         const int blk = a.ulist[grp * MAX_UNION + i];
@@ -490,6 +490,7 @@ __device__ __forceinline__ void select_rows(const SelectArgs& a, SelectSmem& sm)
 }
 
 __global__ __launch_bounds__(ST) void select_kernel(SelectArgs a) {
+  fetch_args<sizeof(SelectArgs)>();
   __shared__ __align__(16) SelectSmem sm;
   if (blockIdx.z == 0)
     select_rows<false>(a, sm);
@@ -522,6 +523,7 @@ struct CompactArgs {
 // bits 24-27 / 28-31: which heads; 0 = neither) and the ascending list of blocks with any flag.
 // Per-group promotion gives every head the union's bits.
 __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
+  fetch_args<sizeof(CompactArgs)>();
   const int tid = threadIdx.x;
   const int64_t grp = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
   int32_t* slot = a.slot + grp * a.slot_stride;
@@ -740,16 +742,18 @@ __device__ __forceinline__ void rank_join(const RankBest& r, float& x, int& ix, 
   wave_best(e, ie);
 }
 __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs a) {
+  fetch_args<sizeof(AdaptiveReduceArgs)>();
   const int tid = threadIdx.x, l = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hq = blockIdx.x, b = blockIdx.y;
   const ReduceArgs& ra = a.ra;
   const int64_t row = (int64_t)b * ra.n_q + hq;
-  const int64_t grp = (int64_t)b * ra.n_kv + hq / (ra.n_q / ra.n_kv);
+  const int shift = group_shift(ra.n_q, ra.n_kv);
+  const int64_t grp = (int64_t)b * ra.n_kv + (hq >> shift);
   const float* l8 = a.lm8 + row * ra.nb;
   const float* lx = a.lmx + row * ra.nb;
   const int32_t* slot = a.slot + grp * a.slot_stride;
   const int32_t* ulist = a.ulist + grp * MAX_UNION;
-  const int kbit = 1 << (SLOT_HK_SHIFT + hq % (ra.n_q / ra.n_kv));   // this head scores the block with FP16 keys
+  const int kbit = 1 << (SLOT_HK_SHIFT + (hq & ((1 << shift) - 1)));   // this head scores the block with FP16 keys
   const float lse8 = a.first[row * 4], delta = a.first[row * 4 + 1];
   const int n_list = min(a.ucount[grp], MAX_UNION);
   int blk = ulist[tid];                    // valid for tid < n_list

@@ -206,18 +206,20 @@ struct Cache {
 };
 
 struct DecodeArgs {
+  // what the first loads' addresses are made of, one 64-byte line of kernel arguments (args_in_one_wait)
   const uint8_t* t1;   // layer base of the Tier-1 quad records
   const float* sigmax; // [Bt * Hkv] of the layer: running max of sigma over sealed blocks and channels
   const __half* q;     // [Bt][Hq][128]
-  float* partials;     // [Bt][Hq][nsplit][PART_FLOATS]
-  float* blk_logmass;  // [Bt][Hq][nb] or null
+  const __half* ap_k_new;   // [Bt][Hkv][1][128]: see below
   int64_t nq_cap;      // quad records per head
   int nb;              // sealed blocks
   int nsplit;
   int n_q, n_kv;
   int pstride;         // partial sets per (batch, q-head) row of `partials` (>= nsplit)
-  int int8_query;      // matrix-core pass: 1 = INT8 x INT8 scoring of the quantised scaled query
   int finish;          // matrix-core pass: 1 = it finishes the rows of a single split itself
+  float* partials;     // [Bt][Hq][nsplit][PART_FLOATS]
+  float* blk_logmass;  // [Bt][Hq][nb] or null
+  int int8_query;      // matrix-core pass: 1 = INT8 x INT8 scoring of the quantised scaled query
   int wpb;             // matrix-core pass: waves per workgroup, 8 or 4 (split_geometry)
   // promoted-block pass of the adaptive decode
   __half* sc_k;             // layer base of the FP16 scratch's key halves [Bt * Hkv][sc_cap][16][128], or null
@@ -230,10 +232,9 @@ struct DecodeArgs {
   int stream_nt;            // 1 = Tier-1 loads carry the non-temporal hint (see stream_hint)
   float* eta_out;           // eta_b per (batch, kv-head, block) written alongside the log-masses, or null
   float* score_dev;         // promoted-block pass: canary output per (batch, q-head), or null
-  // one-token append carried by the decode launch (null k_new = none): the new (k, v) of every
+  // one-token append carried by the decode launch (null ap_k_new = none): the new (k, v) of every
   // (batch, kv-head) goes to slot `ap_slot` of the trailing FP16 block and, unless ap_t2_k is
   // null, to position ap_pos of the pinned originals
-  const __half* ap_k_new;   // [Bt][Hkv][1][128]
   const __half* ap_v_new;
   __half* ap_trail_k;       // layer base: [Bt * Hkv][16][128]
   __half* ap_trail_v;
@@ -280,6 +281,23 @@ struct PromArgs {
 inline int64_t head_index(const Cache* c, int layer, int b, int kvh) {
   return ((int64_t)layer * c->desc.batch + b) * c->desc.n_kv_heads + kvh;
 }
+
+// Kernel arguments lie in memory, and the compiler loads one where it is first used: behind a branch or the wait for another,
+// each 64-byte line of them is a miss of some 550 cycles of its own (in the split pass 2400 of a short step's 9400
+// cycles went by before the first data was requested).  This asks for one word of each of a kernel's first 2 to 8 lines, at once, so
+// that one miss is all: from here on arguments come from the scalar cache.
+template <int BYTES>
+__device__ __forceinline__ void fetch_args() {
+  constexpr int N = (BYTES + 63) / 64 < 8 ? (BYTES + 63) / 64 : 8;
+  const uint32_t* const w = (const uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+#define CQA_LINE(I) w[(I) < N ? 16 * (I) : 0]
+  asm volatile("" ::"s"(CQA_LINE(0)), "s"(CQA_LINE(1)), "s"(CQA_LINE(2)), "s"(CQA_LINE(3)), "s"(CQA_LINE(4)), "s"(CQA_LINE(5)),
+               "s"(CQA_LINE(6)), "s"(CQA_LINE(7)));
+#undef CQA_LINE
+}
+
+// heads per KV group: 1, 2 or 4; its logarithm, without a division
+__device__ __forceinline__ int group_shift(int n_q, int n_kv) { return n_q >= 4 * n_kv ? 2 : (n_q >= 2 * n_kv ? 1 : 0); }
 
 // Reads of the caller's q, k and v, which need no more than the alignment of an FP16 number: the device reads a
 // lane's 4 or 16 bytes at any address with the same instruction, the compiler only has to be told.
@@ -348,6 +366,8 @@ constexpr int LADDER_MAX_SPLITS = 64;
 // times at these limits stand beside it).
 constexpr int FINISH_ROWS = 8, FINISH_SETS = 8;
 struct LadderArgs {
+  const uint32_t* raised;   // equals raised_tag when some head of this step requests a fallback (it may
+  uint32_t raised_tag;      // do so without one: a recorded step that is replayed keeps its number)
   const __half* q;          // [Bt][Hq][128]
   const __half* t2_k;       // layer base of the pinned originals: [Bt * Hkv][max_tokens][128]
   const __half* t2_v;
@@ -358,8 +378,6 @@ struct LadderArgs {
   float* ws;                // [Bt * Hq][nsplit][4 + 128]
   uint32_t* tickets;        // [Bt * Hkv], zero between launches
   uint32_t* counts;         // [2]: steps served by Rung 3, by Rung 4
-  const uint32_t* raised;   // equals raised_tag when some head of this step requests a fallback (it may
-  uint32_t raised_tag;      // do so without one: a recorded step that is replayed keeps its number)
   int groups;               // Bt * Hkv
   int many_items;           // more served (KV group, split) items than this are walked by many_walkers workgroups
   int many_walkers;

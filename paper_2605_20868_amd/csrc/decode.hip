@@ -203,6 +203,7 @@ __device__ __forceinline__ void prom_scan(const DecodeArgs& a, const PromArgs& p
 //               workgroup's linear index.  Further workgroups sum up the blocks left in INT8.
 template <int G, bool PROM>
 __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a, PromArgs p) {
+  fetch_args<sizeof(DecodeArgs) + (PROM ? sizeof(PromArgs) : 0)>();
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int tok = l & 15, kg = l >> 4;              // roles in the score phase
   const int vn = l & 15, vgh = (l >> 4) & 1, vo = l >> 5;  // roles in the value phase
@@ -624,12 +625,14 @@ __global__ __launch_bounds__(256) void certified_split_kernel(DecodeArgs a, Prom
 
 // Stand-alone cross-split reduction.
 __global__ __launch_bounds__(64 * (RED_WAVES + 2)) void certified_reduce_kernel(ReduceArgs a) {
+  fetch_args<sizeof(ReduceArgs)>();
   __shared__ __align__(16) ReduceSmem sm;
   HeadRow row;
-  if (reduce_row(a, blockIdx.y, blockIdx.x, (int)(blockDim.x >> 6), sm, row)) store_row(a, blockIdx.y, blockIdx.x, row);
+  if (reduce_row(a, blockIdx.y, blockIdx.x, reduce_waves(a.nsplit), sm, row)) store_row(a, blockIdx.y, blockIdx.x, row);
 }
 
 __global__ __launch_bounds__(64) void certified_reduce_wave_kernel(ReduceArgs a) {
+  fetch_args<sizeof(ReduceArgs)>();
   store_row(a, blockIdx.y, blockIdx.x, reduce_row_wave(a, blockIdx.y, blockIdx.x));
 }
 
@@ -833,8 +836,7 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     hipEvent_t ev1 = prof ? c->prof_ev[2 * c->prof_n + 1] : nullptr;
     if (prof && c->variant != 0) CQA_HIP(hipEventRecord(ev0, st));
     if (c->variant == 0 || a.eta_out != nullptr) {   // eta_b comes from this kernel only
-      // one-dimensional grid: the kernel decodes (head, partial set) from the linear index
-      const int32_t rc = launch_split_mfma(a, ra, hq / hkv, dim3((unsigned)nsplit * hkv * bt), ev0, ev1, st);
+      const int32_t rc = launch_split_mfma(a, ra, hq / hkv, grid, ev0, ev1, st);
       if (rc != CQA_OK) return rc;
       reduced = a.finish != 0;
     } else {
@@ -856,8 +858,6 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     *defer = ra;
     return CQA_OK;
   }
-  // a wave per eight sets, while there are waves
-  const int nw = std::min(std::max((nsplit + 7) / 8, 1), RED_WAVES);
   // With a mirror and more than four rows per compute unit, one wave per row: a row's waves side by side bring the stores
   // to the mirror closer together, where they wait for one another.  A host-resolved step of 4 heads per group, three waves a row and
   // one: 1152 rows of three sets 79.5, 78.9 us; 2240 of two 97.7, 91.7; 2816 102.1, 97.0.  (Two heads per group, level: 1152
@@ -866,7 +866,7 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
   if (flags_mirror != nullptr && (int64_t)bt * hq > 4 * (int64_t)c->n_cu && nsplit <= 8)
     hipLaunchKernelGGL(certified_reduce_wave_kernel, dim3(hq, bt), dim3(64), 0, st, ra);
   else
-    hipLaunchKernelGGL(certified_reduce_kernel, dim3(hq, bt), dim3(64 * (nw + 2)), 0, st, ra);
+    hipLaunchKernelGGL(certified_reduce_kernel, dim3(hq, bt), dim3(64 * reduce_waves(nsplit)), 0, st, ra);
   CQA_HIP(hipGetLastError());
   return CQA_OK;
 }

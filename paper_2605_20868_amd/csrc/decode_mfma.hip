@@ -145,13 +145,14 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   // a granularity of one quad (~4.5 us of work) even an ideal greedy schedule gains < 1 us.
   // Likewise uneven static deals -- longer runs for the first workgroup of every compute unit,
   // shares weighted by XCD -- measured no faster.)
+  fetch_args<sizeof(DecodeArgs) + sizeof(ReduceArgs)>();
   const int nquads = (a.nb + 3) >> 2;
-  const int L = blockIdx.x;
-  const int head = L / a.nsplit, split = L - head * a.nsplit;
+  const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+  const uint32_t head = (uint32_t)b * (uint32_t)a.n_kv + (uint32_t)kvh;
   // a SIMD holds two waves: w and w + 4 of the one workgroup on its compute unit (W = 8), or wave w
   // of each of the two (W = 4; the second half of the launch order presumably arrives later);
   // "younger" names the second of them in the priority scheme below
-  const bool younger = W == 8 ? w >= 4 : 2 * L >= (int)gridDim.x;
+  const bool younger = W == 8 ? w >= 4 : 2 * (head * (uint32_t)a.nsplit + (uint32_t)split) >= gridDim.x * gridDim.y * gridDim.z;
   constexpr int Q_NONE = 0x40000000;   // "no quad": larger than any quad index
   int q_cur, q_next, q_stop;
   const int q_step = W * a.nsplit;     // waves of the head
@@ -161,8 +162,6 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
     q_cur = ci < nquads ? ci : Q_NONE;
     q_next = !ONE && ci + q_step < nquads ? ci + q_step : Q_NONE;
   }
-  const int b = head / a.n_kv, kvh = head - b * a.n_kv;
-  const int64_t head_rec = (int64_t)head * a.nq_cap;
   const float inv_sqrt_d = 0.08838834764831845f;
 
   __shared__ __align__(16) float kmbuf[W][4][KM_ROW];    // [wave][block of quad][sigma | z]
@@ -181,7 +180,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   // the pinned originals.  This pass reads sealed blocks only; the reduction, which attends the
   // trailing tokens, runs after this launch has completed.
   if (a.ap_k_new != nullptr && split == 0 && w == 0) {
-    const int64_t grp = (int64_t)b * a.n_kv + kvh;
+    const int64_t grp = head;
     const uint32_t kx = ld4_any(a.ap_k_new + grp * D + 2 * l);
     const uint32_t vx = ld4_any(a.ap_v_new + grp * D + 2 * l);
     reinterpret_cast<uint32_t*>(a.ap_trail_k + (grp * BLK + a.ap_slot) * D)[l] = kx;
@@ -200,11 +199,10 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   // one in the high phase: of the four phase combinations each wave then wins two.
   __builtin_amdgcn_s_setprio(3);
   // This wave's query row (head w of the group), requested before the bulk loads: loads return in
-  // order, so the row arrives first and the set-up below does not wait for a whole quad.
-  __half2 q_in = __floats2half2_rn(0.0f, 0.0f);
-  if (w < G)
-    q_in = ld_half2_any(a.q + ((int64_t)b * a.n_q + kvh * G + w) * D + 2 * l);
-  const float sigmax_head = a.sigmax[(int64_t)b * a.n_kv + kvh];
+  // order, so the row arrives first and the set-up below does not wait for a whole quad.  Every wave asks for one: in a
+  // branch the compiler moves the request down to its use, behind everything.
+  const uint32_t q_in = ld4_any(a.q + (int64_t)((uint32_t)(b * a.n_q + kvh * G + min(w, G - 1))) * D + 2 * l);
+  const float sigmax_head = a.sigmax[head];
 
   // Loads of one quad = one Tier-1 record.  Every address is the record's wave-uniform base plus
   // a constant plus a per-lane 32-bit offset that never changes, so the loop carries no vector
@@ -218,7 +216,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   //   V codes : pair P, group set gs; lane (channel n, 8-token slice kg)
   //   metadata: each byte once per wave -- K meta of block i bytes [16 l, +16); V meta of blocks
   //             2P + (l >> 5) bytes [16 (l & 31), +16); (eta, nu) of block i (wave-uniform)
-  const uint8_t* const head_base = a.t1 + head_rec * QUAD_BYTES;
+  const uint8_t* const head_base = a.t1 + (int64_t)head * a.nq_cap * QUAD_BYTES;
   const uint32_t lo16 = (uint32_t)l * 16u;
   const uint32_t vo16 = (uint32_t)kg * 512u + (uint32_t)n * 16u;
 // QI: a quad index, or Q_NONE (then the head's first record absorbs the load)
@@ -256,22 +254,22 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   uint4 kraw[4][2], vraw[2][2];
   u32x4 km_n[4], vm_n[2];
   float2 an_n[4];
-  if (q_cur < nquads) {
-    CQA_LOAD_META(q_cur)
-    CQA_LOAD_K(q_cur, 0)
-    CQA_LOAD_K(q_cur, 1)
-    CQA_LOAD_V(q_cur, 0)
-    CQA_LOAD_V(q_cur, 1)
-  }
+  // (Unconditional as well: behind a branch the wait for the query row, which was requested first, becomes one for
+  // everything.)
+  CQA_LOAD_META(q_cur)
+  CQA_LOAD_K(q_cur, 0)
+  CQA_LOAD_K(q_cur, 1)
+  CQA_LOAD_V(q_cur, 0)
+  CQA_LOAD_V(q_cur, 1)
 
   // Queries of the group as FP32 in LDS, rows of absent heads zero, each head pre-scaled by a
   // power of two S_h chosen so that |q S_h sigma| <= 2^14 for every sigma of this KV head (its
   // running maximum is kept at seal time): the scaled query then fits FP16 without overflow, and
   // elements too small for a normal FP16 low part are negligible against the largest ones.
-  // Wave w prepares the row of head w.
   // Lane (h, kg) reads channels (u>>1)*64 + kg*16 + (u&1)*8 + e of head h when it forms slice u.
-  if (w < 4) {   // qbuf has four rows; the other waves of the workgroup have none to prepare
-    float2 qq = __half22float2(q_in);
+  if (W == 4 || w < 4) {   // qbuf has four rows; the other waves of the workgroup have none to prepare
+    float2 qq = __half22float2(__builtin_bit_cast(__half2, q_in));
+    if (w >= G) qq = make_float2(0.0f, 0.0f);
     const float qmax = wave_max(fmaxf(fabsf(qq.x), fabsf(qq.y)));
     const float bound = qmax * sigmax_head;
     int e = 0;
@@ -283,6 +281,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
     *reinterpret_cast<float2*>(&qbuf[w][2 * l]) = qq;
     if (l == 0) sbuf[w] = ldexpf(1.0f, -e);
   }
+  asm volatile("" ::"v"(q_in), "v"(sigmax_head));   // (used on both sides of the branch: the requests stay above)
   __syncthreads();
   const float unscale_op = sbuf[h];                // 1 / S of my operand head
   // raw MFMA sum -> logit in units of ln 2 (the softmax state below is kept in base 2: v_exp_f32

@@ -529,6 +529,7 @@ __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
 // copies of the work get in each other's way.)
 template <int G>
 __global__ __launch_bounds__(64 * FINISH_ROWS) void finish_ladder_kernel(ReduceArgs ra, LadderArgs a) {
+  fetch_args<sizeof(ReduceArgs) + sizeof(LadderArgs)>();
   const int r = threadIdx.x >> 6, l = threadIdx.x & 63;   // this wave's row
   __shared__ uint32_t s_fl[FINISH_ROWS];
   HeadRow row;

@@ -136,6 +136,7 @@ __device__ __forceinline__ void store_originals(const __half* in, __half* t2, in
 // (Measured and not adopted: fetching the keys as whole rows with 128-bit loads and handing the
 // columns to the channel lanes through LDS.)
 __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
+  fetch_args<sizeof(SealArgs)>();
   const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int j = (int)blockIdx.x * a.per;      // new block index
   const int j1 = min(j + a.per, a.n_seal);

@@ -414,7 +414,7 @@ struct TrailRegs {
 __device__ __forceinline__ void load_trail(const ReduceArgs& a, int b, int hq, const __half* new_k,
                                            const __half* new_v, TrailRegs& t) {
   const int l = threadIdx.x & 63;
-  const int64_t grp = (int64_t)b * a.n_kv + hq / (a.n_q / a.n_kv);
+  const int64_t grp = (int64_t)b * a.n_kv + (hq >> group_shift(a.n_q, a.n_kv));
   const __half* tk = a.trail_k + grp * BLK * D;
   const __half* tv = a.trail_v + grp * BLK * D;
   const int last = max(a.r - 1, 0);
@@ -609,6 +609,11 @@ __device__ __forceinline__ void finish_head(const ReduceArgs& a, int b, int hq, 
 // key term's functions; the first then joins their results and returns true.  Where one wave per head did all this in turn
 // (8500 cycles), a step of 8 KV heads, four layers: 8229 tokens 64.4 -> 57.7 us, 3000 tokens 59.6 -> 50.6.
 constexpr int RED_WAVES = 8;
+// waves of such a workgroup: one per eight sets, while there are, and two
+__host__ __device__ inline int reduce_waves(int nsplit) {
+  const int nw = (nsplit + 7) / 8;
+  return (nw < 1 ? 1 : (nw > RED_WAVES ? RED_WAVES : nw)) + 2;
+}
 struct ReduceSmem {
   float sc[RED_WAVES][12];
   float o[RED_WAVES][D];
