@@ -46,6 +46,11 @@ int32_t cqa_set_splits(cqa_cache* c, int32_t n_splits);
  * the non-temporal hint.  Results do not depend on it.  For tests and measurement. */
 int32_t cqa_set_stream_hint(cqa_cache* c, int32_t mode);
 
+/* 1 = the split pass of an enqueue-only step takes the workgroups of a KV group to be spread over two dies, whatever die
+ * they are on, and leaves the reduction of the rows to the ladder's launch: the route of a device that
+ * deals its workgroups in another way.  0 restores the default.  For tests. */
+int32_t cqa_set_scatter(cqa_cache* c, int32_t on);
+
 /* Chooses the split-K decode kernel: 0 = matrix-core (MFMA) kernel, the default;
  * 1 = the vector-ALU kernel (same results to rounding; kept as a cross-check). */
 int32_t cqa_set_kernel_variant(cqa_cache* c, int32_t variant);

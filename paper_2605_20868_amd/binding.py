@@ -147,6 +147,7 @@ def _load():
         "cqa_decode_splits": (i32, [vp, i32, C.POINTER(i32)]),
         "cqa_set_splits": (i32, [vp, i32]),
         "cqa_set_stream_hint": (i32, [vp, i32]),
+        "cqa_set_scatter": (i32, [vp, i32]),
         "cqa_set_kernel_variant": (i32, [vp, i32]),
         "cqa_strerror": (C.c_char_p, [i32]),
         "cqa_version": (i32, []),
@@ -426,6 +427,10 @@ def cqa_decode_splits(h, layer) -> int:
 
 def cqa_set_kernel_variant(h, variant) -> None:
     _check(_lib.cqa_set_kernel_variant(h, variant), "cqa_set_kernel_variant")
+
+
+def cqa_set_scatter(h, on) -> None:
+    _check(_lib.cqa_set_scatter(h, on), "cqa_set_scatter")
 
 
 def cqa_set_stream_hint(h, mode) -> None:

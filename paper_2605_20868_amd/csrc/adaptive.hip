@@ -892,7 +892,7 @@ __global__ __launch_bounds__(ART) void adaptive_reduce_kernel(AdaptiveReduceArgs
   ad.lse8 = lse8;
   if (l == 0) a.alpha_out[row] = ad.alpha;
   float2 o2;
-  const OctState st = merge_lds(sm.sc[0], 12, sm.o[0], D, RED_WAVES, o2);
+  const OctState st = merge_lds<RED_WAVES>(sm.sc[0], 12, sm.o[0], D, RED_WAVES, o2);
   finish_head(ra, b, hq, head_state(st, o2), trail_of(sm), key_of(sm), &ad);
 }
 

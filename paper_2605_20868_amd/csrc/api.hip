@@ -97,7 +97,7 @@ static void release(cqa_cache* h) {
   (void)hipFree(c->dense_ws);
   (void)hipFree(c->select_dev);
   (void)hipFree(c->ladder_ws);
-  (void)hipFree(c->ladder_tickets);
+  (void)hipFree(c->tickets);
   (void)hipFree(c->ladder_counts);
   (void)hipFree(c->ad.lm8);
   (void)hipFree(c->ad.lmx);
@@ -216,7 +216,7 @@ int32_t cqa_workspace_bytes(const cqa_cache_desc* desc, int64_t* device_bytes,
     if (t2) {
       n += 3 * s.ad_lm + 2 * s.ad_sel + 3 * s.ad_head + s.ad_sums + 2 * s.ad_mask + s.ad_slot + s.ad_group + s.ad_ulist +
            s.ad_eta + 8;
-      n += 4 * s.stage + s.ladder_ws + groups * 4 + 12;
+      n += 4 * s.stage + s.ladder_ws + groups * (TICKET_STRIDE + 2) * 4 + 12;
       // ... and what the first cqa_set_scratch_slots(n > 0) adds: key and value halves, map, three words per slot
       n += 2 * s.sc_k + s.sc_map + 3 * s.sc_tag;
     }
@@ -321,8 +321,14 @@ static int32_t create_cache(const cqa_cache_desc* desc, __half* caller_k, __half
     for (int i = 0; i < 2; ++i)
       for (int j = 0; j < 2; ++j) CQA_ALLOC_DEV(c->stage[i][j], s.stage);
     CQA_ALLOC_DEV(c->ladder_ws, s.ladder_ws);
-    CQA_ALLOC_DEV(c->ladder_tickets, (int64_t)desc->batch * desc->n_kv_heads * 4);
-    CQA_TRY(hipMemset(c->ladder_tickets, 0, (size_t)desc->batch * desc->n_kv_heads * 4));
+    // the split pass's tickets on 128-byte boundaries, the ladder's behind them
+    const int64_t groups = (int64_t)desc->batch * desc->n_kv_heads, words = groups * (TICKET_STRIDE + 2);
+    uint32_t* tickets = nullptr;
+    CQA_ALLOC_DEV(tickets, words * 4);
+    c->tickets = tickets;
+    CQA_TRY(hipMemset(tickets, 0, (size_t)words * 4));
+    c->ladder_tickets = tickets + groups * (TICKET_STRIDE + 1);
+    if (c->n_cu == 32 * DIES) c->split_tickets = tickets;   // the whole device, not a partition of it
     CQA_ALLOC_DEV(c->ladder_counts, 12);
     CQA_TRY(hipMemset(c->ladder_counts, 0, 12));
     if (c->t2_borrowed) {
@@ -495,6 +501,12 @@ int32_t cqa_set_splits(cqa_cache* h, int32_t n_splits) {
 int32_t cqa_set_stream_hint(cqa_cache* h, int32_t mode) {
   if (h == nullptr || mode < 0 || mode > 2) return CQA_ERR_INVALID_ARG;
   h->impl.stream_hint = mode;
+  return CQA_OK;
+}
+
+int32_t cqa_set_scatter(cqa_cache* h, int32_t on) {
+  if (h == nullptr || on < 0 || on > 1) return CQA_ERR_INVALID_ARG;
+  h->impl.scatter = on;
   return CQA_OK;
 }
 

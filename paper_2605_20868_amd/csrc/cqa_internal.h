@@ -90,6 +90,11 @@ constexpr int P_O = 16;     // o[128]
 constexpr int PART_FLOATS = 16 + D;  // 144
 constexpr int MAX_SPLITS = 1024;     // upper bound on splits per (batch, kv-head)
 
+// ---- split pass that reduces its partial sets itself (certified_split_mfma_kernel) ----
+constexpr int DIES = 8;              // workgroups whose indices leave the same remainder by 8 run on one die
+constexpr int TICKET_STRIDE = 32;    // words: a KV group's counters, one per die, have a line of their own
+constexpr int REDUCED_ROWS = 1024;   // most (batch, query head) rows of such a step
+
 // ---- adaptive key precision ------------------------------------------------------
 constexpr int MAX_K_LIMIT = 512;            // blocks one head may promote (Rung-1 growth included)
 constexpr int MAX_UNION = 8 * MAX_K_LIMIT;  // blocks one KV group may promote (keys and values, <= 4 heads each)
@@ -171,6 +176,11 @@ struct Cache {
   uint32_t* ladder_tickets;
   uint32_t* ladder_counts;   // [2] steps served by Rung 3 / 4, [1] word of the last step that raised a flag
   uint32_t ladder_seq;       // host: number of the last enqueue-only step, never 0
+  uint32_t* tickets;         // the allocation of split_tickets and ladder_tickets
+  uint32_t* split_tickets;   // of the split pass that reduces its partial sets itself (split_reduces): [batch * n_kv_heads][TICKET_STRIDE]
+                             // arrivals on each die, zero between launches, then [batch * n_kv_heads] the number of the last
+                             // step whose rows are reduced; null = it leaves the reduction to a launch of its own
+  int scatter;               // test hook: every other workgroup of a KV group counts as one of the next die
   float* sigmax;             // [heads_total] running max of sigma (non-negative: ordered as ints) over the sealed
                              // blocks; a sequence's first seal sets it, so it holds nothing while there are none
   // trailing FP16 partial blocks [heads_total][16][128]
@@ -217,10 +227,15 @@ struct DecodeArgs {
   int n_q, n_kv;
   int pstride;         // partial sets per (batch, q-head) row of `partials` (>= nsplit)
   int finish;          // matrix-core pass: 1 = it finishes the rows of a single split itself
+  // matrix-core pass that reduces several splits itself (split_reduces)
+  uint32_t* tickets;   // split_tickets, or null: it does not
+  int heads;           // Bt * Hkv
+  int scatter;         // test hook
   float* partials;     // [Bt][Hq][nsplit][PART_FLOATS]
   float* blk_logmass;  // [Bt][Hq][nb] or null
   int int8_query;      // matrix-core pass: 1 = INT8 x INT8 scoring of the quantised scaled query
-  int wpb;             // matrix-core pass: waves per workgroup, 8 or 4 (split_geometry)
+  int wpb;             // matrix-core pass: waves per workgroup that take quads, 8 or 4 (split_geometry)
+  int waves;           // ... and in all, where it reduces several splits itself (split_reduces)
   // promoted-block pass of the adaptive decode
   __half* sc_k;             // layer base of the FP16 scratch's key halves [Bt * Hkv][sc_cap][16][128], or null
   __half* sc_v;             // ... and of its value halves (null exactly when sc_k is)
@@ -296,6 +311,24 @@ __device__ __forceinline__ void fetch_args() {
 #undef CQA_LINE
 }
 
+// A kernel's argument at `offset`, read where this stands and not before: what only a rare branch needs would otherwise be loaded,
+// and waited for, ahead of the branch.
+template <typename T>
+__device__ __forceinline__ T arg_read_here(int offset) {
+  typedef const __attribute__((address_space(4))) uint32_t* Words;
+  uint64_t base = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(base));
+  const Words w = (Words)(base + (uint64_t)offset);
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  union {
+    uint32_t u[sizeof(T) / 4];
+    T x;
+  } r;
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(T) / 4); ++i) r.u[i] = w[i];
+  return r.x;
+}
+
 // heads per KV group: 1, 2 or 4; its logarithm, without a division
 __device__ __forceinline__ int group_shift(int n_q, int n_kv) { return n_q >= 4 * n_kv ? 2 : (n_q >= 2 * n_kv ? 1 : 0); }
 
@@ -334,8 +367,8 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
                          const __half* v_new = nullptr, int pstride = 0, float* eta_out = nullptr,
                          float* partials = nullptr,   // null = the cache's own split workspace
                          uint32_t* raised = nullptr, uint32_t raised_tag = 0u,
-                         ReduceArgs* defer = nullptr,    // nsplit set > 0: the reduction is left to the caller,
-                         bool always = false);           // ... not only where the ladder's launch takes it
+                         ReduceArgs* defer = nullptr,    // always: the reduction is left to the caller; else nsplit set > 0:
+                         bool always = false);           // the split pass reduces, and the ladder's launch looks after it
 int32_t static_scratch(int device, void** out);
 int pick_splits(const Cache* c, int64_t n_blocks);
 int stream_nt(const Cache* c, int64_t n_blocks);
@@ -362,12 +395,13 @@ int64_t dense_ws_floats(int group, int64_t n_tokens);
 
 // Device-resolved fallback ladder (dense_ladder_kernel).
 constexpr int LADDER_MAX_SPLITS = 64;
-// Steps that finish_ladder_kernel reduces as well: up to this many (batch, q-head) rows and partial sets per row (the
-// times at these limits stand beside it).
-constexpr int FINISH_ROWS = 8, FINISH_SETS = 8;
 struct LadderArgs {
   const uint32_t* raised;   // equals raised_tag when some head of this step requests a fallback (it may
   uint32_t raised_tag;      // do so without one: a recorded step that is replayed keeps its number)
+  int groups;               // Bt * Hkv
+  // the split pass was to reduce the rows: where the number that it left for a KV group is not raised_tag, its workgroups
+  // were not on one die, and the rows are reduced here; null = the rows are there
+  uint32_t* split_tickets;
   const __half* q;          // [Bt][Hq][128]
   const __half* t2_k;       // layer base of the pinned originals: [Bt * Hkv][max_tokens][128]
   const __half* t2_v;
@@ -378,7 +412,6 @@ struct LadderArgs {
   float* ws;                // [Bt * Hq][nsplit][4 + 128]
   uint32_t* tickets;        // [Bt * Hkv], zero between launches
   uint32_t* counts;         // [2]: steps served by Rung 3, by Rung 4
-  int groups;               // Bt * Hkv
   int many_items;           // more served (KV group, split) items than this are walked by many_walkers workgroups
   int many_walkers;
   float* O;
@@ -389,7 +422,7 @@ int ladder_splits(const Cache* c, int64_t n_tokens);
 int64_t ladder_ws_floats(int64_t rows);
 int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_groups, float* O,
                             cqa_head_cert* cert, uint32_t* flags, uint32_t raised_tag, hipStream_t st,
-                            const ReduceArgs* reduce = nullptr);   // set = the rows are still to be reduced, here
+                            const ReduceArgs* reduce = nullptr);   // set = the split pass reduces the rows itself
 // certified decode and ladder, enqueue-only (k_new, v_new: a token that rides on the split launch, or null);
 // *launched (may be null) tells whether the split launch, which stores that token, was reached
 int32_t launch_step(Cache* c, int layer, const __half* q, const cqa_tolerances& tol, float* O, cqa_head_cert* cert,

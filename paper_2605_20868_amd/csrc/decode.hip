@@ -628,12 +628,13 @@ __global__ __launch_bounds__(64 * (RED_WAVES + 2)) void certified_reduce_kernel(
   fetch_args<sizeof(ReduceArgs)>();
   __shared__ __align__(16) ReduceSmem sm;
   HeadRow row;
-  if (reduce_row(a, blockIdx.y, blockIdx.x, reduce_waves(a.nsplit), sm, row)) store_row(a, blockIdx.y, blockIdx.x, row);
+  if (reduce_row(a, blockIdx.y, blockIdx.x, reduce_waves(a.nsplit), sm, row)) store_row(a, row_of(a, blockIdx.y, blockIdx.x), row);
 }
 
 __global__ __launch_bounds__(64) void certified_reduce_wave_kernel(ReduceArgs a) {
   fetch_args<sizeof(ReduceArgs)>();
-  store_row(a, blockIdx.y, blockIdx.x, reduce_row_wave(a, blockIdx.y, blockIdx.x));
+  const int64_t row = row_of(a, blockIdx.y, blockIdx.x);
+  store_row(a, row, reduce_row_wave(a, row));
 }
 
 // Workgroups ("splits") per (batch, kv-head) and waves per workgroup of the matrix-core split pass.
@@ -703,6 +704,28 @@ int stream_nt(const Cache* c, int64_t n_blocks) {
   if (c->stream_hint == 2) return 1;
   const int64_t pass = (int64_t)c->desc.batch * c->desc.n_kv_heads * ((n_blocks + 3) / 4) * QUAD_BYTES;
   return pass * c->desc.n_layers > ((int64_t)256 << 20) ? 1 : 0;
+}
+
+// Whether the split pass of a step with the ladder behind it reduces its partial sets itself, and with how many waves per workgroup
+// (0 = the reduction stays a launch of its own).  Its last workgroup's rows of waves (one wave per head) have a trip of eight
+// sets each, all but the one that takes the side work where there are three or more.  A step enqueued one after the other, and
+// recorded (device time alone), us, with the launch and without: 8 KV heads x 4, 1000 tokens 11.9, 9.6 and 10.1, 9.6; 3000 12.0, 10.4 and
+// 10.5, 10.4; 4000 (no trailing tokens) 11.9, 10.5 and 10.2, 10.4; x 1, 8000 11.7, 10.3 and 10.7, 10.2; 32 x 4 of 4000 14.1, 13.8 and
+// 14.2, 14.0; 128 x 4 of 1000 15.9, 15.0 and 16.1, 15.2.  With a second trip per wave the launch is better: 8 x 4 of 8229
+// 12.6, 13.2 and 12.5, 13.1; 16000 14.3, 16.1; 128K 57.2, 58.7; 2 x 4 of 8000 11.8, 12.1 and 10.3, 11.8; 8 x 2 of 8000 11.7, 11.1 and 10.7, 11.1.
+// A KV group's workgroups share a die, so the dies have to be evenly loaded: as many groups on each, or no more
+// workgroups on the fullest than it has compute units.
+static int split_reduces(const Cache* c, int64_t n_blocks, int nsplit, int wpb) {
+  const int64_t heads = (int64_t)c->desc.batch * c->desc.n_kv_heads, rows = (int64_t)c->desc.batch * c->desc.n_q_heads;
+  const int g = c->desc.n_q_heads / c->desc.n_kv_heads;
+  if (c->split_tickets == nullptr || c->variant != 0 || nsplit < 2 || rows > REDUCED_ROWS) return 0;
+  if (heads % DIES != 0 && (heads + DIES - 1) / DIES * nsplit > c->n_cu / DIES) return 0;
+  // Four waves with a quad each and a compute unit to themselves are joined by four or eight without: the trailing tokens are attended
+  // and the key term taken beside the rest (8 x 4 of 1000 tokens 10.5 -> 9.6 us a recorded step, of 3000 11.3 -> 10.4).
+  const int trips = (nsplit + 7) / 8;
+  const bool alone = wpb == 4 && 4 * (int64_t)nsplit >= (n_blocks + 3) / 4 && heads * nsplit <= c->n_cu;
+  const int waves = alone ? (g == 4 && trips > 1 ? 12 : 8) : wpb, np = waves / g;
+  return trips <= std::min(np > 2 ? np - 1 : 1, wpb) ? waves : 0;
 }
 
 int pick_splits(const Cache* c, int64_t n_blocks) {
@@ -827,6 +850,12 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     // A host-resolved step, the reduction's launch and this one finishing the rows: 4 heads per group, 32 rows 19.2, 15.9 us; 128
     // 20.9, 16.2; 256 22.2, 16.5; 1024 27.9, 17.9; 2048 40.6, 25.3; two, 1440 rows 48.6, 35.5; one, 720 42.6, 36.0.
     a.finish = nsplit == 1 && !always ? 1 : 0;
+    a.heads = bt * hkv;
+    a.waves = defer != nullptr && !always ? split_reduces(c, nb, nsplit, wpb) : 0;
+    if (a.waves != 0) {
+      a.tickets = c->split_tickets;
+      a.scatter = c->scatter;
+    }
     // the quantised-query scoring exists in the matrix-core pass (and in the promoted-block pass of
     // the adaptive calls), not in the vector-ALU cross-check kernel
     if (tol.int8_query != 0 && c->variant != 0) return CQA_ERR_UNSUPPORTED;
@@ -836,9 +865,11 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     hipEvent_t ev1 = prof ? c->prof_ev[2 * c->prof_n + 1] : nullptr;
     if (prof && c->variant != 0) CQA_HIP(hipEventRecord(ev0, st));
     if (c->variant == 0 || a.eta_out != nullptr) {   // eta_b comes from this kernel only
-      const int32_t rc = launch_split_mfma(a, ra, hq / hkv, grid, ev0, ev1, st);
+      const dim3 by_die(DIES, nsplit, (a.heads + DIES - 1) / DIES);
+      const int32_t rc = launch_split_mfma(a, ra, hq / hkv, a.tickets != nullptr ? by_die : grid, ev0, ev1, st);
       if (rc != CQA_OK) return rc;
-      reduced = a.finish != 0;
+      reduced = a.finish != 0 || a.tickets != nullptr;
+      if (a.tickets != nullptr) *defer = ra;
     } else {
       switch (hq / hkv) {
         case 1: hipLaunchKernelGGL((certified_split_kernel<1, false>), grid, dim3(256), 0, st, a, PromArgs{}); break;
@@ -854,7 +885,7 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     }
   }
   if (reduced) return CQA_OK;
-  if (defer != nullptr && (always || (nsplit > 1 && nsplit <= FINISH_SETS && (int64_t)bt * hq <= FINISH_ROWS))) {
+  if (always) {
     *defer = ra;
     return CQA_OK;
   }

@@ -126,8 +126,10 @@ constexpr int P_HEAD = 4 * BLK + 16;    // floats per head in the probability bu
 //     slices is read from LDS ahead of the products (152 registers instead of 242).  Four-wave workgroups, 8 KV heads: 3000
 //     tokens a step 15.3 -> 14.9 us, a prompt of 1000 tokens with 24 steps 418 -> 408.  Eight-wave ones: 8 KV heads of 8229
 //     tokens 13.4 -> 12.9 us a call, 16 x 8 of 250 9.6 -> 8.8, of 500 11.1 -> 10.3.
-template <int G, bool LM, bool NT, bool Q8, int W, bool ONE>
-__global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(DecodeArgs a, ReduceArgs ra) {
+// WT: waves of the workgroup in all.  Beyond W they take no quads: with four quad waves, where a workgroup has a compute unit to
+//     itself, four more attend the trailing tokens while the first loads are on their way and share the merging.
+template <int G, bool LM, bool NT, bool Q8, int W, bool ONE, int WT>
+__global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_mfma_kernel(DecodeArgs a, ReduceArgs ra) {
   const int l = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = l & 15, kg = l >> 4;
@@ -147,12 +149,19 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   // shares weighted by XCD -- measured no faster.)
   fetch_args<sizeof(DecodeArgs) + sizeof(ReduceArgs)>();
   const int nquads = (a.nb + 3) >> 2;
-  const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-  const uint32_t head = (uint32_t)b * (uint32_t)a.n_kv + (uint32_t)kvh;
+  int split = blockIdx.x;
+  uint32_t head = blockIdx.z * (uint32_t)a.n_kv + blockIdx.y;
+  if (a.tickets != nullptr) {   // a KV group's workgroups on one die (see the end of the kernel)
+    split = blockIdx.y;
+    head = blockIdx.z * DIES + blockIdx.x;
+    if (head >= (uint32_t)a.heads) return;
+    if (split == 0 && threadIdx.x == 0) a.tickets[(uint32_t)a.heads * TICKET_STRIDE + head] = 0u;
+  }
+  const int64_t row0 = (int64_t)head * G;   // the group's first (batch, query head) row
   // a SIMD holds two waves: w and w + 4 of the one workgroup on its compute unit (W = 8), or wave w
   // of each of the two (W = 4; the second half of the launch order presumably arrives later);
   // "younger" names the second of them in the priority scheme below
-  const bool younger = W == 8 ? w >= 4 : 2 * (head * (uint32_t)a.nsplit + (uint32_t)split) >= gridDim.x * gridDim.y * gridDim.z;
+  const bool younger = W == 8 ? w >= 4 : 2 * head >= (uint32_t)a.heads;
   constexpr int Q_NONE = 0x40000000;   // "no quad": larger than any quad index
   int q_cur, q_next, q_stop;
   const int q_step = W * a.nsplit;     // waves of the head
@@ -174,6 +183,8 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   __shared__ __align__(16) float mo[W][G][D];
   __shared__ float ms[W][G][12];
   __shared__ uint32_t s_fl[4];                           // [head] flag word of a finished row
+  __shared__ float s_side[G][6];                         // [head] trailing tokens' M, L, V; key terms
+  __shared__ __align__(16) float s_tail[G][D];           // [head] ... and their channels
 
   // A one-token append that rides on this launch: the first wave of each KV group's first
   // workgroup stores the group's new key and value (2 x 256 bytes) into the trailing block and
@@ -198,10 +209,33 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   // the presumably younger workgroup (second half of the launch order) one level above the older
   // one in the high phase: of the four phase combinations each wave then wins two.
   __builtin_amdgcn_s_setprio(3);
+  constexpr int NP = WT / G;
+  // the waves are NP rows of one per head: row SP takes what does not depend on the merge
+  constexpr bool SIDE = NP >= 2;
+  constexpr int SP = WT > W ? W / G : 1;
+  const int hh = w % G, part = w / G;
+  TrailRegs tr;
+  TrailState ts{};
+  const auto keep_trail = [&] {
+    *reinterpret_cast<float2*>(&s_tail[hh][2 * l]) = ts.o;
+    if (l == 0) {
+      s_side[hh][0] = ts.M;
+      s_side[hh][1] = ts.L;
+      s_side[hh][2] = ts.V;
+    }
+  };
+  if (WT > W && w >= W) {
+    __syncthreads();   // the others' query set-up
+    if (part == SP && ra.r > 0) {   // under their scores and values
+      load_trail(ra, head, row0 + hh, a.ap_k_new, a.ap_v_new, tr);
+      ts = trail_state(ra, tr);
+      keep_trail();
+    }
+  } else {
   // This wave's query row (head w of the group), requested before the bulk loads: loads return in
   // order, so the row arrives first and the set-up below does not wait for a whole quad.  Every wave asks for one: in a
   // branch the compiler moves the request down to its use, behind everything.
-  const uint32_t q_in = ld4_any(a.q + (int64_t)((uint32_t)(b * a.n_q + kvh * G + min(w, G - 1))) * D + 2 * l);
+  const uint32_t q_in = ld4_any(a.q + (row0 + min(w, G - 1)) * D + 2 * l);
   const float sigmax_head = a.sigmax[head];
 
   // Loads of one quad = one Tier-1 record.  Every address is the record's wave-uniform base plus
@@ -542,12 +576,12 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           if (live[i])
-            a.blk_logmass[((int64_t)b * a.n_q + kvh * G + kg) * a.nb + qb + i] = lbv[i];
+            a.blk_logmass[(row0 + kg) * a.nb + qb + i] = lbv[i];
       }
       if (a.eta_out != nullptr && l == 0) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (live[i]) a.eta_out[((int64_t)b * a.n_kv + kvh) * a.nb + qb + i] = an[i].x;
+          if (live[i]) a.eta_out[(int64_t)head * a.nb + qb + i] = an[i].x;
       }
     }
     abuf[w][kg] = alpha;   // every lane of the row stores the same word
@@ -666,34 +700,112 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
     m[P_T2] = t2;
     m[P_I1] = __int_as_float(i1);
   }
-  // ---- the rows themselves: a sequence served by one workgroup is finished here, from the waves'
-  //      states, and needs no launch for the reduction (64 sequences x 8 KV heads of 4107 tokens:
-  //      115 -> 106 us a step, with the ladder's early exit).  With several workgroups the reduction is a launch of its own: the last one
-  //      to arrive finishing the rows (agent-scope stores, a ticket, agent-scope loads) measured
-  //      8.9 -> 15.8 us for this launch at 1K and 11.7 -> 18.2 us at 8K, against a reduction of 4.7 us.
-  const int hq0 = kvh * G;
+  }
+  // ---- the rows themselves.  A sequence served by one workgroup is finished here, from the waves' states in LDS, and needs
+  //      no launch for the reduction (64 sequences x 8 KV heads of 4107 tokens: 115 -> 106 us a step, with the ladder's early exit).
+  //      Several workgroups of a KV group leave partial sets, and with tickets the last of them to arrive finishes
+  //      the rows.  All of them are on one die then, and meet in its L2.  That workgroups whose indices leave the
+  //      same remainder by 8 share a die is how the hardware deals them, but nothing says it must: a workgroup counts
+  //      on the counter of the die that it finds itself on.  Where a KV group's are not together no count
+  //      gets full, the number that its first workgroup cleared stays clear, and the ladder's launch, which comes behind,
+  //      reduces the rows from the partial sets.
   const bool finish = a.finish != 0;
-  TrailRegs tr;
-  if (finish && w < G) {
+  // The trailing tokens: by waves without quads where there are any, else while the waves that are not through yet keep the
+  // others waiting (of the two waves on a SIMD the first is through 3000 cycles before the second).
+  const bool spare = WT > W || (SIDE && finish && nquads <= W - G);
+  if (WT == W && ra.r > 0 && (finish || (SIDE && a.tickets != nullptr)) && (spare ? w >= W - G : part == 0)) {
     __builtin_amdgcn_s_setprio(2);
-    if (ra.r > 0) load_trail(ra, b, hq0 + w, a.ap_k_new, a.ap_v_new, tr);
+    load_trail(ra, head, row0 + hh, a.ap_k_new, a.ap_v_new, tr);
+    if (SIDE) ts = trail_state(ra, tr);
+    if (spare) keep_trail();
   }
   __syncthreads();
-  // one wave per head merges the waves' states
-  if (w < G) {
-    float2 o2;
-    const OctState st = merge_lds(ms[0][w], G * 12, mo[0][w], G * D, W, o2);
-    if (!finish) {
-      float* pp = a.partials + (((int64_t)b * a.n_q + hq0 + w) * a.pstride + split) * PART_FLOATS;
-      store_state(st, o2, pp, pp + P_O);
-    } else {
-      TrailState ts{};
-      if (ra.r > 0) ts = trail_state(ra, tr);
-      const HeadState hs = head_state(st, o2);
-      const HeadRow row = finish_row(ra, hs, ts, key_terms(ra, hs.DM), nullptr);
-      store_row(ra, b, hq0 + w, row, G == 1);
-      if (l == 0) s_fl[w] = row.fl;
+  OctState st{};
+  float2 o2;
+  KeyTerms kt{};
+  if (part == 0) st = merge_lds<W>(ms[0][w], G * 12, mo[0][w], G * D, W, o2);   // one wave per head merges the waves' states
+  const auto side_work = [&](float delta) {
+    const KeyTerms k = key_terms(ra, delta);
+    if (l == 0) {
+      s_side[hh][3] = k.full;
+      s_side[hh][4] = k.grow;
+      s_side[hh][5] = k.widen;
     }
+  };
+  if (!finish) {
+    float* const sets = a.partials + (row0 + hh) * a.pstride * PART_FLOATS;
+    if (part == 0) {
+      float* pp = sets + (int64_t)split * PART_FLOATS;
+      store_state(st, o2, pp, pp + P_O);
+    }
+    if (a.tickets == nullptr) return;
+    if (part == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the set is in the die's L2
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t die;
+      asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(die));
+      if (a.scatter) die += (uint32_t)split & 1u;
+      uint32_t* const tk = a.tickets + head * TICKET_STRIDE + die % DIES;
+      const bool last = __hip_atomic_fetch_add(tk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == (uint32_t)a.nsplit - 1u;
+      s_fl[0] = last ? 1u : 0u;
+      if (last) {
+        __hip_atomic_store(tk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);   // for the next launch
+        a.tickets[(uint32_t)a.heads * TICKET_STRIDE + head] = ra.raised_tag;
+      }
+    }
+    if (!SIDE && ra.r > 0) load_trail(ra, head, row0 + hh, a.ap_k_new, a.ap_v_new, tr);
+    __syncthreads();
+    if (s_fl[0] == 0u) return;
+    // Eight sets a trip.  One trip's result is the row's; several take the place of the waves' states in LDS.  Row SP has
+    // its side work first and takes fewer of them (none where there are more than two rows).
+    const int trips = (a.nsplit + 7) >> 3;
+    const int most = trips <= 2 ? trips : (trips + 2) >> 1;   // of two rows, the first one's
+    int t = NP == 1 ? 0 : (NP == 2 ? part * most : (part == SP ? trips : (part < SP ? part : part - 1)));
+    const int t_end = NP == 2 && part == 0 ? most : trips, t_step = NP <= 2 ? 1 : NP - 1;
+    SetRegs next;
+    if (t < t_end) next = load_sets<true>(sets, 8 * t, a.nsplit);
+    if (!SIDE && ra.r > 0) ts = trail_state(ra, tr);
+    if (SIDE && part == SP) {
+      float delta = 0.0f;
+      for (int s = l; s < a.nsplit; s += 64) delta = fmaxf(delta, ld_set<true>(sets, (uint32_t)s * PART_FLOATS + P_DMAX));
+      side_work(wave_max(delta));
+    }
+    for (; t < t_end; t += t_step) {
+      const SetRegs cur = next;
+      if (t + t_step < t_end) next = load_sets<true>(sets, 8 * (t + t_step), a.nsplit);
+      st = merge_loaded(cur, 8 * t, a.nsplit, 0, a.nsplit, o2);
+      if (NP <= 2 ? trips > 1 : (trips > 2 || t > 0)) store_state(st, o2, (&ms[0][0][0]) + (t * G + hh) * 12, (&mo[0][0][0]) + (t * G + hh) * D);
+    }
+    if (NP > 1) __syncthreads(); else wave_sync();
+    if (part == 0 && trips > 1) {
+      if (NP > 2 && trips == 2)
+        st = join_lds(st, &ms[0][0][0] + (G + hh) * 12, &mo[0][0][0] + (G + hh) * D, o2);
+      else
+        st = merge_lds(ms[0][w], G * 12, mo[0][w], G * D, trips, o2);
+    }
+  } else if (SIDE) {
+    if (part == SP) {
+      float delta = 0.0f;
+#pragma unroll
+      for (int i = 0; i < W; ++i) delta = fmaxf(delta, ms[i][hh][P_DMAX]);
+      side_work(delta);
+    }
+    __syncthreads();
+  } else if (ra.r > 0) {
+    ts = trail_state(ra, tr);
+  }
+  if (part == 0) {
+    const HeadState hs = head_state(st, o2);
+    if (SIDE) {
+      const float* x = s_side[w];
+      if (spare) ts = TrailState{x[0], x[1], x[2], *reinterpret_cast<const float2*>(&s_tail[w][2 * l])};
+      kt = KeyTerms{x[3], x[4], x[5]};
+    } else {
+      kt = key_terms(ra, hs.DM);
+    }
+    const HeadRow row = finish_row(ra, hs, ts, kt, nullptr);
+    store_row(ra, row0 + w, row, G == 1);
+    if (l == 0) s_fl[w] = row.fl;
   }
   // The group's mirrored flag words, neighbours in host memory, by one store: by one of each wave, at the same moment, they
   // wait for one another.  A host-resolved step, a store per wave and one: 2 heads per group, 720 KV heads of 300 tokens 44.4 -> 35.9
@@ -702,7 +814,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void certified_split_mfma_kernel(Dec
   if (G > 1 && finish && ra.flags_mirror != nullptr) {
     __syncthreads();
     if (w == 0 && l < G)
-      __hip_atomic_store(ra.flags_mirror + (int64_t)b * a.n_q + hq0 + l, s_fl[l] | ra.mirror_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(ra.flags_mirror + row0 + l, s_fl[l] | ra.mirror_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -766,17 +878,21 @@ int32_t launch_split_mfma(const DecodeArgs& a, const ReduceArgs& ra, int group, 
   if (a.wpb != 4 && a.wpb != 8) return CQA_ERR_INVALID_ARG;
 // The launch that takes events costs the host 2.3 us more than the plain one (a step of three launches 10.8, 8.4 us), which
 // short steps wait for, so it is used for timing only.
-#define CQA_LAUNCH_LM(GG, LMV, NTV, Q8V, WV, ONEV)                                                 \
+#define CQA_LAUNCH_LM(GG, LMV, NTV, Q8V, WV, ONEV, WTV)                                            \
   if (ev0 != nullptr)                                                                              \
-    hipExtLaunchKernelGGL((certified_split_mfma_kernel<GG, LMV, NTV, Q8V, WV, ONEV>), grid, dim3(64 * WV), 0, st, ev0, \
+    hipExtLaunchKernelGGL((certified_split_mfma_kernel<GG, LMV, NTV, Q8V, WV, ONEV, WTV>), grid, dim3(64 * WTV), 0, st, ev0, \
                           ev1, 0, a, ra);                                                          \
   else                                                                                             \
-    hipLaunchKernelGGL((certified_split_mfma_kernel<GG, LMV, NTV, Q8V, WV, ONEV>), grid, dim3(64 * WV), 0, st, a, ra);
+    hipLaunchKernelGGL((certified_split_mfma_kernel<GG, LMV, NTV, Q8V, WV, ONEV, WTV>), grid, dim3(64 * WTV), 0, st, a, ra);
 #define CQA_LAUNCH_W(GG, NTV, Q8V, WV, ONEV)                                                       \
-  if (lm) { CQA_LAUNCH_LM(GG, true, NTV, Q8V, WV, ONEV) } else { CQA_LAUNCH_LM(GG, false, NTV, Q8V, WV, ONEV) }
+  if (lm) { CQA_LAUNCH_LM(GG, true, NTV, Q8V, WV, ONEV, WV) } else { CQA_LAUNCH_LM(GG, false, NTV, Q8V, WV, ONEV, WV) }
 #define CQA_LAUNCH_Q(GG, NTV, Q8V)                                                                 \
   if (a.wpb == 8) {                                                                                \
     if (one) { CQA_LAUNCH_W(GG, NTV, Q8V, 8, true) } else { CQA_LAUNCH_W(GG, NTV, Q8V, 8, false) } \
+  } else if (a.waves == 8) {                                                                       \
+    CQA_LAUNCH_LM(GG, false, NTV, Q8V, 4, true, 8)                                                 \
+  } else if (GG == 4 && a.waves == 12) {                                                           \
+    CQA_LAUNCH_LM(4, false, NTV, Q8V, 4, true, 12)                                                 \
   } else {                                                                                         \
     if (one) { CQA_LAUNCH_W(GG, NTV, Q8V, 4, true) } else { CQA_LAUNCH_W(GG, NTV, Q8V, 4, false) } \
   }

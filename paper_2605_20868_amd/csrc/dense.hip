@@ -451,6 +451,8 @@ __device__ __forceinline__ void ladder_serve(const LadderArgs& a, int rung, int 
   }
 }
 
+static_assert(sizeof(LadderArgs) % 8 == 0 && alignof(ReduceArgs) == 8, "the second argument follows the first");
+
 // The fallback ladder resolved on the device (the paper's "Fallback Ladder": Rung 3 returns the
 // dense FP16 result for the flagged heads, Rung 4 for every head of the layer-step).  Launched
 // behind the reduction on every step.  The reduction leaves the step's number in `raised` when it
@@ -462,11 +464,40 @@ __device__ __forceinline__ void ladder_serve(const LadderArgs& a, int rung, int 
 // straight from the pinned host arrays (the device reads host memory over the link: no copy
 // call, no staging buffer, no host decision), and the last of a group's items to arrive merges the
 // splits and rewrites O, the certificate and the rung bits of the heads that are served.
-template <int G>
-__global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
-  if (*a.raised != a.raised_tag) return;
+// Behind a split pass that reduces the rows itself every wave also looks at the numbers that it left.  Where one is not
+// this step's, every workgroup reduces all rows, to know every flag without waiting for another one, and the
+// first one writes them, leaving out the outputs that a rung replaces.
+// Leaving is what nearly every launch does, so no more than the first line of the arguments is read up to there (with all of
+// them first, 0.6 us more for a step of 64 x 4 heads, 2000 tokens).
+template <int G, typename... RA>
+__global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs first, RA...) {
+  constexpr bool CHECK = sizeof...(RA) > 0;
+  bool strayed = false;
+  const uint32_t raised = *first.raised;
+  if constexpr (CHECK) {
+    const uint32_t* const reduced = first.split_tickets + (int64_t)first.groups * TICKET_STRIDE;
+    for (int g = threadIdx.x & 63; g < first.groups; g += 64) strayed = strayed | (reduced[g] != first.raised_tag);
+    strayed = __any(strayed);
+  }
+  if (raised != first.raised_tag && !strayed) return;
+  const LadderArgs a = arg_read_here<LadderArgs>(0);
   __shared__ int s_rung, s_walkers;
   __shared__ int s_cnt[4], s_pre[4];
+  __shared__ uint32_t s_flags[CHECK ? REDUCED_ROWS : 1];   // of rows reduced here
+  if constexpr (CHECK) {
+    if (strayed) {
+      const ReduceArgs ra = arg_read_here<ReduceArgs>(sizeof(LadderArgs));
+      for (int r = threadIdx.x >> 6; r < a.n_rows; r += 4) {
+        const HeadRow row = reduce_row_wave(ra, r);
+        if ((threadIdx.x & 63) == 0) s_flags[r] = row.fl;
+      }
+      if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < a.groups * DIES; i += 256)
+          a.split_tickets[(int64_t)(i / DIES) * TICKET_STRIDE + i % DIES] = 0u;
+      __syncthreads();
+    }
+  }
+  const auto flag_of = [&](int64_t r) { return CHECK && strayed ? s_flags[r] : a.flags[r]; };
   {
     // each wave takes every fourth chunk of 64 flag words (a group's heads never straddle a
     // chunk: G divides 64), four chunks per trip with all loads issued first
@@ -478,7 +509,7 @@ __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int i = base + (j * 4 + w) * 64 + l;
-        f[j] = i < a.n_rows ? a.flags[i] : 0u;
+        f[j] = i < a.n_rows ? flag_of(i) : 0u;
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -513,58 +544,28 @@ __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs a) {
   }
   __syncthreads();
   const int rung = s_rung;
+  if constexpr (CHECK) {
+    for (int r = threadIdx.x >> 6; r < (strayed && blockIdx.x == 0 ? a.n_rows : 0); r += 4) {
+      HeadRow row = reduce_row_wave(arg_read_here<ReduceArgs>(sizeof(LadderArgs)), r);
+      if (rung == 4 || (rung == 3 && (row.fl & CQA_FLAG_ANY) != 0u)) {
+        row.ct.E_key = 0.0f;
+        row.ct.E_val = 0.0f;
+        row.ct.served_rung = rung;
+        row.fl = (row.fl & ~(7u << CQA_RUNG_SHIFT)) | ((uint32_t)rung << CQA_RUNG_SHIFT);
+      } else {
+        reinterpret_cast<float2*>(a.O + (int64_t)r * D)[threadIdx.x & 63] = row.out;
+      }
+      if ((threadIdx.x & 63) == 0) {
+        a.cert[r] = row.ct;
+        a.flags[r] = row.fl;
+      }
+    }
+  }
   if (rung == 0) return;
 
   __shared__ __align__(16) DenseSmem<G, 4> sm;
   // (the rung bits that a finished group's rows get do not touch the bits looked at here)
-  ladder_serve<G, 4>(a, rung, s_walkers, [&](int64_t row) { return (a.flags[row] & CQA_FLAG_ANY) != 0u; }, true, sm);
-}
-
-// Reduction and ladder of a short step of few rows (at most FINISH_ROWS heads with at most FINISH_SETS partial sets
-// each) in one launch: every workgroup merges all rows, one per wave, and so knows every flag
-// without waiting for another one; the first one writes the rows, leaving out the outputs that a
-// rung replaces, and the others leave unless a head asks for a fallback.  A step in two launches and in one:
-// 4 rows 12.4, 10.5 us at 3 sets and 11.8, 10.9 at 8; 8 rows of 8 KV heads 13.3, 12.3 at 3 and 13.0, 12.4 at 8, of
-// 2 KV heads level (11.9, 12.0; 12.1, 12.1).  (32 rows, two per wave of 16, with an earlier merge: 13 -> 23 us, the workgroups'
-// copies of the work get in each other's way.)
-template <int G>
-__global__ __launch_bounds__(64 * FINISH_ROWS) void finish_ladder_kernel(ReduceArgs ra, LadderArgs a) {
-  fetch_args<sizeof(ReduceArgs) + sizeof(LadderArgs)>();
-  const int r = threadIdx.x >> 6, l = threadIdx.x & 63;   // this wave's row
-  __shared__ uint32_t s_fl[FINISH_ROWS];
-  HeadRow row;
-  row.fl = 0u;
-  if (r < a.n_rows) row = reduce_row_wave(ra, r / ra.n_q, r % ra.n_q);
-  if (l == 0) s_fl[r] = row.fl;
-  __syncthreads();
-  const uint32_t f = l < FINISH_ROWS ? s_fl[l] : 0u;
-  const uint32_t any = (uint32_t)__ballot((f & CQA_FLAG_ANY) != 0u);       // bit i: row i
-  const bool pre = __ballot((f & CQA_FLAG_PRECOND) != 0u) != 0ull;
-  uint32_t gm = any;
-#pragma unroll
-  for (int jj = 1; jj < G; ++jj) gm |= any >> jj;
-  gm &= G == 1 ? ~0u : (G == 2 ? 0x55555555u : 0x11111111u);
-  const int cnt = __popc(gm);
-  int rung = cnt > 0 ? 3 : 0;
-  if (rung != 0 && (pre || (a.rung4_min_groups > 0 && cnt >= a.rung4_min_groups))) rung = 4;
-  if (blockIdx.x == 0 && r < a.n_rows) {
-    if (rung == 4 || (rung == 3 && ((any >> r) & 1u) != 0u)) {
-      row.ct.E_key = 0.0f;
-      row.ct.E_val = 0.0f;
-      row.ct.served_rung = rung;
-      row.fl = (row.fl & ~(7u << CQA_RUNG_SHIFT)) | ((uint32_t)rung << CQA_RUNG_SHIFT);
-    } else {
-      reinterpret_cast<float2*>(a.O + (int64_t)r * D)[l] = row.out;
-    }
-    if (l == 0) {
-      a.cert[r] = row.ct;
-      a.flags[r] = row.fl;
-    }
-    if (rung != 0 && threadIdx.x == 0) atomicAdd(a.counts + (rung - 3), 1u);
-  }
-  if (rung == 0) return;
-  __shared__ __align__(16) DenseSmem<G, FINISH_ROWS> sm;
-  ladder_serve<G, FINISH_ROWS>(a, rung, (int)gridDim.x, [&](int64_t i) { return ((any >> (int)i) & 1u) != 0u; }, false, sm);
+  ladder_serve<G, 4>(a, rung, s_walkers, [&](int64_t row) { return (flag_of(row) & CQA_FLAG_ANY) != 0u; }, !strayed, sm);
 }
 
 int ladder_splits(const Cache* c, int64_t n_tokens) {
@@ -612,26 +613,22 @@ int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_
   a.O = O;
   a.cert = cert;
   a.flags = flags;
+  const dim3 grid((unsigned)std::min<int64_t>((int64_t)a.nsplit * a.groups, 2 * (int64_t)c->n_cu));
   if (reduce != nullptr) {
-    // Each of the workgroups merges the rows: no more of them than keep the host link busy when a rung serves.  Eight
-    // groups of one head, all served, on 64, 128, 256 and 512 workgroups: 600 tokens 121, 111, 116, 119 us, 1100
-    // tokens 165, 146, 162, 188, 2000 tokens 242, 250, 277, 278 (without a flag all four take 13.1 - 14.2; 512 16).
-    const dim3 fgrid((unsigned)std::min<int64_t>((int64_t)a.nsplit * a.groups, std::max(c->n_cu / 2, 1)));
+    a.split_tickets = c->split_tickets;
     switch (g) {
-      case 1: hipLaunchKernelGGL(finish_ladder_kernel<1>, fgrid, dim3(64 * FINISH_ROWS), 0, st, *reduce, a); break;
-      case 2: hipLaunchKernelGGL(finish_ladder_kernel<2>, fgrid, dim3(64 * FINISH_ROWS), 0, st, *reduce, a); break;
-      case 4: hipLaunchKernelGGL(finish_ladder_kernel<4>, fgrid, dim3(64 * FINISH_ROWS), 0, st, *reduce, a); break;
+      case 1: hipLaunchKernelGGL((dense_ladder_kernel<1, ReduceArgs>), grid, dim3(256), 0, st, a, *reduce); break;
+      case 2: hipLaunchKernelGGL((dense_ladder_kernel<2, ReduceArgs>), grid, dim3(256), 0, st, a, *reduce); break;
+      case 4: hipLaunchKernelGGL((dense_ladder_kernel<4, ReduceArgs>), grid, dim3(256), 0, st, a, *reduce); break;
       default: return CQA_ERR_UNSUPPORTED;
     }
-    CQA_HIP(hipGetLastError());
-    return CQA_OK;
-  }
-  const dim3 grid((unsigned)std::min<int64_t>((int64_t)a.nsplit * a.groups, 2 * (int64_t)c->n_cu));
-  switch (g) {
-    case 1: hipLaunchKernelGGL(dense_ladder_kernel<1>, grid, dim3(256), 0, st, a); break;
-    case 2: hipLaunchKernelGGL(dense_ladder_kernel<2>, grid, dim3(256), 0, st, a); break;
-    case 4: hipLaunchKernelGGL(dense_ladder_kernel<4>, grid, dim3(256), 0, st, a); break;
-    default: return CQA_ERR_UNSUPPORTED;
+  } else {
+    switch (g) {
+      case 1: hipLaunchKernelGGL(dense_ladder_kernel<1>, grid, dim3(256), 0, st, a); break;
+      case 2: hipLaunchKernelGGL(dense_ladder_kernel<2>, grid, dim3(256), 0, st, a); break;
+      case 4: hipLaunchKernelGGL(dense_ladder_kernel<4>, grid, dim3(256), 0, st, a); break;
+      default: return CQA_ERR_UNSUPPORTED;
+    }
   }
   CQA_HIP(hipGetLastError());
   return CQA_OK;

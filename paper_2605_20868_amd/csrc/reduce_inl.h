@@ -338,8 +338,58 @@ __device__ __forceinline__ HeadState head_state(const OctState& m, float2 o2) {
   return r;
 }
 
-// Merges partial sets first, first + 1, ..., first + 7, first + jump, ... of one head's n_sets (set s at part +
-// s * PART_FLOATS); of sets outside [pos0, pos1) only the channels (and maxima) count.  o2: channels 2l, 2l + 1.
+// Eight partial sets' scalars, as merge_oct takes them, and channels 2l, 2l + 1 of each.  LIVE: other workgroups of the same launch and
+// die have stored them: past the compute unit's own cache.
+struct SetRegs {
+  float v, m, t1, t2, i1;
+  float2 x[8];
+};
+template <bool LIVE>
+__device__ __forceinline__ float ld_set(const float* part, uint32_t at) {
+  const float* p = part + at;
+  return LIVE ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+// sets s0, s0 + 1, ... of one head's n_sets (set s at part + s * PART_FLOATS; 32 bits hold the offsets of MAX_SPLITS sets)
+template <bool LIVE>
+__device__ __forceinline__ SetRegs load_sets(const float* part, int s0, int n_sets) {
+  const uint32_t l = threadIdx.x & 63;
+  SetRegs r;
+  const uint32_t at = (uint32_t)min(s0 + (int)(l & 7), n_sets - 1) * PART_FLOATS;
+  r.v = ld_set<LIVE>(part, at + (l >> 3));
+  r.m = ld_set<LIVE>(part, at + P_M);
+  r.t1 = ld_set<LIVE>(part, at + P_T1);
+  r.t2 = ld_set<LIVE>(part, at + P_T2);
+  r.i1 = ld_set<LIVE>(part, at + P_I1);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float* po = part + (uint32_t)min(s0 + i, n_sets - 1) * PART_FLOATS + P_O;   // (uniform)
+    if (LIVE) {
+      const unsigned long long u =
+          __hip_atomic_load(reinterpret_cast<const unsigned long long*>(po) + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      r.x[i] = make_float2(__uint_as_float((uint32_t)u), __uint_as_float((uint32_t)(u >> 32)));
+    } else {
+      r.x[i] = reinterpret_cast<const float2*>(po)[l];
+    }
+  }
+  return r;
+}
+// ... merged; of sets outside [pos0, pos1) only the channels (and maxima) count
+__device__ __forceinline__ OctState merge_loaded(const SetRegs& g, int s0, int n_sets, int pos0, int pos1, float2& o) {
+  const int s = s0 + (threadIdx.x & 7);
+  float f;
+  const OctState t = merge_oct(g.v, g.m, g.t1, g.t2, __float_as_int(g.i1), s < n_sets, s >= pos0 && s < pos1, f);
+  o = make_float2(0.0f, 0.0f);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float fi = lane_of(f, i);            // zero for sets past the end
+    o.x = fmaf(fi, g.x[i].x, o.x);
+    o.y = fmaf(fi, g.x[i].y, o.y);
+  }
+  return t;
+}
+
+// Merges partial sets first, first + 1, ..., first + 7, first + jump, ... of one head's n_sets; of sets outside
+// [pos0, pos1) only the channels (and maxima) count.  o2: channels 2l, 2l + 1.
 // All loads of a trip are issued before anything is consumed.
 __device__ __forceinline__ OctState merge_sets(const float* part, int first, int jump, int n_sets, int pos0, int pos1, float2& o2) {
   const int l = threadIdx.x & 63;
@@ -349,22 +399,8 @@ __device__ __forceinline__ OctState merge_sets(const float* part, int first, int
   r.x = (l >> 3) >= P_L && (l >> 3) <= P_VMAX ? 0.0f : -INFINITY;
   o2 = make_float2(0.0f, 0.0f);
   for (int s0 = first; s0 < n_sets; s0 += jump) {
-    const int s = s0 + (l & 7);
-    const float* ps = part + (int64_t)min(s, n_sets - 1) * PART_FLOATS;
-    const float v = ps[l >> 3], m = ps[P_M], t1 = ps[P_T1], t2 = ps[P_T2], i1 = ps[P_I1];
-    float2 x[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      x[i] = *reinterpret_cast<const float2*>(part + (int64_t)min(s0 + i, n_sets - 1) * PART_FLOATS + P_O + 2 * l);
-    float f;
-    const OctState t = merge_oct(v, m, t1, t2, __float_as_int(i1), s < n_sets, s >= pos0 && s < pos1, f);
-    float2 o = make_float2(0.0f, 0.0f);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float fi = lane_of(f, i);            // zero for sets past the end
-      o.x = fmaf(fi, x[i].x, o.x);
-      o.y = fmaf(fi, x[i].y, o.y);
-    }
+    float2 o;
+    const OctState t = merge_loaded(load_sets<false>(part, s0, n_sets), s0, n_sets, pos0, pos1, o);
     if (s0 == first) {
       r = t;
       o2 = o;
@@ -380,18 +416,54 @@ __device__ __forceinline__ OctState merge_sets(const float* part, int first, int
 
 // Merges the states of n <= 8 waves kept in LDS: scalars at ms + i * ms_stride, channels at mo + i * mo_stride.
 // Waves that saw no block hold zeros and a maximum of -infinity; the result of only such waves is one more of the kind.
+// N: the number when it is known, and all reads are on their way at once (else four at a time).
+template <int N = 0>
 __device__ __forceinline__ OctState merge_lds(const float* ms, int ms_stride, const float* mo, int mo_stride, int n, float2& o2) {
   const int l = threadIdx.x & 63, i = l & 7;
+  if (N > 0) n = N;
   const float* m = ms + (i < n ? i : 0) * ms_stride;
   float f;
   const OctState r = merge_oct(m[l >> 3], m[P_M], m[P_T1], m[P_T2], __float_as_int(m[P_I1]), i < n, true, f);
   o2 = make_float2(0.0f, 0.0f);
-  for (int k = 0; k < n; ++k) {
-    const float fk = lane_of(f, k);
-    const float2 x = *reinterpret_cast<const float2*>(mo + k * mo_stride + 2 * l);
-    o2.x = fmaf(fk, x.x, o2.x);
-    o2.y = fmaf(fk, x.y, o2.y);
+  if (N > 0) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const float fk = lane_of(f, k);
+      const float2 x = *reinterpret_cast<const float2*>(mo + k * mo_stride + 2 * l);
+      o2.x = fmaf(fk, x.x, o2.x);
+      o2.y = fmaf(fk, x.y, o2.y);
+    }
+    return r;
   }
+  for (int k0 = 0; k0 < n; k0 += 4) {
+    float2 x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = *reinterpret_cast<const float2*>(mo + min(k0 + k, n - 1) * mo_stride + 2 * l);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (k0 + k >= n) break;
+      const float fk = lane_of(f, k0 + k);
+      o2.x = fmaf(fk, x[k].x, o2.x);
+      o2.y = fmaf(fk, x[k].y, o2.y);
+    }
+  }
+  return r;
+}
+
+// state a, channels o2, joined by one that store_state has left: what merge_lds gives for the two, bit for bit
+__device__ __forceinline__ OctState join_lds(const OctState& a, const float* ms, const float* mo, float2& o2) {
+#pragma clang fp contract(off)
+  const int l = threadIdx.x & 63;
+  OctState b;
+  b.x = ms[l >> 3];
+  b.M = ms[P_M];
+  b.T1 = ms[P_T1];
+  b.i1 = __float_as_int(ms[P_I1]);
+  const float2 x = *reinterpret_cast<const float2*>(mo + 2 * l);
+  float fa, fb;
+  const OctState r = merge_two(a, b, fa, fb);
+  o2.x = fmaf(fb, x.x, fa * o2.x);
+  o2.y = fmaf(fb, x.y, fa * o2.y);
   return r;
 }
 // a state as merge_lds reads it / as a partial set
@@ -405,16 +477,19 @@ __device__ __forceinline__ void store_state(const OctState& m, float2 o2, float*
 // Trailing FP16 tokens of one head (at most 15), requested before the partial sets and used after them.
 //   scores / norms: lane (t = l >> 2, cpart = l & 3) covers channels 32 cpart .. 32 cpart + 31 of
 //   token t; values for the output: lane l covers channels 2l, 2l + 1 of every token.
+__device__ __forceinline__ int64_t row_of(const ReduceArgs& a, int b, int hq) { return (int64_t)b * a.n_q + hq; }
+__device__ __forceinline__ int64_t group_of(const ReduceArgs& a, int b, int hq) {
+  return (int64_t)b * a.n_kv + (hq >> group_shift(a.n_q, a.n_kv));
+}
 struct TrailRegs {
   uint4 kq[4], vq[4], qq[4];
   __half2 vt[BLK - 1];
 };
 
 // new_k, new_v (null = none): the last trailing token, when the launch that calls this also appends it
-__device__ __forceinline__ void load_trail(const ReduceArgs& a, int b, int hq, const __half* new_k,
+__device__ __forceinline__ void load_trail(const ReduceArgs& a, int64_t grp, int64_t row, const __half* new_k,
                                            const __half* new_v, TrailRegs& t) {
   const int l = threadIdx.x & 63;
-  const int64_t grp = (int64_t)b * a.n_kv + (hq >> group_shift(a.n_q, a.n_kv));
   const __half* tk = a.trail_k + grp * BLK * D;
   const __half* tv = a.trail_v + grp * BLK * D;
   const int last = max(a.r - 1, 0);
@@ -422,7 +497,7 @@ __device__ __forceinline__ void load_trail(const ReduceArgs& a, int b, int hq, c
   const bool fresh = new_k != nullptr && tt == last;
   const __half* kp = (fresh ? new_k + grp * D : tk + tt * D) + cpart * 32;
   const __half* vp = (fresh ? new_v + grp * D : tv + tt * D) + cpart * 32;
-  const __half* qp = a.q + ((int64_t)b * a.n_q + hq) * D + cpart * 32;
+  const __half* qp = a.q + row * D + cpart * 32;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     t.kq[i] = ld16_any(kp + 8 * i);
@@ -532,11 +607,13 @@ __device__ __forceinline__ HeadRow finish_row(const ReduceArgs& a, const HeadSta
   row.out = make_float2(o2.x / L, o2.y / L);
   const bool bad = __any(!isfinite(row.out.x) || !isfinite(row.out.y));
 
-  // certificate scalars in FP32 (a handful of operations; their rounding is ~1e-7 relative)
-  const float e_val = EV / L;
+  // certificate scalars in FP32 (a handful of operations; their rounding is ~1e-7 relative); three quotients by one division, a lane each
+  const int lane = threadIdx.x & 63;
+  const float share = (lane == 0 ? EV : (lane == 1 ? EVM : L_sealed)) / L;
+  const float e_val = lane_of(share, 0);
   const float lse = M + logf(L);
-  const float maxc = EVM / L;
-  const float alpha_hat = ad != nullptr ? ad->alpha : L_sealed / L;
+  const float maxc = lane_of(share, 1);
+  const float alpha_hat = ad != nullptr ? ad->alpha : lane_of(share, 2);
   const float delta = ad != nullptr ? ad->delta : DM;
   const float vmax = VM;
   float t_tail = 0.0f;
@@ -582,9 +659,8 @@ __device__ __forceinline__ HeadRow finish_row(const ReduceArgs& a, const HeadSta
 }
 
 // mirror: the row's own store of its mirrored flag word (the caller makes it otherwise, behind these stores)
-__device__ __forceinline__ void store_row(const ReduceArgs& a, int b, int hq, const HeadRow& row, bool mirror = true) {
+__device__ __forceinline__ void store_row(const ReduceArgs& a, int64_t r, const HeadRow& row, bool mirror = true) {
   const int l = threadIdx.x & 63;
-  const int64_t r = (int64_t)b * a.n_q + hq;
   reinterpret_cast<float2*>(a.O + r * D)[l] = row.out;
   if (l == 0) {
     a.cert[r] = row.ct;
@@ -600,7 +676,7 @@ __device__ __forceinline__ void store_row(const ReduceArgs& a, int b, int hq, co
 
 __device__ __forceinline__ void finish_head(const ReduceArgs& a, int b, int hq, const HeadState& hs, const TrailState& ts,
                                             const KeyTerms& kt, const AdaptiveIn* ad) {
-  store_row(a, b, hq, finish_row(a, hs, ts, kt, ad));
+  store_row(a, row_of(a, b, hq), finish_row(a, hs, ts, kt, ad));
 }
 
 // One (batch, query head) by a workgroup of `waves` waves, at least three.  It runs on the critical tail of a step, alone on the
@@ -625,7 +701,7 @@ __device__ __forceinline__ void trail_part(const ReduceArgs& a, int b, int hq, R
   if (a.r <= 0) return;
   const int l = threadIdx.x & 63;
   TrailRegs tr;
-  load_trail(a, b, hq, nullptr, nullptr, tr);
+  load_trail(a, group_of(a, b, hq), row_of(a, b, hq), nullptr, nullptr, tr);
   const TrailState ts = trail_state(a, tr);
   *reinterpret_cast<float2*>(&sm.trail_o[2 * l]) = ts.o;
   if (l == 0) {
@@ -671,13 +747,12 @@ __device__ __forceinline__ bool reduce_row(const ReduceArgs& a, int b, int hq, i
 }
 
 // ... by one wave, its parts one after the other.
-__device__ __forceinline__ HeadRow reduce_row_wave(const ReduceArgs& a, int b, int hq) {
+__device__ __forceinline__ HeadRow reduce_row_wave(const ReduceArgs& a, int64_t row) {
   TrailRegs tr;
   TrailState ts{};
-  if (a.r > 0) load_trail(a, b, hq, nullptr, nullptr, tr);
+  if (a.r > 0) load_trail(a, row >> group_shift(a.n_q, a.n_kv), row, nullptr, nullptr, tr);
   float2 o2;
-  const OctState st = merge_sets(a.partials + ((int64_t)b * a.n_q + hq) * (a.pstride > 0 ? a.pstride : a.nsplit) * PART_FLOATS,
-                                 0, 8, a.nsplit, 0, a.nsplit, o2);
+  const OctState st = merge_sets(a.partials + row * (a.pstride > 0 ? a.pstride : a.nsplit) * PART_FLOATS, 0, 8, a.nsplit, 0, a.nsplit, o2);
   if (a.r > 0) ts = trail_state(a, tr);
   const HeadState hs = head_state(st, o2);
   return finish_row(a, hs, ts, key_terms(a, hs.DM), nullptr);

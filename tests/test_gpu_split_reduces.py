@@ -1,0 +1,130 @@
+"""Enqueue-only steps whose split pass reduces its partial sets itself: the last workgroup of a KV group to arrive finishes the
+rows, or, where the group's workgroups are not on one die, the ladder's launch does.  Rows are those of the certified call, which
+reduces in a launch of its own, bit for bit up to 64 sets."""
+import numpy as np
+import pytest
+
+from helpers import GpuLayerCache
+
+pytestmark = pytest.mark.gpu
+
+
+def make(bt, hkv, g, n):
+    rng = np.random.default_rng(n + 31 * bt + hkv)
+    k = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    v = rng.standard_normal((bt, hkv, n, 128), dtype=np.float32).astype(np.float16)
+    return k, v, rng.standard_normal((bt, hkv * g, 128)).astype(np.float16)
+
+
+def step(gc, q, tol, kv=(None, None)):
+    gc.O.fill_(float("nan"))
+    gc.cqa.cqa_decode_step_enqueue(gc.h, 0, kv[0], kv[1], gc.to_dev(q), tol, gc.O, gc.cert, gc.flags)
+    return [x.copy() for x in gc.results()]
+
+
+# (batch, kv heads, group, tokens, sets): first and last of what each form takes, groups that do not divide among the dies
+SHAPES = [
+    (1, 8, 4, 64 * 8 + 16, 3),        # four quad waves and four without, one quad in the last workgroup
+    (1, 8, 4, 64 * 32 + 5, 8),        # ... the most sets of one trip
+    (1, 8, 4, 64 * 32 + 17, 9),       # twelve waves, two trips
+    (1, 4, 4, 64 * 64, 16),           # ... the most; nothing behind the sealed blocks
+    (1, 1, 4, 64 * 64 + 16, 17),      # one set more: the reduction's launch
+    (2, 4, 2, 64 * 96, 24),           # three trips of three rows of waves
+    (1, 8, 1, 64 * 128 + 3, 32),      # four trips, the most that four quad waves keep
+    (3, 1, 2, 64 * 20 + 9, 5),        # three KV groups, one to a die
+    (11, 1, 4, 64 * 40 + 1, 10),      # eleven, two on some dies
+    (11, 1, 1, 64 * 80 + 1, 20),      # ... with more workgroups there than compute units: the reduction's launch
+    (4, 8, 4, 64 * 63 + 40, 8),       # eight quad waves, one quad each
+    (16, 8, 4, 64 * 16 + 1, 2),       # ... two sets, a workgroup on every compute unit
+    (1, 16, 1, 64 * 400 + 30, 16),    # ... several quads each, two trips
+    (36, 8, 1, 16 * 96 + 5, 3),       # four quad waves in more than one generation
+]
+
+
+@pytest.mark.parametrize("int8", [False, True])
+@pytest.mark.parametrize("bt,hkv,g,n,sets", SHAPES)
+def test_rows_are_those_of_the_certified_call(bt, hkv, g, n, sets, int8):
+    import torch
+    print("split reduces", bt, hkv, g, n, int8, flush=True)
+    k, v, q = make(bt, hkv, g, n)
+    with GpuLayerCache(bt, hkv * g, hkv, n + 32) as gc:
+        gc.append(k, v)
+        if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+            assert gc.cqa.cqa_decode_splits(gc.h, 0) == sets
+        tol = gc.cqa.Tolerances(int8_query=int8)
+        O, cert, flags = [x.copy() for x in gc.certified_decode(q, tol)]
+        assert np.isfinite(O).all()
+        for on in (0, 0, 1, 0):
+            gc.cqa.cqa_set_scatter(gc.h, on)
+            O2, cert2, flags2 = step(gc, q, tol)
+            assert (flags2 == flags).all()
+            if on == 0 or sets <= 8:
+                assert np.array_equal(O, O2) and cert.tobytes() == cert2.tobytes(), on
+            else:
+                # one wave merges eight sets after the other: another order of the same binary32 sums (8 trips of 2^-23)
+                assert np.abs(O2 - O).max() <= 1e-5 * np.abs(O).max()
+                for f in ("E_key", "E_val", "lse", "alpha_tail_hat"):
+                    assert np.allclose(cert2[f], cert[f], rtol=1e-5, atol=1e-9), f
+                assert (cert2["top_block"] == cert["top_block"]).all()
+
+
+@pytest.mark.parametrize("scatter", [0, 1])
+@pytest.mark.parametrize("bt,hkv,g,n", [(1, 8, 4, 64 * 20 + 7), (2, 4, 2, 64 * 30 + 11), (1, 8, 1, 64 * 30), (16, 8, 4, 64 * 12 + 3)])
+def test_heads_over_a_threshold_are_served(bt, hkv, g, n, scatter):
+    """Rung 3 for the heads that ask and no other, Rung 4 with a limit on the groups, the token of the step among the
+    attended ones; on both routes, and a plain step behind each."""
+    print("split reduces, served", bt, hkv, g, n, scatter, flush=True)
+    k, v, q = make(bt, hkv, g, n + 1)
+    with GpuLayerCache(bt, hkv * g, hkv, n + 32) as gc, GpuLayerCache(bt, hkv * g, hkv, n + 32) as other:
+        gc.append(k[:, :, :n], v[:, :, :n])
+        other.append(k, v)
+        O, cert, _ = [x.copy() for x in other.certified_decode(q)]
+        total = cert["E_key"] + cert["E_val"]
+        order = np.sort(total.ravel())
+        eps = float(np.float32(0.5 * (order[-3] + order[-2])))
+        over = total > np.float32(eps)
+        assert 0 < over.sum() < over.size
+        cqa = gc.cqa
+        cqa.cqa_set_scatter(gc.h, scatter)
+        new = [gc.to_dev(np.ascontiguousarray(x[:, :, n:])) for x in (k, v)]
+        O2, cert2, flags2 = step(gc, q, cqa.Tolerances(eps_total=eps), new)
+        assert (cert2["served_rung"] == np.where(over, 3, 0)).all()
+        assert (((flags2 & cqa.FLAG_TOTAL) != 0) == over).all()
+        assert np.array_equal(O2[~over], O[~over])
+        dense = step(other, q, cqa.Tolerances(force_flags=cqa.FLAG_TOTAL))[0]
+        assert np.abs(O2 - dense)[over].max() <= 1e-5 * np.abs(dense).max()   # binary32 sums in another order
+        O4, cert4, _ = step(gc, q, cqa.Tolerances(eps_total=eps, rung4_min_groups=1))
+        assert (cert4["served_rung"] == 4).all() and np.abs(O4 - dense).max() <= 1e-5 * np.abs(dense).max()
+        for on in (scatter, 0):
+            cqa.cqa_set_scatter(gc.h, on)
+            O5, cert5, flags5 = step(gc, q, cqa.Tolerances())
+            assert np.array_equal(O5, O) and (cert5["served_rung"] == 0).all() and (flags5 == 0).all()
+
+
+@pytest.mark.parametrize("bt,hkv,g,n", [(1, 8, 4, 64 * 20 + 7), (1, 8, 4, 64 * 40 + 7)])
+def test_recorded_steps_find_their_counters_cleared(bt, hkv, g, n):
+    """A recorded pair of steps, the first left to the ladder's launch, replayed with eager steps in between."""
+    print("split reduces, recorded", bt, hkv, g, n, flush=True)
+    k, v, q = make(bt, hkv, g, n)
+    with GpuLayerCache(bt, hkv * g, hkv, n + 32) as gc:
+        t, cqa = gc.torch, gc.cqa
+        gc.append(k, v)
+        tol = cqa.Tolerances()
+        O, cert, _ = [x.copy() for x in gc.certified_decode(q)]
+        qd, O1 = gc.to_dev(q).clone(), t.zeros_like(gc.O)
+        s, graph = t.cuda.Stream(), t.cuda.CUDAGraph()
+        t.cuda.synchronize()
+        with t.cuda.graph(graph, stream=s):
+            cqa.cqa_set_scatter(gc.h, 1)
+            cqa.cqa_decode_step_enqueue(gc.h, 0, None, None, qd, tol, O1, gc.cert, gc.flags, s.cuda_stream)
+            cqa.cqa_set_scatter(gc.h, 0)
+            cqa.cqa_decode_step_enqueue(gc.h, 0, None, None, qd, tol, gc.O, gc.cert, gc.flags, s.cuda_stream)
+        for _ in range(3):
+            gc.O.fill_(float("nan"))
+            O1.fill_(float("nan"))
+            t.cuda.synchronize()
+            graph.replay()
+            t.cuda.synchronize()
+            assert np.array_equal(gc.results()[0], O) and gc.results()[1].tobytes() == cert.tobytes()
+            assert np.abs(O1.cpu().numpy() - O).max() <= 1e-5 * np.abs(O).max()
+            assert np.array_equal(step(gc, q, tol)[0], O)
