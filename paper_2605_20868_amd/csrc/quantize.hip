@@ -32,7 +32,8 @@ struct SealArgs {
   int r;                // tokens in the trailing block before this append
   int r_new;            // ... and after it: the last r_new of the new tokens
   int layer, batch, n_kv;
-  int n_seal, per;      // blocks to seal, consecutive ones per workgroup
+  int n_seal, runs;     // blocks to seal, workgroups per head: blocks w first, + step, + 2 step, ... of workgroup w, `most` of them
+  int first, step, most;
   // the kernel also stores the FP16 originals of the new tokens into the pinned Tier-2 arrays, unless they go
   // through the copy engines (null)
   __half* t2_k;         // [heads][t2_cap][128]
@@ -116,8 +117,9 @@ __device__ __forceinline__ void store_originals(const __half* in, __half* t2, in
   }
 }
 
-// One workgroup of two waves seals a run of up to eight consecutive blocks of 16 tokens, each wave requesting its
-// share of the next block while it works on one; the waves do not wait for each other.
+// One workgroup of two waves seals blocks of 16 tokens of a head, every `runs`-th as a rule, each wave requesting its
+// share of the next block while it works on one; the waves do not wait for each other.  The workgroups, all resident at once,
+// advance together, so a launch writes a window of consecutive records that moves through each head.
 //   wave 0, keys   : lane = channels 2 l, 2 l + 1; its 2 x 16 values give l_c, u_c, sigma_c, z_c and the
 //                    32 codes;
 //   wave 1, values : lane = (token t, quarter p) = (l >> 2, l & 3), groups p and 4 + p; its 2 x 16 values
@@ -128,8 +130,8 @@ __device__ __forceinline__ void store_originals(const __half* in, __half* t2, in
 // are taken on packed FP16, a code is one subtraction, product, rounding and saturating byte
 // conversion, and elements near a half-integer are looked at again only in lanes that have one.
 // 65549 tokens x 8 heads (268 MB in, 151 MB out): 168 us with both roles in every wave, one after the
-// other; 105 us like this one block at a time, 95 us in runs of eight = 4.4 TB/s.  (Four waves per SIMD
-// instead of three spill: 112 us; runs of 2: 98 us, of 21: 108 us.  FP32 annotation sums: no faster.)
+// other; 105 us like this one block at a time, 95 us in runs of eight consecutive ones, 93 us = 4.5 TB/s dealt like this.  (Four
+// waves per SIMD instead of three spill: 112 us; runs of 21 consecutive blocks: 108 us.  FP32 annotation sums: no faster.)
 // The first workgroup of a head also moves the tokens that stay unsealed into the trailing block
 // (it is the one that reads the old ones), the last clears the metadata of the blocks that
 // its quad record does not hold yet (the decode pass reads whole records).
@@ -138,8 +140,8 @@ __device__ __forceinline__ void store_originals(const __half* in, __half* t2, in
 __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
   fetch_args<sizeof(SealArgs)>();
   const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int j = (int)blockIdx.x * a.per;      // new block index
-  const int j1 = min(j + a.per, a.n_seal);
+  int j = (int)blockIdx.x * a.first;    // new block index
+  const int j1 = min(j + a.most * a.step, a.n_seal);
   const int kvh = blockIdx.y, b = blockIdx.z;
   const int64_t grp = (int64_t)b * a.n_kv + kvh;
   const int64_t head = (int64_t)a.layer * a.batch * a.n_kv + grp;
@@ -167,13 +169,13 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
       for (int t = 0; t < BLK; ++t) kn[t] = (kin + (int64_t)j * (BLK * D / 2))[t * (D / 2) + l];
     }
     float smax = 0.0f;
-    for (; j < j1; ++j) {
+    for (; j < j1; j += a.step) {
       const int64_t blk = a.nb_old + j;
 #pragma unroll
       for (int t = 0; t < BLK; ++t) kx[t] = kn[t];
-      if (j + 1 < j1) {
+      if (j + a.step < j1) {
 #pragma unroll
-        for (int t = 0; t < BLK; ++t) kn[t] = (kin + (int64_t)(j + 1) * (BLK * D / 2))[t * (D / 2) + l];
+        for (int t = 0; t < BLK; ++t) kn[t] = (kin + (int64_t)(j + a.step) * (BLK * D / 2))[t * (D / 2) + l];
       }
       uint32_t mn = kx[0], mx = kx[0];
 #pragma unroll
@@ -238,7 +240,7 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
     // atomic is issued only by a workgroup that raises it
     if (l == 0) {
       int* const word = reinterpret_cast<int*>(a.sigmax + grp);
-      if (a.nb_old == 0 && gridDim.x == 1)
+      if (a.nb_old == 0 && a.runs == 1)
         *word = __float_as_int(smax);   // the sequence's first blocks, and no other workgroup has any: starts afresh
       else if (__float_as_int(smax) > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
         atomicMax(word, __float_as_int(smax));
@@ -253,12 +255,12 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) nxt[k >> 1][k & 1] = ld16_any(row + 8 * (8 * (k >> 1) + 2 * p + (k & 1)));
     }
-    for (; j < j1; ++j) {
+    for (; j < j1; j += a.step) {
       const int64_t blk = a.nb_old + j;
 #pragma unroll
       for (int k = 0; k < 4; ++k) raw[k >> 1][k & 1] = nxt[k >> 1][k & 1];
-      if (j + 1 < j1) {
-        const __half* row = vin + (int64_t)(j + 1) * (BLK * D);
+      if (j + a.step < j1) {
+        const __half* row = vin + (int64_t)(j + a.step) * (BLK * D);
 #pragma unroll
         for (int k = 0; k < 4; ++k) nxt[k >> 1][k & 1] = ld16_any(row + 8 * (8 * (k >> 1) + 2 * p + (k & 1)));
       }
@@ -355,9 +357,9 @@ __global__ __launch_bounds__(128, 3) void seal_kernel(SealArgs a) {
       if (t2 != nullptr) reinterpret_cast<uint4*>(t2 + (head * a.t2_cap + a.len_before + src) * D)[l & 15] = x;
     }
   }
-  if (j1 == a.n_seal) {
+  if (j1 == a.n_seal && (a.step == 1 || (a.n_seal - 1) % a.step == (int)blockIdx.x)) {
     const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
-    for (int64_t nb = a.nb_old + j1; (nb & 3) != 0; ++nb) {
+    for (int64_t nb = a.nb_old + a.n_seal; (nb & 3) != 0; ++nb) {
       if (w == 0) {
         reinterpret_cast<uint4*>(a.t1 + t1_offset(rec, nb, Q_KM, KM_BYTES))[l] = zero;
       } else {
@@ -429,12 +431,20 @@ int32_t launch_seal(Cache* c, int layer, const __half* k_in, const __half* v_in,
     a.t2_v = tier2_by_kernel ? c->t2_v : nullptr;
     a.t2_cap = c->desc.max_tokens;
     a.len_before = len_before;
-    // one block per workgroup until the launch has two thousand of them (about what is resident at a
-    // time), then runs of up to eight
+    // One generation of workgroups, four to a compute unit, six (as many as there is room for) from 8192 blocks on: with more,
+    // a last generation leaves part of the chip idle.  Times with four, with six and with as many as make runs of up to
+    // eight blocks: 2 x 8 heads of 4000 tokens 37.3, 42.8, 56.8 us; 8 of 5000 30.7, 32.9, 39.9; 8 of 32000 63.3, 58.6, 63.6; 64 of 8200
+    // 115.5, 115.9, 142.7; 512 of 2000 200.3, 202.3, 222.8; 8 of 65549 112.1, 107.9, 109.8.
+    // Several long heads are sealed one after the other all the same, in runs of eight blocks: 8 of 65549 gain next to nothing, and
+    // the first decode, which walks all heads side by side, finds more of them in the memory-side cache (prompt and decode 139.5, 141.5).
     a.n_seal = (int)n_seal;
-    a.per = (int)std::min<int64_t>(std::max<int64_t>(n_seal * hkv * bt / 2048, 1), 8);
-    // grid.x is limited to 2^31-1 blocks; n_seal <= nb_cap is far below that
-    const unsigned runs = (unsigned)((n_seal + a.per - 1) / a.per);
+    const int64_t heads = (int64_t)bt * hkv, wgs = (n_seal * heads < 8192 ? 4 : 6) * (int64_t)c->n_cu;
+    const bool dealt = n_seal < 2048 || n_seal * heads < 16384;
+    const unsigned runs = (unsigned)(dealt ? std::min<int64_t>(n_seal, std::max<int64_t>(wgs / heads, 1)) : (n_seal + 7) / 8);
+    a.runs = (int)runs;
+    a.first = dealt ? 1 : 8;
+    a.step = dealt ? a.runs : 1;
+    a.most = dealt ? (int)((n_seal + runs - 1) / runs) : 8;
     if (a.nb_old == 0 && runs > 1) {
       const int n = bt * hkv;
       hipLaunchKernelGGL(clear_sigmax_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a.sigmax, n);

@@ -119,3 +119,23 @@ def test_a_reset_cache_equals_a_fresh_one(first, second, int8_query):
                 for x, y in zip(a, b):
                     assert np.array_equal(x, y), (rounds, x.dtype)
             gc.cqa.cqa_cache_reset(gc.h, 0)
+
+
+@pytest.mark.parametrize("bt,hkv,pieces", [
+    (40, 32, [5, 16 * 3 + 4, 16]),      # more heads than workgroups: one each takes all blocks, the waiting tokens' among them
+    (16, 16, [16 * 9 + 3, 16 * 7]),     # four workgroups of a head: two or three blocks each, the last block with the first one
+    (8, 16, [7, 16 * 8 + 10]),          # eight: one block each, a record left half empty
+])
+def test_blocks_dealt_round_the_workgroups(bt, hkv, pieces):
+    print("seal dealt", bt, hkv, pieces, flush=True)
+    rng = np.random.default_rng(bt)
+    n = sum(pieces)
+    k, v = _special(rng, (bt, hkv, n, 128)), _special(rng, (bt, hkv, n, 128))
+    oc = oracle.OracleLayerCache(bt, hkv)
+    with GpuLayerCache(bt, hkv, hkv, n + 16) as gc:
+        at = 0
+        for p in pieces:
+            gc.append(k[:, :, at:at + p], v[:, :, at:at + p])
+            oc.append(k[:, :, at:at + p], v[:, :, at:at + p])
+            at += p
+        _check(gc, oc, pieces)
