@@ -473,13 +473,16 @@ template <int G, typename... RA>
 __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs first, RA...) {
   constexpr bool CHECK = sizeof...(RA) > 0;
   bool strayed = false;
-  const uint32_t raised = *first.raised;
+  asm volatile("" ::"s"(first.raised), "s"(first.raised_tag), "s"(first.groups), "s"(first.split_tickets));   // one wait
+  int zero = 0;   // (a vector load, under way together with the others: a scalar one would be waited for ahead of them)
+  if constexpr (CHECK) asm volatile("" : "+v"(zero));
+  const uint32_t raised = first.raised[zero];
   if constexpr (CHECK) {
     const uint32_t* const reduced = first.split_tickets + (int64_t)first.groups * TICKET_STRIDE;
     for (int g = threadIdx.x & 63; g < first.groups; g += 64) strayed = strayed | (reduced[g] != first.raised_tag);
     strayed = __any(strayed);
   }
-  if (raised != first.raised_tag && !strayed) return;
+  if (!__any(raised == first.raised_tag) && !strayed) return;
   const LadderArgs a = arg_read_here<LadderArgs>(0);
   __shared__ int s_rung, s_walkers;
   __shared__ int s_cnt[4], s_pre[4];

@@ -10,8 +10,8 @@
 //   E_val = sum_b rho_b eta_b,   E_key = 2 V_max min(tanh Delta_h, min{1, e^{c Delta_h} alpha_hat}(e^{2 Delta_h} - 1))
 // (key_bound_mode 1 / 2 select the second / first factor alone), the interval form of the
 // ranking test  l_(1) - l_(2) <= 2 Delta_h + eps_guard,  and the flag word.
-// Used by the split pass (rows of one workgroup), the reduction kernels of the one-pass and of the adaptive decode, the
-// selector and the short steps' launch with the ladder.
+// Used by the split pass (rows of one workgroup, and short steps of several), the reduction kernels of the one-pass and of the adaptive
+// decode, the selector, and the ladder's launch where the workgroups of a short step were not on one die.
 #pragma once
 
 #include "cqa_internal.h"
