@@ -183,6 +183,8 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
   __shared__ __align__(16) float mo[W][G][D];
   __shared__ float ms[W][G][12];
   __shared__ uint32_t s_fl[4];                           // [head] flag word of a finished row
+  __shared__ uint32_t s_last;                            // this workgroup is the last of its group (no flag word's place: the
+                                                         // first row's may be stored while a wave has yet to look here)
   __shared__ float s_side[G][6];                         // [head] trailing tokens' M, L, V; key terms
   __shared__ __align__(16) float s_tail[G][D];           // [head] ... and their channels
 
@@ -747,7 +749,7 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
       if (a.scatter) die += (uint32_t)split & 1u;
       uint32_t* const tk = a.tickets + head * TICKET_STRIDE + die % DIES;
       const bool last = __hip_atomic_fetch_add(tk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == (uint32_t)a.nsplit - 1u;
-      s_fl[0] = last ? 1u : 0u;
+      s_last = last ? 1u : 0u;
       if (last) {
         __hip_atomic_store(tk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);   // for the next launch
         a.tickets[(uint32_t)a.heads * TICKET_STRIDE + head] = ra.raised_tag;
@@ -755,7 +757,7 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
     }
     if (!SIDE && ra.r > 0) load_trail(ra, head, row0 + hh, a.ap_k_new, a.ap_v_new, tr);
     __syncthreads();
-    if (s_fl[0] == 0u) return;
+    if (s_last == 0u) return;
     // Eight sets a trip.  One trip's result is the row's; several take the place of the waves' states in LDS.  Row SP has
     // its side work first and takes fewer of them (none where there are more than two rows).
     const int trips = (a.nsplit + 7) >> 3;

@@ -38,6 +38,9 @@ SHAPES = [
     (16, 8, 4, 64 * 16 + 1, 2),       # ... two sets, a workgroup on every compute unit
     (1, 16, 1, 64 * 400 + 30, 16),    # ... several quads each, two trips
     (36, 8, 1, 16 * 96 + 5, 3),       # four quad waves in more than one generation
+    (9, 8, 4, 16 * 98 + 5, 7),        # ... with a wave per head and no more: one quad each
+    (9, 8, 4, 16 * 98, 7),            # ... nothing behind the sealed blocks
+    (19, 8, 4, 7000, 3),              # ... several quads each
 ]
 
 
@@ -69,7 +72,8 @@ def test_rows_are_those_of_the_certified_call(bt, hkv, g, n, sets, int8):
 
 
 @pytest.mark.parametrize("scatter", [0, 1])
-@pytest.mark.parametrize("bt,hkv,g,n", [(1, 8, 4, 64 * 20 + 7), (2, 4, 2, 64 * 30 + 11), (1, 8, 1, 64 * 30), (16, 8, 4, 64 * 12 + 3)])
+@pytest.mark.parametrize("bt,hkv,g,n", [(1, 8, 4, 64 * 20 + 7), (2, 4, 2, 64 * 30 + 11), (1, 8, 1, 64 * 30), (16, 8, 4, 64 * 12 + 3),
+                                        (9, 8, 4, 16 * 98 + 5)])
 def test_heads_over_a_threshold_are_served(bt, hkv, g, n, scatter):
     """Rung 3 for the heads that ask and no other, Rung 4 with a limit on the groups, the token of the step among the
     attended ones; on both routes, and a plain step behind each."""
