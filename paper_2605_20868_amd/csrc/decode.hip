@@ -707,8 +707,7 @@ int stream_nt(const Cache* c, int64_t n_blocks) {
 }
 
 // Whether the split pass of a step with the ladder behind it reduces its partial sets itself, and with how many waves per workgroup
-// (0 = the reduction stays a launch of its own).  Its last workgroup's rows of waves (one wave per head) have a trip of eight
-// sets each, all but the one that takes the side work where there are three or more.  A step enqueued one after the other, and
+// (0 = the reduction stays a launch of its own).  The sets that its last workgroup joins: reduced_sets.  A step enqueued one after the other, and
 // recorded (device time alone), us, with the launch and without: 8 KV heads x 4, 1000 tokens 11.9, 9.6 and 10.1, 9.6; 3000 12.0, 10.4 and
 // 10.5, 10.4; 4000 (no trailing tokens) 11.9, 10.5 and 10.2, 10.4; x 1, 8000 11.7, 10.3 and 10.7, 10.2; 32 x 4 of 4000 14.1, 13.8 and
 // 14.2, 14.0; 128 x 4 of 1000 15.9, 15.0 and 16.1, 15.2.  With a second trip per wave the launch is better: 8 x 4 of 8229
@@ -722,10 +721,9 @@ static int split_reduces(const Cache* c, int64_t n_blocks, int nsplit, int wpb) 
   if (heads % DIES != 0 && (heads + DIES - 1) / DIES * nsplit > c->n_cu / DIES) return 0;
   // Four waves with a quad each and a compute unit to themselves are joined by four or eight without: the trailing tokens are attended
   // and the key term taken beside the rest (8 x 4 of 1000 tokens 10.5 -> 9.6 us a recorded step, of 3000 11.3 -> 10.4).
-  const int trips = (nsplit + 7) / 8;
   const bool alone = wpb == 4 && 4 * (int64_t)nsplit >= (n_blocks + 3) / 4 && heads * nsplit <= c->n_cu;
-  const int waves = alone ? (g == 4 && trips > 1 ? 12 : 8) : wpb, np = waves / g;
-  return trips <= std::min(np > 2 ? np - 1 : 1, wpb) ? waves : 0;
+  const int waves = alone ? (g == 4 && nsplit > reduced_sets(4, 4, 8) ? 12 : 8) : wpb;
+  return nsplit <= reduced_sets(g, wpb, waves) ? waves : 0;
 }
 
 int pick_splits(const Cache* c, int64_t n_blocks) {

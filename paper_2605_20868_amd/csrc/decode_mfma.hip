@@ -758,29 +758,26 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
     if (!SIDE && ra.r > 0) load_trail(ra, head, row0 + hh, a.ap_k_new, a.ap_v_new, tr);
     __syncthreads();
     if (s_last == 0u) return;
-    // Eight sets a trip.  One trip's result is the row's; several take the place of the waves' states in LDS.  Row SP has
-    // its side work first and takes fewer of them (none where there are more than two rows).
-    const int trips = (a.nsplit + 7) >> 3;
-    const int most = trips <= 2 ? trips : (trips + 2) >> 1;   // of two rows, the first one's
-    int t = NP == 1 ? 0 : (NP == 2 ? part * most : (part == SP ? trips : (part < SP ? part : part - 1)));
-    const int t_end = NP == 2 && part == 0 ? most : trips, t_step = NP <= 2 ? 1 : NP - 1;
-    SetRegs next;
-    if (t < t_end) next = load_sets<true>(sets, 8 * t, a.nsplit);
+    // Eight sets a trip, no more than one trip for each row of waves (the host sees to it).  One trip's result is the row's; several take
+    // the place of the waves' states in LDS.  Row SP has the side work instead.
+    constexpr int TRIPS = reduced_sets(G, W, WT) / 8;
+    const int trips = (a.nsplit + 7) >> 3, t = part < SP ? part : part - 1;
+    const bool merges = (!SIDE || part != SP) && t < trips;
+    SetRegs eight;
+    if (merges) eight = load_sets<true>(sets, 8 * t, a.nsplit);
     if (!SIDE && ra.r > 0) ts = trail_state(ra, tr);
     if (SIDE && part == SP) {
       float delta = 0.0f;
       for (int s = l; s < a.nsplit; s += 64) delta = fmaxf(delta, ld_set<true>(sets, (uint32_t)s * PART_FLOATS + P_DMAX));
       side_work(wave_max(delta));
     }
-    for (; t < t_end; t += t_step) {
-      const SetRegs cur = next;
-      if (t + t_step < t_end) next = load_sets<true>(sets, 8 * (t + t_step), a.nsplit);
-      st = merge_loaded(cur, 8 * t, a.nsplit, 0, a.nsplit, o2);
-      if (NP <= 2 ? trips > 1 : (trips > 2 || t > 0)) store_state(st, o2, (&ms[0][0][0]) + (t * G + hh) * 12, (&mo[0][0][0]) + (t * G + hh) * D);
+    if (merges) {
+      st = merge_loaded(eight, 8 * t, a.nsplit, 0, a.nsplit, o2);
+      if (TRIPS > 1 && (trips > 2 || t > 0)) store_state(st, o2, (&ms[0][0][0]) + (t * G + hh) * 12, (&mo[0][0][0]) + (t * G + hh) * D);
     }
-    if (NP > 1) __syncthreads(); else wave_sync();
-    if (part == 0 && trips > 1) {
-      if (NP > 2 && trips == 2)
+    if (SIDE) __syncthreads();
+    if (TRIPS > 1 && part == 0 && trips > 1) {
+      if (trips == 2)
         st = join_lds(st, &ms[0][0][0] + (G + hh) * 12, &mo[0][0][0] + (G + hh) * D, o2);
       else
         st = merge_lds(ms[0][w], G * 12, mo[0][w], G * D, trips, o2);
@@ -878,6 +875,8 @@ int32_t launch_split_mfma(const DecodeArgs& a, const ReduceArgs& ra, int group, 
   const bool lm = a.blk_logmass != nullptr;
   const bool one = a.wpb * a.nsplit >= (a.nb + 3) / 4;   // no wave takes a second quad
   if (a.wpb != 4 && a.wpb != 8) return CQA_ERR_INVALID_ARG;
+  // what the form launched below takes of the partial sets (split_reduces admits no more)
+  if (a.tickets != nullptr && (lm || (a.waves > a.wpb && !one) || a.nsplit > reduced_sets(group, a.wpb, a.waves))) return CQA_ERR_INVALID_ARG;
 // The launch that takes events costs the host 2.3 us more than the plain one (a step of three launches 10.8, 8.4 us), which
 // short steps wait for, so it is used for timing only.
 #define CQA_LAUNCH_LM(GG, LMV, NTV, Q8V, WV, ONEV, WTV)                                            \

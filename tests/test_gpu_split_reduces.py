@@ -22,7 +22,8 @@ def step(gc, q, tol, kv=(None, None)):
     return [x.copy() for x in gc.results()]
 
 
-# (batch, kv heads, group, tokens, sets): first and last of what each form takes, groups that do not divide among the dies
+# (batch, kv heads, group, tokens, sets): every form of the kernel that reduces (heads per group, waves, quads per wave) at every
+# number of trips that it takes, first and last of what some take, groups that do not divide among the dies
 SHAPES = [
     (1, 8, 4, 64 * 8 + 16, 3),        # four quad waves and four without, one quad in the last workgroup
     (1, 8, 4, 64 * 32 + 5, 8),        # ... the most sets of one trip
@@ -41,6 +42,16 @@ SHAPES = [
     (9, 8, 4, 16 * 98 + 5, 7),        # ... with a wave per head and no more: one quad each
     (9, 8, 4, 16 * 98, 7),            # ... nothing behind the sealed blocks
     (19, 8, 4, 7000, 3),              # ... several quads each
+    # what the rows of waves deal among themselves, form by form: four quad waves and no more, two heads and one
+    (18, 8, 2, 16 * 33, 3), (17, 8, 2, 16 * 65 + 5, 3),
+    (17, 8, 1, 16 * 33 + 3, 3), (7, 8, 1, 16 * 129, 9), (7, 8, 1, 16 * 257 + 7, 9), (3, 8, 1, 16 * 321 + 15, 21), (3, 8, 1, 16 * 642, 21),
+    # ... four quad waves and four without
+    (1, 1, 2, 16 * 129 + 2, 9), (1, 1, 1, 16 * 33 + 1, 3), (1, 3, 1, 16 * 129 + 5, 9), (5, 1, 1, 16 * 257 + 2, 17),
+    # ... eight quad waves with a quad each
+    (11, 8, 2, 16 * 33 + 8, 2), (13, 1, 2, 16 * 305 + 1, 10), (7, 1, 2, 16 * 577, 19),
+    (11, 8, 1, 16 * 33 + 9, 2), (13, 1, 1, 16 * 305, 10), (7, 1, 1, 16 * 577 + 3, 19), (5, 1, 1, 16 * 817 + 11, 26),
+    # ... with several
+    (13, 8, 4, 16 * 65 + 10, 2), (13, 8, 2, 16 * 65 + 1, 2), (3, 8, 2, 16 * 337 + 13, 10), (13, 8, 1, 16 * 65 + 4, 2), (1, 8, 1, 16 * 1027 + 6, 32),
 ]
 
 
