@@ -47,9 +47,16 @@ int32_t cqa_set_splits(cqa_cache* c, int32_t n_splits);
 int32_t cqa_set_stream_hint(cqa_cache* c, int32_t mode);
 
 /* 1 = the split pass of an enqueue-only step takes the workgroups of a KV group to be spread over two dies, whatever die
- * they are on, and leaves the reduction of the rows to the ladder's launch: the route of a device that
- * deals its workgroups in another way.  0 restores the default.  For tests. */
-int32_t cqa_set_scatter(cqa_cache* c, int32_t on);
+ * they are on, and leaves the reduction of the rows to the ladder's launch, in every step: what a device that
+ * deals its workgroups in another way does in its first one.  2 = as on such a device: after the first step the reduction is a
+ * launch of its own.  0 restores the default.  Forgets that steps have strayed; a step still on its way can bring
+ * that back.  For tests. */
+int32_t cqa_set_scatter(cqa_cache* c, int32_t mode);
+
+/* Who reduced the rows of the last cqa_decode_step_enqueue (host): 0 = a launch of its own, or there was
+ * one partial set; 1 = the split pass, every KV group; 2 = the ladder's launch, for a KV group at least had strayed.  Synchronises the device;
+ * not under capture.  For tests. */
+int32_t cqa_step_route(cqa_cache* c, int32_t* route);
 
 /* Chooses the split-K decode kernel: 0 = matrix-core (MFMA) kernel, the default;
  * 1 = the vector-ALU kernel (same results to rounding; kept as a cross-check). */

@@ -148,6 +148,7 @@ def _load():
         "cqa_set_splits": (i32, [vp, i32]),
         "cqa_set_stream_hint": (i32, [vp, i32]),
         "cqa_set_scatter": (i32, [vp, i32]),
+        "cqa_step_route": (i32, [vp, C.POINTER(i32)]),
         "cqa_set_kernel_variant": (i32, [vp, i32]),
         "cqa_strerror": (C.c_char_p, [i32]),
         "cqa_version": (i32, []),
@@ -429,8 +430,14 @@ def cqa_set_kernel_variant(h, variant) -> None:
     _check(_lib.cqa_set_kernel_variant(h, variant), "cqa_set_kernel_variant")
 
 
-def cqa_set_scatter(h, on) -> None:
-    _check(_lib.cqa_set_scatter(h, on), "cqa_set_scatter")
+def cqa_set_scatter(h, mode) -> None:
+    _check(_lib.cqa_set_scatter(h, mode), "cqa_set_scatter")
+
+
+def cqa_step_route(h) -> int:
+    r = C.c_int32(0)
+    _check(_lib.cqa_step_route(h, C.byref(r)), "cqa_step_route")
+    return r.value
 
 
 def cqa_set_stream_hint(h, mode) -> None:

@@ -222,7 +222,7 @@ int32_t cqa_workspace_bytes(const cqa_cache_desc* desc, int64_t* device_bytes,
     }
     *device_bytes = n;
   }
-  if (pinned_bytes) *pinned_bytes = 2 * s.t2 + s.select;
+  if (pinned_bytes) *pinned_bytes = 2 * s.t2 + s.select + 4;
   return CQA_OK;
 }
 
@@ -310,8 +310,9 @@ static int32_t create_cache(const cqa_cache_desc* desc, __half* caller_k, __half
     c->ad.sc_slots = 0;
     c->ad.sc_step = 0u;
   }
-  CQA_ALLOC_PIN(c->flags_host, s.select);
-  memset(c->flags_host, 0, s.select);
+  CQA_ALLOC_PIN(c->flags_host, s.select + 4);
+  memset(c->flags_host, 0, s.select + 4);
+  c->strayed = c->flags_host + (int64_t)desc->batch * desc->n_q_heads;
   c->need = new (std::nothrow) uint32_t[(size_t)desc->batch * desc->n_q_heads];
   if (c->need == nullptr) {
     release(h);
@@ -504,9 +505,25 @@ int32_t cqa_set_stream_hint(cqa_cache* h, int32_t mode) {
   return CQA_OK;
 }
 
-int32_t cqa_set_scatter(cqa_cache* h, int32_t on) {
-  if (h == nullptr || on < 0 || on > 1) return CQA_ERR_INVALID_ARG;
-  h->impl.scatter = on;
+int32_t cqa_set_scatter(cqa_cache* h, int32_t mode) {
+  if (h == nullptr || mode < 0 || mode > 2) return CQA_ERR_INVALID_ARG;
+  h->impl.scatter = mode;
+  __atomic_store_n(h->impl.strayed, 0u, __ATOMIC_RELAXED);
+  return CQA_OK;
+}
+
+int32_t cqa_step_route(cqa_cache* h, int32_t* route) {
+  if (h == nullptr || route == nullptr) return CQA_ERR_INVALID_ARG;
+  Cache* c = &h->impl;
+  *route = 0;
+  if (c->reducing_tag == 0u) return CQA_OK;
+  const size_t groups = (size_t)c->desc.batch * c->desc.n_kv_heads;
+  uint32_t number[REDUCED_ROWS];   // such a step has no more rows, hence groups
+  CQA_HIP(hipDeviceSynchronize());
+  CQA_HIP(hipMemcpy(number, c->split_tickets + groups * TICKET_STRIDE, groups * 4, hipMemcpyDeviceToHost));
+  *route = 1;
+  for (size_t i = 0; i < groups; ++i)
+    if (number[i] != c->reducing_tag) *route = 2;
   return CQA_OK;
 }
 

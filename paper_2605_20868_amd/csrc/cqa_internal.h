@@ -93,7 +93,7 @@ constexpr int MAX_SPLITS = 1024;     // upper bound on splits per (batch, kv-hea
 // ---- split pass that reduces its partial sets itself (certified_split_mfma_kernel) ----
 constexpr int DIES = 8;              // workgroups whose indices leave the same remainder by 8 run on one die
 constexpr int TICKET_STRIDE = 32;    // words: a KV group's counters, one per die, have a line of their own
-constexpr int REDUCED_ROWS = 1024;   // most (batch, query head) rows of such a step
+constexpr int REDUCED_ROWS = 1024;   // most (batch, query head) rows of such a step: the ladder's launch keeps as many flag words in LDS
 // Most sets that its last workgroup joins, of `waves` waves, `quad_waves` of them with quads, for `group` heads: eight by each row of
 // waves (one wave per head), all but the row that takes the side work where there are three or more; the rows' results take
 // the places of the quad waves' states.
@@ -187,7 +187,10 @@ struct Cache {
   uint32_t* split_tickets;   // of the split pass that reduces its partial sets itself (split_reduces): [batch * n_kv_heads][TICKET_STRIDE]
                              // arrivals on each die, zero between launches, then [batch * n_kv_heads] the number of the last
                              // step whose rows are reduced; null = it leaves the reduction to a launch of its own
+  uint32_t* strayed;         // pinned, behind flags_host: not 0 once the workgroups of a KV group were not on one die in such a step, after
+                             // which steps leave the reduction to a launch of its own
   int scatter;               // test hook: every other workgroup of a KV group counts as one of the next die
+  uint32_t reducing_tag;     // number of the last enqueue-only step if its split pass was to reduce, else 0
   float* sigmax;             // [heads_total] running max of sigma (non-negative: ordered as ints) over the sealed
                              // blocks; a sequence's first seal sets it, so it holds nothing while there are none
   // trailing FP16 partial blocks [heads_total][16][128]
@@ -202,7 +205,7 @@ struct Cache {
   float* dense_ws;           // dense partials for one (batch, kv-head) group x 2 buffers
   __half* stage[2][2];       // [buffer][K|V] : max_tokens * 128 halves each
   uint32_t* select_dev;      // [batch][Hq]
-  uint32_t* flags_host;      // pinned [batch][Hq]
+  uint32_t* flags_host;      // pinned [batch][Hq], and a word more: strayed
   uint32_t step_seq;         // 16-bit tag of the decode step whose flags the mirror must carry
   uint32_t* need;            // host [batch][Hq]: ladder scratch, heads to recompute
   hipStream_t side;
@@ -419,6 +422,7 @@ struct LadderArgs {
   float* ws;                // [Bt * Hq][nsplit][4 + 128]
   uint32_t* tickets;        // [Bt * Hkv], zero between launches
   uint32_t* counts;         // [2]: steps served by Rung 3, by Rung 4
+  uint32_t* strayed;        // ... and the host learns of it here
   int many_items;           // more served (KV group, split) items than this are walked by many_walkers workgroups
   int many_walkers;
   float* O;

@@ -718,6 +718,7 @@ static int split_reduces(const Cache* c, int64_t n_blocks, int nsplit, int wpb) 
   const int64_t heads = (int64_t)c->desc.batch * c->desc.n_kv_heads, rows = (int64_t)c->desc.batch * c->desc.n_q_heads;
   const int g = c->desc.n_q_heads / c->desc.n_kv_heads;
   if (c->split_tickets == nullptr || c->variant != 0 || nsplit < 2 || rows > REDUCED_ROWS) return 0;
+  if (__atomic_load_n(c->strayed, __ATOMIC_RELAXED) != 0u && c->scatter != 1) return 0;   // this device deals workgroups otherwise
   if (heads % DIES != 0 && (heads + DIES - 1) / DIES * nsplit > c->n_cu / DIES) return 0;
   // Four waves with a quad each and a compute unit to themselves are joined by four or eight without: the trailing tokens are attended
   // and the key term taken beside the rest (8 x 4 of 1000 tokens 10.5 -> 9.6 us a recorded step, of 3000 11.3 -> 10.4).
@@ -908,6 +909,7 @@ int32_t launch_step(Cache* c, int layer, const __half* q, const cqa_tolerances& 
                                       nullptr, ladder_raised(c), tag, &ra);
   if (launched != nullptr) *launched = rc == CQA_OK;
   if (rc != CQA_OK) return rc;
+  c->reducing_tag = ra.nsplit > 0 ? tag : 0u;
   return launch_dense_ladder(c, layer, q, tol.rung4_min_groups, O, cert, flags, tag, st, ra.nsplit > 0 ? &ra : nullptr);
 }
 

@@ -466,7 +466,9 @@ static_assert(sizeof(LadderArgs) % 8 == 0 && alignof(ReduceArgs) == 8, "the seco
 // splits and rewrites O, the certificate and the rung bits of the heads that are served.
 // Behind a split pass that reduces the rows itself every wave also looks at the numbers that it left.  Where one is not
 // this step's, every workgroup reduces all rows, to know every flag without waiting for another one, and the
-// first one writes them, leaving out the outputs that a rung replaces.
+// first one writes them, leaving out the outputs that a rung replaces.  That is for once: a step of 32 rows takes 50 us instead of 10 so, of 256
+// 170 instead of 15, of 512 603 instead of 15, so the first workgroup also tells the host, whose later steps reduce in a launch
+// of their own (a recorded step goes on as it was recorded).
 // Leaving is what nearly every launch does, so no more than the first line of the arguments is read up to there (with all of
 // them first, 0.6 us more for a step of 64 x 4 heads, 2000 tokens).
 template <int G, typename... RA>
@@ -494,9 +496,11 @@ __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs first, RA.
         const HeadRow row = reduce_row_wave(ra, r);
         if ((threadIdx.x & 63) == 0) s_flags[r] = row.fl;
       }
-      if (blockIdx.x == 0)
+      if (blockIdx.x == 0) {
         for (int i = threadIdx.x; i < a.groups * DIES; i += 256)
           a.split_tickets[(int64_t)(i / DIES) * TICKET_STRIDE + i % DIES] = 0u;
+        if (threadIdx.x == 0) __hip_atomic_store(a.strayed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      }
       __syncthreads();
     }
   }
@@ -619,6 +623,7 @@ int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_
   const dim3 grid((unsigned)std::min<int64_t>((int64_t)a.nsplit * a.groups, 2 * (int64_t)c->n_cu));
   if (reduce != nullptr) {
     a.split_tickets = c->split_tickets;
+    a.strayed = c->strayed;
     switch (g) {
       case 1: hipLaunchKernelGGL((dense_ladder_kernel<1, ReduceArgs>), grid, dim3(256), 0, st, a, *reduce); break;
       case 2: hipLaunchKernelGGL((dense_ladder_kernel<2, ReduceArgs>), grid, dim3(256), 0, st, a, *reduce); break;

@@ -54,6 +54,9 @@ SHAPES = [
     (13, 8, 4, 16 * 65 + 10, 2), (13, 8, 2, 16 * 65 + 1, 2), (3, 8, 2, 16 * 337 + 13, 10), (13, 8, 1, 16 * 65 + 4, 2), (1, 8, 1, 16 * 1027 + 6, 32),
 ]
 
+# ... of these the reduction is a launch of its own
+OWN_LAUNCH = [(1, 1, 4, 64 * 64 + 16, 17), (11, 1, 1, 64 * 80 + 1, 20)]
+
 
 @pytest.mark.parametrize("int8", [False, True])
 @pytest.mark.parametrize("bt,hkv,g,n,sets", SHAPES)
@@ -71,6 +74,9 @@ def test_rows_are_those_of_the_certified_call(bt, hkv, g, n, sets, int8):
         for on in (0, 0, 1, 0):
             gc.cqa.cqa_set_scatter(gc.h, on)
             O2, cert2, flags2 = step(gc, q, tol)
+            if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+                reduces = (bt, hkv, g, n, sets) not in OWN_LAUNCH
+                assert gc.cqa.cqa_step_route(gc.h) == (0 if not reduces else 1 + on)
             assert (flags2 == flags).all()
             if on == 0 or sets <= 8:
                 assert np.array_equal(O, O2) and cert.tobytes() == cert2.tobytes(), on
@@ -142,4 +148,31 @@ def test_recorded_steps_find_their_counters_cleared(bt, hkv, g, n):
             t.cuda.synchronize()
             assert np.array_equal(gc.results()[0], O) and gc.results()[1].tobytes() == cert.tobytes()
             assert np.abs(O1.cpu().numpy() - O).max() <= 1e-5 * np.abs(O).max()
-            assert np.array_equal(step(gc, q, tol)[0], O)
+            cqa.cqa_set_scatter(gc.h, 0)     # (the first of the pair has told the host that steps stray)
+            assert np.array_equal(step(gc, q, tol)[0], O) and cqa.cqa_step_route(gc.h) == 1
+
+
+@pytest.mark.parametrize("bt,hkv,g,n", [(1, 8, 4, 64 * 20 + 7), (16, 8, 4, 64 * 12 + 3)])
+def test_a_device_that_deals_otherwise_is_left_alone_after_its_first_step(bt, hkv, g, n):
+    """The step whose KV groups were not together is reduced behind it, the host learns of it, and the steps that follow reduce in a
+    launch of their own, served heads among them; a token rides on each."""
+    print("split reduces, strays once", bt, hkv, g, n, flush=True)
+    k, v, q = make(bt, hkv, g, n + 3)
+    with GpuLayerCache(bt, hkv * g, hkv, n + 32) as gc, GpuLayerCache(bt, hkv * g, hkv, n + 32) as other:
+        cqa = gc.cqa
+        gc.append(k[:, :, :n], v[:, :, :n])
+        other.append(k[:, :, :n], v[:, :, :n])
+        cqa.cqa_set_scatter(gc.h, 2)
+        for i, (route, force) in enumerate(((2, 0), (0, 0), (0, cqa.FLAG_TOTAL))):
+            new = [np.ascontiguousarray(x[:, :, n + i:n + i + 1]) for x in (k, v)]
+            other.append(*new)
+            tol = cqa.Tolerances(force_flags=force)
+            O, cert, flags = step(gc, q, tol, [gc.to_dev(x) for x in new])
+            if gc.torch.cuda.get_device_properties(0).multi_processor_count == 256:
+                assert cqa.cqa_step_route(gc.h) == route, i
+            O2, cert2, flags2 = step(other, q, tol)
+            assert np.array_equal(O, O2) and cert.tobytes() == cert2.tobytes() and (flags == flags2).all(), i
+        cqa.cqa_set_scatter(gc.h, 0)
+        step(gc, q, cqa.Tolerances())
+        if gc.torch.cuda.get_device_properties(0).multi_processor_count == 256:
+            assert cqa.cqa_step_route(gc.h) == 1
