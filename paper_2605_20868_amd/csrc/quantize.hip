@@ -117,8 +117,8 @@ __device__ __forceinline__ void store_originals(const __half* in, __half* t2, in
   }
 }
 
-// One workgroup of two waves seals blocks of 16 tokens of a head, every `runs`-th as a rule, each wave requesting its
-// share of the next block while it works on one; the waves do not wait for each other.  The workgroups, all resident at once,
+// One workgroup of two waves seals blocks of 16 tokens of a head, every `runs`-th or consecutive ones (seal_dealt), each wave requesting its
+// share of the next block while it works on one; the waves do not wait for each other.  Where they are dealt the workgroups
 // advance together, so a launch writes a window of consecutive records that moves through each head.
 //   wave 0, keys   : lane = channels 2 l, 2 l + 1; its 2 x 16 values give l_c, u_c, sigma_c, z_c and the
 //                    32 codes;
@@ -406,6 +406,32 @@ __global__ __launch_bounds__(256) void trail_kernel(const __half* k_in, const __
   }
 }
 
+// Whether a launch that seals deals the blocks round `runs` workgroups per head, all of them resident at once (four to a compute
+// unit, six, as many as there is room for, from 8192 blocks on), or cuts each head into short runs of consecutive ones, which the hardware
+// hands out as workgroups end.  Dealt, the launch has no last generation that leaves part of the chip idle: us, dealt over four, over six and
+// in runs of up to eight: 2 x 8 heads of 4000 tokens 37.3, 42.8, 56.8; 8 of 5000 30.7, 32.9, 39.9; 8 of 32000 63.3, 58.6, 63.6; 64 of
+// 8200 115.5, 115.9, 142.7; 512 of 2000 200.3, 202.3, 222.8; 8 of 65549 112.1, 107.9, 109.8.
+// That holds while the one generation fills the chip.  From about 500 heads on a head has one or two workgroups, and what is left over of a
+// compute unit's six places, or a second generation of whole heads, costs more (2000 tokens, dealt and consecutive: 520 heads 244, 221; 800 348, 321;
+// 1100 471, 428; 1600 738, 601; 3200 1255, 1158; but 480 196, 208; 1000 366, 390; 1500 555, 567; 290 tokens: 1100 79, 75; 1600 115, 101;
+// but 700 52, 56; 1500 88, 95).  Both times in blocks of the busiest compute unit: consecutive, an equal share and a tail; dealt, blocks a workgroup
+// times what w of them to a compute unit cost (two waves each: beyond four, a SIMD has a third wave), from the times at 11, 18, 40 and 125 blocks and
+// 520 to 1500 heads, whose ratios it gives within 5 % (furthest off: 1300 heads of 290 tokens, dealt 87, consecutive 90, are not dealt).
+// Heads of a thousand blocks and more are the better read and written one after the other when there are many (100 of 1000 blocks
+// level, 130 402, 382, 330 1041, 911), and several of 32000 tokens and more because the first decode, which walks all heads side by side, finds more of them in
+// the memory-side cache (8 of 65549, prompt and decode: dealt 141.5, consecutive 139.5).
+// Heads of up to ten blocks lose nothing by it at any number (2000 of 4 blocks 37.6, 48.6), nor do those of up to thirteen beyond a generation (2500 of 13 113, 119).
+static bool seal_dealt(int64_t n_seal, int64_t heads, int64_t runs, int n_cu) {
+  const int64_t blocks = n_seal * heads;
+  if (n_seal >= 2048 && blocks >= 16384) return false;
+  if (n_seal >= 1000 && blocks > 100000) return false;
+  if (n_seal <= 10) return true;
+  if (heads * runs > 6 * (int64_t)n_cu) return n_seal <= 13;
+  const double w = (double)(heads * runs) / n_cu, n = (double)n_seal;
+  const double tail = std::min(std::max(0.3 * n, 7.0), std::max(55.0 - n / 20, 7.0));
+  return n / runs * (w <= 4 ? 1.95 + 0.51 * w : 3.0 + 0.5 * w) <= (double)blocks / n_cu + tail;
+}
+
 int32_t launch_seal(Cache* c, int layer, const __half* k_in, const __half* v_in, int64_t n_new,
                     int64_t len_before, bool tier2_by_kernel, hipStream_t st) {
   const int r = (int)(len_before % BLK);
@@ -431,20 +457,21 @@ int32_t launch_seal(Cache* c, int layer, const __half* k_in, const __half* v_in,
     a.t2_v = tier2_by_kernel ? c->t2_v : nullptr;
     a.t2_cap = c->desc.max_tokens;
     a.len_before = len_before;
-    // One generation of workgroups, four to a compute unit, six (as many as there is room for) from 8192 blocks on: with more,
-    // a last generation leaves part of the chip idle.  Times with four, with six and with as many as make runs of up to
-    // eight blocks: 2 x 8 heads of 4000 tokens 37.3, 42.8, 56.8 us; 8 of 5000 30.7, 32.9, 39.9; 8 of 32000 63.3, 58.6, 63.6; 64 of 8200
-    // 115.5, 115.9, 142.7; 512 of 2000 200.3, 202.3, 222.8; 8 of 65549 112.1, 107.9, 109.8.
-    // Several long heads are sealed one after the other all the same, in runs of eight blocks: 8 of 65549 gain next to nothing, and
-    // the first decode, which walks all heads side by side, finds more of them in the memory-side cache (prompt and decode 139.5, 141.5).
     a.n_seal = (int)n_seal;
-    const int64_t heads = (int64_t)bt * hkv, wgs = (n_seal * heads < 8192 ? 4 : 6) * (int64_t)c->n_cu;
-    const bool dealt = n_seal < 2048 || n_seal * heads < 16384;
-    const unsigned runs = (unsigned)(dealt ? std::min<int64_t>(n_seal, std::max<int64_t>(wgs / heads, 1)) : (n_seal + 7) / 8);
-    a.runs = (int)runs;
-    a.first = dealt ? 1 : 8;
-    a.step = dealt ? a.runs : 1;
-    a.most = dealt ? (int)((n_seal + runs - 1) / runs) : 8;
+    const int64_t heads = (int64_t)bt * hkv, most_wgs = (n_seal * heads < 8192 ? 4 : 6) * (int64_t)c->n_cu;
+    const int64_t one_gen = std::min<int64_t>(n_seal, std::max<int64_t>(most_wgs / heads, 1));
+    if (seal_dealt(n_seal, heads, one_gen, c->n_cu)) {
+      a.runs = (int)one_gen;
+      a.first = 1;
+      a.step = a.runs;
+      a.most = (int)((n_seal + one_gen - 1) / one_gen);
+    } else {   // consecutive blocks: one per workgroup until there are two thousand of them, then up to eight
+      a.most = (int)std::min<int64_t>(std::max<int64_t>(n_seal * heads / 2048, 1), 8);
+      a.runs = (int)((n_seal + a.most - 1) / a.most);
+      a.first = a.most;
+      a.step = 1;
+    }
+    const unsigned runs = (unsigned)a.runs;
     if (a.nb_old == 0 && runs > 1) {
       const int n = bt * hkv;
       hipLaunchKernelGGL(clear_sigmax_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a.sigmax, n);

@@ -125,6 +125,8 @@ def test_a_reset_cache_equals_a_fresh_one(first, second, int8_query):
     (40, 32, [5, 16 * 3 + 4, 16]),      # more heads than workgroups: one each takes all blocks, the waiting tokens' among them
     (16, 16, [16 * 9 + 3, 16 * 7]),     # four workgroups of a head: two or three blocks each, the last block with the first one
     (8, 16, [7, 16 * 8 + 10]),          # eight: one block each, a record left half empty
+    (65, 8, [16 * 11 + 5, 16 * 41]),    # two workgroups a head would fill five of a compute unit's six places: runs of two, then of eight blocks
+    (35, 32, [3, 16 * 19 + 6]),         # one a head, unevenly: runs of eight, a record left half empty
 ])
 def test_blocks_dealt_round_the_workgroups(bt, hkv, pieces):
     print("seal dealt", bt, hkv, pieces, flush=True)
