@@ -54,8 +54,8 @@ int32_t cqa_set_stream_hint(cqa_cache* c, int32_t mode);
 int32_t cqa_set_scatter(cqa_cache* c, int32_t mode);
 
 /* Who reduced the rows of the last cqa_decode_step_enqueue (host): 0 = a launch of its own, or there was
- * one partial set; 1 = the split pass, every KV group; 2 = the ladder's launch, for a KV group at least had strayed.  Synchronises the device;
- * not under capture.  For tests. */
+ * one partial set; 1 = the split pass, every KV group; 2 = the ladder's launch, for a KV group at least had strayed; 3 = the
+ * ladder's launch, few rows.  Synchronises the device; not under capture.  For tests. */
 int32_t cqa_step_route(cqa_cache* c, int32_t* route);
 
 /* Chooses the split-K decode kernel: 0 = matrix-core (MFMA) kernel, the default;

@@ -930,7 +930,7 @@ int32_t launch_adaptive(Cache* c, int layer, const __half* q, const cqa_toleranc
   }
   ReduceArgs first{};   // its reduction is left to the selector
   int32_t rc = launch_certified(c, layer, q, loose, O, cert, flags, nullptr, 0u, w.lm8, st, nullptr, nullptr,
-                                total, w.eta_blk, nullptr, nullptr, 0u, &first, true);
+                                total, w.eta_blk, nullptr, nullptr, 0u, &first);
   if (rc != CQA_OK) return rc;
 
   // ---- 2. selection per head (+ Rung 1), union bit mask per group

@@ -516,14 +516,15 @@ int32_t cqa_step_route(cqa_cache* h, int32_t* route) {
   if (h == nullptr || route == nullptr) return CQA_ERR_INVALID_ARG;
   Cache* c = &h->impl;
   *route = 0;
-  if (c->reducing_tag == 0u) return CQA_OK;
+  if (c->rows_by == RowsBy::ladder) *route = 3;
+  if (c->rows_by != RowsBy::split) return CQA_OK;
   const size_t groups = (size_t)c->desc.batch * c->desc.n_kv_heads;
   uint32_t number[REDUCED_ROWS];   // such a step has no more rows, hence groups
   CQA_HIP(hipDeviceSynchronize());
   CQA_HIP(hipMemcpy(number, c->split_tickets + groups * TICKET_STRIDE, groups * 4, hipMemcpyDeviceToHost));
   *route = 1;
   for (size_t i = 0; i < groups; ++i)
-    if (number[i] != c->reducing_tag) *route = 2;
+    if (number[i] != c->rows_tag) *route = 2;
   return CQA_OK;
 }
 

@@ -167,6 +167,10 @@ constexpr int SLOT_KEYS = 1, SLOT_VALUES = 2, SLOT_FILL = 4, SLOT_VFILL = 8, SLO
 // attends the block's FP16 values.  With per-group promotion every head's bit follows bits 0 / 1.
 constexpr int SLOT_HK_SHIFT = 24, SLOT_HV_SHIFT = 28;
 
+// Who reduces the rows of an enqueue-only step: a launch of its own (or the split pass of a one-workgroup sequence); the split
+// pass, and the ladder's launch looks after it; the ladder's launch.
+enum class RowsBy { launch, split, ladder };
+
 struct Cache {
   cqa_cache_desc desc;
   int device;
@@ -190,7 +194,8 @@ struct Cache {
   uint32_t* strayed;         // pinned, behind flags_host: not 0 once the workgroups of a KV group were not on one die in such a step, after
                              // which steps leave the reduction to a launch of its own
   int scatter;               // test hook: every other workgroup of a KV group counts as one of the next die
-  uint32_t reducing_tag;     // number of the last enqueue-only step if its split pass was to reduce, else 0
+  RowsBy rows_by;            // of the last enqueue-only step, whose number is ...
+  uint32_t rows_tag;
   float* sigmax;             // [heads_total] running max of sigma (non-negative: ordered as ints) over the sealed
                              // blocks; a sequence's first seal sets it, so it holds nothing while there are none
   // trailing FP16 partial blocks [heads_total][16][128]
@@ -377,8 +382,8 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
                          const __half* v_new = nullptr, int pstride = 0, float* eta_out = nullptr,
                          float* partials = nullptr,   // null = the cache's own split workspace
                          uint32_t* raised = nullptr, uint32_t raised_tag = 0u,
-                         ReduceArgs* defer = nullptr,    // always: the reduction is left to the caller; else nsplit set > 0:
-                         bool always = false);           // the split pass reduces, and the ladder's launch looks after it
+                         ReduceArgs* defer = nullptr,    // the reduction's arguments, where it is not a launch of its own: it is left
+                         RowsBy* by = nullptr);          // to the caller (by null) or to what *by says
 int32_t static_scratch(int device, void** out);
 int pick_splits(const Cache* c, int64_t n_blocks);
 int stream_nt(const Cache* c, int64_t n_blocks);
@@ -405,6 +410,8 @@ int64_t dense_ws_floats(int group, int64_t n_tokens);
 
 // Device-resolved fallback ladder (dense_ladder_kernel).
 constexpr int LADDER_MAX_SPLITS = 64;
+// Steps that finish_ladder_kernel reduces as well: up to this many (batch, query head) rows and partial sets per row.
+constexpr int FINISH_ROWS = 8, FINISH_SETS = 8;
 struct LadderArgs {
   const uint32_t* raised;   // equals raised_tag when some head of this step requests a fallback (it may
   uint32_t raised_tag;      // do so without one: a recorded step that is replayed keeps its number)
@@ -433,7 +440,7 @@ int ladder_splits(const Cache* c, int64_t n_tokens);
 int64_t ladder_ws_floats(int64_t rows);
 int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_groups, float* O,
                             cqa_head_cert* cert, uint32_t* flags, uint32_t raised_tag, hipStream_t st,
-                            const ReduceArgs* reduce = nullptr);   // set = the split pass reduces the rows itself
+                            RowsBy by = RowsBy::launch, const ReduceArgs* reduce = nullptr);   // reduce: null = the rows are there
 // certified decode and ladder, enqueue-only (k_new, v_new: a token that rides on the split launch, or null);
 // *launched (may be null) tells whether the split launch, which stores that token, was reached
 int32_t launch_step(Cache* c, int layer, const __half* q, const cqa_tolerances& tol, float* O, cqa_head_cert* cert,

@@ -727,6 +727,19 @@ static int split_reduces(const Cache* c, int64_t n_blocks, int nsplit, int wpb) 
   return nsplit <= reduced_sets(g, wpb, waves) ? waves : 0;
 }
 
+// Whether the ladder's launch can reduce a step's rows as well (finish_ladder_kernel), and whether it does where the split pass could.
+// Both ways are two launches: in the ladder's one wave per row does in turn what a group's last workgroup shares among its waves, which has to be
+// waited for, through the die's cache.  Without trailing tokens, or with one KV group, the ladder's launch is no slower.  Recorded steps,
+// reduced by it and by the split pass, us: no trailing tokens, 1 KV head x 4 of 1024 tokens 8.2, 9.2; x 1 8.0, 8.7; 2 x 2 8.4, 8.9; 2 x 4 8.7, 9.4; 3 x 2
+// 8.7, 8.9; 4 x 1 8.3, 8.9; 5 x 1 8.6, 8.9; 8 x 1 8.9, 9.0.  With them: 1 x 4 9.1, 9.2; 1 x 1 8.7, 8.6; 1 x 2 of 2049 8.9, 9.0; but 2 x 4 10.6,
+// 9.4; 2 x 2 9.4, 9.2; 8 x 1 10.8, 8.9.
+static bool ladder_reduces(const Cache* c, int nsplit) {
+  return nsplit > 1 && nsplit <= FINISH_SETS && (int64_t)c->desc.batch * c->desc.n_q_heads <= FINISH_ROWS;
+}
+static bool ladder_reduces_first(const Cache* c, int nsplit, int r) {
+  return ladder_reduces(c, nsplit) && (r == 0 || (int64_t)c->desc.batch * c->desc.n_kv_heads == 1);
+}
+
 int pick_splits(const Cache* c, int64_t n_blocks) {
   int nsplit = 0, wpb = 0;
   split_geometry(c, n_blocks, &nsplit, &wpb);
@@ -779,7 +792,8 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
                          cqa_head_cert* cert, uint32_t* flags, uint32_t* flags_mirror,
                          uint32_t mirror_tag, float* blk_logmass, hipStream_t st,
                          const __half* k_new, const __half* v_new, int pstride, float* eta_out,
-                         float* partials, uint32_t* raised, uint32_t raised_tag, ReduceArgs* defer, bool always) {
+                         float* partials, uint32_t* raised, uint32_t raised_tag, ReduceArgs* defer, RowsBy* by) {
+  const bool always = defer != nullptr && by == nullptr;   // the reduction is left to the caller in any case
   const int bt = c->desc.batch, hq = c->desc.n_q_heads, hkv = c->desc.n_kv_heads;
   if (partials == nullptr) partials = c->partials;
   const int64_t len = c->length[layer];
@@ -850,7 +864,7 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     // 20.9, 16.2; 256 22.2, 16.5; 1024 27.9, 17.9; 2048 40.6, 25.3; two, 1440 rows 48.6, 35.5; one, 720 42.6, 36.0.
     a.finish = nsplit == 1 && !always ? 1 : 0;
     a.heads = bt * hkv;
-    a.waves = defer != nullptr && !always ? split_reduces(c, nb, nsplit, wpb) : 0;
+    a.waves = by != nullptr && !ladder_reduces_first(c, nsplit, r) ? split_reduces(c, nb, nsplit, wpb) : 0;
     if (a.waves != 0) {
       a.tickets = c->split_tickets;
       a.scatter = c->scatter;
@@ -867,8 +881,12 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
       const dim3 by_die(DIES, nsplit, (a.heads + DIES - 1) / DIES);
       const int32_t rc = launch_split_mfma(a, ra, hq / hkv, a.tickets != nullptr ? by_die : grid, ev0, ev1, st);
       if (rc != CQA_OK) return rc;
-      reduced = a.finish != 0 || a.tickets != nullptr;
-      if (a.tickets != nullptr) *defer = ra;
+      reduced = a.finish != 0;
+      if (a.tickets != nullptr) {
+        reduced = true;
+        *defer = ra;
+        *by = RowsBy::split;
+      }
     } else {
       switch (hq / hkv) {
         case 1: hipLaunchKernelGGL((certified_split_kernel<1, false>), grid, dim3(256), 0, st, a, PromArgs{}); break;
@@ -884,8 +902,10 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     }
   }
   if (reduced) return CQA_OK;
-  if (always) {
+  const bool by_ladder = by != nullptr && ladder_reduces(c, nsplit);
+  if (always || by_ladder) {
     *defer = ra;
+    if (by_ladder) *by = RowsBy::ladder;
     return CQA_OK;
   }
   // With a mirror and more than four rows per compute unit, one wave per row: a row's waves side by side bring the stores
@@ -905,12 +925,14 @@ int32_t launch_step(Cache* c, int layer, const __half* q, const cqa_tolerances& 
                     uint32_t* flags, hipStream_t st, const __half* k_new, const __half* v_new, bool* launched) {
   const uint32_t tag = next_ladder_tag(c);
   ReduceArgs ra{};
+  RowsBy by = RowsBy::launch;
   const int32_t rc = launch_certified(c, layer, q, tol, O, cert, flags, nullptr, 0u, nullptr, st, k_new, v_new, 0, nullptr,
-                                      nullptr, ladder_raised(c), tag, &ra);
+                                      nullptr, ladder_raised(c), tag, &ra, &by);
   if (launched != nullptr) *launched = rc == CQA_OK;
   if (rc != CQA_OK) return rc;
-  c->reducing_tag = ra.nsplit > 0 ? tag : 0u;
-  return launch_dense_ladder(c, layer, q, tol.rung4_min_groups, O, cert, flags, tag, st, ra.nsplit > 0 ? &ra : nullptr);
+  c->rows_by = by;
+  c->rows_tag = tag;
+  return launch_dense_ladder(c, layer, q, tol.rung4_min_groups, O, cert, flags, tag, st, by, &ra);
 }
 
 }  // namespace cqa

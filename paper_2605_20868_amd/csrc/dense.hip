@@ -575,6 +575,51 @@ __global__ __launch_bounds__(256) void dense_ladder_kernel(LadderArgs first, RA.
   ladder_serve<G, 4>(a, rung, s_walkers, [&](int64_t row) { return (flag_of(row) & CQA_FLAG_ANY) != 0u; }, !strayed, sm);
 }
 
+// Reduction and ladder of a short step of few rows (ladder_reduces) in one launch: every workgroup merges all rows, one per
+// wave, and so knows every flag without waiting for another one; the first one writes the rows, leaving out the outputs that a
+// rung replaces, and the others leave unless a head asks for a fallback.  A step in two launches and in one:
+// 4 rows 12.4, 10.5 us at 3 sets and 11.8, 10.9 at 8; 8 rows of 8 KV heads 13.3, 12.3 at 3 and 13.0, 12.4 at 8, of
+// 2 KV heads level (11.9, 12.0; 12.1, 12.1).  (32 rows, two per wave of 16, with an earlier merge: 13 -> 23 us, the workgroups'
+// copies of the work get in each other's way.)
+template <int G>
+__global__ __launch_bounds__(64 * FINISH_ROWS) void finish_ladder_kernel(ReduceArgs ra, LadderArgs a) {
+  const int r = threadIdx.x >> 6, l = threadIdx.x & 63;   // this wave's row
+  __shared__ uint32_t s_fl[FINISH_ROWS];
+  HeadRow row;
+  row.fl = 0u;
+  if (r < a.n_rows) row = reduce_row_wave(ra, r);
+  if (l == 0) s_fl[r] = row.fl;
+  __syncthreads();
+  const uint32_t f = l < FINISH_ROWS ? s_fl[l] : 0u;
+  const uint32_t any = (uint32_t)__ballot((f & CQA_FLAG_ANY) != 0u);       // bit i: row i
+  const bool pre = __ballot((f & CQA_FLAG_PRECOND) != 0u) != 0ull;
+  uint32_t gm = any;
+#pragma unroll
+  for (int jj = 1; jj < G; ++jj) gm |= any >> jj;
+  gm &= G == 1 ? ~0u : (G == 2 ? 0x55555555u : 0x11111111u);
+  const int cnt = __popc(gm);
+  int rung = cnt > 0 ? 3 : 0;
+  if (rung != 0 && (pre || (a.rung4_min_groups > 0 && cnt >= a.rung4_min_groups))) rung = 4;
+  if (blockIdx.x == 0 && r < a.n_rows) {
+    if (rung == 4 || (rung == 3 && ((any >> r) & 1u) != 0u)) {
+      row.ct.E_key = 0.0f;
+      row.ct.E_val = 0.0f;
+      row.ct.served_rung = rung;
+      row.fl = (row.fl & ~(7u << CQA_RUNG_SHIFT)) | ((uint32_t)rung << CQA_RUNG_SHIFT);
+    } else {
+      reinterpret_cast<float2*>(a.O + (int64_t)r * D)[l] = row.out;
+    }
+    if (l == 0) {
+      a.cert[r] = row.ct;
+      a.flags[r] = row.fl;
+    }
+    if (rung != 0 && threadIdx.x == 0) atomicAdd(a.counts + (rung - 3), 1u);
+  }
+  if (rung == 0) return;
+  __shared__ __align__(16) DenseSmem<G, FINISH_ROWS> sm;
+  ladder_serve<G, FINISH_ROWS>(a, rung, (int)gridDim.x, [&](int64_t i) { return ((any >> (int)i) & 1u) != 0u; }, false, sm);
+}
+
 int ladder_splits(const Cache* c, int64_t n_tokens) {
   const int64_t groups = (int64_t)c->desc.batch * c->desc.n_kv_heads;
   int64_t want = (2 * (int64_t)c->n_cu) / groups;   // the launch's cost does not depend on it
@@ -590,7 +635,7 @@ int64_t ladder_ws_floats(int64_t rows) { return rows * LADDER_MAX_SPLITS * DP_FL
 
 int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_groups, float* O,
                             cqa_head_cert* cert, uint32_t* flags, uint32_t raised_tag, hipStream_t st,
-                            const ReduceArgs* reduce) {
+                            RowsBy by, const ReduceArgs* reduce) {
   if (c->desc.tier2_mode != CQA_TIER2_PINNED) return CQA_ERR_NO_TIER2;
   const int64_t len = c->length[layer];
   if (len <= 0 || q == nullptr || O == nullptr || cert == nullptr || flags == nullptr)
@@ -621,7 +666,18 @@ int32_t launch_dense_ladder(Cache* c, int layer, const __half* q, int rung4_min_
   a.cert = cert;
   a.flags = flags;
   const dim3 grid((unsigned)std::min<int64_t>((int64_t)a.nsplit * a.groups, 2 * (int64_t)c->n_cu));
-  if (reduce != nullptr) {
+  if (by == RowsBy::ladder) {
+    // Each of the workgroups merges the rows: no more of them than keep the host link busy when a rung serves.  Eight
+    // groups of one head, all served, on 64, 128, 256 and 512 workgroups: 600 tokens 121, 111, 116, 119 us, 1100
+    // tokens 165, 146, 162, 188, 2000 tokens 242, 250, 277, 278 (without a flag all four take 13.1 - 14.2; 512 16).
+    const dim3 fgrid((unsigned)std::min<int64_t>((int64_t)a.nsplit * a.groups, std::max(c->n_cu / 2, 1)));
+    switch (g) {
+      case 1: hipLaunchKernelGGL(finish_ladder_kernel<1>, fgrid, dim3(64 * FINISH_ROWS), 0, st, *reduce, a); break;
+      case 2: hipLaunchKernelGGL(finish_ladder_kernel<2>, fgrid, dim3(64 * FINISH_ROWS), 0, st, *reduce, a); break;
+      case 4: hipLaunchKernelGGL(finish_ladder_kernel<4>, fgrid, dim3(64 * FINISH_ROWS), 0, st, *reduce, a); break;
+      default: return CQA_ERR_UNSUPPORTED;
+    }
+  } else if (by == RowsBy::split) {
     a.split_tickets = c->split_tickets;
     a.strayed = c->strayed;
     switch (g) {

@@ -11,7 +11,7 @@
 // (key_bound_mode 1 / 2 select the second / first factor alone), the interval form of the
 // ranking test  l_(1) - l_(2) <= 2 Delta_h + eps_guard,  and the flag word.
 // Used by the split pass (rows of one workgroup, and short steps of several), the reduction kernels of the one-pass and of the adaptive
-// decode, the selector, and the ladder's launch where the workgroups of a short step were not on one die.
+// decode, the selector, and the ladder's launch where rows are few or the workgroups of a short step were not on one die.
 #pragma once
 
 #include "cqa_internal.h"

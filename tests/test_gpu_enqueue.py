@@ -319,8 +319,9 @@ def test_random_small_shapes_against_oracle():
 @pytest.mark.parametrize("bt,hkv,g,n", [(1, 1, 4, 16 * 40 + 3), (1, 1, 1, 16 * 100), (2, 2, 2, 16 * 64 + 15), (1, 8, 1, 16 * 36 + 1),
                                         (1, 2, 4, 16 * 120), (1, 3, 4, 16 * 50 + 2), (1, 1, 2, 16 * 200 + 9)])
 def test_reduction_and_ladder_in_one_launch_for_few_rows(bt, hkv, g, n):
-    """Up to eight (batch, query head) rows with two to eight partial sets are reduced and served by one launch; more
-    rows (3 x 4) and more sets (3200 tokens) take two.  Every rung against the oracle, and against the host-resolved step."""
+    """Up to eight (batch, query head) rows with two to eight partial sets are reduced and served by one launch without trailing tokens, or
+    with one KV group; the split pass reduces the others, more rows (3 x 4) and more sets (3200 tokens).  Every rung against the oracle, and
+    against the host-resolved step."""
     say(f"few rows: Bt={bt} Hkv={hkv} G={g} N={n}")
     import torch
     rng = np.random.default_rng(n + g)

@@ -46,7 +46,7 @@ SHAPES = [
     (18, 8, 2, 16 * 33, 3), (17, 8, 2, 16 * 65 + 5, 3),
     (17, 8, 1, 16 * 33 + 3, 3), (7, 8, 1, 16 * 129, 9), (7, 8, 1, 16 * 257 + 7, 9), (3, 8, 1, 16 * 321 + 15, 21), (3, 8, 1, 16 * 642, 21),
     # ... four quad waves and four without
-    (1, 1, 2, 16 * 129 + 2, 9), (1, 1, 1, 16 * 33 + 1, 3), (1, 3, 1, 16 * 129 + 5, 9), (5, 1, 1, 16 * 257 + 2, 17),
+    (1, 1, 2, 16 * 129 + 2, 9), (1, 2, 1, 16 * 33 + 1, 3), (1, 3, 1, 16 * 129 + 5, 9), (5, 1, 1, 16 * 257 + 2, 17),
     # ... eight quad waves with a quad each
     (11, 8, 2, 16 * 33 + 8, 2), (13, 1, 2, 16 * 305 + 1, 10), (7, 1, 2, 16 * 577, 19),
     (11, 8, 1, 16 * 33 + 9, 2), (13, 1, 1, 16 * 305, 10), (7, 1, 1, 16 * 577 + 3, 19), (5, 1, 1, 16 * 817 + 11, 26),
@@ -176,3 +176,49 @@ def test_a_device_that_deals_otherwise_is_left_alone_after_its_first_step(bt, hk
         step(gc, q, cqa.Tolerances())
         if gc.torch.cuda.get_device_properties(0).multi_processor_count == 256:
             assert cqa.cqa_step_route(gc.h) == 1
+
+
+# (batch, kv heads, group, tokens, route of the first step): either side of each limit of the ladder's launch
+FEW = [(1, 1, 4, 2048, 3), (1, 1, 4, 2049, 3), (1, 1, 4, 16 * 129, 1), (1, 2, 4, 1024, 3), (1, 2, 4, 1025, 1), (2, 1, 1, 16 * 36, 3), (1, 4, 1, 1009, 1),
+       (1, 3, 2, 1008, 3), (5, 1, 1, 1504, 3), (1, 8, 1, 605, 1), (1, 9, 1, 1008, 1), (1, 1, 1, 16 * 33 + 1, 3)]
+
+
+@pytest.mark.parametrize("bt,hkv,g,n,first", FEW)
+def test_few_rows_are_reduced_by_the_ladders_launch(bt, hkv, g, n, first):
+    """Up to eight rows and sets without trailing tokens or with one KV group, and with any after a step that has strayed: plain steps, steps with
+    heads served by either rung, and a token that rides, against the calls that reduce in a launch of their own."""
+    import torch
+    print("few rows", bt, hkv, g, n, first, flush=True)
+    k, v, q = make(bt, hkv, g, n + 1)
+    with GpuLayerCache(bt, hkv * g, hkv, n + 32) as gc:
+        cqa = gc.cqa
+        gc.append(k[:, :, :n], v[:, :, :n])
+        whole = torch.cuda.get_device_properties(0).multi_processor_count == 256
+        few = gc.cqa.cqa_decode_splits(gc.h, 0) <= 8 and bt * hkv * g <= 8
+        O, cert, flags = [x.copy() for x in gc.certified_decode(q)]
+        total = np.sort((cert["E_key"] + cert["E_val"]).ravel())
+        eps = float(np.float32(0.5 * (total[-1] + total[-2]))) if total.size > 1 else -1.0
+        assert np.isfinite(O).all()
+        for strays in (0, 2):
+            cqa.cqa_set_scatter(gc.h, strays)
+            for i in range(2):
+                O2, cert2, flags2 = step(gc, q, cqa.Tolerances())
+                if whole:
+                    want = first if strays == 0 else (3 if few and (first == 3 or i == 1) else (0 if i == 1 else 2))
+                    assert cqa.cqa_step_route(gc.h) == want, (strays, i)
+                if few or cqa.cqa_step_route(gc.h) != 2:
+                    assert np.array_equal(O, O2) and cert.tobytes() == cert2.tobytes() and (flags == flags2).all(), (strays, i)
+            for tol, rung in ((cqa.Tolerances(eps_total=eps), 3), (cqa.Tolerances(eps_total=eps, rung4_min_groups=1), 4),
+                              (cqa.Tolerances(force_flags=cqa.FLAG_TOTAL), 3)):
+                O2, cert2, flags2 = step(gc, q, tol)
+                _, O3, cert3, flags3 = gc.decode_step(q, tol)
+                served = cert2["served_rung"] == rung
+                assert served.any() and (flags2 == flags3).all() and cert2.tobytes() == cert3.tobytes()
+                assert np.array_equal(O2[~served], O3[~served])
+                assert np.abs(O2 - O3)[served].max() <= 1e-5 * np.abs(O3).max()     # binary32 sums in another order
+        new = [gc.to_dev(np.ascontiguousarray(x[:, :, n:])) for x in (k, v)]
+        O2, cert2, flags2 = step(gc, q, cqa.Tolerances(), new)
+        if whole:
+            assert cqa.cqa_step_route(gc.h) == (2 if first == 3 and bt * hkv > 1 else (3 if few else 0))    # the first one to stray, or not
+        O, cert, flags = gc.certified_decode(q)
+        assert np.array_equal(O, O2) and cert.tobytes() == cert2.tobytes()
