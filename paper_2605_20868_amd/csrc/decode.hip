@@ -706,6 +706,18 @@ int stream_nt(const Cache* c, int64_t n_blocks) {
   return pass * c->desc.n_layers > ((int64_t)256 << 20) ? 1 : 0;
 }
 
+// Whether what is launched on the stream is recorded into a graph.  (The null stream cannot be, and asking about it while another
+// stream is recorded would be an error.)
+static bool recorded(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (st == nullptr) return false;
+  if (hipStreamIsCapturing(st, &s) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return s == hipStreamCaptureStatusActive;
+}
+
 // Whether the split pass of a step with the ladder behind it reduces its partial sets itself, and with how many waves per workgroup
 // (0 = the reduction stays a launch of its own).  The sets that its last workgroup joins: reduced_sets.  A step enqueued one after the other, and
 // recorded (device time alone), us, with the launch and without: 8 KV heads x 4, 1000 tokens 11.9, 9.6 and 10.1, 9.6; 3000 12.0, 10.4 and
@@ -714,7 +726,7 @@ int stream_nt(const Cache* c, int64_t n_blocks) {
 // 12.6, 13.2 and 12.5, 13.1; 16000 14.3, 16.1; 128K 57.2, 58.7; 2 x 4 of 8000 11.8, 12.1 and 10.3, 11.8; 8 x 2 of 8000 11.7, 11.1 and 10.7, 11.1.
 // A KV group's workgroups share a die, so the dies have to be evenly loaded: as many groups on each, or no more
 // workgroups on the fullest than it has compute units.
-static int split_reduces(const Cache* c, int64_t n_blocks, int nsplit, int wpb) {
+static int split_reduces(const Cache* c, int64_t n_blocks, int nsplit, int wpb, int r, hipStream_t st) {
   const int64_t heads = (int64_t)c->desc.batch * c->desc.n_kv_heads, rows = (int64_t)c->desc.batch * c->desc.n_q_heads;
   const int g = c->desc.n_q_heads / c->desc.n_kv_heads;
   if (c->split_tickets == nullptr || c->variant != 0 || nsplit < 2 || rows > REDUCED_ROWS) return 0;
@@ -724,6 +736,10 @@ static int split_reduces(const Cache* c, int64_t n_blocks, int nsplit, int wpb) 
   // and the key term taken beside the rest (8 x 4 of 1000 tokens 10.5 -> 9.6 us a recorded step, of 3000 11.3 -> 10.4).
   const bool alone = wpb == 4 && 4 * (int64_t)nsplit >= (n_blocks + 3) / 4 && heads * nsplit <= c->n_cu;
   const int waves = alone ? (g == 4 && nsplit > reduced_sets(4, 4, 8) ? 12 : 8) : wpb;
+  // Twelve waves and nothing for the four that are to attend the trailing tokens: it is the host that gains by two launches (called
+  // in a loop 12.1 -> 10.3 us), the device alone is quicker with three (recorded, three and two: 8 x 4 of 4000 tokens 10.0, 10.2; 4 x 4 9.8,
+  // 10.2; 1 x 4 9.5, 10.2; 10 x 4 10.0, 10.2; 16 x 4 10.1, 10.3): a step that is being recorded takes three.
+  if (waves == 12 && r == 0 && recorded(st)) return 0;
   return nsplit <= reduced_sets(g, wpb, waves) ? waves : 0;
 }
 
@@ -864,7 +880,7 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     // 20.9, 16.2; 256 22.2, 16.5; 1024 27.9, 17.9; 2048 40.6, 25.3; two, 1440 rows 48.6, 35.5; one, 720 42.6, 36.0.
     a.finish = nsplit == 1 && !always ? 1 : 0;
     a.heads = bt * hkv;
-    a.waves = by != nullptr && !ladder_reduces_first(c, nsplit, r) ? split_reduces(c, nb, nsplit, wpb) : 0;
+    a.waves = by != nullptr && !ladder_reduces_first(c, nsplit, r) ? split_reduces(c, nb, nsplit, wpb, r, st) : 0;
     if (a.waves != 0) {
       a.tickets = c->split_tickets;
       a.scatter = c->scatter;

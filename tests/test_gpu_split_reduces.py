@@ -222,3 +222,32 @@ def test_few_rows_are_reduced_by_the_ladders_launch(bt, hkv, g, n, first):
             assert cqa.cqa_step_route(gc.h) == (2 if first == 3 and bt * hkv > 1 else (3 if few else 0))    # the first one to stray, or not
         O, cert, flags = gc.certified_decode(q)
         assert np.array_equal(O, O2) and cert.tobytes() == cert2.tobytes()
+
+
+@pytest.mark.parametrize("bt,hkv,n,recorded,eager", [(1, 8, 64 * 40, 0, 1), (1, 1, 4000, 0, 1), (1, 8, 64 * 40 + 1, 1, 1), (2, 8, 64 * 40, 0, 1), (1, 8, 64 * 32, 1, 1)])
+def test_steps_of_many_sets_recorded_and_not(bt, hkv, n, recorded, eager):
+    """Nine to sixteen sets, four heads, no trailing tokens: recorded with a launch for the reduction, without when called."""
+    print("split reduces, recorded or not", bt, hkv, n, flush=True)
+    k, v, q = make(bt, hkv, 4, n)
+    with GpuLayerCache(bt, hkv * 4, hkv, n + 32) as gc:
+        t, cqa = gc.torch, gc.cqa
+        whole = t.cuda.get_device_properties(0).multi_processor_count == 256
+        gc.append(k, v)
+        tol = cqa.Tolerances()
+        O, cert, _ = [x.copy() for x in gc.certified_decode(q)]
+        qd = gc.to_dev(q).clone()
+        s, graph = t.cuda.Stream(), t.cuda.CUDAGraph()
+        t.cuda.synchronize()
+        with t.cuda.graph(graph, stream=s):
+            cqa.cqa_decode_step_enqueue(gc.h, 0, None, None, qd, tol, gc.O, gc.cert, gc.flags, s.cuda_stream)
+        graph.replay()
+        if whole:
+            assert cqa.cqa_step_route(gc.h) == recorded
+        for _ in range(3):
+            gc.O.fill_(float("nan"))
+            t.cuda.synchronize()
+            graph.replay()
+            assert np.array_equal(gc.results()[0], O) and gc.results()[1].tobytes() == cert.tobytes()
+            assert np.array_equal(step(gc, q, tol)[0], O)
+            if whole:
+                assert cqa.cqa_step_route(gc.h) == eager
