@@ -190,8 +190,8 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
 
   // A one-token append that rides on this launch: the first wave of each KV group's first
   // workgroup stores the group's new key and value (2 x 256 bytes) into the trailing block and
-  // the pinned originals.  This pass reads sealed blocks only; the reduction, which attends the
-  // trailing tokens, runs after this launch has completed.
+  // the pinned originals.  Nothing in this launch reads what it stores: the pass reads sealed blocks only, and where it reduces the
+  // rows itself it takes the new token from the caller's buffer (load_trail); a launch that reduces, and the ladder's, come behind.
   if (a.ap_k_new != nullptr && split == 0 && w == 0) {
     const int64_t grp = head;
     const uint32_t kx = ld4_any(a.ap_k_new + grp * D + 2 * l);
@@ -711,6 +711,10 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
   //      on the counter of the die that it finds itself on.  Where a KV group's are not together no count
   //      gets full, the number that its first workgroup cleared stays clear, and the ladder's launch, which comes behind,
   //      reduces the rows from the partial sets.
+  //      The memory model would have a release in front of the count and an acquire behind it, at agent scope, which write back and
+  //      drop what the die's whole L2 holds (a toy of this shape 1.5 to 3.6 us, without 1.0 to 2.1).  Neither is needed while all are on that
+  //      die: the compute unit's cache writes through, so a store that the wait has seen completed is in the L2; the count is
+  //      added up there; and the last one's loads of the sets go past its own cache (load_sets<true>).
   const bool finish = a.finish != 0;
   // The trailing tokens: by waves without quads where there are any, else while the waves that are not through yet keep the
   // others waiting (of the two waves on a SIMD the first is through 3000 cycles before the second).
@@ -748,10 +752,10 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
       asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(die));
       if (a.scatter) die += (uint32_t)split & 1u;
       uint32_t* const tk = a.tickets + head * TICKET_STRIDE + die % DIES;
-      const bool last = __hip_atomic_fetch_add(tk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == (uint32_t)a.nsplit - 1u;
+      const bool last = __hip_atomic_fetch_add(tk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)a.nsplit - 1u;
       s_last = last ? 1u : 0u;
       if (last) {
-        __hip_atomic_store(tk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);   // for the next launch
+        __hip_atomic_store(tk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
         a.tickets[(uint32_t)a.heads * TICKET_STRIDE + head] = ra.raised_tag;
       }
     }
