@@ -290,35 +290,57 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
   uint4 kraw[4][2], vraw[2][2];
   u32x4 km_n[4], vm_n[2];
   float2 an_n[4];
-  // (Unconditional as well: behind a branch the wait for the query row, which was requested first, becomes one for
-  // everything.)
-  CQA_LOAD_META(q_cur)
-  CQA_LOAD_K(q_cur, 0)
-  CQA_LOAD_K(q_cur, 1)
-  CQA_LOAD_V(q_cur, 0)
-  CQA_LOAD_V(q_cur, 1)
-
   // Queries of the group as FP32 in LDS, rows of absent heads zero, each head pre-scaled by a
   // power of two S_h chosen so that |q S_h sigma| <= 2^14 for every sigma of this KV head (its
   // running maximum is kept at seal time): the scaled query then fits FP16 without overflow, and
   // elements too small for a normal FP16 low part are negligible against the largest ones.
   // Lane (h, kg) reads channels (u>>1)*64 + kg*16 + (u&1)*8 + e of head h when it forms slice u.
-  if (W == 4 || w < 4) {   // qbuf has four rows; the other waves of the workgroup have none to prepare
-    float2 qq = __half22float2(__builtin_bit_cast(__half2, q_in));
-    if (w >= G) qq = make_float2(0.0f, 0.0f);
-    const float qmax = wave_max(fmaxf(fabsf(qq.x), fabsf(qq.y)));
-    const float bound = qmax * sigmax_head;
-    int e = 0;
-    (void)frexpf(bound, &e);                       // bound < 2^e
-    e = bound > 0.0f ? min(max(14 - e, -100), 100) : 0;
-    const float S = ldexpf(1.0f, e);
-    qq.x *= S;
-    qq.y *= S;
-    *reinterpret_cast<float2*>(&qbuf[w][2 * l]) = qq;
-    if (l == 0) sbuf[w] = ldexpf(1.0f, -e);
-  }
-  asm volatile("" ::"v"(q_in), "v"(sigmax_head));   // (used on both sides of the branch: the requests stay above)
-  __syncthreads();
+  const auto set_up = [&](uint32_t row) {
+    if (W == 4 || w < 4) {   // qbuf has four rows; the other waves of the workgroup have none to prepare
+      float2 qq = __half22float2(__builtin_bit_cast(__half2, row));
+      if (w >= G) qq = make_float2(0.0f, 0.0f);
+      const float qmax = wave_max(fmaxf(fabsf(qq.x), fabsf(qq.y)));
+      const float bound = qmax * sigmax_head;
+      int e = 0;
+      (void)frexpf(bound, &e);                       // bound < 2^e
+      e = bound > 0.0f ? min(max(14 - e, -100), 100) : 0;
+      const float S = ldexpf(1.0f, e);
+      qq.x *= S;
+      qq.y *= S;
+      *reinterpret_cast<float2*>(&qbuf[w][2 * l]) = qq;
+      if (l == 0) sbuf[w] = ldexpf(1.0f, -e);
+    }
+    asm volatile("" ::"v"(row), "v"(sigmax_head));   // (used on both sides of the branch: the requests stay above)
+    __syncthreads();
+  };
+  // A wave without a quad (where waves have one at most: of a short head, or in the last workgroup) requests none: a record, 18 KB, would take
+  // the compute unit's data path from the waves that have one.  It leaves an empty state.  (A step of 72 heads of 32 tokens 6.7 -> 6.0 us.
+  // All of it stands in branches of their own: where they join, the compiler waits for every request of the other one.)
+  if (ONE && __builtin_expect(q_cur >= nquads, 0)) {
+    uint32_t row = q_in;
+    asm volatile("" : "+v"(row));   // (or what both set-ups begin with, the wait, moves ahead of the other one's requests)
+    set_up(row);
+#pragma unroll
+    for (int i = 0; i < G; ++i) *reinterpret_cast<float2*>(&mo[w][i][2 * l]) = make_float2(0.0f, 0.0f);
+    if (l < G) {
+      float* m = ms[w][l];
+      m[P_M] = m[P_T1] = m[P_T2] = -INFINITY;
+      m[P_L] = m[P_EV] = m[P_EVMAX] = m[P_DMAX] = m[P_VMAX] = 0.0f;
+      m[P_I1] = __int_as_float(-1);
+    }
+  } else {
+  // (In the loop's order, or its waits, which hold for these requests too, become waits for later ones.)
+  CQA_LOAD_META(q_cur)
+  __builtin_amdgcn_sched_barrier(0);
+  CQA_LOAD_K(q_cur, 0)
+  __builtin_amdgcn_sched_barrier(0);
+  CQA_LOAD_K(q_cur, 1)
+  __builtin_amdgcn_sched_barrier(0);
+  CQA_LOAD_V(q_cur, 0)
+  __builtin_amdgcn_sched_barrier(0);
+  CQA_LOAD_V(q_cur, 1)
+  __builtin_amdgcn_sched_barrier(0);
+  set_up(q_in);
   const float unscale_op = sbuf[h];                // 1 / S of my operand head
   // raw MFMA sum -> logit in units of ln 2 (the softmax state below is kept in base 2: v_exp_f32
   // and v_log_f32 are base-2 instructions), for my softmax head
@@ -668,7 +690,11 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if constexpr (ONE) break;
+    if constexpr (ONE) {
+      // (all of it computed here, under the products, and not moved to the masked stores below)
+      asm volatile("" : "+v"(l_run), "+v"(ev), "+v"(evmax), "+v"(dmax), "+v"(vmax), "+v"(t1), "+v"(t2), "+v"(i1));
+      break;
+    }
     wave_sync();
     // advance: the quad whose data was requested during this iteration becomes current
     q_cur = q_next;
@@ -701,6 +727,7 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
     m[P_T1] = t1;
     m[P_T2] = t2;
     m[P_I1] = __int_as_float(i1);
+  }
   }
   }
   // ---- the rows themselves.  A sequence served by one workgroup is finished here, from the waves' states in LDS, and needs
