@@ -93,12 +93,13 @@ constexpr int MAX_SPLITS = 1024;     // upper bound on splits per (batch, kv-hea
 // ---- split pass that reduces its partial sets itself (certified_split_mfma_kernel) ----
 constexpr int DIES = 8;              // workgroups whose indices leave the same remainder by 8 run on one die
 constexpr int TICKET_STRIDE = 32;    // words: a KV group's counters, one per die, have a line of their own
-constexpr int REDUCED_ROWS = 1024;   // most (batch, query head) rows of such a step: the ladder's launch keeps as many flag words in LDS
+constexpr int REDUCED_ROWS = 4 * 32 * DIES;   // most (batch, query head) rows of such a step, with a KV group per compute unit: the ladder's
+                                              // launch keeps as many flag words in LDS
 // Most sets that its last workgroup joins, of `waves` waves, `quad_waves` of them with quads, for `group` heads: eight by each row of
-// waves (one wave per head), all but the row that takes the side work where there are three or more; the rows' results take
+// waves (one wave per head) but the one that takes the side work, so none where there is no other; the rows' results take
 // the places of the quad waves' states.
 __host__ __device__ constexpr int reduced_sets(int group, int quad_waves, int waves) {
-  const int np = waves / group, rows = np > 2 ? np - 1 : 1;
+  const int rows = waves / group - 1;
   return 8 * (rows < quad_waves ? rows : quad_waves);
 }
 

@@ -726,10 +726,12 @@ static bool recorded(hipStream_t st) {
 // 12.6, 13.2 and 12.5, 13.1; 16000 14.3, 16.1; 128K 57.2, 58.7; 2 x 4 of 8000 11.8, 12.1 and 10.3, 11.8; 8 x 2 of 8000 11.7, 11.1 and 10.7, 11.1.
 // A KV group's workgroups share a die, so the dies have to be evenly loaded: as many groups on each, or no more
 // workgroups on the fullest than it has compute units.
+// Four waves for four heads have no second row to share the tail: the launch is better (17 x 8 x 4 of 2005 tokens 25.1, 26.0; 9 x 8 x 4 of 3145 22.1,
+// 23.0; 20 x 8 x 4 of 1350 21.8, 22.7).  So it is with more groups than compute units (33 x 8 x 2 of 1350 31.8, 33.4; 40 x 8 x 1 of 2005 42.7, 43.1).
 static int split_reduces(const Cache* c, int64_t n_blocks, int nsplit, int wpb, int r, hipStream_t st) {
-  const int64_t heads = (int64_t)c->desc.batch * c->desc.n_kv_heads, rows = (int64_t)c->desc.batch * c->desc.n_q_heads;
+  const int64_t heads = (int64_t)c->desc.batch * c->desc.n_kv_heads;
   const int g = c->desc.n_q_heads / c->desc.n_kv_heads;
-  if (c->split_tickets == nullptr || c->variant != 0 || nsplit < 2 || rows > REDUCED_ROWS) return 0;
+  if (c->split_tickets == nullptr || c->variant != 0 || nsplit < 2 || heads > c->n_cu) return 0;
   if (__atomic_load_n(c->strayed, __ATOMIC_RELAXED) != 0u && c->scatter != 1) return 0;   // this device deals workgroups otherwise
   if (heads % DIES != 0 && (heads + DIES - 1) / DIES * nsplit > c->n_cu / DIES) return 0;
   // Four waves with a quad each and a compute unit to themselves are joined by four or eight without: the trailing tokens are attended

@@ -743,10 +743,15 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
   //      die: the compute unit's cache writes through, so a store that the wait has seen completed is in the L2; the count is
   //      added up there; and the last one's loads of the sets go past its own cache (load_sets<true>).
   const bool finish = a.finish != 0;
-  // The trailing tokens: by waves without quads where there are any, else while the waves that are not through yet keep the
-  // others waiting (of the two waves on a SIMD the first is through 3000 cycles before the second).
-  const bool spare = WT > W || (SIDE && finish && nquads <= W - G);
-  if (WT == W && ra.r > 0 && (finish || (SIDE && a.tickets != nullptr)) && (spare ? w >= W - G : part == 0)) {
+  // The trailing tokens: by waves that have no quad, or one less than the others, where there are any; else while the waves that are not
+  // through yet keep the others waiting (of the two waves on a SIMD the first is through 3000 cycles before the second).  Four quad waves
+  // and no more are through at the same time, and every workgroup would wait for what only the last one needs: there it is row
+  // TP's, behind the count and beside the merging (steps, before and behind: 9 x 8 KV heads x 1 of 3145 tokens 21.0, 20.2; 17 x 8 x 2 of 3145 31.6,
+  // 30.6; 20 x 8 x 1 of 610 12.7, 11.9; with eight quad waves it is longer: 9 x 8 x 4 of 1350 12.4, 13.0).
+  constexpr bool LATE = SIDE && WT == W && W == 4;
+  constexpr int TP = NP > 2 ? NP - 1 : SP;
+  const bool spare = WT > W || (SIDE && finish && nquads % W > 0 && nquads % W <= W - G);
+  if (WT == W && ra.r > 0 && (finish || (!LATE && a.tickets != nullptr)) && (spare ? w >= W - G : part == 0)) {
     __builtin_amdgcn_s_setprio(2);
     load_trail(ra, head, row0 + hh, a.ap_k_new, a.ap_v_new, tr);
     if (SIDE) ts = trail_state(ra, tr);
@@ -771,7 +776,7 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
       float* pp = sets + (int64_t)split * PART_FLOATS;
       store_state(st, o2, pp, pp + P_O);
     }
-    if (a.tickets == nullptr) return;
+    if (!SIDE || a.tickets == nullptr) return;   // (one row of waves does not reduce: reduced_sets)
     if (part == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the set is in the die's L2
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -786,18 +791,21 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
         a.tickets[(uint32_t)a.heads * TICKET_STRIDE + head] = ra.raised_tag;
       }
     }
-    if (!SIDE && ra.r > 0) load_trail(ra, head, row0 + hh, a.ap_k_new, a.ap_v_new, tr);
+    if (LATE && part == TP && ra.r > 0) load_trail(ra, head, row0 + hh, a.ap_k_new, a.ap_v_new, tr);
     __syncthreads();
     if (s_last == 0u) return;
     // Eight sets a trip, no more than one trip for each row of waves (the host sees to it).  One trip's result is the row's; several take
     // the place of the waves' states in LDS.  Row SP has the side work instead.
     constexpr int TRIPS = reduced_sets(G, W, WT) / 8;
     const int trips = (a.nsplit + 7) >> 3, t = part < SP ? part : part - 1;
-    const bool merges = (!SIDE || part != SP) && t < trips;
+    const bool merges = part != SP && t < trips;
     SetRegs eight;
     if (merges) eight = load_sets<true>(sets, 8 * t, a.nsplit);
-    if (!SIDE && ra.r > 0) ts = trail_state(ra, tr);
-    if (SIDE && part == SP) {
+    if (LATE && part == TP && ra.r > 0) {
+      ts = trail_state(ra, tr);
+      keep_trail();
+    }
+    if (part == SP) {
       float delta = 0.0f;
       for (int s = l; s < a.nsplit; s += 64) delta = fmaxf(delta, ld_set<true>(sets, (uint32_t)s * PART_FLOATS + P_DMAX));
       side_work(wave_max(delta));
@@ -806,7 +814,7 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
       st = merge_loaded(eight, 8 * t, a.nsplit, 0, a.nsplit, o2);
       if (TRIPS > 1 && (trips > 2 || t > 0)) store_state(st, o2, (&ms[0][0][0]) + (t * G + hh) * 12, (&mo[0][0][0]) + (t * G + hh) * D);
     }
-    if (SIDE) __syncthreads();
+    __syncthreads();
     if (TRIPS > 1 && part == 0 && trips > 1) {
       if (trips == 2)
         st = join_lds(st, &ms[0][0][0] + (G + hh) * 12, &mo[0][0][0] + (G + hh) * D, o2);
@@ -828,7 +836,7 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
     const HeadState hs = head_state(st, o2);
     if (SIDE) {
       const float* x = s_side[w];
-      if (spare) ts = TrailState{x[0], x[1], x[2], *reinterpret_cast<const float2*>(&s_tail[w][2 * l])};
+      if (spare || (LATE && !finish)) ts = TrailState{x[0], x[1], x[2], *reinterpret_cast<const float2*>(&s_tail[w][2 * l])};
       kt = KeyTerms{x[3], x[4], x[5]};
     } else {
       kt = key_terms(ra, hs.DM);

@@ -38,12 +38,11 @@ SHAPES = [
     (4, 8, 4, 64 * 63 + 40, 8),       # eight quad waves, one quad each
     (16, 8, 4, 64 * 16 + 1, 2),       # ... two sets, a workgroup on every compute unit
     (1, 16, 1, 64 * 400 + 30, 16),    # ... several quads each, two trips
-    (36, 8, 1, 16 * 96 + 5, 3),       # four quad waves in more than one generation
-    (9, 8, 4, 16 * 98 + 5, 7),        # ... with a wave per head and no more: one quad each
-    (9, 8, 4, 16 * 98, 7),            # ... nothing behind the sealed blocks
-    (19, 8, 4, 7000, 3),              # ... several quads each
+    (36, 8, 1, 16 * 96 + 5, 3),       # more KV groups than compute units
+    (21, 8, 1, 16 * 129 + 5, 3), (21, 8, 2, 16 * 129, 3),   # fewer, two workgroups on most
+    (9, 8, 4, 16 * 98 + 5, 7), (9, 8, 4, 16 * 98, 7), (19, 8, 4, 7000, 3),   # four quad waves with a wave per head and no more
     # what the rows of waves deal among themselves, form by form: four quad waves and no more, two heads and one
-    (18, 8, 2, 16 * 33, 3), (17, 8, 2, 16 * 65 + 5, 3),
+    (18, 8, 2, 16 * 33, 3), (17, 8, 2, 16 * 65 + 5, 3), (9, 8, 2, 3145, 7),
     (17, 8, 1, 16 * 33 + 3, 3), (7, 8, 1, 16 * 129, 9), (7, 8, 1, 16 * 257 + 7, 9), (3, 8, 1, 16 * 321 + 15, 21), (3, 8, 1, 16 * 642, 21),
     # ... four quad waves and four without
     (1, 1, 2, 16 * 129 + 2, 9), (1, 2, 1, 16 * 33 + 1, 3), (1, 3, 1, 16 * 129 + 5, 9), (5, 1, 1, 16 * 257 + 2, 17),
@@ -55,7 +54,8 @@ SHAPES = [
 ]
 
 # ... of these the reduction is a launch of its own
-OWN_LAUNCH = [(1, 1, 4, 64 * 64 + 16, 17), (11, 1, 1, 64 * 80 + 1, 20)]
+OWN_LAUNCH = [(1, 1, 4, 64 * 64 + 16, 17), (11, 1, 1, 64 * 80 + 1, 20), (36, 8, 1, 16 * 96 + 5, 3), (9, 8, 4, 16 * 98 + 5, 7), (9, 8, 4, 16 * 98, 7),
+              (19, 8, 4, 7000, 3)]
 
 
 @pytest.mark.parametrize("int8", [False, True])
