@@ -252,6 +252,7 @@ struct DecodeArgs {
   int int8_query;      // matrix-core pass: 1 = INT8 x INT8 scoring of the quantised scaled query
   int wpb;             // matrix-core pass: waves per workgroup that take quads, 8 or 4 (split_geometry)
   int waves;           // ... and in all, where it reduces several splits itself (split_reduces)
+  int settle;          // ... four of several quads each wait for all of their first one (certified_split_mfma_kernel)
   // promoted-block pass of the adaptive decode
   __half* sc_k;             // layer base of the FP16 scratch's key halves [Bt * Hkv][sc_cap][16][128], or null
   __half* sc_v;             // ... and of its value halves (null exactly when sc_k is)

@@ -882,6 +882,8 @@ int32_t launch_certified(Cache* c, int layer, const __half* q, const cqa_toleran
     // 20.9, 16.2; 256 22.2, 16.5; 1024 27.9, 17.9; 2048 40.6, 25.3; two, 1440 rows 48.6, 35.5; one, 720 42.6, 36.0.
     a.finish = nsplit == 1 && !always ? 1 : 0;
     a.heads = bt * hkv;
+    const int64_t last = (int64_t)a.heads * nsplit % (2 * c->n_cu);   // workgroups of the last generation
+    a.settle = wpb == 4 && last >= c->n_cu && 2 * last <= 3 * c->n_cu ? 1 : 0;
     a.waves = by != nullptr && !ladder_reduces_first(c, nsplit, r) ? split_reduces(c, nb, nsplit, wpb, r, st) : 0;
     if (a.waves != 0) {
       a.tickets = c->split_tickets;

@@ -341,6 +341,12 @@ __global__ __launch_bounds__(64 * WT, WT == W ? 8 / W : 1) void certified_split_
   if (ONE) __builtin_amdgcn_sched_barrier(0);
   CQA_LOAD_V(q_cur, 1)
   if (ONE) __builtin_amdgcn_sched_barrier(0);
+  // Where a last generation gives most compute units one workgroup of four waves and some two, the launch is quicker if the waves have
+  // their whole first quad before they go on; why is not known (neither the loop's waits nor the deal of the workgroups).  Between one and one and a half
+  // workgroups to a compute unit, without and with the wait: 264 KV heads x 2 of 700 tokens 20.5, 19.4 us a decode; x 4 of 3136 in three sets 52.3, 51.3; 320 x
+  // 4 of 979 25.2, 24.3; 384 x 2 of 700 21.5, 20.4; 800 x 4 of 979 50.3, 49.5.  Otherwise level or worse: 448 x 2 of 2000 44.6, 44.7; 512 x 2 of 2000 51.8, 52.3;
+  // 640 x 2 of 2000 69.8, 73.3; 160 x 4 of 2000 in three sets 25.5, 25.8.
+  if (W == 4 && !ONE && a.settle) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   set_up(q_in);
   const float unscale_op = sbuf[h];                // 1 / S of my operand head
   // raw MFMA sum -> logit in units of ln 2 (the softmax state below is kept in base 2: v_exp_f32
