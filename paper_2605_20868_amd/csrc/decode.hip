@@ -719,15 +719,18 @@ static bool recorded(hipStream_t st) {
 }
 
 // Whether the split pass of a step with the ladder behind it reduces its partial sets itself, and with how many waves per workgroup
-// (0 = the reduction stays a launch of its own).  The sets that its last workgroup joins: reduced_sets.  A step enqueued one after the other, and
-// recorded (device time alone), us, with the launch and without: 8 KV heads x 4, 1000 tokens 11.9, 9.6 and 10.1, 9.6; 3000 12.0, 10.4 and
-// 10.5, 10.4; 4000 (no trailing tokens) 11.9, 10.5 and 10.2, 10.4; x 1, 8000 11.7, 10.3 and 10.7, 10.2; 32 x 4 of 4000 14.1, 13.8 and
-// 14.2, 14.0; 128 x 4 of 1000 15.9, 15.0 and 16.1, 15.2.  With a second trip per wave the launch is better: 8 x 4 of 8229
-// 12.6, 13.2 and 12.5, 13.1; 16000 14.3, 16.1; 128K 57.2, 58.7; 2 x 4 of 8000 11.8, 12.1 and 10.3, 11.8; 8 x 2 of 8000 11.7, 11.1 and 10.7, 11.1.
+// (0 = the reduction stays a launch of its own).  The sets that its last workgroup joins: reduced_sets.  Recorded steps (device time
+// alone), us, with the launch and without: 8 KV heads x 4 of 1000 tokens 9.9, 9.8; of 3000 10.4, 10.3; x 1 of 605 11.1, 9.1; of 8000 10.7, 10.2; x 2 of 1500 10.4,
+// 9.5; 2 x 4 of 2005 10.8, 9.5; 32 x 4 of 4000 14.4, 14.1; 128 x 4 of 1000 16.0, 15.1; 72 x 1 of 3145 21.0, 20.2; 136 x 2 of 3145 31.3, 30.8; 16 x 2 of 9005 19.6, 19.4.  A
+// host that takes longer for a launch gains more (8 x 4 of 1000 called in a loop 12.3, 10.7).  With a second trip per wave the launch is
+// better: 8 x 4 of 8229 12.6, 13.2; 16000 14.3, 16.1; 128K 57.2, 58.7; 2 x 4 of 8000 10.3, 11.8.
 // A KV group's workgroups share a die, so the dies have to be evenly loaded: as many groups on each, or no more
 // workgroups on the fullest than it has compute units.
 // Four waves for four heads have no second row to share the tail: the launch is better (17 x 8 x 4 of 2005 tokens 25.1, 26.0; 9 x 8 x 4 of 3145 22.1,
-// 23.0; 20 x 8 x 4 of 1350 21.8, 22.7).  So it is with more groups than compute units (33 x 8 x 2 of 1350 31.8, 33.4; 40 x 8 x 1 of 2005 42.7, 43.1).
+// 23.0; 20 x 8 x 4 of 1350 21.8, 22.7).  So it is with more groups than compute units (33 x 8 x 2 of 1350 31.8, 33.4; 40 x 8 x 1 of 2005 42.7, 43.1), and
+// for four heads by eight waves with two quads each at most, of which the first row's attend the trailing tokens and are not yet far ahead of
+// the others (9 x 8 x 4 of 2005 18.2, 18.8; 11 x 8 x 4 of 1365 17.1, 17.8; 4 x 8 x 4 of 8005 21.6, 21.9; but with one quad, 8 x 8 x 4 of 2005, 15.2, 14.7, and with
+// more, 10 x 8 x 4 of 5005, 30.0, 29.3).
 static int split_reduces(const Cache* c, int64_t n_blocks, int nsplit, int wpb, int r, hipStream_t st) {
   const int64_t heads = (int64_t)c->desc.batch * c->desc.n_kv_heads;
   const int g = c->desc.n_q_heads / c->desc.n_kv_heads;
@@ -742,6 +745,8 @@ static int split_reduces(const Cache* c, int64_t n_blocks, int nsplit, int wpb, 
   // in a loop 12.1 -> 10.3 us), the device alone is quicker with three (recorded, three and two: 8 x 4 of 4000 tokens 10.0, 10.2; 4 x 4 9.8,
   // 10.2; 1 x 4 9.5, 10.2; 10 x 4 10.0, 10.2; 16 x 4 10.1, 10.3): a step that is being recorded takes three.
   if (waves == 12 && r == 0 && recorded(st)) return 0;
+  const int64_t quads = (n_blocks + 3) / 4, quad_waves = (int64_t)wpb * nsplit;
+  if (g == 4 && wpb == 8 && quads > quad_waves && quads <= 2 * quad_waves) return 0;
   return nsplit <= reduced_sets(g, wpb, waves) ? waves : 0;
 }
 

@@ -50,12 +50,12 @@ SHAPES = [
     (11, 8, 2, 16 * 33 + 8, 2), (13, 1, 2, 16 * 305 + 1, 10), (7, 1, 2, 16 * 577, 19),
     (11, 8, 1, 16 * 33 + 9, 2), (13, 1, 1, 16 * 305, 10), (7, 1, 1, 16 * 577 + 3, 19), (5, 1, 1, 16 * 817 + 11, 26),
     # ... with several
-    (13, 8, 4, 16 * 65 + 10, 2), (13, 8, 2, 16 * 65 + 1, 2), (3, 8, 2, 16 * 337 + 13, 10), (13, 8, 1, 16 * 65 + 4, 2), (1, 8, 1, 16 * 1027 + 6, 32),
+    (13, 8, 4, 16 * 130 + 10, 2), (13, 8, 4, 16 * 128 + 10, 2), (13, 8, 2, 16 * 65 + 1, 2), (3, 8, 2, 16 * 337 + 13, 10), (13, 8, 1, 16 * 65 + 4, 2), (1, 8, 1, 16 * 1027 + 6, 32),
 ]
 
 # ... of these the reduction is a launch of its own
 OWN_LAUNCH = [(1, 1, 4, 64 * 64 + 16, 17), (11, 1, 1, 64 * 80 + 1, 20), (36, 8, 1, 16 * 96 + 5, 3), (9, 8, 4, 16 * 98 + 5, 7), (9, 8, 4, 16 * 98, 7),
-              (19, 8, 4, 7000, 3)]
+              (19, 8, 4, 7000, 3), (13, 8, 4, 16 * 128 + 10, 2)]
 
 
 @pytest.mark.parametrize("int8", [False, True])
