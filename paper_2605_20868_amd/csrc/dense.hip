@@ -466,8 +466,8 @@ static_assert(sizeof(LadderArgs) % 8 == 0 && alignof(ReduceArgs) == 8, "the seco
 // splits and rewrites O, the certificate and the rung bits of the heads that are served.
 // Behind a split pass that reduces the rows itself every wave also looks at the numbers that it left.  Where one is not
 // this step's, every workgroup reduces all rows, to know every flag without waiting for another one, and the
-// first one writes them, leaving out the outputs that a rung replaces.  That is for once: a step of 32 rows takes 50 us instead of 10 so, of 256
-// 170 instead of 15, of 512 603 instead of 15, so the first workgroup also tells the host, whose later steps reduce in a launch
+// first one writes them, leaving out the outputs that a rung replaces.  That is for once: a step of 32 rows takes 47 us instead of 10 so, of 256
+// 266 instead of 15, of 512 516 instead of 15, so the first workgroup also tells the host, whose later steps reduce in a launch
 // of their own (a recorded step goes on as it was recorded).
 // Leaving is what nearly every launch does, so no more than the first line of the arguments is read up to there (with all of
 // them first, 0.6 us more for a step of 64 x 4 heads, 2000 tokens).
